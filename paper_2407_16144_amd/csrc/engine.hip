@@ -301,32 +301,20 @@ static void build_sliced(const int32_t* cnt, int64_t nrows, int64_t base, int in
   }
 }
 
-// Blocks per product of a column-sorted LP: at least kMinSortedBlocks (rows
-// down to kMaxRows) in engines of many LPs, whose products share each
-// launch; for an LP among few, enough that the engine's products have about
-// kTailBlocks workgroups (rows down to kMinSortedRows), since its blocks are
-// most of what the launch has (measured on MI355X, LPs of 12.8k and 18.6k
-// rows alone: 21.4 and 36.8 us per iteration with 256-row blocks, 13.0 and
-// 17.5 us with 128-row blocks; in a batch of 512 such LPs 64-row blocks
-// everywhere cost 7% over the default).  Engines re-block their running LPs
-// as LPs finish (refine_layouts).
-constexpr int64_t kMinSortedBlocks = 64;
-constexpr int64_t kMinSortedRows = 64;
-// the products of an engine with few LPs keep at least this many
-// workgroups in all: blocks are sized for the LPs that share the launches
-constexpr int64_t kTailBlocks = 768;
-
-// Blocks per product (at least) and smallest row cap of the column-sorted
-// blocks of an LP that shares the launches with `live` LPs in all.
-static void plain_shape(int64_t live, int64_t* min_blocks, int64_t* min_rows) {
+// Column-sorted blocks per product, at most, and rows per block, at least, of
+// an LP that shares the launches with `live` LPs in all.  A lone LP gets one
+// block per CU: more blocks only repeat the chain of loads a block starts with
+// (20k x 70k: 256 blocks 16.0 us per iteration, 512 17.6, 128 19.2; 100k x
+// 400k: 42.8, 45.6, 45.3), and a block of a small LP is over soon however few
+// rows it has (2.4k x 8k: 16 rows or more 10.4 us, 64 or more 12.0).  In a
+// batch the launches are full anyway, and fewer, larger blocks share more
+// lines of the gathered vector (128 LPs: 16 blocks each 146 us, 24 151, 32
+// 158, 64 173; 48 LPs: 16 blocks 56.4, 24 54.5, 32 58.8).  Engines re-block
+// their running LPs as LPs finish (refine_layouts).
+static void plain_shape(int64_t live, int64_t* max_blocks, int64_t* min_rows) {
   live = std::max<int64_t>(live, 1);
-  if (live * kMinSortedBlocks >= kTailBlocks) {
-    *min_blocks = kMinSortedBlocks;
-    *min_rows = kMaxRows;
-  } else {
-    *min_blocks = (kTailBlocks + live - 1) / live;
-    *min_rows = kMinSortedRows;
-  }
+  *max_blocks = std::max<int64_t>(16, std::min<int64_t>(kCUs, 4 * kCUs / live));
+  *min_rows = std::max<int64_t>(16, std::min<int64_t>(256, 8 * live));
 }
 
 struct Slot {
@@ -337,7 +325,7 @@ struct Slot {
   std::vector<Blk> bPS, bDS;  // slice blocks of sliced groups (empty when not sliced)
   int64_t brpP0 = 0, brpPn = 0, brpD0 = 0, brpDn = 0;  // ranges in the brp spaces
   int rowsP = 0, rowsD = 0;  // rows of the largest sorted group of K^T / K (0: not grouped)
-  int64_t plainP = 0, plainD = 0;  // row cap of K^T's / K's column-sorted plain blocks (0: none)
+  int64_t plainP = 0, plainD = 0;  // blocks K^T's / K's rows were cut into for column-sorted blocks (0: none)
   bool watched = false;
   bool reported = false;
 };
@@ -419,8 +407,11 @@ class Engine final : public EngineBase {
   void launch_group(unsigned g, int tpb, size_t lds, const IterArgs<T>& A, int step);
   int ldsP_ = 0, ldsD_ = 0;  // rows of the largest sorted group in the current schedules
   int tpbP_ = 256, tpbD_ = 256;  // threads per workgroup of the sorted-group kernels
-  void mark_streaming(const std::vector<int>& live, std::vector<Blk>& P, std::vector<Blk>& PS,
-                      std::vector<Blk>& DS, std::vector<Blk>& D) const;
+  template <bool DUAL>
+  void launch_sorted(const IterArgs<T>& A, int step);
+  int ldsPB_ = 0, ldsDB_ = 0;      // LDS words of the largest column-sorted block in the current schedules
+  int tpbPB_ = 256, tpbDB_ = 256;  // threads per workgroup of the column-sorted blocks' kernels
+  void mark_streaming(const std::vector<int>& live, std::initializer_list<std::vector<Blk>*> lists) const;
   int scheduled_ = 0;          // LPs in the current schedules
   bool compacted_ = false;     // current schedules leave finished LPs out
   const int* finished_ = nullptr;  // status words used to leave finished LPs out (compaction)
@@ -433,9 +424,8 @@ class Engine final : public EngineBase {
   void group_sorted(int id, bool dual, int nsl, int64_t rows);
   bool group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* rows) const;
   int group_lds_rows(bool dual) const;
-  void sort_blocks(int id, bool dual, int64_t min_blocks, int64_t min_rows, bool reblock);
+  void sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_rows, bool reblock);
   void reblock_for(const int* status);
-  int64_t plain_rows(int64_t nrows, int64_t width, int64_t min_blocks, int64_t min_rows) const;
   IterArgs<T> args() const;
   void pull_states();
 
@@ -475,8 +465,10 @@ class Engine final : public EngineBase {
   int* d_status = nullptr;
   int* d_cnt = nullptr;
   int64_t* d_gbase = nullptr;
-  Blk *d_schedP = nullptr, *d_schedD = nullptr;
+  Blk *d_schedP = nullptr, *d_schedD = nullptr, *d_schedPB = nullptr, *d_schedDB = nullptr;
   int64_t capP_ = 0, capD_ = 0, nP_ = 0, nD_ = 0;
+  int64_t capPB_ = 0, capDB_ = 0, nPB_ = 0, nDB_ = 0;  // column-sorted blocks (sorted_step)
+  int64_t cap_partP_ = 0, cap_partD_ = 0;              // blocks that partP / partD hold sums of
   double *partP = nullptr, *partD = nullptr;
   int* h_status[2] = {nullptr, nullptr};
   hipEvent_t ev_[2] = {nullptr, nullptr};
@@ -552,7 +544,7 @@ void Engine<T>::allocate() {
   }
   h_st_.resize(nslots_);
   // sorted groups keep up to kSortRows row sums in dynamic LDS
-  const int lds_max = (int)(sizeof(double) * kSortRows);
+  const int lds_max = (int)(sizeof(double) * (kSortRows + kSpareWords));
   for (const void* f : {(const void*)sorted_group_step<T, true, 256, true>, (const void*)sorted_group_step<T, true, 256, false>,
                         (const void*)sorted_group_step<T, true, 512, true>, (const void*)sorted_group_step<T, true, 512, false>,
                         (const void*)sorted_group_step<T, true, 1024, true>, (const void*)sorted_group_step<T, true, 1024, false>,
@@ -561,6 +553,9 @@ void Engine<T>::allocate() {
                         (const void*)sorted_group_step<T, false, 1024, true>,
                         (const void*)sorted_group_step<T, false, 1024, false>})
     HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
+  for (const void* f : {(const void*)sorted_step<T, true, 256>, (const void*)sorted_step<T, true, 512>,
+                        (const void*)sorted_step<T, false, 256>, (const void*)sorted_step<T, false, 512>})
+    HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(double) * (kSortWordsPlain + kSpareWords)));
   HIPCHECK(hipStreamSynchronize(stream_));
 }
 
@@ -605,6 +600,8 @@ void Engine<T>::release_all() {
   dfree(d_gbase);
   dfree(d_schedP);
   dfree(d_schedD);
+  dfree(d_schedPB);
+  dfree(d_schedDB);
   dfree(partP);
   dfree(partD);
   for (int i = 0; i < 2; ++i) {
@@ -670,6 +667,8 @@ IterArgs<T> Engine<T>::args() const {
   A.partD = partD;
   A.schedP = d_schedP;
   A.schedD = d_schedD;
+  A.schedPB = d_schedPB;
+  A.schedDB = d_schedDB;
   A.schedPS = d_schedPS;
   A.schedDS = d_schedDS;
   return A;
@@ -1016,9 +1015,9 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
                  (slice || rows > std::min<int64_t>(opt_.sort_rows, kSortRowsPlain))) {
         group_sorted(id, dual, nsl, rows);
       } else if (opt_.plain_sort) {
-        int64_t minb = 0, minr = 0;
-        plain_shape(live_after, &minb, &minr);
-        sort_blocks(id, dual, minb, minr, false);
+        int64_t maxb = 0, minr = 0;
+        plain_shape(live_after, &maxb, &minr);
+        sort_blocks(id, dual, maxb, minr, false);
       }
     }
   }
@@ -1272,16 +1271,9 @@ void Engine<T>::slice_matrix(int id, bool dual) {
 }
 
 
-// Row cap of the column-sorted plain blocks of a product of nrows rows over
-// `width` columns (the packed index holds the column and the row in the
-// block in 32 bits).
-template <class T>
-int64_t Engine<T>::plain_rows(int64_t nrows, int64_t width, int64_t min_blocks, int64_t min_rows) const {
-  int cb = 0;
-  while (((int64_t)1 << cb) < width) ++cb;
-  const int64_t rows =
-      std::min<int64_t>(std::min<int64_t>(opt_.sort_rows, kSortRowsPlain), (int64_t)1 << (32 - std::min(cb, 31)));
-  return std::min<int64_t>(rows, std::max<int64_t>(min_rows, (nrows + min_blocks - 1) / min_blocks));
+// Blocks that the rows of a column-sorted product are cut into.
+static int64_t plain_blocks(int64_t nrows, int64_t max_blocks, int64_t min_rows) {
+  return std::max<int64_t>(1, std::min<int64_t>(max_blocks, (nrows + min_rows - 1) / min_rows));
 }
 
 // Smaller column-sorted blocks for the LPs still running (status) when few
@@ -1294,8 +1286,8 @@ void Engine<T>::reblock_for(const int* status) {
   for (int s = 0; s < nslots_; ++s)
     if (slots_[s].used && status[s] == ST_RUNNING) run.push_back(s);
   if (run.empty()) return;
-  int64_t minb = 0, minr = 0;
-  plain_shape((int64_t)run.size(), &minb, &minr);
+  int64_t maxb = 0, minr = 0;
+  plain_shape((int64_t)run.size(), &maxb, &minr);
   bool changed = false;
   for (int s : run) {
     for (int d = 0; d < 2; ++d) {
@@ -1303,8 +1295,8 @@ void Engine<T>::reblock_for(const int* status) {
       const Slot& S = slots_[s];
       const int64_t cur = dual ? S.plainD : S.plainP;
       if (cur == 0) continue;
-      if (plain_rows(dual ? S.m : S.n, dual ? S.n : S.m, minb, minr) < cur) {
-        sort_blocks(s, dual, minb, minr, true);
+      if (plain_blocks(dual ? S.m : S.n, maxb, minr) > cur) {
+        sort_blocks(s, dual, maxb, minr, true);
         changed = true;
       }
     }
@@ -1323,7 +1315,7 @@ void Engine<T>::reblock_for(const int* status) {
 // already in column-sorted blocks into smaller ones (reblock true: each
 // entry's row and column are read back from its packed key).
 template <class T>
-void Engine<T>::sort_blocks(int id, bool dual, int64_t min_blocks, int64_t min_rows, bool reblock) {
+void Engine<T>::sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_rows, bool reblock) {
   Slot& S = slots_[id];
   const int64_t nrows = dual ? S.m : S.n;
   const int64_t base = dual ? S.row0 : S.col0;
@@ -1336,44 +1328,63 @@ void Engine<T>::sort_blocks(int id, bool dual, int64_t min_blocks, int64_t min_r
   if (nrows == 0 || S.nnz == 0) return;
   int cb = 0;
   while (((int64_t)1 << cb) < width) ++cb;
-  if (cb >= 32) return;
-  const int64_t rows = plain_rows(nrows, width, min_blocks, min_rows);
+  if (cb > kSortColBits) return;
+  // most rows per block: the packed index holds the column and the row in 32 bits
+  const int64_t rows =
+      std::min<int64_t>(std::min<int64_t>(opt_.sort_rows, kSortRowsPlain), (int64_t)1 << (32 - std::min(cb, 31)));
   int rb = 0;
   while (((int64_t)1 << rb) < rows) ++rb;
   std::vector<int32_t> rp(nrows + 1);
   HIPCHECK(hipMemcpy(rp.data(), rpd + base, sizeof(int32_t) * (nrows + 1), hipMemcpyDeviceToHost));
   std::vector<Blk> out, sorted;
+  int64_t longest_row = 0;  // of the block being filled
   auto emit = [&](int64_t a, int64_t e, int kind) {
     Blk k;
     k.r0 = (int32_t)(base + a);
     k.r1 = (int32_t)(base + e);
     k.inst = id;
-    k.meta = blk_meta(kind, 1, 0) | (kind == BK_SORTED ? (rb << 25) : 0);
     k.gid = (int32_t)out.size();
     k.rp_off = kind == BK_SORTED ? (int32_t)c0 : 0;
     k.p0 = rp[a];
     k.pn = rp[e] - rp[a];
+    int rs = 0;  // copies of the row sums where one long row gets more than 4 of 64 consecutive products
+    if (kind == BK_SORTED && longest_row >= kRepRow && longest_row * 16 > k.pn)
+      while (rs < kMaxRepShift && ((e - a) << (rs + 1)) <= kSortWordsPlain) ++rs;
+    if (rs < kMinRepShift) rs = 0;
+    k.meta = blk_meta(kind, 1, rs) | (kind == BK_SORTED ? (rb << 25) : 0);
     out.push_back(k);
     if (kind == BK_SORTED) {
       sorted.push_back(k);
     }
+    longest_row = 0;
   };
-  int64_t start = 0, acc = 0;
+  // blocks of equal weight (entries, and kRowWeight per row for its epilogue):
+  // a block ends at the row whose middle passes the next multiple of the
+  // average weight
+  const int64_t nblk_want = plain_blocks(nrows, max_blocks, min_rows);
+  const double per = (double)((int64_t)S.nnz + kRowWeight * nrows) / (double)nblk_want;
+  int64_t start = 0, acc = 0, cum = 0;
+  double bound = per;
   for (int64_t r = 0; r < nrows; ++r) {
     const int64_t len = (int64_t)rp[r + 1] - rp[r];
-    if (len > kPlainNB) {
+    const int64_t w = len + kRowWeight;
+    if (len > kSortedRowMax) {
       if (r > start) emit(start, r, BK_SORTED);
       emit(r, r + 1, BK_LONG);
       start = r + 1;
       acc = 0;
-      continue;
+    } else {
+      if (r > start && ((r - start) >= rows || acc + len > kSortEntries || (double)cum + 0.5 * (double)w > bound)) {
+        emit(start, r, BK_SORTED);
+        start = r;
+        acc = 0;
+      }
+      longest_row = std::max(longest_row, len);
+      acc += len;
     }
-    if ((r - start) >= rows || acc + len > kSortEntries) {
-      if (r > start) emit(start, r, BK_SORTED);
-      start = r;
-      acc = 0;
-    }
-    acc += len;
+    if (r == start || start == r + 1)
+      while (bound < (double)cum + 0.5 * per + (start == r + 1 ? (double)w : 0.0)) bound += per;
+    cum += w;
   }
   if (nrows > start) emit(start, nrows, BK_SORTED);
   if (!sorted.empty()) {
@@ -1445,7 +1456,7 @@ void Engine<T>::sort_blocks(int id, bool dual, int64_t min_blocks, int64_t min_r
     dfree(d_blk);
     dfree(d_all);
   }
-  (dual ? S.plainD : S.plainP) = sorted.empty() ? 0 : rows;
+  (dual ? S.plainD : S.plainP) = sorted.empty() ? 0 : nblk_want;
   if (dual) S.bD = out;
   else S.bP = out;
 }
@@ -1467,7 +1478,7 @@ bool Engine<T>::group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl,
     const int64_t w = (width + q - 1) / q + 1;
     int cb = 0;
     while (((int64_t)1 << cb) < w) ++cb;
-    if (cb >= 31) continue;
+    if (cb > kSortColBits) continue;
     int64_t r = std::min<int64_t>(std::min<int64_t>(opt_.sort_rows, kSortRows), (int64_t)1 << (32 - cb));
     while (r > kMaxRows && ((nrows + r - 1) / r) * q < opt_.group_blocks) r /= 2;
     if (r > best_r) {
@@ -1685,21 +1696,27 @@ void Engine<T>::set_params(const std::vector<int>& ids, double tol, int64_t max_
 // Many LPs in one schedule: each LP's blocks go to one XCD.  Workgroups are
 // dispatched round-robin over the 8 XCDs, so schedule position p runs on XCD
 // p % 8; LPs are assigned to 8 lanes (largest first, to the lane with the
-// fewest blocks) and lane q fills positions q, q + 8, ... (padded with no-op
+// least work) and lane q fills positions q, q + 8, ... (padded with no-op
 // blocks).  Each XCD's L2 then caches only the gathered vectors of its own
 // LPs instead of every running LP's.
 template <class T>
 void Engine<T>::pin_to_xcds(std::vector<Blk>& v, const std::vector<std::pair<int, int>>& ranges) const {
+  if (v.empty()) return;
   std::vector<int> order(ranges.size());
-  for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-    return ranges[a].second - ranges[a].first > ranges[b].second - ranges[b].first;
-  });
+  std::vector<int64_t> weight(ranges.size(), 0);
+  for (size_t i = 0; i < order.size(); ++i) {
+    order[i] = (int)i;
+    for (int p = ranges[i].first; p < ranges[i].second; ++p)
+      weight[i] += v[p].pn + kRowWeight * (v[p].r1 - v[p].r0) + kBlockWeight;
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return weight[a] > weight[b]; });
   std::vector<std::vector<Blk>> lane(kSlices);
+  int64_t load[kSlices] = {0};
   for (int i : order) {
     int q = 0;
     for (int k = 1; k < kSlices; ++k)
-      if (lane[k].size() < lane[q].size()) q = k;
+      if (load[k] < load[q]) q = k;
+    load[q] += weight[i];
     for (int p = ranges[i].first; p < ranges[i].second; ++p) lane[q].push_back(v[p]);
   }
   size_t len = 0;
@@ -1719,8 +1736,7 @@ void Engine<T>::pin_to_xcds(std::vector<Blk>& v, const std::vector<std::pair<int
 // they do not evict what fits.  (A matrix pair larger than the cache read
 // round-robin would otherwise evict every line before its next use.)
 template <class T>
-void Engine<T>::mark_streaming(const std::vector<int>& live, std::vector<Blk>& P, std::vector<Blk>& PS,
-                               std::vector<Blk>& DS, std::vector<Blk>& D) const {
+void Engine<T>::mark_streaming(const std::vector<int>& live, std::initializer_list<std::vector<Blk>*> lists) const {
   const int64_t budget = opt_.cache_budget_bytes;
   int64_t used = 0;
   for (int s : live) {
@@ -1730,45 +1746,51 @@ void Engine<T>::mark_streaming(const std::vector<int>& live, std::vector<Blk>& P
     if (!sl.bDS.empty()) used += (int64_t)(sizeof(T) + 4) * kSlices * sl.m;
     if (!sl.bPS.empty()) used += (int64_t)(sizeof(T) + 4) * kSlices * sl.n;
   }
-  auto mark = [&](std::vector<Blk>& v) {
-    for (Blk& k : v) {
+  for (std::vector<Blk>* v : lists) {
+    for (Blk& k : *v) {
       k.meta &= ~kBlkNT;
       if (blk_kind(k) == BK_PAD) continue;
       const int64_t bytes = (int64_t)k.pn * (int64_t)(sizeof(T) + 4);
       if (budget >= 0 && used + bytes > budget) k.meta |= kBlkNT;
       else used += bytes;
     }
-  };
-  mark(P);
-  mark(PS);
-  mark(DS);
-  mark(D);
+  }
 }
 
 template <class T>
 void Engine<T>::rebuild_schedules() {
-  std::vector<Blk> P, D, PS, DS;
+  // P / D: tiles and slice-sum blocks of the step kernels; PB / DB: their
+  // column-sorted blocks; PS / DS: slice blocks.  gids number an LP's step
+  // blocks of both kinds in one range.
+  std::vector<Blk> P, D, PB, DB, PS, DS;
   std::vector<int> live;
   std::vector<int4> rg;
-  auto append = [](std::vector<Blk>& dst, const std::vector<Blk>& src, int32_t goff) {
+  std::vector<std::pair<int, int>> rP, rD, rPB, rDB;
+  int gP = 0, gD = 0;
+  auto append = [](std::vector<Blk>& tiles, std::vector<Blk>& sorted, const std::vector<Blk>& src, int& g,
+                   std::vector<std::pair<int, int>>& rt, std::vector<std::pair<int, int>>& rs) {
+    const int t0 = (int)tiles.size(), s0 = (int)sorted.size();
     for (Blk k : src) {
-      k.gid += goff;
-      dst.push_back(k);
+      k.gid += g;
+      (blk_kind(k) == BK_SORTED ? sorted : tiles).push_back(k);
     }
+    g += (int)src.size();
+    rt.push_back({t0, (int)tiles.size()});
+    rs.push_back({s0, (int)sorted.size()});
   };
   for (int s = 0; s < nslots_; ++s) {
     const Slot& sl = slots_[s];
     if (!sl.used) continue;
     if (finished_ && finished_[s] != ST_RUNNING) continue;  // done: its blocks would only exit
     int4 r;
-    r.x = (int)P.size();
-    append(PS, sl.bPS, r.x);
-    append(P, sl.bP, r.x);
-    r.y = (int)P.size();
-    r.z = (int)D.size();
-    append(DS, sl.bDS, r.z);
-    append(D, sl.bD, r.z);
-    r.w = (int)D.size();
+    r.x = gP;
+    r.z = gD;
+    PS.insert(PS.end(), sl.bPS.begin(), sl.bPS.end());
+    DS.insert(DS.end(), sl.bDS.begin(), sl.bDS.end());
+    append(P, PB, sl.bP, gP, rP, rPB);
+    append(D, DB, sl.bD, gD, rD, rDB);
+    r.y = gP;
+    r.w = gD;
     live.push_back(s);
     rg.push_back(r);
   }
@@ -1779,42 +1801,60 @@ void Engine<T>::rebuild_schedules() {
     sched_size_[2] += (double)slots_[s].m;
   }
   if (opt_.xcd_pin && (int)live.size() >= kPinMinLPs) {
-    std::vector<std::pair<int, int>> rp, rd;
-    for (const int4& r : rg) {
-      rp.push_back({r.x, r.y});
-      rd.push_back({r.z, r.w});
-    }
-    pin_to_xcds(P, rp);
-    pin_to_xcds(D, rd);
+    pin_to_xcds(P, rP);
+    pin_to_xcds(D, rD);
+    pin_to_xcds(PB, rPB);
+    pin_to_xcds(DB, rDB);
   }
   ldsP_ = ldsD_ = 0;
   for (int s2 : live) {
     ldsP_ = std::max(ldsP_, slots_[s2].rowsP);
     ldsD_ = std::max(ldsD_, slots_[s2].rowsD);
   }
-  // threads per sorted-group workgroup: the configured count, or enough for
-  // about eight waves per CU over the product's workgroups (measured: the
-  // products are bound by cache-line gathers, so large groups with few
-  // workgroups need wide ones)
+  // threads per sorted-group workgroup: the configured count, or 1024 where
+  // each CU has one workgroup, else enough for about eight waves per CU (the
+  // entries in flight are bound by the 32 KB of L1: more waves only queue)
   auto pick = [&](size_t nb) {
     if (opt_.group_threads > 0) return opt_.group_threads;
-    const int64_t t = (int64_t)kCUs * 8 * 64 / std::max<int64_t>(1, (int64_t)nb);
-    return t >= 1024 ? 1024 : t >= 512 ? 512 : 256;
+    if (nb <= (size_t)kCUs) return 1024;
+    return (int64_t)kCUs * 8 * 64 / (int64_t)nb >= 512 ? 512 : 256;
   };
   tpbP_ = pick(PS.size());
   tpbD_ = pick(DS.size());
-  mark_streaming(live, P, PS, DS, D);
+  auto words = [](const std::vector<Blk>& v) {
+    int w = 1;
+    for (const Blk& k : v)
+      if (blk_kind(k) == BK_SORTED) w = std::max(w, (k.r1 - k.r0) << blk_rep_shift(k));
+    return w;
+  };
+  ldsPB_ = words(PB);
+  ldsDB_ = words(DB);
+  // threads per column-sorted block: 512 where each CU has one large block
+  // (100k x 400k: 42.6 us per iteration against 43.4 with 256), else 256 (20k x
+  // 70k: 16.0 against 16.3; a batch of 128: 146 against 155)
+  auto pick_sorted = [](const std::vector<Blk>& v) {
+    int64_t entries = 0;
+    for (const Blk& k : v) entries += k.pn;
+    return v.size() <= (size_t)kCUs && entries > 8192 * (int64_t)v.size() ? 512 : 256;
+  };
+  tpbPB_ = pick_sorted(PB);
+  tpbDB_ = pick_sorted(DB);
+  mark_streaming(live, {&P, &PB, &PS, &DS, &D, &DB});
   HIPCHECK(hipStreamSynchronize(stream_));
-  auto upload = [&](std::vector<Blk>& v, Blk*& d, int64_t& cap, int64_t& n, double** part) {
+  auto upload = [&](std::vector<Blk>& v, Blk*& d, int64_t& cap, int64_t& n) {
     if ((int64_t)v.size() > cap) {
       dfree(d);
-      if (part) dfree(*part);
       cap = std::max<int64_t>((int64_t)v.size(), 2 * cap);
       dalloc(&d, cap);
-      if (part) dalloc(part, cap * kNS);
     }
     n = (int64_t)v.size();
     if (n) HIPCHECK(hipMemcpyAsync(d, v.data(), sizeof(Blk) * n, hipMemcpyHostToDevice, stream_));
+  };
+  auto sums = [&](int64_t n, double*& part, int64_t& cap) {
+    if (n <= cap) return;
+    dfree(part);
+    cap = std::max<int64_t>(n, 2 * cap);
+    dalloc(&part, cap * kNS);
   };
   scheduled_ = (int)live.size();
   if ((int64_t)live.size() > cap_live_) {
@@ -1824,10 +1864,14 @@ void Engine<T>::rebuild_schedules() {
   }
   if (!live.empty())
     HIPCHECK(hipMemcpyAsync(d_live_, live.data(), sizeof(int) * live.size(), hipMemcpyHostToDevice, stream_));
-  upload(P, d_schedP, capP_, nP_, &partP);
-  upload(D, d_schedD, capD_, nD_, &partD);
-  upload(PS, d_schedPS, capPS_, nPS_, nullptr);
-  upload(DS, d_schedDS, capDS_, nDS_, nullptr);
+  upload(P, d_schedP, capP_, nP_);
+  upload(D, d_schedD, capD_, nD_);
+  upload(PB, d_schedPB, capPB_, nPB_);
+  upload(DB, d_schedDB, capDB_, nDB_);
+  upload(PS, d_schedPS, capPS_, nPS_);
+  upload(DS, d_schedDS, capDS_, nDS_);
+  sums(gP, partP, cap_partP_);
+  sums(gD, partD, cap_partD_);
   if (!live.empty()) {
     int* d_ids = nullptr;
     int4* d_rg = nullptr;
@@ -1876,10 +1920,21 @@ void Engine<T>::launch_group(unsigned g, int tpb, size_t lds, const IterArgs<T>&
 }
 
 template <class T>
+template <bool DUAL>
+void Engine<T>::launch_sorted(const IterArgs<T>& A, int step) {
+  const unsigned g = (unsigned)(DUAL ? nDB_ : nPB_);
+  const size_t lds = sizeof(double) * (size_t)((DUAL ? ldsDB_ : ldsPB_) + kSpareWords);
+  switch (DUAL ? tpbDB_ : tpbPB_) {
+    case 512: sorted_step<T, DUAL, 512><<<g, 512, lds, stream_>>>(A, step); break;
+    default: sorted_step<T, DUAL, 256><<<g, 256, lds, stream_>>>(A, step); break;
+  }
+}
+
+template <class T>
 void Engine<T>::launch_slices(bool dual, const IterArgs<T>& A, int step) {
   const unsigned g = (unsigned)(dual ? nDS_ : nPS_);
   if (opt_.slice_sort) {
-    const size_t lds = sizeof(double) * (size_t)std::max(1, dual ? ldsD_ : ldsP_);
+    const size_t lds = sizeof(double) * (size_t)((dual ? ldsD_ : ldsP_) + kSpareWords);
     if (dual) launch_group<true>(g, dual ? tpbD_ : tpbP_, lds, A, step);
     else launch_group<false>(g, dual ? tpbD_ : tpbP_, lds, A, step);
     return;
@@ -1903,7 +1958,7 @@ void Engine<T>::launch_slices(bool dual, const IterArgs<T>& A, int step) {
 template <class T>
 void Engine<T>::launch_chunk() {
   if (sched_dirty_ && !compacted_) rebuild_schedules();
-  if (nP_ == 0 || nD_ == 0) return;
+  if (scheduled_ == 0) return;
   const IterArgs<T> A = args();
   const int CH = opt_.chunk;
   const bool prof = opt_.profile > 0 && (chunk_count_ % opt_.profile) == 0;
@@ -1923,11 +1978,13 @@ void Engine<T>::launch_chunk() {
       if (timed) HIPCHECK(hipEventRecord(e[0], stream_));
       if (nPS_) launch_slices(false, A, i);
       if (timed) HIPCHECK(hipEventRecord(e[1], stream_));
-      primal_step<T><<<(unsigned)nP_, kThreads, 0, stream_>>>(A, i);
+      if (nP_) primal_step<T><<<(unsigned)nP_, kThreads, 0, stream_>>>(A, i);
+      if (nPB_) launch_sorted<false>(A, i);
       if (timed) HIPCHECK(hipEventRecord(e[2], stream_));
       if (nDS_) launch_slices(true, A, i);
       if (timed) HIPCHECK(hipEventRecord(e[3], stream_));
-      dual_step<T><<<(unsigned)nD_, kThreads, 0, stream_>>>(A, i);
+      if (nD_) dual_step<T><<<(unsigned)nD_, kThreads, 0, stream_>>>(A, i);
+      if (nDB_) launch_sorted<true>(A, i);
       if (timed) {
         HIPCHECK(hipEventRecord(e[4], stream_));
         HIPCHECK(hipEventRecord(e[5], stream_));  // empty pair: the events' own cost

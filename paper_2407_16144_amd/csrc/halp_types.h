@@ -82,8 +82,31 @@ constexpr int kCUs = 256;        // compute units of an MI355X
 // A plain block of the step kernels may be column-sorted too (kind
 // BK_SORTED, same packing, rp_off = the LP's first column): at most
 // kSortRowsPlain rows (its row sums share the step kernel's LDS with the
-// plain tile), rows of at most kPlainNB entries.
+// plain tile).
 constexpr int kSortRowsPlain = 2048;
+// Its row sums, with the copies a block with a row of kRepRow entries or more
+// may keep (blk_rep_shift), take at most this many LDS words.
+constexpr int kSortWordsPlain = 4096;
+constexpr int kRepRow = 256;
+constexpr int kMinRepShift = 3, kMaxRepShift = 5;
+constexpr int kSpareWords = 64;  // LDS words behind the row sums (SortedStream)
+// Longest row of a column-sorted plain block; longer ones get a block of
+// their own (BK_LONG).
+constexpr int kSortedRowMax = 1 << 15;
+// Work of a block in entries: per row (its epilogue) and per block
+constexpr int kRowWeight = 4;
+constexpr int kBlockWeight = 256;
+// Most column bits of a column-sorted block's slice: the byte offset of a
+// gather from the slice's first column stays below 2^32.
+constexpr int kSortColBits = 28;
+// Entry pipeline of the column-sorted products: entries per batch of a group
+// workgroup, and entries per thread and batches loaded ahead in a plain block
+constexpr int kGroupEntries = 1024;
+constexpr int kPlainU = 2;
+constexpr int kPlainD = 2;
+// log2 of the copies of each LDS row sum that a BK_SORTED block keeps (in the
+// meta bits that hold the slice of a slice block)
+__host__ __device__ inline int blk_rep_shift(const Blk& b) { return (b.meta >> 16) & 0xff; }
 __host__ __device__ inline int blk_rowbits(const Blk& b) { return (b.meta >> 25) & 31; }
 __host__ __device__ inline int32_t blk_meta(int kind, int nsl, int slice) {
   return kind | (nsl << 8) | (slice << 16);

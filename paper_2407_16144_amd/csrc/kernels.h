@@ -63,6 +63,8 @@ struct IterArgs {
   double* partD;
   const Blk* schedP;   // one block per row group (primal / dual step kernels)
   const Blk* schedD;
+  const Blk* schedPB;  // column-sorted blocks (sorted_step), gids shared with schedP / schedD
+  const Blk* schedDB;
   const Blk* schedPS;  // slice blocks of sliced row groups (slice kernel)
   const Blk* schedDS;
 };

@@ -32,6 +32,7 @@ __device__ __forceinline__ T wave_sum(T v) {
 }
 
 // Sum of kNS per-thread values over the block; result valid in s_out[0..kNS).
+template <int TPB = kThreads>
 __device__ __forceinline__ void block_sum_ns(double (&v)[kNS], double (*s_red)[kNS], double* s_out) {
 #pragma unroll
   for (int s = 0; s < kNS; ++s) v[s] = wave_sum(v[s]);
@@ -44,7 +45,7 @@ __device__ __forceinline__ void block_sum_ns(double (&v)[kNS], double (*s_red)[k
   if (threadIdx.x < kNS) {
     double a = s_red[0][threadIdx.x];
 #pragma unroll
-    for (int w = 1; w < kThreads / 64; ++w) a += s_red[w][threadIdx.x];
+    for (int w = 1; w < TPB / 64; ++w) a += s_red[w][threadIdx.x];
     s_out[threadIdx.x] = a;
   }
   __syncthreads();
@@ -282,16 +283,42 @@ __device__ __forceinline__ void gather_slices(const Blk& b, const T* __restrict_
 // step modes
 // ---------------------------------------------------------------------------
 
+// Device memory that no wave of the running kernel writes (schedules, the step
+// counter, LP states in the step kernels): uniform loads of it are scalar.
+template <class V>
+using cptr = const __attribute__((address_space(4))) V*;
+// Device memory, vector loads.
+template <class V>
+using gptr = const __attribute__((address_space(1))) V*;
+
+// A block's descriptor, loaded whole.
+typedef int BlkWords __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ Blk load_blk(cptr<BlkWords> p) {
+  const BlkWords w = *p;
+  return Blk{w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
+}
+
 // Mode of step g for one LP.  Checks fall at inner counters k = C, 2C, ...
 // of an epoch (k = g - kbase); the controller keeps the step index of the
 // next one in next_check.
-__device__ __forceinline__ int step_mode(const InstState& S, int64_t g) {
-  if (S.status != ST_RUNNING) return M_SKIP;
-  if (S.phase == PH_EVAL) return M_EVAL;
-  if (S.phase == PH_RESID) return M_RESID;
-  if (g < S.kbase) return M_SKIP;
-  if (g == S.next_check) return M_CHECK;
+__device__ __forceinline__ int mode_of(int status, int phase, int64_t kbase, int64_t next, int64_t g) {
+  if (status != ST_RUNNING) return M_SKIP;
+  if (phase == PH_EVAL) return M_EVAL;
+  if (phase == PH_RESID) return M_RESID;
+  if (g < kbase) return M_SKIP;
+  if (g == next) return M_CHECK;
   return M_NORMAL;
+}
+__device__ __forceinline__ int step_mode(const InstState& S, int64_t g) {
+  return mode_of(S.status, S.phase, S.kbase, S.next_check, g);
+}
+// The same in a step kernel: the four fields are loaded together (the asm ties
+// them), in one round trip instead of one per test.
+__device__ __forceinline__ int step_mode(cptr<InstState> S, int64_t g) {
+  int status = S->status, phase = S->phase;
+  int64_t kbase = S->kbase, next = S->next_check;
+  asm("" : "+s"(status), "+s"(phase), "+s"(kbase), "+s"(next));
+  return mode_of(status, phase, kbase, next, g);
 }
 
 template <class T>
@@ -309,41 +336,109 @@ __device__ __forceinline__ T rec_proj(T d, bool lf, bool uf) {
 // primal step (rows of K^T = variables)
 // ---------------------------------------------------------------------------
 
-// Row sums of one column-sorted block (a plain BK_SORTED block) for the
-// gathered vector src, accumulated in FP64 LDS words whatever the compute
-// type (products in the compute type; on gfx950 ds_add_f64 measured 1.8x
-// faster than ds_add_f32 on these scattered adds):
-// consecutive entries gather nearby elements of the slice, so the rows of
-// the group share the cache lines of their gathers.  Products go to the LDS
-// row sums s_row by atomic adds, so the order of the additions within a row
-// is not fixed (the last bits of a sum can differ from run to run).
-// U: entries in flight per thread (measured on the large LP: 8 for the
-// slice groups of K, 4 for the blocks of K^T, whose step kernel also holds
-// the epilogue's registers)
-template <class T, bool NT, int U>
-__device__ __forceinline__ void sorted_rows_sum(const Blk& b, const uint32_t* __restrict__ w,
-                                                const T* __restrict__ val, const T* __restrict__ src,
-                                                double* s_row) {
-  const int rb = blk_rowbits(b);
-  const uint32_t rmask = (1u << rb) - 1u;
-  const T* srcb = src + b.rp_off;
-  for (int e0 = threadIdx.x; e0 < b.pn; e0 += kThreads * U) {
-    uint32_t k[U];
-    T v[U];
+// The entries of one column-sorted block (a plain BK_SORTED block or one
+// (group, slice) block of a sorted-group product) as a software pipeline: TPB
+// threads take U entries each per batch; a batch's packed indices and values
+// are loaded D batches before its gathers, and its gathers are issued one
+// batch before its products are added into the LDS row sums.  Consecutive
+// entries gather nearby elements of the vector, so the lanes of one gather
+// share cache lines.  The row sums are FP64 LDS words whatever the compute
+// type (products in the compute type; ds_add_f64 measured 1.8x faster than
+// ds_add_f32 on these scattered adds), added by LDS atomics: the order of the
+// additions within a row is not fixed (the last bits of a sum can differ from
+// run to run).
+//
+// Loads start at the block's first entry rounded down to 32 entries (whole
+// 128-byte lines per wave: neighbouring waves otherwise both wait for the
+// line they share) and go through buffer descriptors that end with the block:
+// a position past the end reads index 0 and value 0.  What lies outside the
+// block is added into kSpareWords words behind the row sums (one per lane), so
+// the loop has no per-entry branch.
+template <class T, int TPB, int U, int D>
+struct SortedStream {
+  static constexpr int NS = D + 2;  // batches in registers
+  static constexpr int BT = TPB * U;
+  __amdgpu_buffer_rsrc_t rk, rv;
+  int lo, hi, rb;
+  bool nt;  // non-temporal loads
+  uint32_t k[NS][U];
+  T v[NS][U];
+
+  template <int AUX>
+  __device__ __forceinline__ void load_as(int i, int slot) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * kThreads;
-      if (e < b.pn) {
-        k[u] = ld_entry<NT>(w + b.p0 + e);
-        v[u] = ld_entry<NT>(val + b.p0 + e);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * kThreads;
-      if (e < b.pn) atomicAdd(&s_row[k[u] & rmask], (double)(v[u] * srcb[k[u] >> rb]));
+      const uint32_t e = (uint32_t)(i * BT + u * TPB) + threadIdx.x;
+      k[slot][u] = __builtin_amdgcn_raw_buffer_load_b32(rk, (int)(e * 4u), 0, AUX);
+      if constexpr (sizeof(T) == 8)
+        v[slot][u] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rv, (int)(e * 8u), 0, AUX));
+      else
+        v[slot][u] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rv, (int)(e * 4u), 0, AUX));
     }
   }
+  // the first batches, issued before anything else the block waits for
+  __device__ __forceinline__ void open(const Blk& b, const int32_t* ci, const T* val) {
+    lo = b.p0 & 31;
+    hi = lo + b.pn;
+    rb = blk_rowbits(b);
+    nt = blk_nt(b);
+    rk = __builtin_amdgcn_make_buffer_rsrc((void*)(ci + (b.p0 - lo)), 0, (int)((uint32_t)hi * 4u), 0x00020000);
+    rv = __builtin_amdgcn_make_buffer_rsrc((void*)(val + (b.p0 - lo)), 0,
+                                           (int)((uint32_t)hi * (uint32_t)sizeof(T)), 0x00020000);
+    if (nt) {
+#pragma unroll
+      for (int d = 0; d <= D; ++d) load_as<2>(d, d);
+    } else {
+#pragma unroll
+      for (int d = 0; d <= D; ++d) load_as<0>(d, d);
+    }
+  }
+  // slice widths keep the byte offset of a gather below 2^32 (kSortColBits)
+  __device__ __forceinline__ void gather(const T* srcb, int slot, T (&g)[U]) const {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      g[u] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(srcb) +
+                                         (size_t)(uint32_t)((k[slot][u] >> rb) * (uint32_t)sizeof(T)));
+  }
+  // products with srcb (the vector from the block's first column on) added
+  // into the row sums s_row[row << rs] (rs > 0: this lane's copy), which the
+  // block has cleared; s_row[spare]: this lane's word for what lies outside the
+  // block
+  __device__ __forceinline__ void sum(const T* srcb, double* s_row, int spare, int rs = 0) {
+    if (nt) sum_as<2>(srcb, s_row, spare, rs);
+    else sum_as<0>(srcb, s_row, spare, rs);
+  }
+  template <int AUX>
+  __device__ __forceinline__ void sum_as(const T* srcb, double* s_row, int spare, int rs) {
+    const uint32_t rmask = (1u << rb) - 1u;
+    const int nb = (hi + BT - 1) / BT;
+    // positions before the block's first entry hold another block's columns
+    if ((int)threadIdx.x < lo) k[0][0] = 0;
+    T g[2][U];
+    gather(srcb, 0, g[0]);
+    constexpr int RND = NS % 2 ? 2 * NS : NS;  // batches per round: register slots repeat
+    for (int i = 0; i < nb; i += RND) {
+#pragma unroll
+      for (int d = 0; d < RND; ++d) {
+        if (i + d >= nb) break;
+        gather(srcb, (d + 1) % NS, g[(d + 1) & 1]);
+        load_as<AUX>(i + d + D + 1, (d + D + 1) % NS);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = (i + d) * BT + u * TPB + (int)threadIdx.x;
+          const int row = (int)((k[d % NS][u] & rmask) << rs);
+          atomicAdd(&s_row[e >= lo && e < hi ? row : spare], (double)(v[d % NS][u] * g[d & 1][u]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+};
+
+// Clears the LDS row sums of a block (a barrier has to follow).
+__device__ __forceinline__ void clear_rows(double* s_row, int words, int tpb) {
+  for (int r = threadIdx.x; r < words; r += tpb) s_row[r] = 0.0;
 }
 
 // One variable's part of a primal step (rows of K^T): j is its space
@@ -422,107 +517,16 @@ __device__ __forceinline__ void primal_row(const IterArgs<T>& A, const InstState
   }
 }
 
-// Row sums of a column-sorted block (BK_SORTED) for the gathered vector src,
-// left in s_row[0 .. nrows).
-template <class T>
-__device__ __forceinline__ void sorted_pass(const Blk& b, const int32_t* __restrict__ ci,
-                                            const T* __restrict__ val, const T* __restrict__ src, double* s_row) {
-  const int nrows = b.r1 - b.r0;
-  for (int r = threadIdx.x; r < nrows; r += kThreads) s_row[r] = 0.0;
-  lds_barrier();
-  const uint32_t* w = reinterpret_cast<const uint32_t*>(ci);
-  if (blk_nt(b)) sorted_rows_sum<T, true, 4>(b, w, val, src, s_row);
-  else sorted_rows_sum<T, false, 4>(b, w, val, src, s_row);
-  lds_barrier();
-}
-
-// The same, stored to out[b.r0 + r] by the thread that later reads it back
-// (row r is handled by thread r mod kThreads in every loop over a block).
-template <class T>
-__device__ __forceinline__ void sorted_pass_to(const Blk& b, const int32_t* __restrict__ ci,
-                                               const T* __restrict__ val, const T* __restrict__ src, double* s_row,
-                                               T* out) {
-  sorted_pass<T>(b, ci, val, src, s_row);
-  const int nrows = b.r1 - b.r0;
-  for (int r = threadIdx.x; r < nrows; r += kThreads) out[(int64_t)b.r0 + r] = (T)s_row[r];
-  lds_barrier();
-}
-
-// A primal step over a column-sorted block of K^T rows (up to kSortRowsPlain
-// variables): the products with y (yT, cy1, cy2 at an eval step) are added
-// into LDS row sums, then each thread takes the epilogue of every
-// kThreads-th variable.
-template <class T>
-__device__ void primal_sorted(const IterArgs<T>& A, const Blk& b, int step, double* s_row,
-                              double (*s_red)[kNS], double* s_out) {
-  const InstState& S = A.st[b.inst];
-  const int64_t g = *A.gbase + step;
-  const int mode = step_mode(S, g);
-  if (mode == M_SKIP) return;
-  const bool resid = (mode == M_RESID);
-  const int nrows = b.r1 - b.r0;
-  if (mode == M_EVAL) {
-    sorted_pass_to<T>(b, A.KT_ci, A.KT_v, A.cy1, s_row, A.kt1);
-    sorted_pass_to<T>(b, A.KT_ci, A.KT_v, A.cy2, s_row, A.kt2);
-    sorted_pass<T>(b, A.KT_ci, A.KT_v, A.yT, s_row);
-  } else if (!resid) {
-    sorted_pass<T>(b, A.KT_ci, A.KT_v, A.y, s_row);
-  }
-  double ps[kNS];
-#pragma unroll
-  for (int s = 0; s < kNS; ++s) ps[s] = 0.0;
-  for (int r = threadIdx.x; r < nrows; r += kThreads) {
-    const int64_t j = (int64_t)b.r0 + r;
-    const T cj = A.c[j], lj = A.l[j], uj = A.u[j];
-    T xo, x0j, kty, g1 = 0, g2 = 0;
-    if (resid) {
-      xo = A.xT[j];
-      x0j = xo;
-      kty = A.ktyp[j];
-    } else {
-      xo = A.x[j];
-      x0j = A.x0[j];
-      kty = (T)s_row[r];
-      if (mode == M_EVAL) {
-        g1 = A.kt1[j];
-        g2 = A.kt2[j];
-      }
-    }
-    primal_row<T>(A, S, mode, g, j, cj, lj, uj, xo, x0j, kty, g1, g2, ps);
-  }
-  if (mode != M_NORMAL) {
-    block_sum_ns(ps, s_red, s_out);
-    if (threadIdx.x < kNS) A.partP[(int64_t)b.gid * kNS + threadIdx.x] = s_out[threadIdx.x];
-  }
-}
-
-// LDS of a step kernel: the plain tile's products, row sums and row
-// pointers, or the row sums of a column-sorted block (never both).
-template <class T>
-union StepSmem {
-  struct {
-    T prod[Tile<T>::NB];
-    T rsum[3][kMaxRows];
-    int rp[kMaxRows + 1];
-  } p;
-  double rows[kSortRowsPlain];
-};
-
 template <class T>
 __global__ __launch_bounds__(kThreads) void primal_step(IterArgs<T> A, int step) {
-  __shared__ StepSmem<T> sm;
+  __shared__ T s_prod[Tile<T>::NB];
+  __shared__ T s_rsum[3][kMaxRows];
+  __shared__ int s_rp[kMaxRows + 1];
   __shared__ double s_red[kThreads / 64][kNS];
   __shared__ double s_out[kNS];
-  T* s_prod = sm.p.prod;
-  T (*s_rsum)[kMaxRows] = sm.p.rsum;
-  int* s_rp = sm.p.rp;
 
   const Blk b = A.schedP[blockIdx.x];
   if (blk_kind(b) == BK_PAD) return;
-  if (blk_kind(b) == BK_SORTED) {
-    primal_sorted<T>(A, b, step, sm.rows, s_red, s_out);
-    return;
-  }
   const int nrows = b.r1 - b.r0;
   const int t = threadIdx.x;
   const bool own = t < nrows;
@@ -623,13 +627,10 @@ __global__ __launch_bounds__(kThreads) void dual_slice_step(IterArgs<T> A, int s
   slice_body<T, true, NB>(A, step);
 }
 
-// Row sums of one (group, slice) block of a sorted-group product, TPB
-// threads, U entries in flight per thread.  BATCHED: per batch the U entry
-// loads, then the U gathers, then the U LDS adds, with no branch between
-// them (the gathers of a thread in flight together); otherwise each gather
-// is guarded by its own bounds test (a gather waits for the previous add).
-// Both orders of the additions within a row depend on wave timing.
-template <class T, int TPB, int U, bool BATCHED, bool NT>
+// Row sums of one (group, slice) block of a sorted-group product, one gather
+// per add (Options::group_batched = 0): each gather is guarded by its own
+// bounds test and waits for the previous add.
+template <class T, int TPB, int U, bool NT>
 __device__ __forceinline__ void group_rows_sum(const Blk& b, const uint32_t* __restrict__ w,
                                                const T* __restrict__ val, const T* __restrict__ src,
                                                double* s_row) {
@@ -639,57 +640,21 @@ __device__ __forceinline__ void group_rows_sum(const Blk& b, const uint32_t* __r
   const uint32_t* kp = w + b.p0;
   const T* vp = val + b.p0;
   const int pn = b.pn;
-  int e0 = threadIdx.x;
-  if constexpr (BATCHED) {
-    const int full = pn - pn % (TPB * U);
-    for (; e0 < full; e0 += TPB * U) {
-      uint32_t k[U];
-      T v[U], g[U];
+  for (int e0 = threadIdx.x; e0 < pn; e0 += TPB * U) {
+    uint32_t k[U];
+    T v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        k[u] = ld_entry<NT>(kp + e0 + u * TPB);
-        v[u] = ld_entry<NT>(vp + e0 + u * TPB);
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * TPB;
+      if (e < pn) {
+        k[u] = ld_entry<NT>(kp + e);
+        v[u] = ld_entry<NT>(vp + e);
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) g[u] = srcb[k[u] >> rb];
-#pragma unroll
-      for (int u = 0; u < U; ++u) atomicAdd(&s_row[k[u] & rmask], (double)(v[u] * g[u]));
     }
-    if (e0 < pn) {
-      // last partial batch: positions past the block read its first entry
-      // (a valid index) and add nothing
-      uint32_t k[U];
-      T v[U], g[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = e0 + u * TPB;
-        const int ec = e < pn ? e : 0;
-        k[u] = ld_entry<NT>(kp + ec);
-        v[u] = ld_entry<NT>(vp + ec);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) g[u] = srcb[k[u] >> rb];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (e0 + u * TPB < pn) atomicAdd(&s_row[k[u] & rmask], (double)(v[u] * g[u]));
-    }
-  } else {
-    for (; e0 < pn; e0 += TPB * U) {
-      uint32_t k[U];
-      T v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = e0 + u * TPB;
-        if (e < pn) {
-          k[u] = ld_entry<NT>(kp + e);
-          v[u] = ld_entry<NT>(vp + e);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = e0 + u * TPB;
-        if (e < pn) atomicAdd(&s_row[k[u] & rmask], (double)(v[u] * srcb[k[u] >> rb]));
-      }
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * TPB;
+      if (e < pn) atomicAdd(&s_row[k[u] & rmask], (double)(v[u] * srcb[k[u] >> rb]));
     }
   }
 }
@@ -704,26 +669,38 @@ template <class T, bool DUAL, int TPB, bool BATCHED>
 __global__ __launch_bounds__(TPB) void sorted_group_step(IterArgs<T> A, int step) {
   extern __shared__ __align__(16) unsigned char group_lds[];
   double* s_row = reinterpret_cast<double*>(group_lds);
-  const Blk b = (DUAL ? A.schedDS : A.schedPS)[blockIdx.x];
+  auto sched = (cptr<BlkWords>)(DUAL ? A.schedDS : A.schedPS);
+  auto gbase = (cptr<int64_t>)A.gbase;
+  auto states = (cptr<InstState>)A.st;
+  const int32_t* ci = DUAL ? A.K_ci : A.KT_ci;
+  const T* val = DUAL ? A.K_v : A.KT_v;
+  int at = step;
+  asm("" : "+s"(sched), "+s"(gbase), "+s"(states), "+s"(ci), "+s"(val), "+s"(at));
+  const Blk b = load_blk(sched + blockIdx.x);
+  const int64_t g = *gbase + at;
   if (blk_kind(b) == BK_PAD) return;
-  const InstState& S = A.st[b.inst];
-  const int64_t g = *A.gbase + step;
-  const int mode = step_mode(S, g);
+  SortedStream<T, TPB, kGroupEntries / TPB, 1> st;
+  if constexpr (BATCHED) st.open(b, ci, val);  // before the LP state is read
+  const int mode = step_mode(states + b.inst, g);
   if (mode == M_SKIP || (!DUAL && mode == M_RESID)) return;
   const int nrows = b.r1 - b.r0;
   const int sl = blk_slice(b);
   const int nv = mode == M_EVAL ? 3 : 1;
-  const uint32_t* w = reinterpret_cast<const uint32_t*>(DUAL ? A.K_ci : A.KT_ci);
-  const T* val = DUAL ? A.K_v : A.KT_v;
   T* spart = DUAL ? A.spartD : A.spartP;
   const int64_t space = DUAL ? A.MS : A.NS;
   for (int a = 0; a < nv; ++a) {
     const T* src = DUAL ? (mode != M_EVAL ? A.xbar : a == 0 ? A.xT : a == 1 ? A.cx1 : A.cx2)
                         : (mode != M_EVAL ? A.y : a == 0 ? A.yT : a == 1 ? A.cy1 : A.cy2);
-    for (int r = threadIdx.x; r < nrows; r += TPB) s_row[r] = 0.0;
+    clear_rows(s_row, nrows, TPB);
     lds_barrier();
-    if (blk_nt(b)) group_rows_sum<T, TPB, 4, BATCHED, true>(b, w, val, src, s_row);
-    else group_rows_sum<T, TPB, 4, BATCHED, false>(b, w, val, src, s_row);
+    if constexpr (BATCHED) {
+      st.sum(src + b.rp_off, s_row, nrows + (threadIdx.x & 63));
+      if (a + 1 < nv) st.open(b, ci, val);
+    } else if (blk_nt(b)) {
+      group_rows_sum<T, TPB, 4, true>(b, reinterpret_cast<const uint32_t*>(ci), val, src, s_row);
+    } else {
+      group_rows_sum<T, TPB, 4, false>(b, reinterpret_cast<const uint32_t*>(ci), val, src, s_row);
+    }
     lds_barrier();
     for (int r = threadIdx.x; r < nrows; r += TPB)
       spart[(int64_t)(a * kSlices + sl) * space + b.r0 + r] = (T)s_row[r];
@@ -931,67 +908,16 @@ __device__ __forceinline__ void dual_row(const IterArgs<T>& A, const InstState& 
   }
 }
 
-// A dual step over a column-sorted block of K rows (up to kSortRowsPlain
-// constraints): products with xbar (xT, cx1, cx2 at an eval step) added into
-// LDS row sums, then each thread takes the epilogue of every kThreads-th row.
-template <class T>
-__device__ void dual_sorted(const IterArgs<T>& A, const Blk& b, int step, double* s_row, double (*s_red)[kNS],
-                            double* s_out) {
-  const InstState& S = A.st[b.inst];
-  const int64_t g = *A.gbase + step;
-  const int mode = step_mode(S, g);
-  if (mode == M_SKIP) return;
-  const bool resid = (mode == M_RESID);
-  const int nrows = b.r1 - b.r0;
-  if (mode == M_EVAL) {
-    sorted_pass_to<T>(b, A.K_ci, A.K_v, A.cx1, s_row, A.kx1);
-    sorted_pass_to<T>(b, A.K_ci, A.K_v, A.cx2, s_row, A.kx2);
-    sorted_pass<T>(b, A.K_ci, A.K_v, A.xT, s_row);
-  } else {
-    sorted_pass<T>(b, A.K_ci, A.K_v, A.xbar, s_row);
-  }
-  double ps[kNS];
-#pragma unroll
-  for (int s = 0; s < kNS; ++s) ps[s] = 0.0;
-  for (int r = threadIdx.x; r < nrows; r += kThreads) {
-    const int64_t i = (int64_t)b.r0 + r;
-    const T qi = A.q[i];
-    T yo, y0i, kxpi = 0, a1 = 0, a2 = 0;
-    if (resid) {
-      yo = A.yT[i];
-      y0i = yo;
-      kxpi = A.kxp[i];
-    } else {
-      yo = A.y[i];
-      y0i = A.y0[i];
-    }
-    if (mode == M_EVAL) {
-      a1 = A.kx1[i];
-      a2 = A.kx2[i];
-    }
-    dual_row<T>(A, S, mode, g, i, qi, yo, y0i, kxpi, (T)s_row[r], a1, a2, ps);
-  }
-  if (mode != M_NORMAL) {
-    block_sum_ns(ps, s_red, s_out);
-    if (threadIdx.x < kNS) A.partD[(int64_t)b.gid * kNS + threadIdx.x] = s_out[threadIdx.x];
-  }
-}
-
 template <class T>
 __global__ __launch_bounds__(kThreads) void dual_step(IterArgs<T> A, int step) {
-  __shared__ StepSmem<T> sm;
+  __shared__ T s_prod[Tile<T>::NB];
+  __shared__ T s_rsum[3][kMaxRows];
+  __shared__ int s_rp[kMaxRows + 1];
   __shared__ double s_red[kThreads / 64][kNS];
   __shared__ double s_out[kNS];
-  T* s_prod = sm.p.prod;
-  T (*s_rsum)[kMaxRows] = sm.p.rsum;
-  int* s_rp = sm.p.rp;
 
   const Blk b = A.schedD[blockIdx.x];
   if (blk_kind(b) == BK_PAD) return;
-  if (blk_kind(b) == BK_SORTED) {
-    dual_sorted<T>(A, b, step, sm.rows, s_red, s_out);
-    return;
-  }
   const int nrows = b.r1 - b.r0;
   const int t = threadIdx.x;
   const bool own = t < nrows;
@@ -1037,6 +963,138 @@ __global__ __launch_bounds__(kThreads) void dual_step(IterArgs<T> A, int step) {
 
   block_sum_ns(ps, s_red, s_out);
   if (t < kNS) A.partD[(int64_t)b.gid * kNS + t] = s_out[t];
+}
+
+// One step over a column-sorted block (BK_SORTED): a block of K^T rows
+// (DUAL false, a primal step) or of K rows (a dual step).  The products with
+// y (yT, cy1, cy2 at an eval step) or xbar (xT, cx1, cx2) are added into LDS
+// row sums, then each thread takes the epilogue of every TPB-th row.  The
+// first entries and the operands of the thread's first row are loaded before
+// the LP state is read (none depends on it).
+//
+// Where one row holds a large part of a block's entries (blk_rep_shift > 0)
+// its products would queue up at one LDS word; such a block keeps 2^shift
+// copies of each row sum, lane l adding into copy l mod 2^shift.
+// The row sums sit in dynamic LDS (FP64 words for the largest block of the
+// schedule, and kSpareWords).
+template <class T, bool DUAL, int TPB>
+__global__ __launch_bounds__(TPB) void sorted_step(IterArgs<T> A, int step) {
+  extern __shared__ __align__(16) unsigned char sorted_lds[];
+  __shared__ double s_red[TPB / 64][kNS];
+  __shared__ double s_out[kNS];
+  double* s_row = reinterpret_cast<double*>(sorted_lds);
+  // The block starts with a chain of loads: kernel arguments, descriptor,
+  // entries, gathers.  The arguments that the chain needs are tied together so
+  // that they cost one round trip.
+  auto sched = (cptr<BlkWords>)(DUAL ? A.schedDB : A.schedPB);
+  auto gbase = (cptr<int64_t>)A.gbase;
+  auto states = (cptr<InstState>)A.st;
+  const int32_t* ci = DUAL ? A.K_ci : A.KT_ci;
+  const T* val = DUAL ? A.K_v : A.KT_v;
+  // q, y, y0 or c, l, u, x, x0
+  gptr<T> v0 = (gptr<T>)(DUAL ? A.q : A.c), v1 = (gptr<T>)(DUAL ? A.y : A.l), v2 = (gptr<T>)(DUAL ? A.y0 : A.u),
+          v3 = (gptr<T>)A.x, v4 = (gptr<T>)A.x0;
+  int at = step;
+  asm("" : "+s"(sched), "+s"(gbase), "+s"(states), "+s"(ci), "+s"(val), "+s"(v0), "+s"(v1), "+s"(v2), "+s"(v3),
+      "+s"(v4), "+s"(at));
+  const Blk b = load_blk(sched + blockIdx.x);
+  const int64_t g = *gbase + at;
+  if (blk_kind(b) == BK_PAD) return;
+  const int nrows = b.r1 - b.r0;
+  const int tid = threadIdx.x;
+  const int64_t p0 = (int64_t)b.r0 + min(tid, nrows - 1);
+  T o0 = v0[p0], o1 = v1[p0], o2 = v2[p0], o3 = 0, o4 = 0;
+  if constexpr (!DUAL) {
+    o3 = v3[p0];
+    o4 = v4[p0];
+  }
+  SortedStream<T, TPB, kPlainU, kPlainD> st;
+  st.open(b, ci, val);
+  const int rs = blk_rep_shift(b);
+  const int words = nrows << rs;
+  clear_rows(s_row, words, TPB);
+  const int mode = step_mode(states + b.inst, g);
+  if (mode == M_SKIP) return;
+  const InstState& S = A.st[b.inst];
+  const bool resid = (mode == M_RESID);
+  // row sum of row r (its copies added in a fixed order)
+  auto row_sum = [&](int r) -> T {
+    const double* w = s_row + (r << rs);
+    if (rs == 0) return (T)w[0];
+    double a = 0.0;
+    for (int c = 0; c < (1 << rs); c += 8)  // kMinRepShift: at least 8 copies
+      a += ((w[c] + w[c + 1]) + (w[c + 2] + w[c + 3])) + ((w[c + 4] + w[c + 5]) + (w[c + 6] + w[c + 7]));
+    return (T)a;
+  };
+  const int copy = tid & ((1 << rs) - 1);
+  // at an eval step first the two ray candidates (their sums are read back
+  // below by the thread that stores them)
+  const int np = mode == M_EVAL ? 3 : (DUAL || !resid) ? 1 : 0;
+  for (int a = np; a > 0; --a) {
+    const T* src = mode != M_EVAL ? (DUAL ? A.xbar : A.y)
+                   : a == 3       ? (DUAL ? A.cx1 : A.cy1)
+                   : a == 2       ? (DUAL ? A.cx2 : A.cy2)
+                                  : (DUAL ? A.xT : A.yT);
+    lds_barrier();
+    st.sum(src + b.rp_off, s_row + copy, words - copy + (tid & 63), rs);
+    lds_barrier();
+    if (a > 1) {
+      T* out = a == 3 ? (DUAL ? A.kx1 : A.kt1) : (DUAL ? A.kx2 : A.kt2);
+      st.open(b, ci, val);
+      for (int r = tid; r < nrows; r += TPB) out[(int64_t)b.r0 + r] = row_sum(r);
+      lds_barrier();
+      clear_rows(s_row, words, TPB);
+    }
+  }
+  double ps[kNS];
+#pragma unroll
+  for (int s = 0; s < kNS; ++s) ps[s] = 0.0;
+  for (int r = tid; r < nrows; r += TPB) {
+    const int64_t i = (int64_t)b.r0 + r;
+    if constexpr (DUAL) {
+      if (r >= TPB) {
+        o0 = A.q[i];
+        o1 = A.y[i];
+        o2 = A.y0[i];
+      }
+      T kxpi = 0, a1 = 0, a2 = 0;
+      if (resid) {
+        o1 = A.yT[i];
+        o2 = o1;
+        kxpi = A.kxp[i];
+      }
+      if (mode == M_EVAL) {
+        a1 = A.kx1[i];
+        a2 = A.kx2[i];
+      }
+      dual_row<T>(A, S, mode, g, i, o0, o1, o2, kxpi, row_sum(r), a1, a2, ps);
+    } else {
+      if (r >= TPB) {
+        o0 = A.c[i];
+        o1 = A.l[i];
+        o2 = A.u[i];
+        o3 = A.x[i];
+        o4 = A.x0[i];
+      }
+      T kty, g1 = 0, g2 = 0;
+      if (resid) {
+        o3 = A.xT[i];
+        o4 = o3;
+        kty = A.ktyp[i];
+      } else {
+        kty = row_sum(r);
+        if (mode == M_EVAL) {
+          g1 = A.kt1[i];
+          g2 = A.kt2[i];
+        }
+      }
+      primal_row<T>(A, S, mode, g, i, o0, o1, o2, o3, o4, kty, g1, g2, ps);
+    }
+  }
+  if (mode != M_NORMAL) {
+    block_sum_ns<TPB>(ps, s_red, s_out);
+    if (tid < kNS) (DUAL ? A.partD : A.partP)[(int64_t)b.gid * kNS + tid] = s_out[tid];
+  }
 }
 
 // Per-LP control after a step (one workgroup per LP slot): at check, eval

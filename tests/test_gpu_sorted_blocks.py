@@ -1,0 +1,65 @@
+"""Column-sorted blocks at the sizes where their kernel can go wrong: a block
+of one row, rows at the limits of the replicated row sums (a row of 256
+entries or more that dominates its block) and of the sorted blocks (2^15
+entries), blocks whose first entry is not aligned to the kernel's 32-entry
+lines, empty rows and columns, blocks large enough for 512 threads.  Each
+trajectory agrees with the oracle's at the same step size to 1e-10, the bound
+of the other FP64 trajectory tests (both sides round the same sums in another
+order)."""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+import lpgen
+import oracle
+from oracle import core
+
+pytestmark = pytest.mark.gpu
+
+halp = pytest.importorskip("paper_2407_16144_amd")
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+
+def _lp(lens, n, seed, m_eq=None):
+    rng = np.random.default_rng(seed)
+    cols = [np.sort(rng.choice(n, L, replace=False)) for L in lens]
+    col = np.concatenate(cols).astype(np.int32)
+    val = rng.standard_normal(col.size)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    m = len(lens)
+    m_eq = (3 * m) // 4 if m_eq is None else m_eq
+    xs = rng.uniform(1.0, 9.0, n)
+    kx = sp.csr_matrix((val, col, rp), shape=(m, n)) @ xs
+    rhs = np.concatenate([kx[:m_eq], kx[m_eq:] - rng.uniform(0.0, 1.0, m - m_eq)])
+    return lpgen.LP(n, m_eq, m - m_eq, rp, col, val, rng.standard_normal(n), rhs, np.zeros(n), np.full(n, 10.0))
+
+
+CASES = {
+    "one row": lambda: _lp([300], 301, 1, m_eq=1),
+    "one entry per row": lambda: _lp([1] * 33, 40, 2),
+    "copies 255": lambda: _lp([255] + [3] * 30, 600, 3),
+    "copies 256": lambda: _lp([256] + [3] * 30, 600, 4),
+    "copies in a wide block": lambda: _lp([3] * 500 + [2000] + [2] * 700, 2500, 5),
+    "row of 2^15": lambda: _lp([7] * 100 + [1 << 15] + [5] * 50, 40000, 6),
+    "row of 2^15 + 1": lambda: _lp([7] * 100 + [(1 << 15) + 1] + [5] * 50, 40000, 7),
+    "empty rows and columns": lambda: _lp([0, 0, 31, 0, 1, 33, 0] * 12 + [0], 500, 8),
+    "512 threads": lambda: _lp(list(np.random.default_rng(9).integers(200, 420, 8000)), 60000, 9),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_sorted_block_trajectory(name):
+    lp = CASES[name]()
+    print(f"case sorted block {name} m={lp.m} n={lp.n} nnz={lp.nnz}", flush=True)
+    P = core.scaled_problem(lp)
+    s, _ = oracle.power_iteration(P.K, 0, max_iters=30)
+    eta = 0.9 / s
+    opt = halp.lp_default_options(eta=eta)
+    res, x, y, _ = halp.solve_lp(lp, tol=0.0, max_iter=130, opt=opt)
+    ref = oracle.solve(lp, oracle.Options(tol=0.0, max_iter=130, eta=eta))
+    assert res["iters"] == ref.iters and res["restarts"] == ref.restarts
+    for a, b in ((x, ref.x), (y, ref.y)):
+        floor = max(1e-2 * float(np.max(np.abs(b))), 1e-300)
+        assert float(np.max(np.abs(a - b) / np.maximum(np.abs(b), floor))) <= 1e-10
