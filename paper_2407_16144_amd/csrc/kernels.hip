@@ -4,10 +4,12 @@
 //   primal_step : y-gather SpMV over the rows of the explicit K^T, fused with
 //                 the primal PDHG step, box projection and Halpern blend;
 //   dual_step   : xbar-gather SpMV over the rows of K, fused with the dual
-//                 step, cone projection and Halpern blend; the last workgroup
-//                 of each LP (arrival counter) reduces that LP's block partial
-//                 sums in a fixed order and runs its restart / termination
-//                 controller on the device.
+//                 step, cone projection and Halpern blend; at check, eval and
+//                 residual steps the last workgroup of each LP (arrival
+//                 counter) reduces that LP's block partial sums in a fixed
+//                 order and runs its restart / termination controller.
+// Column-sorted blocks of either product run in sorted_step, and the products
+// of large LPs in slice kernels (sorted_group_step) before the step kernels.
 // The path is bandwidth bound (about 2 flop per 12 bytes of matrix), so there
 // is no MFMA: the work is coalesced entry loads, gathers, LDS staging and
 // wave64 shuffle reductions.
@@ -66,15 +68,16 @@ __device__ __forceinline__ T block_sum1(T v, double (*s_red)[kNS]) {
 }
 
 // Fixed-order sum of nb rows of kNS partials; all threads call, result in s_out.
+template <int TPB = kThreads>
 __device__ void sum_partials(const double* part, int nb, double (*s_red)[kNS], double* s_out) {
   double v[kNS];
 #pragma unroll
   for (int s = 0; s < kNS; ++s) v[s] = 0.0;
-  for (int b = threadIdx.x; b < nb; b += kThreads) {
+  for (int b = threadIdx.x; b < nb; b += TPB) {
 #pragma unroll
     for (int s = 0; s < kNS; ++s) v[s] += part[(int64_t)b * kNS + s];
   }
-  block_sum_ns(v, s_red, s_out);
+  block_sum_ns<TPB>(v, s_red, s_out);
 }
 
 __device__ __forceinline__ int group_size(int nrows) {
@@ -283,8 +286,9 @@ __device__ __forceinline__ void gather_slices(const Blk& b, const T* __restrict_
 // step modes
 // ---------------------------------------------------------------------------
 
-// Device memory that no wave of the running kernel writes (schedules, the step
-// counter, LP states in the step kernels): uniform loads of it are scalar.
+// Device memory that no wave of the running kernel writes before the block has
+// read it (schedules, the step counter, an LP's state, which the last of its
+// blocks updates): uniform loads of it are scalar.
 template <class V>
 using cptr = const __attribute__((address_space(4))) V*;
 // Device memory, vector loads.
@@ -832,6 +836,37 @@ __device__ void controller(InstState& S, const double* sp, const double* sd, int
 // dual step (rows of K = constraints) + per-LP controller
 // ---------------------------------------------------------------------------
 
+// End of a check, eval or residual step: the LP's dual blocks (of both step
+// kernels) count themselves in, and the last one sums the partial sums of the
+// step in a fixed order and runs the controller.  Normal steps (61 of 64) do
+// none of this, so the fences, which write back and drop an XCD's L2, are
+// rare; a control kernel of its own cost every step its launch and a round
+// trip for the LP state (1.3 us of 8.8 at 60 x 120, 4.6 us at 20k rows or more).
+// Every other block has read the LP state before it counts itself in.
+template <int TPB, class T>
+__device__ __forceinline__ void finish_step(const IterArgs<T>& A, int inst, int mode, int64_t g,
+                                            double (*s_red)[kNS], double* s_out) {
+  __shared__ double s_sum[kNS];
+  __shared__ int s_last;
+  InstState& S = A.st[inst];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    const int blocks = S.db1 - S.db0;
+    const int last = __hip_atomic_fetch_add(A.cnt + inst, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == blocks - 1;
+    if (last) {
+      A.cnt[inst] = 0;
+      __threadfence();
+    }
+    s_last = last;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  sum_partials<TPB>(A.partP + (int64_t)S.pb0 * kNS, S.pb1 - S.pb0, s_red, s_out);
+  sum_partials<TPB>(A.partD + (int64_t)S.db0 * kNS, S.db1 - S.db0, s_red, s_sum);
+  if (threadIdx.x == 0) controller(S, s_out, s_sum, mode, g, A.status_out, inst);
+}
+
 // One constraint's part of a dual step (rows of K): i is its space
 // position, s0 its row sum (K xbar, or K xT at an eval step, where a1 and a2
 // are K cx1 and K cx2; at a residual step the caller passes T(z) as yo and
@@ -963,6 +998,7 @@ __global__ __launch_bounds__(kThreads) void dual_step(IterArgs<T> A, int step) {
 
   block_sum_ns(ps, s_red, s_out);
   if (t < kNS) A.partD[(int64_t)b.gid * kNS + t] = s_out[t];
+  finish_step<kThreads>(A, b.inst, mode, g, s_red, s_out);
 }
 
 // One step over a column-sorted block (BK_SORTED): a block of K^T rows
@@ -1094,27 +1130,8 @@ __global__ __launch_bounds__(TPB) void sorted_step(IterArgs<T> A, int step) {
   if (mode != M_NORMAL) {
     block_sum_ns<TPB>(ps, s_red, s_out);
     if (tid < kNS) (DUAL ? A.partD : A.partP)[(int64_t)b.gid * kNS + tid] = s_out[tid];
+    if constexpr (DUAL) finish_step<TPB>(A, b.inst, mode, g, s_red, s_out);
   }
-}
-
-// Per-LP control after a step (one workgroup per LP slot): at check, eval
-// and residual steps, the fixed-order sums of the step kernels' per-workgroup
-// partial sums, then the controller.  A kernel of its own, so that the
-// partial sums of every XCD are visible without device-scope fences inside
-// the step kernels (each of which would write back the XCD's L2).
-__global__ __launch_bounds__(kThreads) void control_kernel(InstState* st, const int* ids, const double* partP,
-                                                           const double* partD, const int64_t* gbase,
-                                                           int step, int* status_out) {
-  __shared__ double s_red[kThreads / 64][kNS];
-  __shared__ double s_sum[2][kNS];
-  const int inst = ids[blockIdx.x];  // the LPs in the current schedules
-  InstState& S = st[inst];
-  const int64_t g = *gbase + step;
-  const int mode = step_mode(S, g);
-  if (mode == M_SKIP || mode == M_NORMAL) return;
-  sum_partials(partP + (int64_t)S.pb0 * kNS, S.pb1 - S.pb0, s_red, s_sum[0]);
-  sum_partials(partD + (int64_t)S.db0 * kNS, S.db1 - S.db0, s_red, s_sum[1]);
-  if (threadIdx.x == 0) controller(S, s_sum[0], s_sum[1], mode, g, status_out, inst);
 }
 
 __global__ void tick_kernel(int64_t* gbase, int64_t add) {
