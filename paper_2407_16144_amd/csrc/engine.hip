@@ -227,11 +227,11 @@ static void build_blocks(const int32_t* rp, int64_t nrows, int64_t base, int ins
 // gets a group of its own and "long" slice blocks).  Each group has kSlices
 // slice blocks in `sl` whose entries are stored group-major, then
 // slice-major, then row-major starting at entry position nz0.  `grp` gets
-// epilogue blocks (nsl = kSlices, kMaxRows rows each) that add up the
+// epilogue blocks (nsl = kSlices, part_rows rows each) that add up the
 // slice partial sums.  Row pointers of slice blocks go to brp (positions from brp_base);
 // dst[r * kSlices + s] receives the first position of row r's slice s.
 static void build_sliced(const int32_t* cnt, int64_t nrows, int64_t base, int inst, int NB, int max_rows,
-                         int64_t nz0,
+                         int part_rows, int64_t nz0,
                          int64_t brp_base, std::vector<Blk>& grp, std::vector<Blk>& sl,
                          std::vector<int32_t>& brp, std::vector<int32_t>& dst) {
   std::vector<std::pair<int64_t, int64_t>> groups;
@@ -262,11 +262,11 @@ static void build_sliced(const int32_t* cnt, int64_t nrows, int64_t base, int in
   if (groups.empty()) groups.emplace_back(0, 0);
   dst.assign(nrows * kSlices, 0);
   int64_t pos = nz0;
-  // epilogue blocks: kMaxRows consecutive rows each, independent of the groups
-  for (int64_t a = 0; a < std::max<int64_t>(nrows, 1); a += kMaxRows) {
+  // epilogue blocks: consecutive rows, independent of the groups
+  for (int64_t a = 0; a < std::max<int64_t>(nrows, 1); a += part_rows) {
     Blk ep;
     ep.r0 = (int32_t)(base + a);
-    ep.r1 = (int32_t)(base + std::min<int64_t>(a + kMaxRows, nrows));
+    ep.r1 = (int32_t)(base + std::min<int64_t>(a + part_rows, nrows));
     ep.inst = inst;
     ep.meta = blk_meta(BK_STREAM, kSlices, 0) | kBlkPart;
     ep.gid = (int32_t)grp.size();
@@ -421,8 +421,9 @@ class Engine final : public EngineBase {
   void preprocess(const std::vector<int>& ids, const std::vector<Blk>& nP, const std::vector<Blk>& nD,
                   const std::vector<int4>& nr);
   void slice_matrix(int id, bool dual);
-  void group_sorted(int id, bool dual, int nsl, int64_t rows);
-  bool group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* rows) const;
+  void need_partials(bool dual, int nsl);
+  void group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_t cap);
+  bool group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* ngroups, int64_t* cap) const;
   int group_lds_rows(bool dual) const;
   void sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_rows, bool reblock);
   void reblock_for(const int* status);
@@ -453,7 +454,8 @@ class Engine final : public EngineBase {
     *xT = nullptr, *ktyp = nullptr, *cx1 = nullptr, *cx2 = nullptr, *xs = nullptr;
   // column-sliced layout
   int32_t *brpK = nullptr, *brpKT = nullptr;
-  T *spartD = nullptr, *spartP = nullptr;
+  T *spartD = nullptr, *spartP = nullptr;  // slice partial sums, allocated on first use
+  int nslD_ = 0, nslP_ = 0;                // slices they hold
   T *kt1_ = nullptr, *kt2_ = nullptr, *kx1_ = nullptr, *kx2_ = nullptr;  // sorted blocks' eval products
   uint8_t *actx = nullptr, *acty = nullptr;  // activity at the last check (two-stage diagnostics)
   Blk *d_schedPS = nullptr, *d_schedDS = nullptr;
@@ -463,9 +465,11 @@ class Engine final : public EngineBase {
   int* d_status = nullptr;
   int* d_cnt = nullptr;
   int64_t* d_gbase = nullptr;
-  Blk *d_schedP = nullptr, *d_schedD = nullptr, *d_schedPB = nullptr, *d_schedDB = nullptr;
+  Blk *d_schedP = nullptr, *d_schedD = nullptr, *d_schedPB = nullptr, *d_schedDB = nullptr,
+      *d_schedPE = nullptr, *d_schedDE = nullptr;
   int64_t capP_ = 0, capD_ = 0, nP_ = 0, nD_ = 0;
   int64_t capPB_ = 0, capDB_ = 0, nPB_ = 0, nDB_ = 0;  // column-sorted blocks (sorted_step)
+  int64_t capPE_ = 0, capDE_ = 0, nPE_ = 0, nDE_ = 0;  // rows of sliced products (part_step)
   int64_t cap_partP_ = 0, cap_partD_ = 0;              // blocks that partP / partD hold sums of
   double *partP = nullptr, *partD = nullptr;
   int* h_status[2] = {nullptr, nullptr};
@@ -599,6 +603,8 @@ void Engine<T>::release_all() {
   dfree(d_schedD);
   dfree(d_schedPB);
   dfree(d_schedDB);
+  dfree(d_schedPE);
+  dfree(d_schedDE);
   dfree(partP);
   dfree(partD);
   for (int i = 0; i < 2; ++i) {
@@ -625,6 +631,8 @@ IterArgs<T> Engine<T>::args() const {
   A.brpKT = brpKT;
   A.spartD = spartD;
   A.spartP = spartP;
+  A.nslD = nslD_;
+  A.nslP = nslP_;
   A.kt1 = kt1_;
   A.kt2 = kt2_;
   A.kx1 = kx1_;
@@ -666,6 +674,8 @@ IterArgs<T> Engine<T>::args() const {
   A.schedD = d_schedD;
   A.schedPB = d_schedPB;
   A.schedDB = d_schedDB;
+  A.schedPE = d_schedPE;
+  A.schedDE = d_schedDE;
   A.schedPS = d_schedPS;
   A.schedDS = d_schedDS;
   return A;
@@ -986,12 +996,13 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   compacted_ = false;
   preprocess(ids, nP, nD, nr);
   // Layout of each product.  A product whose gathered vector would not stay
-  // in one XCD's L2 is column-sliced (8 slices): in sorted groups by default,
-  // in row-major slice tiles with slice_sort = 0.  With sorted layouts on, a
-  // product large enough for sorted groups of more rows than a plain sorted
-  // block holds is stored in sorted groups of 1 or 2 slices (larger groups:
-  // more entries share each cache line of the gathered vector).  The other
-  // products get column-sorted plain blocks (plain_sort) or plain tiles.
+  // in one XCD's L2 is column-sliced: in sorted groups by default, in row-major
+  // slice tiles with slice_sort = 0.  With sorted layouts on, a product with
+  // more rows than one plain sorted block per CU holds is stored in sorted
+  // groups of 1 or 2 slices (the fused step of plain blocks is the better one
+  // as long as it fits: 100k x 400k, K^T in 256 plain blocks 36.5 us per
+  // iteration, in 2 slices x 128 groups 40.0).  The other products get
+  // column-sorted plain blocks (plain_sort) or plain tiles.
   const int64_t live_after = live();
   for (int id : ids) {
     const Slot& S = slots_[id];
@@ -1004,13 +1015,13 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
         while (nsl_min < kSlices && width * (int64_t)sizeof(T) > opt_.slice_min_bytes * nsl_min) nsl_min *= 2;
       const bool slice = nsl_min > 1;
       int nsl = 0;
-      int64_t rows = 0;
+      int64_t ngroups = 0, cap = 0;
       if (slice && !opt_.slice_sort) {
         slice_matrix(id, dual);
       } else if (S.nnz > 0 && opt_.slice_sort && (slice || opt_.plain_sort) &&
-                 group_shape(nrows, width, nsl_min, &nsl, &rows) &&
-                 (slice || rows > std::min<int64_t>(opt_.sort_rows, kSortRowsPlain))) {
-        group_sorted(id, dual, nsl, rows);
+                 group_shape(nrows, width, nsl_min, &nsl, &ngroups, &cap) &&
+                 (slice || nrows > kCUs * std::min<int64_t>(opt_.sort_rows, kSortRowsPlain))) {
+        group_sorted(id, dual, nsl, ngroups, cap);
       } else if (opt_.plain_sort) {
         int64_t maxb = 0, minr = 0;
         plain_shape(live_after, &maxb, &minr);
@@ -1223,7 +1234,7 @@ void Engine<T>::slice_matrix(int id, bool dual) {
     dfree(d_cnt);
     throw Error(-2, "no room for sliced row pointers");
   }
-  build_sliced(cnt.data(), nrows, r0, id, NB, opt_.slice_rows, S.nz0, at, grp, sl, brp, dst);
+  build_sliced(cnt.data(), nrows, r0, id, NB, opt_.slice_rows, kPartRows(dual), S.nz0, at, grp, sl, brp, dst);
   if ((int64_t)brp.size() > cap) throw Error(-3, "sliced row pointer overflow");
   ab.release(at + (int64_t)brp.size(), cap - (int64_t)brp.size());
   int32_t* brp_d = dual ? brpK : brpKT;
@@ -1262,9 +1273,21 @@ void Engine<T>::slice_matrix(int id, bool dual) {
     S.brpP0 = at;
     S.brpPn = (int64_t)brp.size();
   }
-  // slice partial sums live in space-sized buffers, allocated on first use
-  if (dual && !spartD) dalloc(&spartD, 3 * kSlices * MS_);
-  if (!dual && !spartP) dalloc(&spartP, 3 * kSlices * NS_);
+  need_partials(dual, kSlices);
+}
+
+// Room for the partial sums of a product of nsl slices (three vectors at an
+// eval step).
+template <class T>
+void Engine<T>::need_partials(bool dual, int nsl) {
+  T*& p = dual ? spartD : spartP;
+  int& have = dual ? nslD_ : nslP_;
+  if (nsl <= have) return;
+  HIPCHECK(hipStreamSynchronize(stream_));
+  dfree(p);
+  have = 0;
+  dalloc(&p, 3 * (int64_t)nsl * (dual ? MS_ : NS_));
+  have = nsl;
 }
 
 
@@ -1461,31 +1484,36 @@ void Engine<T>::sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_r
 // Shape of a sorted-group layout for a product of nrows rows over `width`
 // columns: the slice count, from nsl_min (the fewest that keep a slice of
 // the gathered vector within slice_min_bytes) up to 8 for a product that
-// must be sliced, else 1 or 2, and the rows per group, the largest that
-// leaves at least group_blocks workgroups per product, fits the packed
-// column index (row bits + column bits of a slice <= 32), Options::sort_rows
-// and kSortRows.  More slices allow larger groups of a product with few
+// must be sliced, else 1 or 2, and the number of row groups: the fewest that
+// keep the groups' rows within *cap (the packed column index: row bits +
+// column bits of a slice <= 32, Options::sort_rows and kSortRows) and leave at
+// least group_blocks workgroups per product, rounded up so that every CU has
+// the same number of workgroups.  Larger groups share more lines of the
+// gathered vector, and more slices allow larger groups of a product with few
 // rows; the slice count with the larger groups wins (a tie goes to fewer
 // slices: fewer partial sums).  False when no shape fits.
 template <class T>
-bool Engine<T>::group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* rows) const {
-  int best_s = 0;
+bool Engine<T>::group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* ngroups, int64_t* cap) const {
   int64_t best_r = 0;
-  for (int q = nsl_min; q <= (nsl_min == 1 ? 2 : kSlices); q *= 2) {
+  for (int q = nsl_min; q <= (nsl_min == 1 ? 2 : kGroupSlices); q *= 2) {
     const int64_t w = (width + q - 1) / q + 1;
     int cb = 0;
     while (((int64_t)1 << cb) < w) ++cb;
     if (cb > kSortColBits) continue;
-    int64_t r = std::min<int64_t>(std::min<int64_t>(opt_.sort_rows, kSortRows), (int64_t)1 << (32 - cb));
-    while (r > kMaxRows && ((nrows + r - 1) / r) * q < opt_.group_blocks) r /= 2;
+    const int64_t most = std::min<int64_t>(std::min<int64_t>(opt_.sort_rows, kSortRows), (int64_t)1 << (32 - cb));
+    int64_t blocks = std::max<int64_t>((nrows + most - 1) / most * q, opt_.group_blocks);
+    if (opt_.group_blocks >= kMinGroupBlocks) blocks = (blocks + kCUs - 1) / kCUs * kCUs;
+    const int64_t g = std::max<int64_t>((nrows + most - 1) / most,
+                                        std::min<int64_t>((blocks + q - 1) / q, (nrows + kMaxRows - 1) / kMaxRows));
+    const int64_t r = (nrows + g - 1) / g;
     if (r > best_r) {
       best_r = r;
-      best_s = q;
+      *nsl = q;
+      *ngroups = g;
+      *cap = most;
     }
   }
-  *nsl = best_s;
-  *rows = best_r;
-  return best_s > 0;
+  return best_r > 0;
 }
 
 // Rows of the largest sorted group among the live LPs' K (dual) or K^T
@@ -1507,7 +1535,7 @@ int Engine<T>::group_lds_rows(bool dual) const {
 // row-major block order, a radix sort by (block, key) (keys are unique in a
 // block, so the order is fixed), a gather of the values.
 template <class T>
-void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t rows) {
+void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_t cap) {
   Slot& S = slots_[id];
   const int64_t nrows = dual ? S.m : S.n, r0 = dual ? S.row0 : S.col0, c0 = dual ? S.col0 : S.row0;
   const int64_t len = dual ? S.n : S.m;
@@ -1516,9 +1544,7 @@ void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t rows) {
   T* val = dual ? K_v : KT_v;
   double* v64 = dual ? K_v64 : KT_v64;
   if (nrows == 0 || S.nnz == 0) return;
-  if (nsl < 1 || nsl > kSlices || kSlices % nsl != 0) throw Error(-3, "bad slice count");
-  int rb = 0;
-  while (((int64_t)1 << rb) < rows) ++rb;
+  if (nsl < 1 || nsl > kGroupSlices || kGroupSlices % nsl != 0) throw Error(-3, "bad slice count");
   int32_t* d_cnt = nullptr;
   dalloc(&d_cnt, nrows * nsl);
   slice_count_kernel<<<nblk(nrows), 256, 0, stream_>>>(rp, ci, r0, nrows, c0, len, nsl, d_cnt);
@@ -1526,29 +1552,40 @@ void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t rows) {
   HIPCHECK(hipMemcpyAsync(cnt.data(), d_cnt, sizeof(int32_t) * cnt.size(), hipMemcpyDeviceToHost, stream_));
   HIPCHECK(hipStreamSynchronize(stream_));
   dfree(d_cnt);
-  // groups
+  // groups of equal work (entries and rows): a group ends at the row whose
+  // middle passes the next multiple of the average
   std::vector<std::pair<int64_t, int64_t>> groups;
-  int64_t start = 0;
-  int64_t acc[kSlices] = {0};
+  int64_t start = 0, maxrows = 0;
+  int64_t acc[kGroupSlices] = {0};
+  const double per = (double)(S.nnz + nrows) / (double)ngroups;
+  double cum = 0.0, bound = per;
   for (int64_t r = 0; r < nrows; ++r) {
     const int32_t* c = cnt.data() + r * nsl;
-    bool over = (r - start) >= rows;
+    int64_t w = 1;
+    for (int q = 0; q < nsl; ++q) w += c[q];
+    bool over = (r - start) >= cap || cum + 0.5 * (double)w > bound;
     for (int q = 0; q < nsl; ++q) over |= acc[q] + c[q] > kSortEntries;
     if (over && r > start) {
       groups.emplace_back(start, r);
       start = r;
       for (int q = 0; q < nsl; ++q) acc[q] = 0;
     }
+    if (r == start)
+      while (bound < cum + 0.5 * per) bound += per;
     for (int q = 0; q < nsl; ++q) acc[q] += c[q];
+    cum += (double)w;
   }
   groups.emplace_back(start, nrows);
-  // step-kernel blocks (kMaxRows rows each, row sums from the partials),
+  for (auto& g : groups) maxrows = std::max(maxrows, g.second - g.first);
+  int rb = 0;
+  while (((int64_t)1 << rb) < maxrows) ++rb;
+  // step blocks (row sums from the partials),
   // slice blocks, row-major positions and the row of each row in its group
   std::vector<Blk> grp, sl;
-  for (int64_t a = 0; a < nrows; a += kMaxRows) {
+  for (int64_t a = 0; a < nrows; a += kPartRows(dual)) {
     Blk ep;
     ep.r0 = (int32_t)(r0 + a);
-    ep.r1 = (int32_t)(r0 + std::min<int64_t>(a + kMaxRows, nrows));
+    ep.r1 = (int32_t)(r0 + std::min<int64_t>(a + kPartRows(dual), nrows));
     ep.inst = id;
     ep.meta = blk_meta(BK_STREAM, nsl, 0) | kBlkPart;
     ep.gid = (int32_t)grp.size();
@@ -1558,10 +1595,9 @@ void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t rows) {
     grp.push_back(ep);
   }
   std::vector<int32_t> dst(nrows * nsl), rloc(nrows), off;
-  int64_t pos = S.nz0, maxrows = 0;
+  int64_t pos = S.nz0;
   for (size_t g = 0; g < groups.size(); ++g) {
     const int64_t a = groups[g].first, e = groups[g].second;
-    maxrows = std::max(maxrows, e - a);
     for (int64_t r = a; r < e; ++r) rloc[r] = (int32_t)(r - a);
     for (int q = 0; q < nsl; ++q) {
       Blk k;
@@ -1635,14 +1671,14 @@ void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t rows) {
     S.brpD0 = 0;
     S.brpDn = 0;
     S.rowsD = (int)maxrows;
-    if (!spartD) dalloc(&spartD, 3 * kSlices * MS_);
+    need_partials(true, nsl);
   } else {
     S.bP = grp;
     S.bPS = sl;
     S.brpP0 = 0;
     S.brpPn = 0;
     S.rowsP = (int)maxrows;
-    if (!spartP) dalloc(&spartP, 3 * kSlices * NS_);
+    need_partials(false, nsl);
   }
 }
 
@@ -1740,8 +1776,8 @@ void Engine<T>::mark_streaming(const std::vector<int>& live, std::initializer_li
     const Slot& sl = slots_[s];
     // n-space: c, l, u, x, x0, xbar; m-space: q, y, y0; row pointers; slice partial sums
     used += (int64_t)sizeof(T) * (6 * sl.n + 3 * sl.m) + 4 * (sl.n + sl.m);
-    if (!sl.bDS.empty()) used += (int64_t)(sizeof(T) + 4) * kSlices * sl.m;
-    if (!sl.bPS.empty()) used += (int64_t)(sizeof(T) + 4) * kSlices * sl.n;
+    if (!sl.bDS.empty()) used += (int64_t)sizeof(T) * blk_nsl(sl.bDS[0]) * sl.m + 4 * sl.brpDn;
+    if (!sl.bPS.empty()) used += (int64_t)sizeof(T) * blk_nsl(sl.bPS[0]) * sl.n + 4 * sl.brpPn;
   }
   for (std::vector<Blk>* v : lists) {
     for (Blk& k : *v) {
@@ -1756,20 +1792,21 @@ void Engine<T>::mark_streaming(const std::vector<int>& live, std::initializer_li
 
 template <class T>
 void Engine<T>::rebuild_schedules() {
-  // P / D: tiles and slice-sum blocks of the step kernels; PB / DB: their
-  // column-sorted blocks; PS / DS: slice blocks.  gids number an LP's step
-  // blocks of both kinds in one range.
-  std::vector<Blk> P, D, PB, DB, PS, DS;
+  // P / D: tiles; PB / DB: column-sorted blocks; PE / DE: rows of sliced
+  // products; PS / DS: slice blocks.  gids number an LP's step blocks of all
+  // three kinds in one range.
+  std::vector<Blk> P, D, PB, DB, PE, DE, PS, DS;
   std::vector<int> live;
   std::vector<int4> rg;
   std::vector<std::pair<int, int>> rP, rD, rPB, rDB;
   int gP = 0, gD = 0;
-  auto append = [](std::vector<Blk>& tiles, std::vector<Blk>& sorted, const std::vector<Blk>& src, int& g,
-                   std::vector<std::pair<int, int>>& rt, std::vector<std::pair<int, int>>& rs) {
+  auto append = [](std::vector<Blk>& tiles, std::vector<Blk>& sorted, std::vector<Blk>& part,
+                   const std::vector<Blk>& src, int& g, std::vector<std::pair<int, int>>& rt,
+                   std::vector<std::pair<int, int>>& rs) {
     const int t0 = (int)tiles.size(), s0 = (int)sorted.size();
     for (Blk k : src) {
       k.gid += g;
-      (blk_kind(k) == BK_SORTED ? sorted : tiles).push_back(k);
+      (blk_part(k) ? part : blk_kind(k) == BK_SORTED ? sorted : tiles).push_back(k);
     }
     g += (int)src.size();
     rt.push_back({t0, (int)tiles.size()});
@@ -1784,8 +1821,8 @@ void Engine<T>::rebuild_schedules() {
     r.z = gD;
     PS.insert(PS.end(), sl.bPS.begin(), sl.bPS.end());
     DS.insert(DS.end(), sl.bDS.begin(), sl.bDS.end());
-    append(P, PB, sl.bP, gP, rP, rPB);
-    append(D, DB, sl.bD, gD, rD, rDB);
+    append(P, PB, PE, sl.bP, gP, rP, rPB);
+    append(D, DB, DE, sl.bD, gD, rD, rDB);
     r.y = gP;
     r.w = gD;
     live.push_back(s);
@@ -1858,6 +1895,8 @@ void Engine<T>::rebuild_schedules() {
   upload(D, d_schedD, capD_, nD_);
   upload(PB, d_schedPB, capPB_, nPB_);
   upload(DB, d_schedDB, capDB_, nDB_);
+  upload(PE, d_schedPE, capPE_, nPE_);
+  upload(DE, d_schedDE, capDE_, nDE_);
   upload(PS, d_schedPS, capPS_, nPS_);
   upload(DS, d_schedDS, capDS_, nDS_);
   sums(gP, partP, cap_partP_);
@@ -1970,11 +2009,13 @@ void Engine<T>::launch_chunk() {
       if (timed) HIPCHECK(hipEventRecord(e[1], stream_));
       if (nP_) primal_step<T><<<(unsigned)nP_, kThreads, 0, stream_>>>(A, i);
       if (nPB_) launch_sorted<false>(A, i);
+      if (nPE_) part_step<T, false><<<(unsigned)nPE_, kThreads, 0, stream_>>>(A, i);
       if (timed) HIPCHECK(hipEventRecord(e[2], stream_));
       if (nDS_) launch_slices(true, A, i);
       if (timed) HIPCHECK(hipEventRecord(e[3], stream_));
       if (nD_) dual_step<T><<<(unsigned)nD_, kThreads, 0, stream_>>>(A, i);
       if (nDB_) launch_sorted<true>(A, i);
+      if (nDE_) part_step<T, true><<<(unsigned)nDE_, kThreads, 0, stream_>>>(A, i);
       if (timed) {
         HIPCHECK(hipEventRecord(e[4], stream_));
         HIPCHECK(hipEventRecord(e[5], stream_));  // empty pair: the events' own cost

@@ -33,6 +33,7 @@ enum BlkKind : int { BK_STREAM = 0, BK_LONG = 1, BK_PAD = 2, BK_SORTED = 3 };
 // workgroups (dispatched round-robin over the XCDs) gather from a slice of the
 // vector small enough to stay in that XCD's L2.
 constexpr int kSlices = 8;
+constexpr int kGroupSlices = 8;  // most column slices of a sorted-group product
 constexpr int kPinMinLPs = 16;   // schedules with at least this many LPs pin each LP to one XCD
 enum Status : int { ST_RUNNING = 0, ST_OPTIMAL = 1, ST_PRIMAL_INFEAS = 2, ST_DUAL_INFEAS = 3,
                     ST_ITER_LIMIT = 4, ST_TIME_LIMIT = 5, ST_NUMERICAL = 6 };
@@ -59,6 +60,8 @@ __host__ __device__ inline bool blk_nt(const Blk& b) { return (b.meta & kBlkNT) 
 // partial sums a slice kernel wrote (sliced or sorted-group products).
 constexpr int32_t kBlkPart = 1 << 30;
 __host__ __device__ inline bool blk_part(const Blk& b) { return (b.meta & kBlkPart) != 0; }
+// Rows per kBlkPart block of K (dual) and of K^T.
+__host__ __device__ constexpr int kPartRows(bool dual) { return dual ? 512 : 1024; }
 
 // Column-sorted row groups (a product stored as "sorted groups": K when its
 // gathered vector is larger than Options::slice_min_bytes, and either

@@ -44,9 +44,10 @@ struct IterArgs {
   T* cy2;
   T* ys;     // average PDHG: sum of the epoch's iterates y^{n,0..k}
   uint8_t* acty;  // activity of y+ at the last check: 1 at zero (inequality rows), 0 else
-  // slice partial row sums of sliced row groups: [3][kSlices][space]
+  // slice partial row sums of sliced row groups: [3][nsl][space]
   T* spartD;   // m-space (dual step)
   T* spartP;   // n-space (primal step)
+  int nslD, nslP;  // most slices of a product in the engine
   // eval-step products of column-sorted blocks with the ray candidates:
   // K^T cy1, K^T cy2 (n-space) and K cx1, K cx2 (m-space)
   T* kt1;
@@ -61,10 +62,12 @@ struct IterArgs {
   int* status_out;
   double* partP;
   double* partD;
-  const Blk* schedP;   // one block per row group (primal / dual step kernels)
+  const Blk* schedP;   // tiles (primal / dual step kernels)
   const Blk* schedD;
   const Blk* schedPB;  // column-sorted blocks (sorted_step), gids shared with schedP / schedD
   const Blk* schedDB;
+  const Blk* schedPE;  // rows whose products the slice kernels computed (part_step)
+  const Blk* schedDE;
   const Blk* schedPS;  // slice blocks of sliced row groups (slice kernel)
   const Blk* schedDS;
 };

@@ -73,6 +73,7 @@ __device__ void sum_partials(const double* part, int nb, double (*s_red)[kNS], d
   double v[kNS];
 #pragma unroll
   for (int s = 0; s < kNS; ++s) v[s] = 0.0;
+#pragma unroll 2
   for (int b = threadIdx.x; b < nb; b += TPB) {
 #pragma unroll
     for (int s = 0; s < kNS; ++s) v[s] += part[(int64_t)b * kNS + s];
@@ -253,33 +254,6 @@ __device__ __forceinline__ void block_spmv(const Blk& b, const int32_t* __restri
   TileRegs<T, kPlainNB> R;
   load_tile<T, kPlainNB>(b, rp, ci, val, R);
   block_spmv_regs<T, NV, kPlainNB>(b, ci, val, R, s0, s1, s2, s_prod, s_rsum, s_rp, s_red, scale0);
-}
-
-// Row sums of a row group whose products a slice kernel computed: the
-// blk_nsl(b) partial sums per row, added in slice order.
-template <class T, int NV>
-__device__ __forceinline__ void gather_slices(const Blk& b, const T* __restrict__ spart, int64_t space,
-                                              T (*s_rsum)[kMaxRows]) {
-  const int nrows = b.r1 - b.r0;
-  const int nsl = blk_nsl(b);
-  const int t = threadIdx.x;
-  if (t < nrows) {
-    // one vector at a time: its partial loads in flight together, but not
-    // the NV * nsl of all vectors (they would set the register budget of the
-    // whole step kernel)
-#pragma unroll 1
-    for (int a = 0; a < NV; ++a) {
-      T part[kSlices];
-#pragma unroll
-      for (int q = 0; q < kSlices; ++q)
-        part[q] = q < nsl ? spart[(int64_t)(a * kSlices + q) * space + b.r0 + t] : (T)0;
-      T acc = part[0];
-#pragma unroll
-      for (int q = 1; q < kSlices; ++q)
-        if (q < nsl) acc += part[q];
-      s_rsum[a][t] = acc;
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -558,10 +532,7 @@ __global__ __launch_bounds__(kThreads) void primal_step(IterArgs<T> A, int step)
     x0j = xo;
     kty = A.ktyp[j];
   }
-  if (blk_part(b)) {
-    if (mode == M_EVAL) gather_slices<T, 3>(b, A.spartP, A.NS, s_rsum);
-    else if (!resid) gather_slices<T, 1>(b, A.spartP, A.NS, s_rsum);
-  } else if (mode == M_EVAL) {
+  if (mode == M_EVAL) {
     block_spmv_regs<T, 3, kPlainNB>(b, A.KT_ci, A.KT_v, R, A.yT, A.cy1, A.cy2, s_prod, s_rsum, s_rp, s_red);
   } else if (!resid) {
     block_spmv1<T, kPlainNB>(b, A.KT_ci, A.KT_v, R, A.y, s_prod, s_rsum[0], s_rp, s_red, (T)1, true);
@@ -616,7 +587,7 @@ __device__ __forceinline__ void slice_body(const IterArgs<T>& A, int step) {
   const int nrows = b.r1 - b.r0;
   const int sl = blk_slice(b);
   for (int r = threadIdx.x; r < nrows; r += kThreads)
-    for (int a = 0; a < nv; ++a) spart[(int64_t)(a * kSlices + sl) * space + b.r0 + r] = s_rsum[a][r];
+    for (int a = 0; a < nv; ++a) spart[(int64_t)(a * (dual ? A.nslD : A.nslP) + sl) * space + b.r0 + r] = s_rsum[a][r];
 }
 
 // NB: entries per slice tile (kSliceTiles lists the compiled sizes; the
@@ -707,7 +678,7 @@ __global__ __launch_bounds__(TPB) void sorted_group_step(IterArgs<T> A, int step
     }
     lds_barrier();
     for (int r = threadIdx.x; r < nrows; r += TPB)
-      spart[(int64_t)(a * kSlices + sl) * space + b.r0 + r] = (T)s_row[r];
+      spart[(int64_t)(a * (DUAL ? A.nslD : A.nslP) + sl) * space + b.r0 + r] = (T)s_row[r];
     lds_barrier();
   }
 }
@@ -977,10 +948,7 @@ __global__ __launch_bounds__(kThreads) void dual_step(IterArgs<T> A, int step) {
     y0i = yo;
     kxpi = A.kxp[i];
   }
-  if (blk_part(b)) {
-    if (mode == M_EVAL) gather_slices<T, 3>(b, A.spartD, A.MS, s_rsum);
-    else gather_slices<T, 1>(b, A.spartD, A.MS, s_rsum);
-  } else if (mode == M_EVAL) {
+  if (mode == M_EVAL) {
     block_spmv_regs<T, 3, kPlainNB>(b, A.K_ci, A.K_v, R, A.xT, A.cx1, A.cx2, s_prod, s_rsum, s_rp, s_red);
   } else {
     block_spmv1<T, kPlainNB>(b, A.K_ci, A.K_v, R, A.xbar, s_prod, s_rsum[0], s_rp, s_red, (T)1, true);
@@ -1131,6 +1099,112 @@ __global__ __launch_bounds__(TPB) void sorted_step(IterArgs<T> A, int step) {
     block_sum_ns<TPB>(ps, s_red, s_out);
     if (tid < kNS) (DUAL ? A.partD : A.partP)[(int64_t)b.gid * kNS + tid] = s_out[tid];
     if constexpr (DUAL) finish_step<TPB>(A, b.inst, mode, g, s_red, s_out);
+  }
+}
+
+// The step of rows whose products a slice kernel computed (kBlkPart blocks of
+// up to kPartRows rows): a row's nsl slice partial sums, added in slice order,
+// then its epilogue.  Streaming work (9 vectors and the partial sums): each
+// thread takes RPT rows, kThreads apart, and issues their loads together,
+// before the LP state is read.  1024 variables or 512 constraints per block
+// instead of 256 also leave fewer partial sums to the controller.
+template <class T, bool DUAL>
+__global__ __launch_bounds__(kThreads) void part_step(IterArgs<T> A, int step) {
+  constexpr int RPT = kPartRows(DUAL) / kThreads;
+  __shared__ double s_red[kThreads / 64][kNS];
+  __shared__ double s_out[kNS];
+  const Blk b = load_blk((cptr<BlkWords>)(DUAL ? A.schedDE : A.schedPE) + blockIdx.x);
+  if (blk_kind(b) == BK_PAD) return;
+  const int64_t g = *(cptr<int64_t>)A.gbase + step;
+  const int nrows = b.r1 - b.r0, nsl = blk_nsl(b);
+  const int tid = threadIdx.x;
+  const int64_t space = DUAL ? A.MS : A.NS;
+  const T* spart = (DUAL ? A.spartD : A.spartP) + b.r0;
+  int r[RPT];
+  T o[RPT][DUAL ? 3 : 5];  // q, y, y0 or c, l, u, x, x0
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    r[k] = min(tid + k * kThreads, max(nrows - 1, 0));
+    const int64_t i = (int64_t)b.r0 + r[k];
+    if constexpr (DUAL) {
+      o[k][0] = A.q[i];
+      o[k][1] = A.y[i];
+      o[k][2] = A.y0[i];
+    } else {
+      o[k][0] = A.c[i];
+      o[k][1] = A.l[i];
+      o[k][2] = A.u[i];
+      o[k][3] = A.x[i];
+      o[k][4] = A.x0[i];
+    }
+  }
+  // sums of vector a's partials (a > 0: the ray candidates of an eval step),
+  // added in slice order, four slices' loads in flight together
+  auto sums = [&](int a, T (&acc)[RPT]) {
+    const T* p = spart + (int64_t)a * (DUAL ? A.nslD : A.nslP) * space;
+    if (nsl <= 2) {
+      T v[2][RPT];
+#pragma unroll
+      for (int k = 0; k < RPT; ++k) {
+        v[0][k] = p[r[k]];
+        v[1][k] = nsl == 2 ? p[space + r[k]] : (T)0;
+      }
+#pragma unroll
+      for (int k = 0; k < RPT; ++k) acc[k] = nsl == 2 ? v[0][k] + v[1][k] : v[0][k];
+      return;
+    }
+    for (int q = 0; q < nsl; q += 4, p += 4 * space) {
+      T v[4][RPT];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) v[j][k] = p[j * space + r[k]];
+#pragma unroll
+      for (int k = 0; k < RPT; ++k)
+        acc[k] = (q == 0 ? v[0][k] : acc[k] + v[0][k]) + v[1][k] + v[2][k] + v[3][k];
+    }
+  };
+  const int mode = step_mode((cptr<InstState>)A.st + b.inst, g);
+  if (mode == M_SKIP) return;
+  const InstState& S = A.st[b.inst];
+  const bool resid = (mode == M_RESID);
+  T s0[RPT], s1[RPT], s2[RPT];
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) s0[k] = s1[k] = s2[k] = 0;
+  if (DUAL || !resid) sums(0, s0);
+  if (mode == M_EVAL) {
+    sums(1, s1);
+    sums(2, s2);
+  }
+  double ps[kNS];
+#pragma unroll
+  for (int s = 0; s < kNS; ++s) ps[s] = 0.0;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    if (tid + k * kThreads < nrows) {
+      const int64_t i = (int64_t)b.r0 + r[k];
+      if constexpr (DUAL) {
+        T kxpi = 0;
+        if (resid) {
+          o[k][1] = A.yT[i];
+          o[k][2] = o[k][1];
+          kxpi = A.kxp[i];
+        }
+        dual_row<T>(A, S, mode, g, i, o[k][0], o[k][1], o[k][2], kxpi, s0[k], s1[k], s2[k], ps);
+      } else {
+        if (resid) {
+          o[k][3] = A.xT[i];
+          o[k][4] = o[k][3];
+          s0[k] = A.ktyp[i];
+        }
+        primal_row<T>(A, S, mode, g, i, o[k][0], o[k][1], o[k][2], o[k][3], o[k][4], s0[k], s1[k], s2[k], ps);
+      }
+    }
+  }
+  if (mode != M_NORMAL) {
+    block_sum_ns(ps, s_red, s_out);
+    if (tid < kNS) (DUAL ? A.partD : A.partP)[(int64_t)b.gid * kNS + tid] = s_out[tid];
+    if constexpr (DUAL) finish_step<kThreads>(A, b.inst, mode, g, s_red, s_out);
   }
 }
 

@@ -93,8 +93,8 @@ __global__ void slice_count_kernel(const int32_t* rp, const int32_t* ci, int64_t
                                    int64_t c0, int64_t len, int nsl, int32_t* cnt) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= nrows) return;
-  int32_t c[kSlices];
-  for (int q = 0; q < kSlices; ++q) c[q] = 0;
+  int32_t c[kGroupSlices];
+  for (int q = 0; q < kGroupSlices; ++q) c[q] = 0;
   for (int32_t e = rp[r0 + r]; e < rp[r0 + r + 1]; ++e) {
     const int q = (int)(((int64_t)(ci[e] - c0) * nsl) / len);
     c[q] += 1;
@@ -130,7 +130,7 @@ __global__ void slice_keys_kernel(const int32_t* rp, const int32_t* ci, int64_t 
                                   uint32_t* key_out, int32_t* src_out) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= nrows) return;
-  int32_t d[kSlices];
+  int32_t d[kGroupSlices];
   for (int q = 0; q < nsl; ++q) d[q] = dst[r * nsl + q];
   for (int32_t e = rp[r0 + r]; e < rp[r0 + r + 1]; ++e) {
     const int64_t c = ci[e] - c0;
