@@ -317,6 +317,10 @@ static void plain_shape(int64_t live, int64_t* max_blocks, int64_t* min_rows) {
   *min_rows = std::max<int64_t>(16, std::min<int64_t>(256, 8 * live));
 }
 
+// Entries that one sort of plain blocks takes together at most (48 bytes of
+// temporary memory each).
+constexpr int64_t kSortRun = 1 << 26;
+
 struct Slot {
   bool used = false;
   int64_t n = 0, m = 0, m_eq = 0, nnz = 0;
@@ -425,7 +429,10 @@ class Engine final : public EngineBase {
   void group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_t cap);
   bool group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* ngroups, int64_t* cap) const;
   int group_lds_rows(bool dual) const;
-  void sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_rows, bool reblock);
+  std::vector<Blk> cut_blocks(int id, bool dual, const int32_t* rp, int64_t max_blocks, int64_t min_rows, int* rb,
+                              int* cb) const;
+  void sort_blocks(const std::vector<int>& ids, bool dual, const std::vector<const int32_t*>& rps, int64_t max_blocks,
+                   int64_t min_rows, bool reblock, int64_t max_entries);
   void reblock_for(const int* status);
   IterArgs<T> args() const;
   void pull_states();
@@ -972,11 +979,17 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     transpose_group(F.nz0, L.nz0 + L.nnz - F.nz0, F.col0, L.col0 + L.n, bD);
     k = e;
   }
+  std::vector<std::vector<int32_t>> host_rpT(probs.size());
+  for (size_t t = 0; t < probs.size(); ++t) {
+    const Slot& S = slots_[ids[t]];
+    host_rpT[t].resize(S.n + 1);
+    HIPCHECK(hipMemcpyAsync(host_rpT[t].data(), KT_rp + S.col0, sizeof(int32_t) * (S.n + 1), hipMemcpyDeviceToHost,
+                            stream_));
+  }
+  HIPCHECK(hipStreamSynchronize(stream_));
   for (size_t t = 0; t < probs.size(); ++t) {
     Slot& S = slots_[ids[t]];
-    std::vector<int32_t> krp(S.n + 1);
-    HIPCHECK(hipMemcpy(krp.data(), KT_rp + S.col0, sizeof(int32_t) * (S.n + 1), hipMemcpyDeviceToHost));
-    build_blocks(krp.data(), S.n, S.col0, ids[t], NB, opt_.tile_rows, S.bP);
+    build_blocks(host_rpT[t].data(), S.n, S.col0, ids[t], NB, opt_.tile_rows, S.bP);
   }
 
   // 4. temporary schedules of the new LPs, preprocessing, power iteration
@@ -1003,8 +1016,10 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   // as long as it fits: 100k x 400k, K^T in 256 plain blocks 36.5 us per
   // iteration, in 2 slices x 128 groups 40.0).  The other products get
   // column-sorted plain blocks (plain_sort) or plain tiles.
-  const int64_t live_after = live();
-  for (int id : ids) {
+  std::vector<int> plain[2];  // LPs whose K^T / K gets column-sorted plain blocks
+  std::vector<const int32_t*> plain_rp[2];
+  for (size_t t = 0; t < ids.size(); ++t) {
+    const int id = ids[t];
     const Slot& S = slots_[id];
     for (const bool dual : {true, false}) {
       const int64_t nrows = dual ? S.m : S.n, width = dual ? S.n : S.m;
@@ -1023,12 +1038,15 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
                  (slice || nrows > kCUs * std::min<int64_t>(opt_.sort_rows, kSortRowsPlain))) {
         group_sorted(id, dual, nsl, ngroups, cap);
       } else if (opt_.plain_sort) {
-        int64_t maxb = 0, minr = 0;
-        plain_shape(live_after, &maxb, &minr);
-        sort_blocks(id, dual, maxb, minr, false);
+        plain[dual].push_back(id);
+        plain_rp[dual].push_back((dual ? host_rp[t] : host_rpT[t]).data());
       }
     }
   }
+  int64_t maxb = 0, minr = 0;
+  plain_shape(live(), &maxb, &minr);
+  for (const bool dual : {true, false})
+    sort_blocks(plain[dual], dual, plain_rp[dual], maxb, minr, false, kSortRun);
   sched_dirty_ = true;
   for (int id : ids) slots_[id].watched = true;
   return ids;
@@ -1309,54 +1327,55 @@ void Engine<T>::reblock_for(const int* status) {
   int64_t maxb = 0, minr = 0;
   plain_shape((int64_t)run.size(), &maxb, &minr);
   bool changed = false;
-  for (int s : run) {
-    for (int d = 0; d < 2; ++d) {
-      const bool dual = d == 1;
+  for (const bool dual : {false, true}) {
+    std::vector<int> ids;
+    std::vector<std::vector<int32_t>> rp;
+    std::vector<const int32_t*> rps;
+    int64_t largest = 0;
+    for (int s : run) {
       const Slot& S = slots_[s];
-      const int64_t cur = dual ? S.plainD : S.plainP;
-      if (cur == 0) continue;
-      if (plain_blocks(dual ? S.m : S.n, maxb, minr) > cur) {
-        sort_blocks(s, dual, maxb, minr, true);
-        changed = true;
-      }
+      const int64_t cur = dual ? S.plainD : S.plainP, nrows = dual ? S.m : S.n;
+      if (cur == 0 || plain_blocks(nrows, maxb, minr) <= cur) continue;
+      ids.push_back(s);
+      largest = std::max(largest, S.nnz);
+      rp.emplace_back(nrows + 1);
+      HIPCHECK(hipMemcpy(rp.back().data(), (dual ? K_rp : KT_rp) + (dual ? S.row0 : S.col0),
+                         sizeof(int32_t) * (nrows + 1), hipMemcpyDeviceToHost));
     }
+    if (ids.empty()) continue;
+    for (auto& v : rp) rps.push_back(v.data());
+    // temporary memory for the largest of them, as a server's budget allows
+    sort_blocks(ids, dual, rps, maxb, minr, true, largest);
+    changed = true;
   }
   if (changed) sched_dirty_ = true;
 }
 
-// Column-sorted blocks of one LP's K (dual = true) or K^T, for a product
-// that is not column-sliced: rows longer than a plain tile keep a long
-// block; the other rows go to blocks of at most min(sort_rows,
-// kSortRowsPlain, max(min_rows, rows / min_blocks)) rows and kSortEntries
-// entries whose entries are put in column order, each column index packed
-// with the entry's row in the block (see blk_rowbits).  Built on the device:
-// a 64-bit key per entry (block index, packed key) and one stable radix
-// sort.  From the row-major input (reblock false), or re-blocking a product
-// already in column-sorted blocks into smaller ones (reblock true: each
-// entry's row and column are read back from its packed key).
+// Column-sorted blocks of one LP's K (dual = true) or K^T over its row pointers
+// rp (space positions): rows longer than kSortedRowMax keep a block of their
+// own; the other rows go to blocks of equal work, of at most min(sort_rows,
+// kSortRowsPlain) rows and kSortEntries entries, whose entries are put in
+// column order, each column index packed with the entry's row in the block
+// (see blk_rowbits).  *rb: row bits, *cb: column bits.
 template <class T>
-void Engine<T>::sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_rows, bool reblock) {
-  Slot& S = slots_[id];
+std::vector<Blk> Engine<T>::cut_blocks(int id, bool dual, const int32_t* rp, int64_t max_blocks, int64_t min_rows,
+                                       int* rb_out, int* cb_out) const {
+  const Slot& S = slots_[id];
   const int64_t nrows = dual ? S.m : S.n;
   const int64_t base = dual ? S.row0 : S.col0;
   const int64_t c0 = dual ? S.col0 : S.row0;
   const int64_t width = dual ? S.n : S.m;
-  const int32_t* rpd = dual ? K_rp : KT_rp;
-  int32_t* ci = dual ? K_ci : KT_ci;
-  T* val = dual ? K_v : KT_v;
-  double* v64 = dual ? K_v64 : KT_v64;
-  if (nrows == 0 || S.nnz == 0) return;
+  std::vector<Blk> out;
   int cb = 0;
   while (((int64_t)1 << cb) < width) ++cb;
-  if (cb > kSortColBits) return;
+  *cb_out = cb;
+  if (nrows == 0 || S.nnz == 0 || cb > kSortColBits) return out;
   // most rows per block: the packed index holds the column and the row in 32 bits
   const int64_t rows =
       std::min<int64_t>(std::min<int64_t>(opt_.sort_rows, kSortRowsPlain), (int64_t)1 << (32 - std::min(cb, 31)));
   int rb = 0;
   while (((int64_t)1 << rb) < rows) ++rb;
-  std::vector<int32_t> rp(nrows + 1);
-  HIPCHECK(hipMemcpy(rp.data(), rpd + base, sizeof(int32_t) * (nrows + 1), hipMemcpyDeviceToHost));
-  std::vector<Blk> out, sorted;
+  *rb_out = rb;
   int64_t longest_row = 0;  // of the block being filled
   auto emit = [&](int64_t a, int64_t e, int kind) {
     Blk k;
@@ -1373,9 +1392,6 @@ void Engine<T>::sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_r
     if (rs < kMinRepShift) rs = 0;
     k.meta = blk_meta(kind, 1, rs) | (kind == BK_SORTED ? (rb << 25) : 0);
     out.push_back(k);
-    if (kind == BK_SORTED) {
-      sorted.push_back(k);
-    }
     longest_row = 0;
   };
   // blocks of equal weight (entries, and kRowWeight per row for its epilogue):
@@ -1407,63 +1423,118 @@ void Engine<T>::sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_r
     cum += w;
   }
   if (nrows > start) emit(start, nrows, BK_SORTED);
-  if (!sorted.empty()) {
-    // one stable sort of the LP's entries by (block, key): the entries of
-    // BK_SORTED blocks end in column order, all others where they were
-    const int64_t nnz = S.nnz;
-    const int nseg = (int)sorted.size();
-    const int nall = (int)out.size();
-    Blk *d_all = nullptr, *d_blk = nullptr;
+  return out;
+}
+
+// Column-sorts the K (dual = true) or K^T products of the LPs `ids` into blocks
+// (cut_blocks).  rps[k]: LP k's row pointers on the host.  Built on the device
+// for all of them together: a 64-bit key per entry (block index, packed column
+// and row) and one stable radix sort by block and column (rows of a column
+// come in order), where a sort per LP spent 75 ms on a batch of 128 in kernels
+// of a few microseconds.  From the row-major input (reblock false), or
+// re-blocking products already in column-sorted blocks into smaller ones
+// (reblock true: each entry's row and column are read back from its packed
+// key).  The LPs are taken in runs of at most max_entries entries (at least
+// one LP), which bounds the temporary memory.
+template <class T>
+void Engine<T>::sort_blocks(const std::vector<int>& ids, bool dual, const std::vector<const int32_t*>& rps,
+                            int64_t max_blocks, int64_t min_rows, bool reblock, int64_t max_entries) {
+  const int32_t* rpd = dual ? K_rp : KT_rp;
+  int32_t* ci = dual ? K_ci : KT_ci;
+  T* val = dual ? K_v : KT_v;
+  double* v64 = dual ? K_v64 : KT_v64;
+  size_t next = 0;
+  while (next < ids.size()) {
+    std::vector<int> lps;                  // of this run
+    std::vector<std::vector<Blk>> blocks;  // their new blocks
+    std::vector<Blk> all, sorted, old;     // for the kernels: gid holds the shift of positions into the key arrays
+    std::vector<int2> where;               // reblock: each row's new block and its row in that block
+    int64_t total = 0;
+    int rb_min = 32, key_bits = 1;
+    for (; next < ids.size(); ++next) {
+      const int id = ids[next];
+      const Slot& S = slots_[id];
+      if (total > 0 && total + S.nnz > max_entries) break;
+      int rb = 0, cb = 0;
+      std::vector<Blk> out = cut_blocks(id, dual, rps[next], max_blocks, min_rows, &rb, &cb);
+      if (out.empty()) continue;
+      const int32_t shift = (int32_t)(total - S.nz0);
+      const int64_t base = dual ? S.row0 : S.col0, nrows = dual ? S.m : S.n;
+      const int first = (int)all.size();
+      int32_t longest = 0;
+      bool any = false;
+      for (const Blk& k : out) {
+        Blk d = k;
+        d.gid = shift;
+        all.push_back(d);
+        any |= blk_kind(k) == BK_SORTED;
+        if (blk_kind(k) == BK_SORTED) sorted.push_back(d);
+        else longest = std::max(longest, k.pn);
+      }
+      if (!any) {  // nothing to sort: the blocks alone
+        all.resize(first);
+        Slot& W = slots_[id];
+        (dual ? W.plainD : W.plainP) = 0;
+        (dual ? W.bD : W.bP) = out;
+        continue;
+      }
+      if (reblock) {
+        const int32_t to_where = (int32_t)((int64_t)where.size() - base);
+        for (const Blk& k : dual ? S.bD : S.bP) {
+          Blk d = k;
+          d.gid = shift;
+          d.rp_off = to_where;
+          d.meta = (k.meta & ~0xff00) | (rb << 8);
+          old.push_back(d);
+        }
+        where.resize(where.size() + nrows);
+        for (size_t bi = 0; bi < out.size(); ++bi)
+          for (int32_t r = out[bi].r0; r < out[bi].r1; ++r)
+            where[(int64_t)r + to_where] = make_int2(first + (int)bi, r - out[bi].r0);
+      }
+      rb_min = std::min(rb_min, rb);
+      key_bits = std::max(key_bits, std::max(std::min(32, cb + rb), bits_for(longest)));
+      total += S.nnz;
+      lps.push_back(id);
+      blocks.push_back(std::move(out));
+    }
+    if (lps.empty()) continue;
+    Blk *d_all = nullptr, *d_blk = nullptr, *d_old = nullptr;
+    int2* d_where = nullptr;
     int32_t *src_in = nullptr, *src_out = nullptr;
     uint64_t *key_in = nullptr, *key_out = nullptr;
     T* v_tmp = nullptr;
     double* v64_tmp = nullptr;
+    const unsigned nall = (unsigned)all.size(), nseg = (unsigned)sorted.size();
     dalloc(&d_all, nall);
     dalloc(&d_blk, nseg);
-    dalloc(&key_in, nnz);
-    dalloc(&key_out, nnz);
-    dalloc(&src_in, nnz);
-    dalloc(&src_out, nnz);
-    dalloc(&v_tmp, nnz);
-    if (sizeof(T) != 8) dalloc(&v64_tmp, nnz);
-    HIPCHECK(hipMemcpyAsync(d_all, out.data(), sizeof(Blk) * nall, hipMemcpyHostToDevice, stream_));
+    dalloc(&key_in, total);
+    dalloc(&key_out, total);
+    dalloc(&src_in, total);
+    dalloc(&src_out, total);
+    dalloc(&v_tmp, total);
+    if (sizeof(T) != 8) dalloc(&v64_tmp, total);
+    HIPCHECK(hipMemcpyAsync(d_all, all.data(), sizeof(Blk) * nall, hipMemcpyHostToDevice, stream_));
     HIPCHECK(hipMemcpyAsync(d_blk, sorted.data(), sizeof(Blk) * nseg, hipMemcpyHostToDevice, stream_));
-    HIPCHECK(hipMemcpyAsync(v_tmp, val + S.nz0, sizeof(T) * nnz, hipMemcpyDeviceToDevice, stream_));
-    if (v64_tmp)
-      HIPCHECK(hipMemcpyAsync(v64_tmp, v64 + S.nz0, sizeof(double) * nnz, hipMemcpyDeviceToDevice, stream_));
-    Blk* d_old = nullptr;
-    int2* d_where = nullptr;
     if (!reblock) {
-      block_keys_kernel<<<(unsigned)nall, kThreads, 0, stream_>>>(d_all, rpd, ci, S.nz0, key_in, src_in);
+      block_keys_kernel<<<nall, kThreads, 0, stream_>>>(d_all, rpd, ci, key_in, src_in);
     } else {
-      // each row's new block and its row in that block
-      const std::vector<Blk>& old_blocks = dual ? S.bD : S.bP;
-      std::vector<int2> where(nrows);
-      for (int bi = 0; bi < nall; ++bi)
-        for (int32_t r = out[bi].r0; r < out[bi].r1; ++r) where[r - base] = make_int2(bi, r - out[bi].r0);
-      dalloc(&d_old, (int64_t)old_blocks.size());
-      dalloc(&d_where, nrows);
-      HIPCHECK(hipMemcpyAsync(d_old, old_blocks.data(), sizeof(Blk) * old_blocks.size(), hipMemcpyHostToDevice,
-                              stream_));
-      HIPCHECK(hipMemcpyAsync(d_where, where.data(), sizeof(int2) * nrows, hipMemcpyHostToDevice, stream_));
-      reblock_keys_kernel<<<(unsigned)old_blocks.size(), kThreads, 0, stream_>>>(d_old, d_where, base, rb, ci,
-                                                                                   S.nz0, key_in, src_in);
+      dalloc(&d_old, (int64_t)old.size());
+      dalloc(&d_where, (int64_t)where.size());
+      HIPCHECK(hipMemcpyAsync(d_old, old.data(), sizeof(Blk) * old.size(), hipMemcpyHostToDevice, stream_));
+      HIPCHECK(hipMemcpyAsync(d_where, where.data(), sizeof(int2) * where.size(), hipMemcpyHostToDevice, stream_));
+      reblock_keys_kernel<<<(unsigned)old.size(), kThreads, 0, stream_>>>(d_old, d_where, ci, key_in, src_in);
     }
     HIPCHECK(hipGetLastError());
-    // low word: packed keys below 2^(cb + rb) in sorted blocks, entry
-    // indices below 2^bits_for(longest block) elsewhere
-    int32_t longest = 0;
-    for (const Blk& b : out) longest = std::max(longest, b.pn);
+    // the input is in row order within a column (entries of other blocks in
+    // their own order), so a stable sort needs the column bits only
     std::vector<int> shifts;
-    radix_shifts(shifts, 0, std::min(32, std::max(cb + rb, bits_for(longest))));
-    radix_shifts(shifts, 32, 32 + bits_for(nall - 1));
-    radix_sort_pairs<uint64_t>(key_in, src_in, key_out, src_out, nnz, shifts, stream_);
-    sorted_block_gather_kernel<T><<<(unsigned)nseg, kThreads, 0, stream_>>>(d_blk, S.nz0, key_out, src_out, val,
-                                                                           v64, ci, v_tmp, v64_tmp);
+    radix_shifts(shifts, rb_min, key_bits);
+    radix_shifts(shifts, 32, 32 + bits_for((int64_t)nall - 1));
+    radix_sort_pairs<uint64_t>(key_in, src_in, key_out, src_out, total, shifts, stream_);
+    sorted_block_gather_kernel<T><<<nseg, kThreads, 0, stream_>>>(d_blk, key_out, src_out, val, v64, ci, v_tmp, v64_tmp);
+    sorted_block_store_kernel<T><<<nseg, kThreads, 0, stream_>>>(d_blk, v_tmp, v64_tmp, val, v64);
     HIPCHECK(hipGetLastError());
-    HIPCHECK(hipMemcpyAsync(val + S.nz0, v_tmp, sizeof(T) * nnz, hipMemcpyDeviceToDevice, stream_));
-    if (v64_tmp)
-      HIPCHECK(hipMemcpyAsync(v64 + S.nz0, v64_tmp, sizeof(double) * nnz, hipMemcpyDeviceToDevice, stream_));
     HIPCHECK(hipStreamSynchronize(stream_));
     dfree(d_where);
     dfree(d_old);
@@ -1475,10 +1546,12 @@ void Engine<T>::sort_blocks(int id, bool dual, int64_t max_blocks, int64_t min_r
     dfree(key_in);
     dfree(d_blk);
     dfree(d_all);
+    for (size_t k = 0; k < lps.size(); ++k) {
+      Slot& S = slots_[lps[k]];
+      (dual ? S.plainD : S.plainP) = plain_blocks(dual ? S.m : S.n, max_blocks, min_rows);
+      (dual ? S.bD : S.bP) = std::move(blocks[k]);
+    }
   }
-  (dual ? S.plainD : S.plainP) = sorted.empty() ? 0 : nblk_want;
-  if (dual) S.bD = out;
-  else S.bP = out;
 }
 
 // Shape of a sorted-group layout for a product of nrows rows over `width`

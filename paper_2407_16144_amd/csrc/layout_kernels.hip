@@ -143,88 +143,101 @@ __global__ void slice_keys_kernel(const int32_t* rp, const int32_t* ci, int64_t 
 }
 
 // Column-sorting of plain blocks, step 1: for every entry of every block of
-// one LP's schedule (blocks in position order, covering its entries), a
-// 64-bit sort key with the block's index in the high word and, in the low
-// word, (column - b.rp_off) << rb | (row - b.r0) for a BK_SORTED block, the
-// entry's index in the block for any other (so that it stays in place), and
-// the entry's position.  Positions are relative to nz0 in the key arrays.
+// the given LPs, a 64-bit sort key with the block's index in the high word
+// and, in the low word, (column - b.rp_off) << rb | (row - b.r0) for a
+// BK_SORTED block, the entry's index in the block for any other (so that it
+// stays in place), and the entry's position.  The key arrays hold the LPs one
+// after the other: position p is at p + b.gid there.
 __global__ __launch_bounds__(kThreads) void block_keys_kernel(const Blk* blks, const int32_t* rp,
-                                                              const int32_t* ci, int64_t nz0, uint64_t* key,
-                                                              int32_t* src) {
+                                                              const int32_t* ci, uint64_t* key, int32_t* src) {
+  __shared__ int32_t s_rp[kSortRowsPlain];
   const Blk b = blks[blockIdx.x];
   const uint64_t hi = (uint64_t)blockIdx.x << 32;
+  const int64_t at = (int64_t)b.p0 + b.gid;
   if (blk_kind(b) == BK_SORTED) {
     // one thread per entry; its row is the last of the block's rows that
-    // starts at or before it (empty rows share the next row's start)
+    // starts at or before it (empty rows share the next row's start), found
+    // among the row starts in LDS
     const int rb = blk_rowbits(b);
     const int nrows = b.r1 - b.r0;
+    for (int r = threadIdx.x; r < nrows; r += kThreads) s_rp[r] = rp[b.r0 + r];
+    __syncthreads();
     for (int k = threadIdx.x; k < b.pn; k += kThreads) {
       const int32_t e = b.p0 + k;
       int lo = 0, up = nrows - 1;
       while (lo < up) {
         const int mid = (lo + up + 1) >> 1;
-        if (rp[b.r0 + mid] <= e) lo = mid; else up = mid - 1;
+        if (s_rp[mid] <= e) lo = mid; else up = mid - 1;
       }
-      key[e - nz0] = hi | (((uint32_t)(ci[e] - b.rp_off) << rb) | (uint32_t)lo);
-      src[e - nz0] = e;
+      key[at + k] = hi | (((uint32_t)(ci[e] - b.rp_off) << rb) | (uint32_t)lo);
+      src[at + k] = e;
     }
   } else {
     for (int e = threadIdx.x; e < b.pn; e += kThreads) {
-      const int64_t p = (int64_t)b.p0 + e;
-      key[p - nz0] = hi | (uint32_t)e;
-      src[p - nz0] = (int32_t)p;
+      key[at + e] = hi | (uint32_t)e;
+      src[at + e] = b.p0 + e;
     }
   }
 }
 
-// Re-blocking of a product stored in column-sorted blocks: every entry of
-// the old blocks `old` (which cover the LP's entries) gets the key of its
-// place in the new blocks, where[row - base] = (new block index, row in that
-// block).  BK_SORTED entries read their row and column back from the packed
-// key (the column relative to b.rp_off, which the new blocks share); BK_LONG
-// entries (rows that stay long) keep their order.
-__global__ __launch_bounds__(kThreads) void reblock_keys_kernel(const Blk* old, const int2* where, int64_t base,
-                                                                int rb_new, const int32_t* ci, int64_t nz0,
+// Re-blocking of products stored in column-sorted blocks: every entry of
+// the old blocks `old` (which cover the LPs' entries) gets the key of its
+// place in the new blocks, where[r + b.rp_off] = (new block index, row in that
+// block) of the row at space position r.  BK_SORTED entries read their row and
+// column back from the packed key (the column relative to the LP's first
+// column, which the new blocks share); other entries (rows that stay in a
+// block of their own) keep their order.  blk_nsl(b): row bits of the new
+// blocks; p + b.gid: place of position p in the key arrays.
+__global__ __launch_bounds__(kThreads) void reblock_keys_kernel(const Blk* old, const int2* where, const int32_t* ci,
                                                                 uint64_t* key, int32_t* src) {
   const Blk b = old[blockIdx.x];
+  const int64_t at = (int64_t)b.p0 + b.gid;
   if (blk_kind(b) == BK_SORTED) {
-    const int rb = blk_rowbits(b);
+    const int rb = blk_rowbits(b), rb_new = blk_nsl(b);
     const uint32_t rmask = (1u << rb) - 1u;
     for (int e = threadIdx.x; e < b.pn; e += kThreads) {
-      const int64_t p = (int64_t)b.p0 + e;
-      const uint32_t w = (uint32_t)ci[p];
-      const int2 t = where[b.r0 + (int64_t)(w & rmask) - base];
-      key[p - nz0] = ((uint64_t)(uint32_t)t.x << 32) | (((w >> rb) << rb_new) | (uint32_t)t.y);
-      src[p - nz0] = (int32_t)p;
+      const uint32_t w = (uint32_t)ci[b.p0 + e];
+      const int2 t = where[b.r0 + (int64_t)(w & rmask) + b.rp_off];
+      key[at + e] = ((uint64_t)(uint32_t)t.x << 32) | (((w >> rb) << rb_new) | (uint32_t)t.y);
+      src[at + e] = b.p0 + e;
     }
   } else {
-    const uint64_t hi = (uint64_t)(uint32_t)where[b.r0 - base].x << 32;
+    const uint64_t hi = (uint64_t)(uint32_t)where[b.r0 + (int64_t)b.rp_off].x << 32;
     for (int e = threadIdx.x; e < b.pn; e += kThreads) {
-      const int64_t p = (int64_t)b.p0 + e;
-      key[p - nz0] = hi | (uint32_t)e;
-      src[p - nz0] = (int32_t)p;
+      key[at + e] = hi | (uint32_t)e;
+      src[at + e] = b.p0 + e;
     }
   }
 }
 
 // Step 2 (after the keys are sorted): the entries of every BK_SORTED block
 // take the low words of the sorted keys as packed column indices and the
-// values of the entries they came from (values staged in v_tmp / v64_tmp,
-// relative to nz0).
+// values of the entries they came from (staged in v_tmp / v64_tmp, in the
+// order of the key arrays).
 template <class V>
-__global__ __launch_bounds__(kThreads) void sorted_block_gather_kernel(const Blk* blks, int64_t nz0,
-                                                                       const uint64_t* key, const int32_t* src,
-                                                                       const V* val, const double* v64,
-                                                                       int32_t* ci_out, V* v_tmp,
+__global__ __launch_bounds__(kThreads) void sorted_block_gather_kernel(const Blk* blks, const uint64_t* key,
+                                                                       const int32_t* src, const V* val,
+                                                                       const double* v64, int32_t* ci_out, V* v_tmp,
                                                                        double* v64_tmp) {
   const Blk b = blks[blockIdx.x];
+  const int64_t at = (int64_t)b.p0 + b.gid;
   for (int e = threadIdx.x; e < b.pn; e += kThreads) {
-    const int64_t p = (int64_t)b.p0 + e;
-    const int64_t rel = p - nz0;
-    const int32_t from = src[rel];
-    ci_out[p] = (int32_t)(uint32_t)key[rel];
-    v_tmp[rel] = val[from];
-    if (v64_tmp) v64_tmp[rel] = v64[from];
+    const int32_t from = src[at + e];
+    ci_out[b.p0 + e] = (int32_t)(uint32_t)key[at + e];
+    v_tmp[at + e] = val[from];
+    if (v64_tmp) v64_tmp[at + e] = v64[from];
+  }
+}
+
+// Step 3: the staged values take their places.
+template <class V>
+__global__ __launch_bounds__(kThreads) void sorted_block_store_kernel(const Blk* blks, const V* v_tmp,
+                                                                      const double* v64_tmp, V* val, double* v64) {
+  const Blk b = blks[blockIdx.x];
+  const int64_t at = (int64_t)b.p0 + b.gid;
+  for (int e = threadIdx.x; e < b.pn; e += kThreads) {
+    val[b.p0 + e] = v_tmp[at + e];
+    if (v64_tmp) v64[b.p0 + e] = v64_tmp[at + e];
   }
 }
 
@@ -275,12 +288,12 @@ __global__ void transpose_rowptr_kernel(const uint32_t* keys, int64_t nnz, int64
   kt_rp[j] = (int32_t)(z0 + lo);
 }
 
-template __global__ void sorted_block_gather_kernel<double>(const Blk*, int64_t, const uint64_t*,
-                                                            const int32_t*, const double*, const double*,
-                                                            int32_t*, double*, double*);
-template __global__ void sorted_block_gather_kernel<float>(const Blk*, int64_t, const uint64_t*,
-                                                           const int32_t*, const float*, const double*,
-                                                           int32_t*, float*, double*);
+template __global__ void sorted_block_gather_kernel<double>(const Blk*, const uint64_t*, const int32_t*, const double*,
+                                                            const double*, int32_t*, double*, double*);
+template __global__ void sorted_block_gather_kernel<float>(const Blk*, const uint64_t*, const int32_t*, const float*,
+                                                           const double*, int32_t*, float*, double*);
+template __global__ void sorted_block_store_kernel<double>(const Blk*, const double*, const double*, double*, double*);
+template __global__ void sorted_block_store_kernel<float>(const Blk*, const float*, const double*, float*, double*);
 template __global__ void sorted_gather_kernel<double>(const uint64_t*, const int32_t*, const double*,
                                                       const double*, int64_t, int32_t*, double*, double*);
 template __global__ void sorted_gather_kernel<float>(const uint64_t*, const int32_t*, const float*,

@@ -63,3 +63,37 @@ def test_sorted_block_trajectory(name):
     for a, b in ((x, ref.x), (y, ref.y)):
         floor = max(1e-2 * float(np.max(np.abs(b))), 1e-300)
         assert float(np.max(np.abs(a - b) / np.maximum(np.abs(b), floor))) <= 1e-10
+
+
+@pytest.mark.parametrize("blocks", ["from the start", "cut again while running"])
+def test_batch_sorted_together(blocks):
+    """The blocks of a whole batch are sorted together: LPs of unequal column
+    counts (another number of row bits and column bits each), one without
+    entries, one of a single entry, one whose long row stays out of the sort.
+    With LPs that finish early the rest are cut into smaller blocks, again
+    together.  Every LP agrees with its solve alone to 1e-10 (the same sums in
+    another order)."""
+    rng = np.random.default_rng(21)
+    lps = [_lp(list(rng.integers(0, 30, 700)), 90, 10), _lp([0, 0, 0], 5, 11), _lp([1], 1, 12, m_eq=1),
+           _lp([7] * 100 + [(1 << 15) + 1] + [5] * 50, 40000, 13), _lp(list(rng.integers(1, 9, 2500)), 70000, 14)]
+    n = len(lps)
+    group = list(lps)
+    if blocks != "from the start":
+        one = dict(n=1, m_eq=1, m_ineq=0, rowptr=np.array([0, 1], np.int32), col=np.array([0], np.int32),
+                   val=np.array([1.0]), c=np.array([1.0]), rhs=np.array([1.0]), lb=np.zeros(1), ub=np.full(1, 10.0))
+        group += [lpgen.LP(**one) for _ in range(40)]
+    opt = halp.lp_default_options(eta=1e-2)
+    print(f"case batch sorted together, {blocks}", flush=True)
+    h = halp.lp_batch_create(group, opt=opt)
+    try:
+        halp.lp_batch_solve(h, 1e-13, 400)
+        got = [(halp.lp_batch_status(h, i).as_dict(), *halp.lp_batch_get_solution(h, i, group[i].n, group[i].m))
+               for i in range(n)]
+    finally:
+        halp.lp_batch_destroy(h)
+    for lp, (res, x, y) in zip(lps, got):
+        ref, xr, yr, _ = halp.solve_lp(lp, tol=1e-13, max_iter=400, opt=opt)
+        assert res["status"] == ref["status"] and res["iters"] == ref["iters"] and res["restarts"] == ref["restarts"]
+        for a, b in ((x, xr), (y, yr)):
+            floor = max(1e-2 * float(np.max(np.abs(b))), 1e-300)
+            assert float(np.max(np.abs(a - b) / np.maximum(np.abs(b), floor))) <= 1e-10
