@@ -76,24 +76,57 @@ class RangeAlloc {
 // ---------------------------------------------------------------------------
 // device memory
 //
-// Every buffer of an engine comes from dalloc.  Normally that is hipMalloc;
+// Every buffer of an engine comes from dalloc or, where it lives only while
+// LPs are added or laid out anew, from talloc.  Normally dalloc is hipMalloc;
 // inside a WorkspaceScope (the allocation-free entry point) the buffers are
 // carved out of `scratch`, a static device array, by a stack allocator: a
 // freed block is reclaimed once every block above it is freed too (the
 // engine frees its temporaries in the reverse order of their allocation).
 // Carved blocks are cleared to zero on the workspace's stream, as fresh
 // device memory would be.
+//
+// An allocation and a release of 16 MiB or more take 0.3 ms each whatever the
+// size (4 GiB: 0.42 and 0.39 ms), so the engine's own buffers are one
+// allocation (Engine::carve), and talloc carves its blocks out of one
+// allocation per TempScope; a block that does not fit there, or is taken
+// outside a scope, is a dalloc.  128 LPs of 2-8k rows, creation 67 -> 60 ms
+// and release 9.9 -> 0.4 ms (221 allocations -> 9).  The engine's work on the blocks is
+// ordered by its one stream, also across blocks that share an address; the
+// scope's end waits for it (hipFree).
 // ---------------------------------------------------------------------------
 
 static __device__ __align__(256) char scratch[kWorkspaceBytes];
 
 struct Workspace {
-  char* base = nullptr;    // this device's copy of `scratch` (from hipGetSymbolAddress)
-  size_t used = 0, peak = 0;
+  char* base = nullptr;    // this device's copy of `scratch` (from hipGetSymbolAddress), or a TempScope's memory
+  size_t size = 0, used = 0, peak = 0;
   hipStream_t stream = nullptr;
   std::vector<std::pair<size_t, bool>> blocks;  // (offset, freed) in allocation order
+
+  bool fits(size_t b) const { return b <= size - used; }
+  char* take(size_t b) {
+    char* p = base + used;
+    blocks.push_back({used, false});
+    used += b;
+    peak = std::max(peak, used);
+    return p;
+  }
+  bool give_back(void* p) {
+    if ((char*)p < base || (char*)p >= base + size) return false;
+    const size_t off = (size_t)((char*)p - base);
+    for (auto& bl : blocks)
+      if (bl.first == off) bl.second = true;
+    while (!blocks.empty() && blocks.back().second) {
+      used = blocks.back().first;
+      blocks.pop_back();
+    }
+    return true;
+  }
 };
-static thread_local Workspace* t_ws = nullptr;
+static thread_local Workspace* t_ws = nullptr;    // of the thread's WorkspaceScope
+static thread_local Workspace* t_temp = nullptr;  // of the thread's TempScope
+
+static inline size_t aligned_bytes(size_t bytes) { return (bytes + 255) & ~size_t(255); }
 
 // Address of this device's copy of `scratch`; looked up once per device with
 // that device current (the array's host-side name is not a device address).
@@ -113,30 +146,14 @@ static char* scratch_base(int device) {
 
 static void* ws_alloc(size_t bytes) {
   Workspace& w = *t_ws;
-  const size_t b = (bytes + 255) & ~size_t(255);
-  if (w.used + b > (size_t)kWorkspaceBytes)
+  const size_t b = aligned_bytes(bytes);
+  if (!w.fits(b))
     throw Error(-2, "static workspace exhausted: " + std::to_string(w.used + b) + " bytes needed of " +
                         std::to_string((long long)kWorkspaceBytes));
-  char* p = w.base + w.used;
-  w.blocks.push_back({w.used, false});
-  w.used += b;
-  w.peak = std::max(w.peak, w.used);
+  char* p = w.take(b);
   const hipError_t e = hipMemsetAsync(p, 0, b, w.stream);
   if (e != hipSuccess) throw Error(-3, std::string("hipMemsetAsync: ") + hipGetErrorString(e));
   return p;
-}
-
-static bool ws_free(void* p) {
-  Workspace* w = t_ws;
-  if (!w || (char*)p < w->base || (char*)p >= w->base + kWorkspaceBytes) return false;
-  const size_t off = (size_t)((char*)p - w->base);
-  for (auto& bl : w->blocks)
-    if (bl.first == off) bl.second = true;
-  while (!w->blocks.empty() && w->blocks.back().second) {
-    w->used = w->blocks.back().first;
-    w->blocks.pop_back();
-  }
-  return true;
 }
 
 template <class P>
@@ -151,11 +168,47 @@ static void dalloc(P** p, int64_t count) {
   if (e != hipSuccess) throw Error(-2, std::string("device allocation failed: ") + hipGetErrorString(e));
 }
 
+// temporaries of add() and reblock_for()
+template <class P>
+static void talloc(P** p, int64_t count) {
+  const size_t b = aligned_bytes(sizeof(P) * (size_t)std::max<int64_t>(count, 1));
+  if (t_temp && t_temp->fits(b)) *p = (P*)t_temp->take(b);
+  else dalloc(p, count);
+}
+
 template <class P>
 static void dfree(P*& p) {
-  if (p && !ws_free((void*)p)) (void)hipFree((void*)p);
+  if (p && !(t_ws && t_ws->give_back((void*)p)) && !(t_temp && t_temp->give_back((void*)p))) (void)hipFree((void*)p);
   p = nullptr;
 }
+
+// Gives talloc `bytes` of device memory on this thread while it lives.  If
+// they cannot be had in one piece (or inside another scope or a
+// WorkspaceScope) talloc allocates block by block.
+class TempScope {
+ public:
+  explicit TempScope(size_t bytes) {
+    if (t_ws || t_temp) return;
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    w_.base = (char*)p;
+    w_.size = bytes;
+    t_temp = &w_;
+  }
+  ~TempScope() {
+    if (!w_.base) return;
+    t_temp = nullptr;
+    (void)hipFree(w_.base);
+  }
+  TempScope(const TempScope&) = delete;
+  TempScope& operator=(const TempScope&) = delete;
+
+ private:
+  Workspace w_;
+};
 
 WorkspaceScope::WorkspaceScope(hipStream_t stream) {
   if (t_ws) throw Error(-4, "nested use of the static workspace");
@@ -163,6 +216,7 @@ WorkspaceScope::WorkspaceScope(hipStream_t stream) {
   if (hipGetDevice(&dev) != hipSuccess) throw Error(-3, "hipGetDevice failed");
   std::unique_ptr<Workspace> w(new Workspace());
   w->base = scratch_base(dev);
+  w->size = (size_t)kWorkspaceBytes;
   w->stream = stream;
   t_ws = w.release();
 }
@@ -320,6 +374,8 @@ static void plain_shape(int64_t live, int64_t* max_blocks, int64_t* min_rows) {
 // Entries that one sort of plain blocks takes together at most (48 bytes of
 // temporary memory each).
 constexpr int64_t kSortRun = 1 << 26;
+// temporary memory per entry of a transpose and its radix sort
+constexpr int64_t kTransposeBytes = 29;
 
 struct Slot {
   bool used = false;
@@ -403,6 +459,7 @@ class Engine final : public EngineBase {
 
  private:
   void allocate();
+  size_t carve(char* base);
   void release_all();
   void rebuild_schedules();
   void pin_to_xcds(std::vector<Blk>& v, const std::vector<std::pair<int, int>>& ranges) const;
@@ -429,6 +486,9 @@ class Engine final : public EngineBase {
   void group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_t cap);
   bool group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* ngroups, int64_t* cap) const;
   int group_lds_rows(bool dual) const;
+  // temporary memory of a sort of nnz entries into blocks: keys and positions
+  // twice over and once more for the radix sort, its counts, and the values
+  static int64_t temp_bytes(int64_t nnz) { return (sizeof(T) == 8 ? 45 : 49) * nnz + (1 << 18); }
   std::vector<Blk> cut_blocks(int id, bool dual, const int32_t* rp, int64_t max_blocks, int64_t min_rows, int* rb,
                               int* cb) const;
   void sort_blocks(const std::vector<int>& ids, bool dual, const std::vector<const int32_t*>& rps, int64_t max_blocks,
@@ -445,6 +505,7 @@ class Engine final : public EngineBase {
   std::vector<Slot> slots_;
   int64_t g_next_ = 0;  // index of the next step to launch
 
+  char* mem_ = nullptr;  // the engine's buffers (carve)
   // nnz-space
   int32_t *K_ci = nullptr, *KT_ci = nullptr;
   double *K_v64 = nullptr, *KT_v64 = nullptr;
@@ -495,43 +556,53 @@ class Engine final : public EngineBase {
   KernelTimes ktimes_;
 };
 
+// Places the engine's buffers one after the other from `base` (each on a
+// 256-byte boundary); returns their size.
 template <class T>
-void Engine<T>::allocate() {
-  dalloc(&K_ci, NZ_);
-  dalloc(&KT_ci, NZ_);
-  dalloc(&K_v64, NZ_);
-  dalloc(&KT_v64, NZ_);
+size_t Engine<T>::carve(char* base) {
+  size_t at = 0;
+  auto take = [&](auto** p, int64_t count) {
+    *p = (std::remove_reference_t<decltype(*p)>)((uintptr_t)base + at);
+    at += aligned_bytes(sizeof(**p) * (size_t)std::max<int64_t>(count, 1));
+  };
+  take(&K_ci, NZ_);
+  take(&KT_ci, NZ_);
+  take(&K_v64, NZ_);
+  take(&KT_v64, NZ_);
   if (sizeof(T) == 8) {
     K_v = (T*)K_v64;
     KT_v = (T*)KT_v64;
   } else {
-    dalloc(&K_v, NZ_);
-    dalloc(&KT_v, NZ_);
+    take(&K_v, NZ_);
+    take(&KT_v, NZ_);
   }
-  dalloc(&K_rp, MS_);
-  dalloc(&q_o, MS_);
-  dalloc(&Dr, MS_);
-  dalloc(&fm, MS_);
-  for (T** p : {&q, &y, &y0, &yT, &dy, &kxbar, &kxp, &cy1, &cy2, &ys}) dalloc(p, MS_);
-  dalloc(&KT_rp, NS_);
-  for (double** p : {&c_o, &l_o, &u_o, &Dc, &fn}) dalloc(p, NS_);
-  for (T** p : {&c, &l, &u, &x, &x0, &xbar, &xT, &ktyp, &cx1, &cx2, &xs}) dalloc(p, NS_);
-  dalloc(&actx, NS_);
-  dalloc(&acty, MS_);
+  take(&K_rp, MS_);
+  for (double** p : {&q_o, &Dr, &fm}) take(p, MS_);
+  for (T** p : {&q, &y, &y0, &yT, &dy, &kxbar, &kxp, &cy1, &cy2, &ys}) take(p, MS_);
+  take(&KT_rp, NS_);
+  for (double** p : {&c_o, &l_o, &u_o, &Dc, &fn}) take(p, NS_);
+  for (T** p : {&c, &l, &u, &x, &x0, &xbar, &xT, &ktyp, &cx1, &cx2, &xs}) take(p, NS_);
+  take(&actx, NS_);
+  take(&acty, MS_);
   if (opt_.plain_sort) {
-    dalloc(&kx1_, MS_);
-    dalloc(&kx2_, MS_);
-    dalloc(&kt1_, NS_);
-    dalloc(&kt2_, NS_);
+    for (T** p : {&kx1_, &kx2_}) take(p, MS_);
+    for (T** p : {&kt1_, &kt2_}) take(p, NS_);
   }
   // row pointers of row-major slice tiles: only where products may be sliced
   const bool may_slice = opt_.slice_min_bytes >= 0;
-  dalloc(&brpK, may_slice ? 2 * kSlices * MS_ : 1);
-  dalloc(&brpKT, may_slice ? 2 * kSlices * NS_ : 1);
-  dalloc(&d_st, nslots_);
-  dalloc(&d_status, nslots_);
-  dalloc(&d_cnt, nslots_);
-  dalloc(&d_gbase, 1);
+  take(&brpK, may_slice ? 2 * kSlices * MS_ : 1);
+  take(&brpKT, may_slice ? 2 * kSlices * NS_ : 1);
+  take(&d_st, nslots_);
+  take(&d_status, nslots_);
+  take(&d_cnt, nslots_);
+  take(&d_gbase, 1);
+  return at;
+}
+
+template <class T>
+void Engine<T>::allocate() {
+  dalloc(&mem_, (int64_t)carve(nullptr));
+  carve(mem_);
   HIPCHECK(hipMemsetAsync(d_cnt, 0, sizeof(int) * nslots_, stream_));
   HIPCHECK(hipMemsetAsync(d_status, 0, sizeof(int) * nslots_, stream_));
   HIPCHECK(hipMemsetAsync(d_st, 0, sizeof(InstState) * nslots_, stream_));
@@ -574,38 +645,10 @@ void Engine<T>::release_all() {
   if (graph_) (void)hipGraphDestroy(graph_);
   gexec_ = nullptr;
   graph_ = nullptr;
-  dfree(K_ci);
-  dfree(KT_ci);
-  if (sizeof(T) != 8) {
-    dfree(K_v);
-    dfree(KT_v);
-  }
-  dfree(K_v64);
-  dfree(KT_v64);
-  dfree(K_rp);
-  dfree(q_o);
-  dfree(Dr);
-  dfree(fm);
-  for (T** p : {&q, &y, &y0, &yT, &dy, &kxbar, &kxp, &cy1, &cy2, &ys}) dfree(*p);
-  dfree(KT_rp);
-  for (double** p : {&c_o, &l_o, &u_o, &Dc, &fn}) dfree(*p);
-  for (T** p : {&c, &l, &u, &x, &x0, &xbar, &xT, &ktyp, &cx1, &cx2, &xs}) dfree(*p);
-  dfree(actx);
-  dfree(acty);
-  dfree(brpK);
-  dfree(brpKT);
   dfree(spartD);
-  dfree(kt1_);
-  dfree(kt2_);
-  dfree(kx1_);
-  dfree(kx2_);
   dfree(spartP);
   dfree(d_schedPS);
   dfree(d_schedDS);
-  dfree(d_st);
-  dfree(d_status);
-  dfree(d_cnt);
-  dfree(d_gbase);
   dfree(d_schedP);
   dfree(d_schedD);
   dfree(d_schedPB);
@@ -614,6 +657,7 @@ void Engine<T>::release_all() {
   dfree(d_schedDE);
   dfree(partP);
   dfree(partD);
+  dfree(mem_);
   for (int i = 0; i < 2; ++i) {
     if (h_status[i]) {
       if (ws_) delete[] h_status[i];
@@ -767,12 +811,12 @@ void Engine<T>::transpose_group(int64_t z0, int64_t nnz, int64_t c0, int64_t c1,
     Blk* d_b = nullptr;
     int32_t *rowid = nullptr, *vin = nullptr, *vout = nullptr;
     uint32_t *keys = nullptr, *kout = nullptr;
-    dalloc(&d_b, (int64_t)bD.size());
-    dalloc(&rowid, nnz);
-    dalloc(&keys, nnz);
-    dalloc(&kout, nnz);
-    dalloc(&vin, nnz);
-    dalloc(&vout, nnz);
+    talloc(&d_b, (int64_t)bD.size());
+    talloc(&rowid, nnz);
+    talloc(&keys, nnz);
+    talloc(&kout, nnz);
+    talloc(&vin, nnz);
+    talloc(&vout, nnz);
     HIPCHECK(hipMemcpyAsync(d_b, bD.data(), sizeof(Blk) * bD.size(), hipMemcpyHostToDevice, stream_));
     row_ids_kernel<<<(unsigned)bD.size(), kThreads, 0, stream_>>>(d_b, K_rp, z0, rowid);
     iota_kernel<<<nblk(nnz), 256, 0, stream_>>>(vin, nnz);
@@ -915,6 +959,18 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     nnzs.resize(ids.size());
   }
   if (ids.empty()) return ids;
+  int64_t total_nz = 0, largest_nz = 0, most_rows = 0;
+  for (int id : ids) {
+    const Slot& S = slots_[id];
+    total_nz += S.nnz;
+    largest_nz = std::max(largest_nz, S.nnz);
+    most_rows = std::max(most_rows, std::max(S.m, S.n));
+  }
+  int64_t temp_size = temp_bytes(std::max(largest_nz, std::min(total_nz, kSortRun)));
+  // sorted groups: a 32-bit key per entry, a position per row and slice
+  if (opt_.slice_min_bytes >= 0 && opt_.slice_sort)
+    temp_size = std::max(temp_size, temp_bytes(largest_nz) + 4 * (largest_nz + (kGroupSlices + 1) * most_rows));
+  TempScope temp(std::max(kTransposeBytes * total_nz, temp_size));
   // 2. upload (K values in FP64, row pointers / columns shifted to space positions)
   std::vector<std::vector<int32_t>> host_rp(probs.size());
   for (size_t k = 0; k < probs.size(); ++k) {
@@ -1074,14 +1130,14 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
     dfree(d_src);
   };
   try {
-    dalloc(&d_nP, (int64_t)nP.size());
-    dalloc(&d_nD, (int64_t)nD.size());
-    dalloc(&d_ids, ni);
-    dalloc(&d_nr, ni);
-    dalloc(&d_pp, (int64_t)nP.size() * kNS);
-    dalloc(&d_norms, 2 * ni);
-    dalloc(&d_active, 1);
-    dalloc(&d_src, ni);
+    talloc(&d_nP, (int64_t)nP.size());
+    talloc(&d_nD, (int64_t)nD.size());
+    talloc(&d_ids, ni);
+    talloc(&d_nr, ni);
+    talloc(&d_pp, (int64_t)nP.size() * kNS);
+    talloc(&d_norms, 2 * ni);
+    talloc(&d_active, 1);
+    talloc(&d_src, ni);
     HIPCHECK(hipMemcpyAsync(d_nP, nP.data(), sizeof(Blk) * nP.size(), hipMemcpyHostToDevice, stream_));
     HIPCHECK(hipMemcpyAsync(d_nD, nD.data(), sizeof(Blk) * nD.size(), hipMemcpyHostToDevice, stream_));
     HIPCHECK(hipMemcpyAsync(d_ids, ids.data(), sizeof(int) * ni, hipMemcpyHostToDevice, stream_));
@@ -1237,7 +1293,7 @@ void Engine<T>::slice_matrix(int id, bool dual) {
   double* v64 = dual ? K_v64 : KT_v64;
   if (nrows == 0 || S.nnz == 0) return;
   int32_t* d_cnt = nullptr;
-  dalloc(&d_cnt, nrows * kSlices);
+  talloc(&d_cnt, nrows * kSlices);
   slice_count_kernel<<<nblk(nrows), 256, 0, stream_>>>(rp, ci, r0, nrows, c0, len, kSlices, d_cnt);
   std::vector<int32_t> cnt(nrows * kSlices);
   HIPCHECK(hipMemcpyAsync(cnt.data(), d_cnt, sizeof(int32_t) * cnt.size(), hipMemcpyDeviceToHost, stream_));
@@ -1261,10 +1317,10 @@ void Engine<T>::slice_matrix(int id, bool dual) {
   int32_t* ci2 = nullptr;
   T* v2 = nullptr;
   double* v642 = nullptr;
-  dalloc(&d_dst, nrows * kSlices);
-  dalloc(&ci2, S.nnz);
-  dalloc(&v2, S.nnz);
-  if (sizeof(T) != 8) dalloc(&v642, S.nnz);
+  talloc(&d_dst, nrows * kSlices);
+  talloc(&ci2, S.nnz);
+  talloc(&v2, S.nnz);
+  if (sizeof(T) != 8) talloc(&v642, S.nnz);
   HIPCHECK(hipMemcpyAsync(d_dst, dst.data(), sizeof(int32_t) * dst.size(), hipMemcpyHostToDevice, stream_));
   // the scatter writes positions nz0..nz0+nnz; shift the temporaries by -nz0
   slice_scatter_kernel<T><<<nblk(nrows), 256, 0, stream_>>>(rp, ci, val, v64, r0, nrows, c0, len, d_dst,
@@ -1344,6 +1400,7 @@ void Engine<T>::reblock_for(const int* status) {
     }
     if (ids.empty()) continue;
     for (auto& v : rp) rps.push_back(v.data());
+    TempScope temp(temp_bytes(largest));
     // temporary memory for the largest of them, as a server's budget allows
     sort_blocks(ids, dual, rps, maxb, minr, true, largest);
     changed = true;
@@ -1506,21 +1563,21 @@ void Engine<T>::sort_blocks(const std::vector<int>& ids, bool dual, const std::v
     T* v_tmp = nullptr;
     double* v64_tmp = nullptr;
     const unsigned nall = (unsigned)all.size(), nseg = (unsigned)sorted.size();
-    dalloc(&d_all, nall);
-    dalloc(&d_blk, nseg);
-    dalloc(&key_in, total);
-    dalloc(&key_out, total);
-    dalloc(&src_in, total);
-    dalloc(&src_out, total);
-    dalloc(&v_tmp, total);
-    if (sizeof(T) != 8) dalloc(&v64_tmp, total);
+    talloc(&d_all, nall);
+    talloc(&d_blk, nseg);
+    talloc(&key_in, total);
+    talloc(&key_out, total);
+    talloc(&src_in, total);
+    talloc(&src_out, total);
+    talloc(&v_tmp, total);
+    if (sizeof(T) != 8) talloc(&v64_tmp, total);
     HIPCHECK(hipMemcpyAsync(d_all, all.data(), sizeof(Blk) * nall, hipMemcpyHostToDevice, stream_));
     HIPCHECK(hipMemcpyAsync(d_blk, sorted.data(), sizeof(Blk) * nseg, hipMemcpyHostToDevice, stream_));
     if (!reblock) {
       block_keys_kernel<<<nall, kThreads, 0, stream_>>>(d_all, rpd, ci, key_in, src_in);
     } else {
-      dalloc(&d_old, (int64_t)old.size());
-      dalloc(&d_where, (int64_t)where.size());
+      talloc(&d_old, (int64_t)old.size());
+      talloc(&d_where, (int64_t)where.size());
       HIPCHECK(hipMemcpyAsync(d_old, old.data(), sizeof(Blk) * old.size(), hipMemcpyHostToDevice, stream_));
       HIPCHECK(hipMemcpyAsync(d_where, where.data(), sizeof(int2) * where.size(), hipMemcpyHostToDevice, stream_));
       reblock_keys_kernel<<<(unsigned)old.size(), kThreads, 0, stream_>>>(d_old, d_where, ci, key_in, src_in);
@@ -1619,7 +1676,7 @@ void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_
   if (nrows == 0 || S.nnz == 0) return;
   if (nsl < 1 || nsl > kGroupSlices || kGroupSlices % nsl != 0) throw Error(-3, "bad slice count");
   int32_t* d_cnt = nullptr;
-  dalloc(&d_cnt, nrows * nsl);
+  talloc(&d_cnt, nrows * nsl);
   slice_count_kernel<<<nblk(nrows), 256, 0, stream_>>>(rp, ci, r0, nrows, c0, len, nsl, d_cnt);
   std::vector<int32_t> cnt(nrows * nsl);
   HIPCHECK(hipMemcpyAsync(cnt.data(), d_cnt, sizeof(int32_t) * cnt.size(), hipMemcpyDeviceToHost, stream_));
@@ -1699,16 +1756,16 @@ void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_
   uint64_t *key_in = nullptr, *key_out = nullptr;
   T* v2 = nullptr;
   double* v642 = nullptr;
-  dalloc(&d_dst, nrows * nsl);
-  dalloc(&d_rloc, nrows);
-  dalloc(&d_off, (int64_t)off.size());
-  dalloc(&key32, nnz);
-  dalloc(&key_in, nnz);
-  dalloc(&key_out, nnz);
-  dalloc(&src_in, nnz);
-  dalloc(&src_out, nnz);
-  dalloc(&v2, nnz);
-  if (sizeof(T) != 8) dalloc(&v642, nnz);
+  talloc(&d_dst, nrows * nsl);
+  talloc(&d_rloc, nrows);
+  talloc(&d_off, (int64_t)off.size());
+  talloc(&key32, nnz);
+  talloc(&key_in, nnz);
+  talloc(&key_out, nnz);
+  talloc(&src_in, nnz);
+  talloc(&src_out, nnz);
+  talloc(&v2, nnz);
+  if (sizeof(T) != 8) talloc(&v642, nnz);
   HIPCHECK(hipMemcpyAsync(d_dst, dst.data(), sizeof(int32_t) * dst.size(), hipMemcpyHostToDevice, stream_));
   HIPCHECK(hipMemcpyAsync(d_rloc, rloc.data(), sizeof(int32_t) * rloc.size(), hipMemcpyHostToDevice, stream_));
   HIPCHECK(hipMemcpyAsync(d_off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice, stream_));

@@ -15,7 +15,7 @@
 //      writes it to base[digit] + rank.
 // Equal digits keep their input order in every pass, so the sort is stable
 // and its result does not depend on timing.  Included by engine.hip (uses
-// dalloc / dfree / HIPCHECK / nblk defined there).
+// talloc / dfree / HIPCHECK / nblk defined there).
 
 namespace halp {
 
@@ -166,19 +166,19 @@ static void radix_sort_pairs(const K* kin, const int32_t* vin, K* kout, int32_t*
   while (len.back() > kScanTile) len.push_back((len.back() + kScanTile - 1) / kScanTile);
   const int L = (int)len.size();
   uint32_t *counts = nullptr, *offs = nullptr;
-  dalloc(&counts, len[0]);
-  dalloc(&offs, len[0]);
+  talloc(&counts, len[0]);
+  talloc(&offs, len[0]);
   std::vector<uint32_t*> sums(L, nullptr), scanned(L, nullptr);
   for (int l = 1; l < L; ++l) {
-    dalloc(&sums[l], len[l]);
-    dalloc(&scanned[l], len[l]);
+    talloc(&sums[l], len[l]);
+    talloc(&scanned[l], len[l]);
   }
   scanned[0] = offs;
   K* kalt = nullptr;
   int32_t* valt = nullptr;
   if (np > 1) {
-    dalloc(&kalt, n);
-    dalloc(&valt, n);
+    talloc(&kalt, n);
+    talloc(&valt, n);
   }
   const K* ks = kin;
   const int32_t* vs = vin;
