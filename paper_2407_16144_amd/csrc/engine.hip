@@ -483,7 +483,7 @@ class Engine final : public EngineBase {
                   const std::vector<int4>& nr);
   void slice_matrix(int id, bool dual);
   void need_partials(bool dual, int nsl);
-  void group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_t cap);
+  void group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int64_t ngroups, int64_t cap);
   bool group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* ngroups, int64_t* cap) const;
   int group_lds_rows(bool dual) const;
   // temporary memory of a sort of nnz entries into blocks: keys and positions
@@ -959,18 +959,12 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     nnzs.resize(ids.size());
   }
   if (ids.empty()) return ids;
-  int64_t total_nz = 0, largest_nz = 0, most_rows = 0;
+  int64_t total_nz = 0, largest_nz = 0;
   for (int id : ids) {
-    const Slot& S = slots_[id];
-    total_nz += S.nnz;
-    largest_nz = std::max(largest_nz, S.nnz);
-    most_rows = std::max(most_rows, std::max(S.m, S.n));
+    total_nz += slots_[id].nnz;
+    largest_nz = std::max(largest_nz, slots_[id].nnz);
   }
-  int64_t temp_size = temp_bytes(std::max(largest_nz, std::min(total_nz, kSortRun)));
-  // sorted groups: a 32-bit key per entry, a position per row and slice
-  if (opt_.slice_min_bytes >= 0 && opt_.slice_sort)
-    temp_size = std::max(temp_size, temp_bytes(largest_nz) + 4 * (largest_nz + (kGroupSlices + 1) * most_rows));
-  TempScope temp(std::max(kTransposeBytes * total_nz, temp_size));
+  TempScope temp(std::max(kTransposeBytes * total_nz, temp_bytes(std::max(largest_nz, std::min(total_nz, kSortRun)))));
   // 2. upload (K values in FP64, row pointers / columns shifted to space positions)
   std::vector<std::vector<int32_t>> host_rp(probs.size());
   for (size_t k = 0; k < probs.size(); ++k) {
@@ -1092,7 +1086,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
       } else if (S.nnz > 0 && opt_.slice_sort && (slice || opt_.plain_sort) &&
                  group_shape(nrows, width, nsl_min, &nsl, &ngroups, &cap) &&
                  (slice || nrows > kCUs * std::min<int64_t>(opt_.sort_rows, kSortRowsPlain))) {
-        group_sorted(id, dual, nsl, ngroups, cap);
+        group_sorted(id, dual, (dual ? host_rp[t] : host_rpT[t]).data(), nsl, ngroups, cap);
       } else if (opt_.plain_sort) {
         plain[dual].push_back(id);
         plain_rp[dual].push_back((dual ? host_rp[t] : host_rpT[t]).data());
@@ -1115,7 +1109,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
   Blk *d_nP = nullptr, *d_nD = nullptr;
   int* d_ids = nullptr;
   int4* d_nr = nullptr;
-  double* d_pp = nullptr;
+  double *d_pp = nullptr, *d_pd = nullptr;
   double* d_norms = nullptr;
   int* d_active = nullptr;
   InstState* d_src = nullptr;
@@ -1124,6 +1118,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
     dfree(d_nD);
     dfree(d_ids);
     dfree(d_nr);
+    dfree(d_pd);
     dfree(d_pp);
     dfree(d_norms);
     dfree(d_active);
@@ -1135,6 +1130,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
     talloc(&d_ids, ni);
     talloc(&d_nr, ni);
     talloc(&d_pp, (int64_t)nP.size() * kNS);
+    talloc(&d_pd, (int64_t)nD.size() * kNS);
     talloc(&d_norms, 2 * ni);
     talloc(&d_active, 1);
     talloc(&d_src, ni);
@@ -1157,8 +1153,8 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
       scale_values_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_ci, K_v64, fm, fn, 0);
       scale_values_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_ci, KT_v64, fm, fn, 1);
     }
-    scale_primal_kernel<T><<<gP, kThreads, 0, stream_>>>(d_nP, Dc, c_o, l_o, u_o, c, l, u);
-    scale_dual_kernel<T><<<gD, kThreads, 0, stream_>>>(d_nD, Dr, q_o, q);
+    scale_primal_kernel<T><<<gP, kThreads, 0, stream_>>>(d_nP, Dc, c_o, l_o, u_o, c, l, u, d_pp);
+    scale_dual_kernel<T><<<gD, kThreads, 0, stream_>>>(d_nD, Dr, q_o, q, d_pd);
 
     // layout constants for the norm and power kernels
     std::vector<InstState> src(ni);
@@ -1177,7 +1173,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
     }
     HIPCHECK(hipMemcpyAsync(d_src, src.data(), sizeof(InstState) * ni, hipMemcpyHostToDevice, stream_));
     write_states_kernel<<<nblk(ni), 256, 0, stream_>>>(d_st, d_status, d_cnt, d_ids, d_src, ni);
-    inst_norms_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, q_o, c_o, Dr, Dc, d_norms);
+    inst_norms_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_nr, d_pp, d_pd, d_norms);
 
     // power iteration on K~^T K~ (u in fm, w in fn)
     int piters = 0;
@@ -1656,16 +1652,15 @@ int Engine<T>::group_lds_rows(bool dual) const {
   return r;
 }
 
-// Sorted groups of one LP's K (dual = true; gathers over its variables) or
-// K^T (gathers over its constraints): rows cut into groups of at most `rows`
-// rows and kSortEntries entries per slice, each group's entries into nsl
-// column slices, the entries of each (group, slice) block in column order,
-// each column index packed with the entry's row in the group (see
-// blk_rowbits).  Built on the device: per-slice counts of every row, keys in
-// row-major block order, a radix sort by (block, key) (keys are unique in a
-// block, so the order is fixed), a gather of the values.
+// Sorted groups of one LP's K (dual = true) or K^T over its row pointers hrp
+// on the host (space positions): about ngroups groups of equal work (entries
+// and rows), of at most cap rows and kSortEntries entries per slice on
+// average, each group's entries in nsl column slices, each (group, slice)
+// block's entries in column order with the row of the group packed beside the
+// column.  Built on the device from the row-major entries: keys, one stable
+// radix sort by block and column (rows of a column come in order), values.
 template <class T>
-void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_t cap) {
+void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int64_t ngroups, int64_t cap) {
   Slot& S = slots_[id];
   const int64_t nrows = dual ? S.m : S.n, r0 = dual ? S.row0 : S.col0, c0 = dual ? S.col0 : S.row0;
   const int64_t len = dual ? S.n : S.m;
@@ -1673,44 +1668,78 @@ void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_
   int32_t* ci = dual ? K_ci : KT_ci;
   T* val = dual ? K_v : KT_v;
   double* v64 = dual ? K_v64 : KT_v64;
-  if (nrows == 0 || S.nnz == 0) return;
+  const int64_t nnz = S.nnz;
+  if (nrows == 0 || nnz == 0) return;
   if (nsl < 1 || nsl > kGroupSlices || kGroupSlices % nsl != 0) throw Error(-3, "bad slice count");
-  int32_t* d_cnt = nullptr;
-  talloc(&d_cnt, nrows * nsl);
-  slice_count_kernel<<<nblk(nrows), 256, 0, stream_>>>(rp, ci, r0, nrows, c0, len, nsl, d_cnt);
-  std::vector<int32_t> cnt(nrows * nsl);
-  HIPCHECK(hipMemcpyAsync(cnt.data(), d_cnt, sizeof(int32_t) * cnt.size(), hipMemcpyDeviceToHost, stream_));
-  HIPCHECK(hipStreamSynchronize(stream_));
-  dfree(d_cnt);
-  // groups of equal work (entries and rows): a group ends at the row whose
-  // middle passes the next multiple of the average
-  std::vector<std::pair<int64_t, int64_t>> groups;
-  int64_t start = 0, maxrows = 0;
-  int64_t acc[kGroupSlices] = {0};
-  const double per = (double)(S.nnz + nrows) / (double)ngroups;
-  double cum = 0.0, bound = per;
-  for (int64_t r = 0; r < nrows; ++r) {
-    const int32_t* c = cnt.data() + r * nsl;
-    int64_t w = 1;
-    for (int q = 0; q < nsl; ++q) w += c[q];
-    bool over = (r - start) >= cap || cum + 0.5 * (double)w > bound;
-    for (int q = 0; q < nsl; ++q) over |= acc[q] + c[q] > kSortEntries;
-    if (over && r > start) {
-      groups.emplace_back(start, r);
-      start = r;
-      for (int q = 0; q < nsl; ++q) acc[q] = 0;
+  // a group ends at the row whose middle passes the next multiple of the
+  // average work, found by bisection (the work of rows 0 .. r - 1 is
+  // hrp[r] - hrp[0] + r)
+  std::vector<int32_t> gstart;
+  int64_t maxrows = 0;
+  const double per = (double)(nnz + nrows) / (double)ngroups;
+  const int64_t most_entries = (int64_t)kSortEntries * nsl;
+  double bound = per;
+  for (int64_t start = 0; start < nrows;) {
+    const double cum = (double)((int64_t)hrp[start] - hrp[0] + start);
+    while (bound < cum + 0.5 * per) bound += per;
+    int64_t lo = start + 1, up = std::min(nrows, start + cap);  // the group's end
+    while (lo < up) {
+      const int64_t r = (lo + up) >> 1;
+      const double mid = (double)((int64_t)hrp[r] - hrp[0] + r) + 0.5 * (double)((int64_t)hrp[r + 1] - hrp[r] + 1);
+      if (mid > bound || (int64_t)hrp[r + 1] - hrp[start] > most_entries) up = r;
+      else lo = r + 1;
     }
-    if (r == start)
-      while (bound < cum + 0.5 * per) bound += per;
-    for (int q = 0; q < nsl; ++q) acc[q] += c[q];
-    cum += (double)w;
+    gstart.push_back((int32_t)start);
+    maxrows = std::max(maxrows, lo - start);
+    start = lo;
   }
-  groups.emplace_back(start, nrows);
-  for (auto& g : groups) maxrows = std::max(maxrows, g.second - g.first);
+  const int ng = (int)gstart.size(), nseg = ng * nsl;
+  gstart.push_back((int32_t)nrows);
   int rb = 0;
   while (((int64_t)1 << rb) < maxrows) ++rb;
-  // step blocks (row sums from the partials),
-  // slice blocks, row-major positions and the row of each row in its group
+  const std::vector<Blk>& tiles = dual ? S.bD : S.bP;
+  Blk* d_tiles = nullptr;
+  int32_t *d_g = nullptr, *d_off = nullptr, *src_in = nullptr, *src_out = nullptr;
+  uint64_t *key_in = nullptr, *key_out = nullptr;
+  T* v2 = nullptr;
+  double* v642 = nullptr;
+  talloc(&d_tiles, (int64_t)tiles.size());
+  talloc(&d_g, ng + 1);
+  talloc(&d_off, nseg + 1);
+  talloc(&key_in, nnz);
+  talloc(&key_out, nnz);
+  talloc(&src_in, nnz);
+  talloc(&src_out, nnz);
+  talloc(&v2, nnz);
+  if (sizeof(T) != 8) talloc(&v642, nnz);
+  HIPCHECK(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(Blk) * tiles.size(), hipMemcpyHostToDevice, stream_));
+  HIPCHECK(hipMemcpyAsync(d_g, gstart.data(), sizeof(int32_t) * gstart.size(), hipMemcpyHostToDevice, stream_));
+  group_keys_kernel<<<(unsigned)tiles.size(), kThreads, 0, stream_>>>(d_tiles, rp, ci, d_g, ng, r0, S.nz0, c0, len, nsl,
+                                                                      rb, key_in, src_in);
+  HIPCHECK(hipGetLastError());
+  std::vector<int> shifts;
+  radix_shifts(shifts, rb, std::min(32, bits_for((len + nsl - 1) / nsl) + rb));
+  radix_shifts(shifts, 32, 32 + bits_for(nseg - 1));
+  radix_sort_pairs<uint64_t>(key_in, src_in, key_out, src_out, nnz, shifts, stream_);
+  segment_offsets_kernel<<<nblk(nseg + 1), 256, 0, stream_>>>(key_out, nnz, nseg, d_off);
+  sorted_gather_kernel<T><<<nblk(nnz), 256, 0, stream_>>>(key_out, src_out, val, v64, nnz, ci + S.nz0, v2, v642);
+  HIPCHECK(hipGetLastError());
+  HIPCHECK(hipMemcpyAsync(val + S.nz0, v2, sizeof(T) * nnz, hipMemcpyDeviceToDevice, stream_));
+  if (v642) HIPCHECK(hipMemcpyAsync(v64 + S.nz0, v642, sizeof(double) * nnz, hipMemcpyDeviceToDevice, stream_));
+  std::vector<int32_t> off(nseg + 1);
+  HIPCHECK(hipMemcpyAsync(off.data(), d_off, sizeof(int32_t) * off.size(), hipMemcpyDeviceToHost, stream_));
+  HIPCHECK(hipStreamSynchronize(stream_));
+  dfree(v642);
+  dfree(v2);
+  dfree(src_out);
+  dfree(src_in);
+  dfree(key_out);
+  dfree(key_in);
+  dfree(d_off);
+  dfree(d_g);
+  dfree(d_tiles);
+  if (off[0] != 0 || off[nseg] != nnz) throw Error(-3, "sorted group layout does not cover the matrix");
+  // step blocks (row sums from the partials) and slice blocks
   std::vector<Blk> grp, sl;
   for (int64_t a = 0; a < nrows; a += kPartRows(dual)) {
     Blk ep;
@@ -1724,77 +1753,19 @@ void Engine<T>::group_sorted(int id, bool dual, int nsl, int64_t ngroups, int64_
     ep.pn = 0;
     grp.push_back(ep);
   }
-  std::vector<int32_t> dst(nrows * nsl), rloc(nrows), off;
-  int64_t pos = S.nz0;
-  for (size_t g = 0; g < groups.size(); ++g) {
-    const int64_t a = groups[g].first, e = groups[g].second;
-    for (int64_t r = a; r < e; ++r) rloc[r] = (int32_t)(r - a);
-    for (int q = 0; q < nsl; ++q) {
-      Blk k;
-      k.r0 = (int32_t)(r0 + a);
-      k.r1 = (int32_t)(r0 + e);
-      k.inst = id;
-      k.gid = (int32_t)g;
-      k.rp_off = (int32_t)(c0 + (q * len + nsl - 1) / nsl);
-      k.p0 = (int32_t)pos;
-      off.push_back((int32_t)(pos - S.nz0));
-      for (int64_t r = a; r < e; ++r) {
-        dst[r * nsl + q] = (int32_t)pos;
-        pos += cnt[r * nsl + q];
-      }
-      k.pn = (int32_t)(pos - k.p0);
-      k.meta = blk_meta(BK_STREAM, nsl, q) | (rb << 25);
-      sl.push_back(k);
-    }
+  for (int s = 0; s < nseg; ++s) {
+    const int g = s / nsl, q = s % nsl;
+    Blk k;
+    k.r0 = (int32_t)(r0 + gstart[g]);
+    k.r1 = (int32_t)(r0 + gstart[g + 1]);
+    k.inst = id;
+    k.gid = g;
+    k.rp_off = (int32_t)(c0 + (q * len + nsl - 1) / nsl);
+    k.p0 = (int32_t)(S.nz0 + off[s]);
+    k.pn = off[s + 1] - off[s];
+    k.meta = blk_meta(BK_STREAM, nsl, q) | (rb << 25);
+    sl.push_back(k);
   }
-  off.push_back((int32_t)(pos - S.nz0));
-  if (pos != S.nz0 + S.nnz) throw Error(-3, "sorted group layout does not cover the matrix");
-  const int64_t nnz = S.nnz;
-  const int nseg = (int)sl.size();
-  int32_t *d_dst = nullptr, *d_rloc = nullptr, *d_off = nullptr, *src_in = nullptr, *src_out = nullptr;
-  uint32_t* key32 = nullptr;
-  uint64_t *key_in = nullptr, *key_out = nullptr;
-  T* v2 = nullptr;
-  double* v642 = nullptr;
-  talloc(&d_dst, nrows * nsl);
-  talloc(&d_rloc, nrows);
-  talloc(&d_off, (int64_t)off.size());
-  talloc(&key32, nnz);
-  talloc(&key_in, nnz);
-  talloc(&key_out, nnz);
-  talloc(&src_in, nnz);
-  talloc(&src_out, nnz);
-  talloc(&v2, nnz);
-  if (sizeof(T) != 8) talloc(&v642, nnz);
-  HIPCHECK(hipMemcpyAsync(d_dst, dst.data(), sizeof(int32_t) * dst.size(), hipMemcpyHostToDevice, stream_));
-  HIPCHECK(hipMemcpyAsync(d_rloc, rloc.data(), sizeof(int32_t) * rloc.size(), hipMemcpyHostToDevice, stream_));
-  HIPCHECK(hipMemcpyAsync(d_off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice, stream_));
-  // positions run from nz0: shift the temporaries by -nz0
-  slice_keys_kernel<<<nblk(nrows), 256, 0, stream_>>>(rp, ci, r0, nrows, c0, len, nsl, d_dst, d_rloc, rb,
-                                                      key32 - S.nz0, src_in - S.nz0);
-  segment_keys_kernel<<<(unsigned)nseg, kThreads, 0, stream_>>>(d_off, key32, key_in);
-  HIPCHECK(hipGetLastError());
-  // one stable sort by (block, packed key): keys are unique within a block,
-  // so each block ends in column order
-  std::vector<int> shifts;
-  radix_shifts(shifts, 0, std::min(32, bits_for((len + nsl - 1) / nsl) + rb));
-  radix_shifts(shifts, 32, 32 + bits_for(nseg - 1));
-  radix_sort_pairs<uint64_t>(key_in, src_in, key_out, src_out, nnz, shifts, stream_);
-  sorted_gather_kernel<T><<<nblk(nnz), 256, 0, stream_>>>(key_out, src_out, val, v64, nnz, ci + S.nz0, v2, v642);
-  HIPCHECK(hipGetLastError());
-  HIPCHECK(hipMemcpyAsync(val + S.nz0, v2, sizeof(T) * nnz, hipMemcpyDeviceToDevice, stream_));
-  if (v642) HIPCHECK(hipMemcpyAsync(v64 + S.nz0, v642, sizeof(double) * nnz, hipMemcpyDeviceToDevice, stream_));
-  HIPCHECK(hipStreamSynchronize(stream_));
-  dfree(v642);
-  dfree(v2);
-  dfree(src_out);
-  dfree(src_in);
-  dfree(key_out);
-  dfree(key_in);
-  dfree(key32);
-  dfree(d_off);
-  dfree(d_rloc);
-  dfree(d_dst);
   if (dual) {
     S.bD = grp;
     S.bDS = sl;
