@@ -1140,18 +1140,22 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
     HIPCHECK(hipMemcpyAsync(d_nr, nr.data(), sizeof(int4) * ni, hipMemcpyHostToDevice, stream_));
     const unsigned gP = (unsigned)nP.size(), gD = (unsigned)nD.size();
 
-    // scaling (Ruiz infinity-norm passes, then Pock-Chambolle)
-    for (int it = 0; it < opt_.ruiz_iters; ++it) {
-      row_factor_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_v64, 0, 1.0, fm, Dr);
-      row_factor_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_v64, 0, 1.0, fn, Dc);
-      scale_values_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_ci, K_v64, fm, fn, 0);
-      scale_values_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_ci, KT_v64, fm, fn, 1);
+    // scaling (Ruiz infinity-norm passes, then Pock-Chambolle): each pass
+    // reads the factors so far from one pair of buffers and writes the other,
+    // ending in Dr and Dc
+    const int passes = opt_.ruiz_iters + (opt_.pc_alpha > 0.0 ? 1 : 0);
+    for (int it = 0; it < passes; ++it) {
+      const bool pc = it == opt_.ruiz_iters, last = (passes - it) & 1;
+      double *r_out = last ? Dr : fm, *c_out = last ? Dc : fn;
+      const double *r_in = it == 0 ? nullptr : last ? fm : Dr, *c_in = it == 0 ? nullptr : last ? fn : Dc;
+      row_factor_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_ci, K_v64, pc, pc ? 2.0 - opt_.pc_alpha : 1.0,
+                                                      c_in, r_in, r_out);
+      row_factor_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_ci, KT_v64, pc, pc ? opt_.pc_alpha : 1.0, r_in,
+                                                      c_in, c_out);
     }
-    if (opt_.pc_alpha > 0.0) {
-      row_factor_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_v64, 1, 2.0 - opt_.pc_alpha, fm, Dr);
-      row_factor_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_v64, 1, opt_.pc_alpha, fn, Dc);
-      scale_values_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_ci, K_v64, fm, fn, 0);
-      scale_values_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_ci, KT_v64, fm, fn, 1);
+    if (passes > 0) {
+      scale_values_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_ci, K_v64, Dr, Dc, 0);
+      scale_values_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_ci, KT_v64, Dr, Dc, 1);
     }
     scale_primal_kernel<T><<<gP, kThreads, 0, stream_>>>(d_nP, Dc, c_o, l_o, u_o, c, l, u, d_pp);
     scale_dual_kernel<T><<<gD, kThreads, 0, stream_>>>(d_nD, Dr, q_o, q, d_pd);

@@ -1216,74 +1216,82 @@ __global__ void tick_kernel(int64_t* gbase, int64_t add) {
 // preprocessing: Ruiz / Pock-Chambolle factors and value scaling
 // ---------------------------------------------------------------------------
 
-// f[r] = sqrt(max_j |v_rj|) (op 0) or sqrt(sum_j |v_rj|) (op 1), 1 if zero;
-// D[r] /= f[r].
-__global__ __launch_bounds__(kThreads) void row_factor_kernel(const Blk* sched, const int32_t* rp,
-                                                              const double* val, int op, double expo,
-                                                              double* f, double* D) {
-  __shared__ double s_red[kThreads / 64][kNS];
+// One scaling pass over one side's rows.  The values stay as they came; with
+// D the row's own factor so far and G the other side's, the scaled row is
+// |v_rj| G[j] D[r], and out[r] = D[r] / sqrt(its largest entry) (op 0) or
+// D[r] / sqrt(sum of its entries^expo) (op 1); rows of zeros keep D[r].  D and
+// G are null in the first pass (all ones).  out is another buffer than D: the
+// other side's pass reads D.  Bound by the gathers of G; without the values
+// rewritten after each pass it streams 12 bytes per entry and side where
+// that took 28.
+__global__ __launch_bounds__(kThreads) void row_factor_kernel(const Blk* sched, const int32_t* rp, const int32_t* ci,
+                                                              const double* val, int op, double expo, const double* G,
+                                                              const double* D, double* out) {
+  __shared__ double s_val[kPlainNB];
+  __shared__ int s_rp[kMaxRows + 1];
+  __shared__ double s_red[kThreads / 64];
   const Blk b = sched[blockIdx.x];
   const int tid = threadIdx.x;
   const int nrows = b.r1 - b.r0;
+  auto entry = [&](int e) { return G ? fabs(val[e]) * G[ci[e]] : fabs(val[e]); };
+  auto add = [&](double a, double v, double d) {
+    if (op == 0) return fmax(a, v);
+    return a + (expo != 1.0 ? pow(v * d, expo) : v);
+  };
+  auto finish = [&](int64_t r, double a, double d) {
+    // sums of powers already hold the row's factor
+    const double f = sqrt(op == 0 || expo == 1.0 ? a * d : a);
+    out[r] = f > 0.0 ? d / f : d;
+  };
   if (blk_kind(b) == BK_LONG) {
-    const int p0 = rp[b.r0], p1 = rp[b.r0 + 1];
+    const double d = D ? D[b.r0] : 1.0;
     double a = 0.0;
-    for (int e = p0 + tid; e < p1; e += kThreads) {
-      double v = fabs(val[e]);
-      if (op == 1 && expo != 1.0) v = pow(v, expo);
-      a = op == 0 ? fmax(a, v) : a + v;
-    }
-    // block reduce (max or sum) through LDS in fixed order
-    __syncthreads();
+#pragma unroll 4
+    for (int k = tid; k < b.pn; k += kThreads) a = add(a, entry(b.p0 + k), d);
+    // max or sum over the block, in fixed order
     if (op == 0) {
       for (int off = 32; off > 0; off >>= 1) a = fmax(a, __shfl_xor(a, off, 64));
     } else {
       a = wave_sum(a);
     }
-    if ((tid & 63) == 0) s_red[tid >> 6][0] = a;
+    if ((tid & 63) == 0) s_red[tid >> 6] = a;
     __syncthreads();
     if (tid == 0) {
-      double r = s_red[0][0];
-      for (int w = 1; w < kThreads / 64; ++w) r = op == 0 ? fmax(r, s_red[w][0]) : r + s_red[w][0];
-      double fr = sqrt(r);
-      if (!(fr > 0.0)) fr = 1.0;
-      f[b.r0] = fr;
-      D[b.r0] /= fr;
+      double r = s_red[0];
+      for (int w = 1; w < kThreads / 64; ++w) r = op == 0 ? fmax(r, s_red[w]) : r + s_red[w];
+      finish(b.r0, r, d);
     }
     return;
   }
-  const int G = group_size(nrows);
-  const int lane = tid & (G - 1);
-  for (int base = 0; base < nrows; base += kThreads / G) {
-    const int r = base + tid / G;
+  for (int r = tid; r <= nrows; r += kThreads) s_rp[r] = rp[b.r0 + r] - b.p0;
+#pragma unroll
+  for (int i = 0; i < (kPlainNB + kThreads - 1) / kThreads; ++i) {
+    const int k = tid + i * kThreads;
+    if (k < b.pn) s_val[k] = entry(b.p0 + k);
+  }
+  __syncthreads();
+  const int L = group_size(nrows);  // lanes per row
+  const int lane = tid & (L - 1);
+  for (int base = 0; base < nrows; base += kThreads / L) {
+    const int r = base + tid / L;
+    const double d = r < nrows && D ? D[b.r0 + r] : 1.0;
     double a = 0.0;
-    if (r < nrows) {
-      const int p1 = rp[b.r0 + r + 1];
-      for (int e = rp[b.r0 + r] + lane; e < p1; e += G) {
-        double v = fabs(val[e]);
-        if (op == 1 && expo != 1.0) v = pow(v, expo);
-        a = op == 0 ? fmax(a, v) : a + v;
-      }
-    }
-    for (int off = G >> 1; off > 0; off >>= 1) {
+    if (r < nrows)
+      for (int k = s_rp[r] + lane; k < s_rp[r + 1]; k += L) a = add(a, s_val[k], d);
+    for (int off = L >> 1; off > 0; off >>= 1) {
       const double o = __shfl_xor(a, off, 64);
       a = op == 0 ? fmax(a, o) : a + o;
     }
-    if (lane == 0 && r < nrows) {
-      double fr = sqrt(a);
-      if (!(fr > 0.0)) fr = 1.0;
-      f[b.r0 + r] = fr;
-      D[b.r0 + r] /= fr;
-    }
+    if (lane == 0 && r < nrows) finish((int64_t)b.r0 + r, a, d);
   }
 }
 
-// v_e <- v_e / fm[m-index] / fn[n-index]; for K the row is the m-index,
+// v_e <- v_e * Dr[m-index] * Dc[n-index]; for K the row is the m-index,
 // for K^T the row is the n-index.  Same operation order for both, so K~ and
 // (K~)^T hold bit-identical values.
 __global__ __launch_bounds__(kThreads) void scale_values_kernel(const Blk* sched, const int32_t* rp,
                                                                 const int32_t* ci, double* val,
-                                                                const double* fm, const double* fn,
+                                                                const double* Dr, const double* Dc,
                                                                 int transposed) {
   const Blk b = sched[blockIdx.x];
   const int nrows = b.r1 - b.r0;
@@ -1297,9 +1305,9 @@ __global__ __launch_bounds__(kThreads) void scale_values_kernel(const Blk* sched
     const int p1 = rp[row + 1];
     for (int e = rp[row] + lane; e < p1; e += G) {
       const int c = ci[e];
-      const double a = transposed ? fm[c] : fm[row];
-      const double d = transposed ? fn[row] : fn[c];
-      val[e] = val[e] / a / d;
+      const double a = transposed ? Dr[c] : Dr[row];
+      const double d = transposed ? Dc[row] : Dc[c];
+      val[e] = val[e] * a * d;
     }
   }
 }
