@@ -486,6 +486,19 @@ class Engine final : public EngineBase {
   void group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int64_t ngroups, int64_t cap);
   bool group_shape(int64_t nrows, int64_t width, int nsl_min, int* nsl, int64_t* ngroups, int64_t* cap) const;
   int group_lds_rows(bool dual) const;
+  // An LP that resident_steps can step.  It does so where all LPs of the
+  // schedule are small (the kernel of a chunk would otherwise hold up the
+  // larger ones' steps) and K and K^T one column-sorted block each.  Timed
+  // engines (profile) step every LP in the kernels they time.
+  bool small(const Slot& S) const {
+    const int64_t rows = std::min<int64_t>({(int64_t)opt_.sort_rows, kSortRowsPlain, kResRows});
+    return opt_.plain_sort && opt_.profile == 0 && S.m > 0 && S.nnz > 0 && S.m <= rows && S.n <= rows &&
+           S.nnz <= (int64_t)kResRows * kResEntries;
+  }
+  bool all_small(const std::vector<int>& ids) const {
+    return std::all_of(ids.begin(), ids.end(), [&](int id) { return small(slots_[id]); });
+  }
+  void recut(const std::vector<int>& ids, int64_t max_blocks, int64_t min_rows, bool solo);
   // temporary memory of a sort of nnz entries into blocks: keys and positions
   // twice over and once more for the radix sort, its counts, and the values
   static int64_t temp_bytes(int64_t nnz) { return (sizeof(T) == 8 ? 45 : 49) * nnz + (1 << 18); }
@@ -537,6 +550,10 @@ class Engine final : public EngineBase {
       *d_schedPE = nullptr, *d_schedDE = nullptr;
   int64_t capP_ = 0, capD_ = 0, nP_ = 0, nD_ = 0;
   int64_t capPB_ = 0, capDB_ = 0, nPB_ = 0, nDB_ = 0;  // column-sorted blocks (sorted_step)
+  Blk* d_schedR = nullptr;
+  int64_t capR_ = 0, nR_ = 0;  // small LPs (resident_steps), two blocks each
+  int tpbR_ = 256;             // threads per workgroup there
+  size_t ldsR_ = 0;            // and its dynamic LDS
   int64_t capPE_ = 0, capDE_ = 0, nPE_ = 0, nDE_ = 0;  // rows of sliced products (part_step)
   int64_t cap_partP_ = 0, cap_partD_ = 0;              // blocks that partP / partD hold sums of
   double *partP = nullptr, *partD = nullptr;
@@ -636,6 +653,10 @@ void Engine<T>::allocate() {
   for (const void* f : {(const void*)sorted_step<T, true, 256>, (const void*)sorted_step<T, true, 512>,
                         (const void*)sorted_step<T, false, 256>, (const void*)sorted_step<T, false, 512>})
     HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(double) * (kSortWordsPlain + kSpareWords)));
+  // row sums of both products with their copies, and the gathered vectors
+  const int lds_res = 2 * (int)sizeof(double) * kSortWordsPlain + 2 * (int)sizeof(T) * kResRows;
+  for (const void* f : {(const void*)resident_steps<T, 256>, (const void*)resident_steps<T, kResRows>})
+    HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_res));
   HIPCHECK(hipStreamSynchronize(stream_));
 }
 
@@ -653,6 +674,7 @@ void Engine<T>::release_all() {
   dfree(d_schedD);
   dfree(d_schedPB);
   dfree(d_schedDB);
+  dfree(d_schedR);
   dfree(d_schedPE);
   dfree(d_schedDE);
   dfree(partP);
@@ -727,6 +749,7 @@ IterArgs<T> Engine<T>::args() const {
   A.schedDB = d_schedDB;
   A.schedPE = d_schedPE;
   A.schedDE = d_schedDE;
+  A.schedR = d_schedR;
   A.schedPS = d_schedPS;
   A.schedDS = d_schedDS;
   return A;
@@ -1095,6 +1118,16 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   }
   int64_t maxb = 0, minr = 0;
   plain_shape(live(), &maxb, &minr);
+  std::vector<int> used, single;  // single: small LPs in one block that now share their launches with larger ones
+  for (int s = 0; s < nslots_; ++s)
+    if (slots_[s].used) used.push_back(s);
+  if (all_small(used)) {
+    maxb = minr = 1;
+  } else {
+    for (int s : used)
+      if (small(slots_[s]) && slots_[s].plainP == 1 && slots_[s].plainD == 1) single.push_back(s);
+    recut(single, maxb, minr, false);
+  }
   for (const bool dual : {true, false})
     sort_blocks(plain[dual], dual, plain_rp[dual], maxb, minr, false, kSortRun);
   sched_dirty_ = true;
@@ -1382,27 +1415,35 @@ void Engine<T>::reblock_for(const int* status) {
   if (run.empty()) return;
   int64_t maxb = 0, minr = 0;
   plain_shape((int64_t)run.size(), &maxb, &minr);
+  recut(run, maxb, minr, all_small(run));
+}
+
+// Lays the plain sorted blocks of the LPs `ids` out anew where the shape calls
+// for more of them, or (solo: all of them are small) for one block each.
+template <class T>
+void Engine<T>::recut(const std::vector<int>& ids, int64_t maxb, int64_t minr, bool solo) {
+  if (solo) maxb = minr = 1;
   bool changed = false;
   for (const bool dual : {false, true}) {
-    std::vector<int> ids;
+    std::vector<int> todo;
     std::vector<std::vector<int32_t>> rp;
     std::vector<const int32_t*> rps;
     int64_t largest = 0;
-    for (int s : run) {
+    for (int s : ids) {
       const Slot& S = slots_[s];
       const int64_t cur = dual ? S.plainD : S.plainP, nrows = dual ? S.m : S.n;
-      if (cur == 0 || plain_blocks(nrows, maxb, minr) <= cur) continue;
-      ids.push_back(s);
+      if (cur == 0 || (solo ? cur == 1 : plain_blocks(nrows, maxb, minr) <= cur)) continue;
+      todo.push_back(s);
       largest = std::max(largest, S.nnz);
       rp.emplace_back(nrows + 1);
       HIPCHECK(hipMemcpy(rp.back().data(), (dual ? K_rp : KT_rp) + (dual ? S.row0 : S.col0),
                          sizeof(int32_t) * (nrows + 1), hipMemcpyDeviceToHost));
     }
-    if (ids.empty()) continue;
+    if (todo.empty()) continue;
     for (auto& v : rp) rps.push_back(v.data());
     TempScope temp(temp_bytes(largest));
     // temporary memory for the largest of them, as a server's budget allows
-    sort_blocks(ids, dual, rps, maxb, minr, true, largest);
+    sort_blocks(todo, dual, rps, maxb, minr, true, largest);
     changed = true;
   }
   if (changed) sched_dirty_ = true;
@@ -1898,9 +1939,10 @@ void Engine<T>::mark_streaming(const std::vector<int>& live, std::initializer_li
 template <class T>
 void Engine<T>::rebuild_schedules() {
   // P / D: tiles; PB / DB: column-sorted blocks; PE / DE: rows of sliced
-  // products; PS / DS: slice blocks.  gids number an LP's step blocks of all
+  // products; PS / DS: slice blocks; R: both blocks of each small LP.  gids number an LP's step blocks of all
   // three kinds in one range.
-  std::vector<Blk> P, D, PB, DB, PE, DE, PS, DS;
+  std::vector<Blk> P, D, PB, DB, PE, DE, PS, DS, R;
+  const std::vector<Blk> none;
   std::vector<int> live;
   std::vector<int4> rg;
   std::vector<std::pair<int, int>> rP, rD, rPB, rDB;
@@ -1918,19 +1960,29 @@ void Engine<T>::rebuild_schedules() {
     rs.push_back({s0, (int)sorted.size()});
   };
   for (int s = 0; s < nslots_; ++s) {
-    const Slot& sl = slots_[s];
-    if (!sl.used) continue;
+    if (!slots_[s].used) continue;
     if (finished_ && finished_[s] != ST_RUNNING) continue;  // done: its blocks would only exit
+    live.push_back(s);
+  }
+  auto one_block = [](const std::vector<Blk>& v) { return v.size() == 1 && blk_kind(v[0]) == BK_SORTED; };
+  const bool solo = std::all_of(live.begin(), live.end(), [&](int s) {
+    return small(slots_[s]) && one_block(slots_[s].bP) && one_block(slots_[s].bD);
+  });
+  for (int s : live) {
+    const Slot& sl = slots_[s];
     int4 r;
     r.x = gP;
     r.z = gD;
     PS.insert(PS.end(), sl.bPS.begin(), sl.bPS.end());
     DS.insert(DS.end(), sl.bDS.begin(), sl.bDS.end());
-    append(P, PB, PE, sl.bP, gP, rP, rPB);
-    append(D, DB, DE, sl.bD, gD, rD, rDB);
+    append(P, PB, PE, solo ? none : sl.bP, gP, rP, rPB);
+    append(D, DB, DE, solo ? none : sl.bD, gD, rD, rDB);
+    if (solo) {
+      R.push_back(sl.bP[0]);
+      R.push_back(sl.bD[0]);
+    }
     r.y = gP;
     r.w = gD;
-    live.push_back(s);
     rg.push_back(r);
   }
   for (double& v : sched_size_) v = 0.0;
@@ -1966,6 +2018,16 @@ void Engine<T>::rebuild_schedules() {
       if (blk_kind(k) == BK_SORTED) w = std::max(w, (k.r1 - k.r0) << blk_rep_shift(k));
     return w;
   };
+  tpbR_ = 256;
+  ldsR_ = 0;
+  for (size_t k = 0; k < R.size(); k += 2) {
+    size_t lds = 0;
+    for (const Blk& b : {R[k], R[k + 1]}) {
+      lds += sizeof(double) * ((size_t)(b.r1 - b.r0) << blk_rep_shift(b)) + sizeof(T) * (size_t)(b.r1 - b.r0);
+      if (b.r1 - b.r0 > 256 || b.pn > 256 * kResEntries) tpbR_ = kResRows;
+    }
+    ldsR_ = std::max(ldsR_, lds);
+  }
   ldsPB_ = words(PB);
   ldsDB_ = words(DB);
   // threads per column-sorted block: 512 where each CU has one large block
@@ -2000,6 +2062,7 @@ void Engine<T>::rebuild_schedules() {
   upload(D, d_schedD, capD_, nD_);
   upload(PB, d_schedPB, capPB_, nPB_);
   upload(DB, d_schedDB, capDB_, nDB_);
+  upload(R, d_schedR, capR_, nR_);
   upload(PE, d_schedPE, capPE_, nPE_);
   upload(DE, d_schedDE, capDE_, nDE_);
   upload(PS, d_schedPS, capPS_, nPS_);
@@ -2107,6 +2170,10 @@ void Engine<T>::launch_chunk() {
   }
   auto enqueue = [&](bool timed) {
     tick_kernel<<<1, 1, 0, stream_>>>(d_gbase, (int64_t)CH);
+    if (nR_) {
+      if (tpbR_ == 256) resident_steps<T, 256><<<(unsigned)(nR_ / 2), 256, ldsR_, stream_>>>(A, CH);
+      else resident_steps<T, kResRows><<<(unsigned)(nR_ / 2), kResRows, ldsR_, stream_>>>(A, CH);
+    }
     for (int i = 0; i < CH; ++i) {
       hipEvent_t* e = timed ? &pev_[6 * i] : nullptr;
       if (timed) HIPCHECK(hipEventRecord(e[0], stream_));

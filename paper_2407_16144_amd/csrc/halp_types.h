@@ -93,6 +93,11 @@ constexpr int kSortWordsPlain = 4096;
 constexpr int kRepRow = 256;
 constexpr int kMinRepShift = 3, kMaxRepShift = 5;
 constexpr int kSpareWords = 64;  // LDS words behind the row sums (SortedStream)
+// LPs of at most kResRows rows on either side and kResEntries entries per
+// thread of a kResRows-thread workgroup step in a kernel that keeps them on one
+// CU for a whole chunk (resident_steps).
+constexpr int kResRows = 1024;
+constexpr int kResEntries = 8;
 // Longest row of a column-sorted plain block; longer ones get a block of
 // their own (BK_LONG).
 constexpr int kSortedRowMax = 1 << 15;

@@ -68,6 +68,7 @@ struct IterArgs {
   const Blk* schedDB;
   const Blk* schedPE;  // rows whose products the slice kernels computed (part_step)
   const Blk* schedDE;
+  const Blk* schedR;  // small LPs: K^T and K block of each
   const Blk* schedPS;  // slice blocks of sliced row groups (slice kernel)
   const Blk* schedDS;
 };

@@ -423,9 +423,9 @@ __device__ __forceinline__ void clear_rows(double* s_row, int words, int tpb) {
 // position, kty its row sum (K^T y, or K^T yT at an eval step, where g1 and
 // g2 are K^T cy1 and K^T cy2; at a residual step the caller passes T(z) as
 // xo and x0j and K^T yT as kty).  Adds the check / eval / residual terms of
-// the variable to ps.
+// the variable to ps.  Returns xbar (eval step: nothing of use).
 template <class T>
-__device__ __forceinline__ void primal_row(const IterArgs<T>& A, const InstState& S, int mode, int64_t g,
+__device__ __forceinline__ T primal_row(const IterArgs<T>& A, const InstState& S, int mode, int64_t g,
                                            int64_t j, T cj, T lj, T uj, T xo, T x0j, T kty, T g1, T g2,
                                            double (&ps)[kNS]) {
   const bool resid = (mode == M_RESID);
@@ -451,7 +451,7 @@ __device__ __forceinline__ void primal_row(const IterArgs<T>& A, const InstState
       ps[2 * a] += sv;
       ps[2 * a + 1] += vv * vv;
     }
-    return;
+    return (T)0;
   }
   const T tau = (T)S.tau;
   const T xp = clampT<T>(xo - tau * (cj - kty), lj, uj);
@@ -493,6 +493,7 @@ __device__ __forceinline__ void primal_row(const IterArgs<T>& A, const InstState
     A.actx[j] = act;
     ps[5] += (was != 255 && was != act) ? 1.0 : 0.0;
   }
+  return xb;
 }
 
 template <class T>
@@ -842,9 +843,9 @@ __device__ __forceinline__ void finish_step(const IterArgs<T>& A, int inst, int 
 // position, s0 its row sum (K xbar, or K xT at an eval step, where a1 and a2
 // are K cx1 and K cx2; at a residual step the caller passes T(z) as yo and
 // y0i and the saved K x+ as kxpi).  Adds the check / eval / residual terms
-// of the row to ps.
+// of the row to ps.  Returns the next y (eval step: nothing of use).
 template <class T>
-__device__ __forceinline__ void dual_row(const IterArgs<T>& A, const InstState& S, int mode, int64_t g,
+__device__ __forceinline__ T dual_row(const IterArgs<T>& A, const InstState& S, int mode, int64_t g,
                                          int64_t i, T qi, T yo, T y0i, T kxpi, T s0, T a1, T a2,
                                          double (&ps)[kNS]) {
   const bool resid = (mode == M_RESID);
@@ -866,24 +867,24 @@ __device__ __forceinline__ void dual_row(const IterArgs<T>& A, const InstState& 
         ps[2 * a] += av * av;
       }
     }
-    return;
+    return (T)0;
   }
   const T sigma = (T)S.sigma;
   T yp = yo + sigma * (qi - s0);
   if (ineq) yp = fmax(yp, (T)0);
   const T yb = (T)2 * yp - yo;
   const int64_t k = g - S.kbase;
-  T yc = yp;  // check candidate
+  T yn = yp, yc = yp;  // next iterate; check candidate
   if (S.avg) {
     const T ysum = (k == 0 ? yo : A.ys[i]) + yp;
     A.ys[i] = ysum;
-    A.y[i] = yp;
     if (mode == M_CHECK) yc = ysum / (T)(k + 2);
   } else {
     const double w = (double)(k + 1) / (double)(k + 2);
     const T yh = S.reflect ? yb : yp;
-    A.y[i] = (T)w * yh + (T)(1.0 - w) * y0i;
+    yn = (T)w * yh + (T)(1.0 - w) * y0i;
   }
+  A.y[i] = yn;
   if (resid) {
     A.y0[i] = yo;
     const double d = (double)yo - (double)yp;
@@ -912,6 +913,7 @@ __device__ __forceinline__ void dual_row(const IterArgs<T>& A, const InstState& 
     A.acty[i] = act;
     ps[5] += (was != 255 && was != act) ? 1.0 : 0.0;
   }
+  return yn;
 }
 
 template <class T>
@@ -1206,6 +1208,180 @@ __global__ __launch_bounds__(kThreads) void part_step(IterArgs<T> A, int step) {
     if (tid < kNS) (DUAL ? A.partD : A.partP)[(int64_t)b.gid * kNS + tid] = s_out[tid];
     if constexpr (DUAL) finish_step<kThreads>(A, b.inst, mode, g, s_red, s_out);
   }
+}
+
+// ---------------------------------------------------------------------------
+// small LPs: all steps of a chunk in one workgroup
+// ---------------------------------------------------------------------------
+
+// One thread's entries of a column-sorted block, kept in registers.
+template <class T, int TPB>
+struct ResidentEntries {
+  uint32_t k[kResEntries];
+  T v[kResEntries];
+  int cnt, rb, rs;
+  __device__ __forceinline__ void load(const Blk& b, const int32_t* ci, const T* val) {
+    const int tid = threadIdx.x;
+    cnt = b.pn > tid ? (b.pn - tid + TPB - 1) / TPB : 0;
+    rb = blk_rowbits(b);
+    rs = blk_rep_shift(b);
+#pragma unroll
+    for (int u = 0; u < kResEntries; ++u) {
+      k[u] = 0;
+      v[u] = (T)0;
+      if (u < cnt) {
+        k[u] = (uint32_t)ci[b.p0 + tid + u * TPB];
+        v[u] = val[b.p0 + tid + u * TPB];
+      }
+    }
+  }
+  // adds the products with src (the vector from the block's first column on)
+  // into the row sums, each lane into its copy of a row's
+  template <class Src>
+  __device__ __forceinline__ void sum(Src src, double* s_row) const {
+    const uint32_t rmask = (1u << rb) - 1u;
+    const uint32_t copy = threadIdx.x & ((1u << rs) - 1u);
+    T g[kResEntries];
+#pragma unroll
+    for (int u = 0; u < kResEntries; ++u)
+      if (u < cnt) g[u] = src[k[u] >> rb];
+#pragma unroll
+    for (int u = 0; u < kResEntries; ++u)
+      if (u < cnt) atomicAdd(&s_row[((k[u] & rmask) << rs) + copy], (double)(v[u] * g[u]));
+  }
+  // row r's sum (copies in a fixed order), which is cleared for the next product
+  __device__ __forceinline__ T take(double* s_row, int r) const {
+    double* w = s_row + (r << rs);
+    double a = 0.0;
+    for (int c = 0; c < (1 << rs); ++c) {
+      a += w[c];
+      w[c] = 0.0;
+    }
+    return (T)a;
+  }
+};
+
+// All steps of a chunk of an LP whose K and K^T are one column-sorted block
+// each of at most TPB rows and kResEntries * TPB entries: one workgroup
+// per LP, one thread per row of either product.  Two kernels per iteration are
+// bound by their launches and by the chain of loads that each begins with
+// (arguments, descriptor, entries, gathers: 3.9 us per kernel at 60 x 120,
+// for 0.1 us of work); here the entries stay in registers, the gathered
+// vectors and the LP state in LDS, and a step waits for LDS only: what is in
+// device memory a thread only reads back itself (x and x0 right after they are
+// stored, a half step before their use).
+template <class T, int TPB>
+__global__ __launch_bounds__(TPB) void resident_steps(IterArgs<T> A, int steps) {
+  extern __shared__ __align__(16) unsigned char resident_lds[];
+  __shared__ double s_red[TPB / 64][kNS];
+  __shared__ double s_p[kNS], s_d[kNS];
+  __shared__ InstState s_S;
+  const int tid = threadIdx.x;
+  const Blk bp = A.schedR[2 * blockIdx.x], bd = A.schedR[2 * blockIdx.x + 1];
+  const int n = bp.r1 - bp.r0, m = bd.r1 - bd.r0;
+  const int wordsP = n << blk_rep_shift(bp), wordsD = m << blk_rep_shift(bd);
+  double* s_rowP = reinterpret_cast<double*>(resident_lds);
+  double* s_rowD = s_rowP + wordsP;
+  T* s_xbar = reinterpret_cast<T*>(s_rowD + wordsD);
+  T* s_y = s_xbar + n;
+  const int64_t g0 = *A.gbase;
+  const int words = (int)(sizeof(InstState) / sizeof(uint32_t));
+  for (int i = tid; i < words; i += TPB)
+    reinterpret_cast<uint32_t*>(&s_S)[i] = reinterpret_cast<const uint32_t*>(A.st + bp.inst)[i];
+  ResidentEntries<T, TPB> eP, eD;
+  eP.load(bp, A.KT_ci, A.KT_v);
+  eD.load(bd, A.K_ci, A.K_v);
+  int64_t j = (int64_t)bp.r0 + min(tid, n - 1), i = (int64_t)bd.r0 + min(tid, m - 1);
+  const T cj = A.c[j], lj = A.l[j], uj = A.u[j], qi = A.q[i];
+  T x = A.x[j], x0 = A.x0[j], y = A.y[i], y0 = A.y0[i];
+  if (tid < n) s_xbar[tid] = A.xbar[j];
+  if (tid < m) s_y[tid] = y;
+  for (int w = tid; w < wordsP + wordsD; w += TPB) s_rowP[w] = 0.0;
+  __syncthreads();
+  for (int s = 0; s < steps; ++s) {
+    const int64_t g = g0 + s;
+    if (s_S.status != ST_RUNNING) break;
+    const int mode = __builtin_amdgcn_readfirstlane(step_mode(s_S, g));
+    if (mode == M_SKIP) continue;
+    // addresses formed where they are used, not kept in registers for all steps
+    asm volatile("" : "+v"(j), "+v"(i));
+    double ps[kNS];
+    T a0 = 0, a1 = 0, a2 = 0;
+    // an eval step puts the vectors that it multiplies in the place of y
+    // (of xbar below, which the next primal step replaces), one after the other
+#pragma unroll 1
+    for (int a = mode == M_EVAL ? 2 : mode == M_RESID ? -1 : 0; a >= 0; --a) {
+      if (mode == M_EVAL) {
+        if (tid < m) s_y[tid] = (a == 0 ? A.yT : a == 1 ? A.cy1 : A.cy2)[i];
+        lds_barrier();
+      }
+      eP.sum(s_y, s_rowP);
+      lds_barrier();
+      a2 = a1;
+      a1 = a0;
+      if (tid < n) a0 = eP.take(s_rowP, tid);
+    }
+    if (mode == M_EVAL && tid < m) s_y[tid] = y;
+#pragma unroll
+    for (int q = 0; q < kNS; ++q) ps[q] = 0.0;
+    if (tid < n) {
+      if (mode == M_RESID) {
+        x = A.xT[j];
+        x0 = x;
+        a0 = A.ktyp[j];
+      }
+      const T xb = primal_row<T>(A, s_S, mode, g, j, cj, lj, uj, x, x0, a0, a1, a2, ps);
+      if (mode != M_EVAL) s_xbar[tid] = xb;
+      x = A.x[j];
+      x0 = A.x0[j];
+    }
+    if (mode == M_NORMAL) {
+      lds_barrier();
+    } else {
+      block_sum_ns<TPB>(ps, s_red, s_p);
+    }
+#pragma unroll 1
+    for (int a = mode == M_EVAL ? 2 : 0; a >= 0; --a) {
+      if (mode == M_EVAL) {
+        if (tid < n) s_xbar[tid] = (a == 0 ? A.xT : a == 1 ? A.cx1 : A.cx2)[j];
+        lds_barrier();
+      }
+      eD.sum(s_xbar, s_rowD);
+      lds_barrier();
+      a2 = a1;
+      a1 = a0;
+      if (tid < m) a0 = eD.take(s_rowD, tid);
+    }
+#pragma unroll
+    for (int q = 0; q < kNS; ++q) ps[q] = 0.0;
+    if (tid < m) {
+      T kxpi = 0;
+      if (mode == M_RESID) {
+        y = A.yT[i];
+        y0 = y;
+        kxpi = A.kxp[i];
+      }
+      const T yn = dual_row<T>(A, s_S, mode, g, i, qi, y, y0, kxpi, a0, a1, a2, ps);
+      if (mode != M_EVAL) {
+        s_y[tid] = yn;
+        y = yn;
+      }
+      if (mode != M_NORMAL) {
+        y = A.y[i];
+        y0 = A.y0[i];
+      }
+    }
+    if (mode == M_NORMAL) {
+      lds_barrier();
+    } else {
+      block_sum_ns<TPB>(ps, s_red, s_d);
+      __syncthreads();
+      if (tid == 0) controller(s_S, s_p, s_d, mode, g, A.status_out, bp.inst);
+      __syncthreads();
+    }
+  }
+  for (int i2 = tid; i2 < words; i2 += TPB)
+    reinterpret_cast<uint32_t*>(A.st + bp.inst)[i2] = reinterpret_cast<const uint32_t*>(&s_S)[i2];
 }
 
 __global__ void tick_kernel(int64_t* gbase, int64_t add) {
@@ -1607,6 +1783,10 @@ template __global__ void dual_slice_step<float, 256>(IterArgs<float>, int);
 template __global__ void dual_slice_step<float, 512>(IterArgs<float>, int);
 template __global__ void dual_slice_step<float, 1024>(IterArgs<float>, int);
 template __global__ void cast_kernel<float>(const double*, float*, int64_t);
+template __global__ void resident_steps<double, 256>(IterArgs<double>, int);
+template __global__ void resident_steps<double, 1024>(IterArgs<double>, int);
+template __global__ void resident_steps<float, 256>(IterArgs<float>, int);
+template __global__ void resident_steps<float, 1024>(IterArgs<float>, int);
 template __global__ void scale_primal_kernel<double>(const Blk*, const double*, const double*, const double*,
                                                      const double*, double*, double*, double*, double*);
 template __global__ void scale_primal_kernel<float>(const Blk*, const double*, const double*, const double*,

@@ -97,3 +97,76 @@ def test_batch_sorted_together(blocks):
         for a, b in ((x, xr), (y, yr)):
             floor = max(1e-2 * float(np.max(np.abs(b))), 1e-300)
             assert float(np.max(np.abs(a - b) / np.maximum(np.abs(b), floor))) <= 1e-10
+
+
+RESIDENT = {
+    "one entry": lambda: _lp([1], 1, 30, m_eq=1),
+    "256 rows, 2048 entries": lambda: _lp([8] * 256, 256, 31),
+    "2049 entries": lambda: _lp([8] * 255 + [9], 256, 32),
+    "257 rows": lambda: _lp([3] * 257, 200, 33),
+    "one dominant row": lambda: _lp([900] + [1] * 50, 1000, 34),
+    "1024 rows, 8192 entries": lambda: _lp([8] * 1024, 1024, 35),
+    "8193 entries": lambda: _lp([8] * 1023 + [9], 1024, 36),
+    "1025 columns": lambda: _lp([4] * 300, 1025, 37),
+    "empty rows and columns": lambda: _lp([0, 0, 31, 0, 1, 33, 0] * 12 + [0], 500, 38),
+}
+
+
+@pytest.mark.parametrize("method", ["r2hpdhg", "rhpdhg", "rapdhg"])
+@pytest.mark.parametrize("name", list(RESIDENT))
+def test_small_lp_on_one_cu(name, method):
+    """LPs at the limits of the kernel that steps a small LP on one CU (rows and
+    entries per workgroup size, one past each), and the same LPs in the kernels
+    per product (a timed engine keeps to them): each agrees with the oracle's
+    trajectory to 1e-10."""
+    if method != "r2hpdhg" and name not in ("257 rows", "one dominant row"):
+        pytest.skip("methods differ in the row functions, which all sizes share")
+    lp = RESIDENT[name]()
+    print(f"case small LP {name} {method} m={lp.m} n={lp.n} nnz={lp.nnz}", flush=True)
+    P = core.scaled_problem(lp)
+    s, _ = oracle.power_iteration(P.K, 0, max_iters=30)
+    eta = 0.9 / s
+    code = {"rhpdhg": 0, "r2hpdhg": 1, "rapdhg": 2}[method]
+    ref = oracle.solve(lp, oracle.Options(tol=0.0, max_iter=330, eta=eta, method=method))
+    for profile in (0, 1):
+        opt = halp.lp_default_options(eta=eta, method=code, profile=profile)
+        res, x, y, _ = halp.solve_lp(lp, tol=0.0, max_iter=330, opt=opt)
+        assert res["iters"] == ref.iters and res["restarts"] == ref.restarts
+        for a, b in ((x, ref.x), (y, ref.y)):
+            floor = max(1e-2 * float(np.max(np.abs(b))), 1e-300)
+            assert float(np.max(np.abs(a - b) / np.maximum(np.abs(b), floor))) <= 1e-10
+
+
+def test_small_lps_joined_by_a_large_one():
+    """A server steps small LPs on one CU each until a larger LP joins them
+    (their blocks are then cut for shared launches) and again once it has
+    retired: every LP ends as it does alone, and the optimal ones meet their
+    tolerance as the oracle measures it."""
+    small = [lpgen.scaled_powerlaw(40 + i, 150 + 60 * i, 400 + 100 * i) for i in range(5)]
+    big = lpgen.scaled_powerlaw(50, 4000, 12000)
+    print("case small LPs joined by a large one", flush=True)
+    lps = small[:3] + [big] + small[3:]
+    h = halp.lp_server_create(1 << 30, 8)
+    try:
+        tickets = [halp.lp_server_submit(h, lp, 1e-6, 200_000, 0.0) for lp in lps[:3]]
+        halp.lp_server_step(h, 1)
+        tickets += [halp.lp_server_submit(h, lp, 1e-6, 200_000, 1.0) for lp in lps[3:]]
+        open_ = set(range(len(lps)))
+        for _ in range(10_000):
+            halp.lp_server_step(h, 4)
+            for k in sorted(open_):
+                r, _t = halp.lp_server_poll(h, tickets[k])
+                if r is None:
+                    continue
+                x, y = halp.lp_server_get_solution(h, tickets[k], lps[k].n, lps[k].m)
+                halp.lp_server_release(h, tickets[k])
+                open_.discard(k)
+                kkt, parts = oracle.rel_kkt(lps[k], x, y)
+                alone, *_ = halp.solve_lp(lps[k], tol=1e-6, max_iter=200_000)
+                assert r.status == alone["status"], k
+                assert r.status != halp.LP_OPTIMAL or kkt <= 1e-6 * (1 + 1e-6), (k, parts)
+            if not open_:
+                break
+        assert not open_
+    finally:
+        halp.lp_server_destroy(h)
