@@ -317,7 +317,10 @@ void run_polish(Polish& P, const halp::Options& opt, hipStream_t stream, halp::E
   o64.precision = 0;
   P.eng = halp::make_engine(o64, stream, ms, ns, zs, (int)which.size());
   std::vector<halp::Problem> probs;
-  for (int i : which) probs.push_back(to_problem(raw[i]->view));
+  for (int i : which) {
+    probs.push_back(to_problem(raw[i]->view));
+    probs.back().scaling = src.scaling(src_ids[i]);
+  }
   const std::vector<int> ids = P.eng->add(probs, raw[which[0]]->on_device);
   double* buf = nullptr;
   if (hipMalloc((void**)&buf, sizeof(double) * buf_len) != hipSuccess)

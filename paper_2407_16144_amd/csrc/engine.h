@@ -16,6 +16,15 @@
 
 namespace halp {
 
+// Scaling and spectral norm of an LP that an engine holds (device pointers,
+// valid while it does).
+struct Scaling {
+  const double* Dr = nullptr;
+  const double* Dc = nullptr;
+  double sigma_hat = 0.0;
+  int power_iters = 0;
+};
+
 struct Problem {  // one input LP; pointers are host or device memory
   int64_t n = 0, m_eq = 0, m_ineq = 0;
   const int32_t* rp = nullptr;
@@ -25,6 +34,7 @@ struct Problem {  // one input LP; pointers are host or device memory
   const double* rhs = nullptr;
   const double* lb = nullptr;
   const double* ub = nullptr;
+  Scaling scaling;  // of the same LP in another engine with the same options: not computed again
 };
 
 struct Options {
@@ -128,6 +138,7 @@ class EngineBase {
   virtual bool fits_empty(int64_t n, int64_t m, int64_t nnz) const = 0;
   virtual KernelTimes kernel_times() const = 0;
   // last check candidate T(z) in the scaled space, as float64 device arrays
+  virtual Scaling scaling(int id) const = 0;
   virtual void export_point(int id, double* x, double* y, double* omega) = 0;
   // start the next solve of `id` from (x, y) (scaled, float64 device arrays)
   // with primal weight omega (omega <= 0: the LP's initial weight

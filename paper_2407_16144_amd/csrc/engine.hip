@@ -449,6 +449,10 @@ class Engine final : public EngineBase {
   Result result(int id) override;
   void solution(int id, double* x, double* y, bool to_device) override;
   void certificate(int id, double* ray, bool to_device) override;
+  Scaling scaling(int id) const override {
+    const Slot& S = slots_[id];
+    return {Dr + S.row0, Dc + S.col0, h_st_[id].sigma_hat, h_st_[id].pw_iter};
+  }
   void export_point(int id, double* x, double* y, double* omega) override;
   void stored_matrix(int id, bool transpose, int32_t* rp, int32_t* ci, double* val) override;
   void refine_layouts() override {
@@ -479,8 +483,8 @@ class Engine final : public EngineBase {
   void launch_chunk();
   void collect_times();
   void transpose_group(int64_t z0, int64_t nnz, int64_t c0, int64_t c1, const std::vector<Blk>& bD);
-  void preprocess(const std::vector<int>& ids, const std::vector<Blk>& nP, const std::vector<Blk>& nD,
-                  const std::vector<int4>& nr);
+  void preprocess(const std::vector<int>& ids, const std::vector<Problem>& probs, const std::vector<Blk>& nP,
+                  const std::vector<Blk>& nD, const std::vector<int4>& nr);
   void slice_matrix(int id, bool dual);
   void need_partials(bool dual, int nsl);
   void group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int64_t ngroups, int64_t cap);
@@ -1025,6 +1029,10 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     HIPCHECK(hipMemcpyAsync(u_o + S.col0, p.ub, sizeof(double) * n, kind, stream_));
     fill_kernel<<<nblk(m + 1), 256, 0, stream_>>>(Dr + S.row0, m + 1, 1.0);
     fill_kernel<<<nblk(n + 1), 256, 0, stream_>>>(Dc + S.col0, n + 1, 1.0);
+    if (p.scaling.Dr) {
+      if (m) HIPCHECK(hipMemcpyAsync(Dr + S.row0, p.scaling.Dr, sizeof(double) * m, hipMemcpyDeviceToDevice, stream_));
+      HIPCHECK(hipMemcpyAsync(Dc + S.col0, p.scaling.Dc, sizeof(double) * n, hipMemcpyDeviceToDevice, stream_));
+    }
   }
   HIPCHECK(hipGetLastError());
   HIPCHECK(hipStreamSynchronize(stream_));
@@ -1080,7 +1088,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     nr.push_back(r);
   }
   compacted_ = false;
-  preprocess(ids, nP, nD, nr);
+  preprocess(ids, probs, nP, nD, nr);
   // Layout of each product.  A product whose gathered vector would not stay
   // in one XCD's L2 is column-sliced: in sorted groups by default, in row-major
   // slice tiles with slice_sort = 0.  With sorted layouts on, a product with
@@ -1136,9 +1144,11 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
 }
 
 template <class T>
-void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& nP,
-                           const std::vector<Blk>& nD, const std::vector<int4>& nr) {
+void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Problem>& probs,
+                           const std::vector<Blk>& nP, const std::vector<Blk>& nD, const std::vector<int4>& nr) {
   const int ni = (int)ids.size();
+  // scaling and spectral norm of every LP are given (Problem::scaling)
+  const bool given = std::all_of(probs.begin(), probs.end(), [](const Problem& p) { return p.scaling.Dr != nullptr; });
   Blk *d_nP = nullptr, *d_nD = nullptr;
   int* d_ids = nullptr;
   int4* d_nr = nullptr;
@@ -1177,7 +1187,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
     // reads the factors so far from one pair of buffers and writes the other,
     // ending in Dr and Dc
     const int passes = opt_.ruiz_iters + (opt_.pc_alpha > 0.0 ? 1 : 0);
-    for (int it = 0; it < passes; ++it) {
+    for (int it = 0; it < passes && !given; ++it) {
       const bool pc = it == opt_.ruiz_iters, last = (passes - it) & 1;
       double *r_out = last ? Dr : fm, *c_out = last ? Dc : fn;
       const double *r_in = it == 0 ? nullptr : last ? fm : Dr, *c_in = it == 0 ? nullptr : last ? fn : Dc;
@@ -1206,7 +1216,11 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
       s.m_eq = (int32_t)S.m_eq;
       s.n = (int32_t)S.n;
       s.status = ST_ITER_LIMIT;  // parked until set_params
-      s.pw_done = opt_.eta > 0.0 ? 1 : 0;
+      s.pw_done = opt_.eta > 0.0 || given ? 1 : 0;
+      if (given) {
+        s.sigma_hat = probs[k].scaling.sigma_hat;
+        s.pw_iter = probs[k].scaling.power_iters;
+      }
     }
     HIPCHECK(hipMemcpyAsync(d_src, src.data(), sizeof(InstState) * ni, hipMemcpyHostToDevice, stream_));
     write_states_kernel<<<nblk(ni), 256, 0, stream_>>>(d_st, d_status, d_cnt, d_ids, d_src, ni);
@@ -1214,7 +1228,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Blk>& 
 
     // power iteration on K~^T K~ (u in fm, w in fn)
     int piters = 0;
-    if (opt_.eta <= 0.0) {
+    if (opt_.eta <= 0.0 && !given) {
       pw_start_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, d_st, opt_.seed, fn, d_pp);
       HIPCHECK(hipMemsetAsync(d_active, 0, sizeof(int), stream_));
       pw_control_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_nr, d_pp, 1, opt_.power_min_iters,
