@@ -555,16 +555,24 @@ def main():
                       opt.plain_sort == 1)
     ty = "double" if s == 8 else "float"
     grouped = opt.slice_sort == 1
-    # sorted-group kernels: named up to their run-time template arguments
-    # (threads per workgroup, gather order)
+    # named up to their run-time template arguments (threads per workgroup,
+    # gather order)
+
+    def step(side, dual, sliced):
+        if sliced and grouped:
+            return f"part_step<{ty}, {dual}"
+        if not sliced and opt.plain_sort == 1:
+            return f"sorted_step<{ty}, {dual}"
+        return f"{side}_step<{ty}>"
+
     kn = {"primal_slice": f"sorted_group_step<{ty}, false" if grouped
           else f"primal_slice_step<{ty}, {opt.slice_entries}>",
-          "primal": f"primal_step<{ty}>",
+          "primal": step("primal", "false", primal_sliced),
           "dual_slice": f"sorted_group_step<{ty}, true" if grouped
           else f"dual_slice_step<{ty}, {opt.slice_entries}>",
-          "dual": f"dual_step<{ty}>"}
-    names = {k: v.split("<")[0] + ("[K]" if k == "dual_slice" and grouped else
-                                   "[K^T]" if k == "primal_slice" and grouped else "") for k, v in kn.items()}
+          "dual": step("dual", "true", dual_sliced)}
+    names = {k: v.split("<")[0] + ("" if v.startswith(k) else "[K]" if k.startswith("dual") else "[K^T]")
+             for k, v in kn.items()}
     byname = {"primal_slice": kb["primal_slice"], "primal": kb["primal_step"],
               "dual_slice": kb["dual_slice"], "dual": kb["dual_step"]}
     dom = max(avg, key=lambda k: avg[k])

@@ -151,29 +151,31 @@ typedef struct {
                                slice tiles with fixed-order sums (slice_entries,
                                slice_rows) */
   int sort_rows;            /* most rows per sorted group or column-sorted block,
-                               1..16384 (default 16384).  Sorted groups: the largest
-                               group that leaves at least group_blocks workgroups per
-                               product and fits the packed column index (fewer rows when
-                               a slice is wider than 2^(32 - log2 rows)).  Column-sorted
-                               plain blocks: at most 2048 rows, sized for the LPs that
-                               share the launches: max(256, rows / 64) with 12 or more
-                               live LPs, else about 768 workgroups per product over the
-                               live LPs (down to 64 rows); engines re-block their
-                               running LPs as others finish */
+                               1..16384 (default 16384).  Sorted groups: groups of equal
+                               work, about one workgroup per CU and product, that fit the
+                               packed column index (fewer rows when a slice is wider than
+                               2^(32 - log2 rows)).  Column-sorted plain blocks: blocks of
+                               equal work of at most 2048 rows, at most 1024 / live LPs
+                               of them per product (16..256) with at least 16..256 rows
+                               on average; engines re-block their running LPs as others
+                               finish.  Where every LP has at most 1024 rows on either
+                               side and 8192 entries, each is one block per product and
+                               steps in one workgroup (not with profile) */
   int plain_sort;           /* products neither sliced nor in sorted groups (those of
                                small and mid-size LPs): 1 (default) stores the rows of at
-                               most 1024 entries in column-sorted blocks (see sort_rows)
+                               most 2^15 entries in column-sorted blocks (see sort_rows)
                                with LDS-atomic row sums (same caveat as slice_sort);
                                0: plain tiles (tile_rows) with fixed-order sums */
   int group_threads;        /* threads per workgroup of the sorted-group slice kernels:
-                               256, 512 or 1024; 0 (default): enough for about eight
-                               waves per CU over the product's workgroups */
+                               256, 512 or 1024; 0 (default): 1024 where each CU has one
+                               workgroup, else enough for about eight waves per CU over
+                               the product's workgroups */
   int group_batched;        /* 1 (default): each thread issues the gathers of a batch of
                                entries together, then adds them into the LDS row sums;
                                0: one gather per add */
   int group_blocks;         /* fewest workgroups a product stored in sorted groups is cut
-                               into (default 240, about one per CU): groups get as many
-                               rows as that allows */
+                               into (default 240; counts of about one per CU are rounded
+                               up to the 256 CUs): groups get as many rows as that allows */
   int polish_weight;        /* FP32 precision: primal weight of the FP64 phase, which
                                starts from the FP32 candidate: 1 (default) the FP32
                                phase's last weight; 0 the LP's initial weight
@@ -254,17 +256,18 @@ int lp_get_solution(const lp_solver* s, double* x, double* y, int to_device);
  * otherwise. */
 int lp_get_certificate(const lp_solver* s, double* ray, int to_device);
 
-/* Durations (ms) of the four kernels of a step, summed over the steps timed
+/* Durations (ms) of the four parts of a step, summed over the steps timed
  * with HIP events on the solver's stream (options.profile > 0: every
- * profile-th chunk of steps is launched without a graph and timed).  The
+ * profile-th chunk of steps is launched without a graph and timed, and small
+ * LPs, too, step in these kernels).  The
  * slice kernels compute the per-XCD column-slice partial products of a
  * column-sliced K^T (primal) or K (dual); where no row group is sliced they
  * launch nothing and their sums stay at (event overhead) ~0. */
 typedef struct {
   double primal_slice_ms;
-  double primal_ms;          /* primal_step: K^T y and the x half of eq. (pdhg) + Halpern blend */
+  double primal_ms;          /* rows of K^T: K^T y and the x half of eq. (pdhg) + Halpern blend */
   double dual_slice_ms;
-  double dual_ms;            /* dual_step: K(2x+ - x), the y half of eq. (pdhg), controller */
+  double dual_ms;            /* rows of K: K(2x+ - x), the y half of eq. (pdhg), controller */
   double event_pair_ms;      /* two events recorded back to back (no kernel between):
                                 the timing overhead contained in each figure above */
   double nnz, n, m;          /* matrix entries, variables and rows of the LPs the timed

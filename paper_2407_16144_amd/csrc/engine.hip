@@ -482,6 +482,9 @@ class Engine final : public EngineBase {
   const int* finished_ = nullptr;  // status words used to leave finished LPs out (compaction)
   void launch_chunk();
   void collect_times();
+  void validate_device(const std::vector<Problem>& probs, std::vector<int64_t>& nnzs);
+  void load_device(const std::vector<Problem>& probs, const std::vector<int>& ids);
+  void download_rows(const std::vector<int>& ids, bool dual, std::vector<std::vector<int32_t>>& out);
   void transpose_group(int64_t z0, int64_t nnz, int64_t c0, int64_t c1, const std::vector<Blk>& bD);
   void preprocess(const std::vector<int>& ids, const std::vector<Problem>& probs, const std::vector<Blk>& nP,
                   const std::vector<Blk>& nD, const std::vector<int4>& nr);
@@ -873,6 +876,121 @@ void Engine<T>::transpose_group(int64_t z0, int64_t nnz, int64_t c0, int64_t c1,
   }
 }
 
+// Workgroups per LP of the kernels that take all LPs of an add at once: 16
+// items per thread of the largest, 2048 workgroups (8 per CU) for one LP, 64 for
+// each of many.
+static int parts_for(int64_t largest, size_t lps) {
+  const int64_t most = std::max<int64_t>(64, 2048 / (int64_t)lps);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(most, (largest + 16 * kThreads - 1) / (16 * kThreads)));
+}
+
+// Checks device-resident LPs (the first one at fault throws) and reads their
+// entry counts.
+template <class T>
+void Engine<T>::validate_device(const std::vector<Problem>& probs, std::vector<int64_t>& nnzs) {
+  std::vector<LpInput> in;
+  const char* sizes = "sizes must satisfy n >= 1, m >= 0";
+  const char* fault = nullptr;  // what the LP after the last of `in` violates
+  for (const Problem& p : probs) {
+    if (p.n < 1 || p.m_eq < 0 || p.m_ineq < 0) {
+      fault = sizes;
+      break;
+    }
+    in.push_back({p.rp, p.ci, p.val, p.c, p.rhs, p.lb, p.ub, nullptr, nullptr, p.m_eq + p.m_ineq, p.n, 0, 0, 0, 0});
+  }
+  LpInput* d_in = nullptr;
+  int2* d_ends = nullptr;
+  int* d_flags = nullptr;
+  std::vector<int> flags;
+  if (!in.empty()) {
+    const int64_t most = (int64_t)in.size();
+    dalloc(&d_in, most);
+    dalloc(&d_ends, most);
+    dalloc(&d_flags, most);
+    HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(LpInput) * in.size(), hipMemcpyHostToDevice, stream_));
+    HIPCHECK(hipStreamSynchronize(stream_));
+    // on the null stream, after the caller's work there that may still write the inputs
+    std::vector<int2> ends(in.size());
+    row_ends_kernel<<<nblk(most), 256, 0, nullptr>>>(d_in, (int)most, d_ends);
+    HIPCHECK(hipGetLastError());
+    HIPCHECK(hipMemcpy(ends.data(), d_ends, sizeof(int2) * in.size(), hipMemcpyDeviceToHost));
+    int64_t largest = 1;
+    for (size_t k = 0; k < in.size(); ++k) {
+      if (ends[k].x != 0 || ends[k].y < 0) {
+        fault = "row_ptr must start at 0 and end at nnz >= 0";
+        in.resize(k);
+        break;
+      }
+      in[k].nnz = nnzs[k] = ends[k].y;
+      largest = std::max({largest, in[k].nnz, in[k].m, in[k].n});
+    }
+    flags.assign(in.size(), 0);
+    if (!in.empty()) {
+      const int parts = parts_for(largest, in.size());
+      HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(LpInput) * in.size(), hipMemcpyHostToDevice, stream_));
+      HIPCHECK(hipMemsetAsync(d_flags, 0, sizeof(int) * in.size(), stream_));
+      validate_lps_kernel<<<(unsigned)(in.size() * parts), kThreads, 0, stream_>>>(d_in, parts, d_flags);
+      HIPCHECK(hipGetLastError());
+      HIPCHECK(hipMemcpyAsync(flags.data(), d_flags, sizeof(int) * in.size(), hipMemcpyDeviceToHost, stream_));
+      HIPCHECK(hipStreamSynchronize(stream_));
+    }
+    dfree(d_flags);
+    dfree(d_ends);
+    dfree(d_in);
+  }
+  for (const int f : flags) {
+    if (f & 1) throw Error(-1, "row_ptr must be non-decreasing from 0 to nnz");
+    if (f & 2) throw Error(-1, "device CSR needs in-range, strictly increasing column indices per row");
+    if (f & 4) throw Error(-1, "non-finite matrix value");
+    if (f & 8) throw Error(-1, "non-finite objective or right-hand side");
+    if (f & 16) throw Error(-1, "invalid bounds (NaN, lb > ub, lb = +inf or ub = -inf)");
+  }
+  if (fault) throw Error(-1, fault);
+}
+
+// Copies device-resident LPs into their places.
+template <class T>
+void Engine<T>::load_device(const std::vector<Problem>& probs, const std::vector<int>& ids) {
+  std::vector<LpInput> in;
+  int64_t largest = 1;
+  for (size_t k = 0; k < ids.size(); ++k) {
+    const Problem& p = probs[k];
+    const Slot& S = slots_[ids[k]];
+    in.push_back({p.rp, p.ci, p.val, p.c, p.rhs, p.lb, p.ub, p.scaling.Dr, p.scaling.Dc, S.m, S.n, S.nnz, S.row0,
+                  S.col0, S.nz0});
+    largest = std::max({largest, S.nnz, S.m, S.n});
+  }
+  LpInput* d_in = nullptr;
+  talloc(&d_in, (int64_t)in.size());
+  HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(LpInput) * in.size(), hipMemcpyHostToDevice, stream_));
+  const int parts = parts_for(largest, in.size());
+  load_lps_kernel<<<(unsigned)(in.size() * parts), kThreads, 0, stream_>>>(d_in, parts, K_rp, K_ci, K_v64, q_o, c_o, l_o,
+                                                                          u_o, Dr, Dc);
+  HIPCHECK(hipGetLastError());
+  HIPCHECK(hipStreamSynchronize(stream_));
+  dfree(d_in);
+}
+
+// Row pointers of the LPs' K (dual) or K^T on the host, one copy per run of
+// neighbouring LPs.
+template <class T>
+void Engine<T>::download_rows(const std::vector<int>& ids, bool dual, std::vector<std::vector<int32_t>>& out) {
+  auto at = [&](size_t k) { return dual ? slots_[ids[k]].row0 : slots_[ids[k]].col0; };
+  auto len = [&](size_t k) { return (dual ? slots_[ids[k]].m : slots_[ids[k]].n) + 1; };
+  std::vector<int32_t> all;
+  for (size_t k = 0; k < ids.size();) {
+    size_t e = k + 1;
+    while (e < ids.size() && at(e) == at(e - 1) + len(e - 1)) ++e;
+    all.resize(at(e - 1) + len(e - 1) - at(k));
+    HIPCHECK(hipMemcpyAsync(all.data(), (dual ? K_rp : KT_rp) + at(k), sizeof(int32_t) * all.size(),
+                            hipMemcpyDeviceToHost, stream_));
+    HIPCHECK(hipStreamSynchronize(stream_));
+    for (size_t t = k; t < e; ++t)
+      out[t].assign(all.begin() + (at(t) - at(k)), all.begin() + (at(t) - at(k)) + len(t));
+    k = e;
+  }
+}
+
 template <class T>
 std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_device, bool partial) {
   std::vector<Problem> probs(probs_in);
@@ -882,53 +1000,16 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   // 1. validate and reserve
   std::vector<HostCSR> canon(probs.size());
   std::vector<char> use_canon(probs.size(), 0);
-  for (size_t k = 0; k < probs.size(); ++k) {
-    const Problem& p = probs[k];
-    if (!on_device) {
-      bool uc = false;
-      validate_host(p, canon[k], uc);
-      use_canon[k] = uc;
-    } else {
-      if (p.n < 1 || p.m_eq < 0 || p.m_ineq < 0) throw Error(-1, "sizes must satisfy n >= 1, m >= 0");
-      const int64_t m = p.m_eq + p.m_ineq;
-      int32_t ends[2] = {0, 0};
-      HIPCHECK(hipMemcpy(&ends[0], p.rp, sizeof(int32_t), hipMemcpyDeviceToHost));
-      HIPCHECK(hipMemcpy(&ends[1], p.rp + m, sizeof(int32_t), hipMemcpyDeviceToHost));
-      if (ends[0] != 0 || ends[1] < 0) throw Error(-1, "row_ptr must start at 0 and end at nnz >= 0");
-      int* d_flags = nullptr;
-      dalloc(&d_flags, 1);
-      HIPCHECK(hipMemsetAsync(d_flags, 0, sizeof(int), stream_));
-      if (m > 0) {
-        validate_rowptr_kernel<<<nblk(m), 256, 0, stream_>>>(p.rp, m, ends[1], d_flags);
-        if (ends[1] > 0)
-          validate_entries_kernel<<<nblk(ends[1]), 256, 0, stream_>>>(p.rp, p.ci, p.val, m, p.n, ends[1], d_flags);
-      }
-      validate_vectors_kernel<<<nblk(std::max<int64_t>(m, p.n)), 256, 0, stream_>>>(p.c, p.rhs, p.lb, p.ub,
-                                                                                     m, p.n, d_flags);
-      int flags = 0;
-      HIPCHECK(hipMemcpyAsync(&flags, d_flags, sizeof(int), hipMemcpyDeviceToHost, stream_));
-      HIPCHECK(hipStreamSynchronize(stream_));
-      dfree(d_flags);
-      if (flags & 1) throw Error(-1, "row_ptr must be non-decreasing from 0 to nnz");
-      if (flags & 2) throw Error(-1, "device CSR needs in-range, strictly increasing column indices per row");
-      if (flags & 4) throw Error(-1, "non-finite matrix value");
-      if (flags & 8) throw Error(-1, "non-finite objective or right-hand side");
-      if (flags & 16) throw Error(-1, "invalid bounds (NaN, lb > ub, lb = +inf or ub = -inf)");
-    }
-  }
   std::vector<int64_t> nnzs(probs.size());
-  for (size_t k = 0; k < probs.size(); ++k) {
-    const Problem& p = probs[k];
-    const int64_t m = p.m_eq + p.m_ineq;
-    if (use_canon[k]) {
-      nnzs[k] = canon[k].rp[m];
-    } else if (!on_device) {
-      nnzs[k] = p.rp[m];
-    } else {
-      int32_t e = 0;
-      HIPCHECK(hipMemcpy(&e, p.rp + m, sizeof(int32_t), hipMemcpyDeviceToHost));
-      nnzs[k] = e;
+  if (!on_device) {
+    for (size_t k = 0; k < probs.size(); ++k) {
+      bool uc = false;
+      validate_host(probs[k], canon[k], uc);
+      use_canon[k] = uc;
+      nnzs[k] = (uc ? canon[k].rp.data() : probs[k].rp)[probs[k].m_eq + probs[k].m_ineq];
     }
+  } else {
+    validate_device(probs, nnzs);
   }
   std::vector<int> fresh;
   try {
@@ -994,45 +1075,38 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   TempScope temp(std::max(kTransposeBytes * total_nz, temp_bytes(std::max(largest_nz, std::min(total_nz, kSortRun)))));
   // 2. upload (K values in FP64, row pointers / columns shifted to space positions)
   std::vector<std::vector<int32_t>> host_rp(probs.size());
-  for (size_t k = 0; k < probs.size(); ++k) {
+  for (size_t k = 0; k < probs.size() && !on_device; ++k) {
     const Problem& p = probs[k];
     Slot& S = slots_[ids[k]];
     const int64_t m = S.m, n = S.n, nnz = S.nnz;
-    const auto kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     const int32_t* rp_src = use_canon[k] ? canon[k].rp.data() : p.rp;
     const int32_t* ci_src = use_canon[k] ? canon[k].ci.data() : p.ci;
     const double* v_src = use_canon[k] ? canon[k].val.data() : p.val;
     host_rp[k].resize(m + 1);
-    if (!on_device) {
-      for (int64_t i = 0; i <= m; ++i) host_rp[k][i] = (int32_t)(rp_src[i] + S.nz0);
-      HIPCHECK(hipMemcpyAsync(K_rp + S.row0, host_rp[k].data(), sizeof(int32_t) * (m + 1),
-                              hipMemcpyHostToDevice, stream_));
-      std::vector<int32_t> cs(nnz);
-      for (int64_t e = 0; e < nnz; ++e) cs[e] = (int32_t)(ci_src[e] + S.col0);
-      if (nnz) {
-        HIPCHECK(hipMemcpyAsync(K_ci + S.nz0, cs.data(), sizeof(int32_t) * nnz, hipMemcpyHostToDevice, stream_));
-        HIPCHECK(hipMemcpyAsync(K_v64 + S.nz0, v_src, sizeof(double) * nnz, hipMemcpyHostToDevice, stream_));
-      }
-      HIPCHECK(hipStreamSynchronize(stream_));
-    } else {
-      shift_copy_kernel<<<nblk(m + 1), 256, 0, stream_>>>(K_rp + S.row0, p.rp, m + 1, S.nz0);
-      if (nnz) {
-        shift_copy_kernel<<<nblk(nnz), 256, 0, stream_>>>(K_ci + S.nz0, p.ci, nnz, S.col0);
-        HIPCHECK(hipMemcpyAsync(K_v64 + S.nz0, p.val, sizeof(double) * nnz, hipMemcpyDeviceToDevice, stream_));
-      }
-      HIPCHECK(hipMemcpyAsync(host_rp[k].data(), K_rp + S.row0, sizeof(int32_t) * (m + 1),
-                              hipMemcpyDeviceToHost, stream_));
+    for (int64_t i = 0; i <= m; ++i) host_rp[k][i] = (int32_t)(rp_src[i] + S.nz0);
+    HIPCHECK(hipMemcpyAsync(K_rp + S.row0, host_rp[k].data(), sizeof(int32_t) * (m + 1), hipMemcpyHostToDevice,
+                            stream_));
+    std::vector<int32_t> cs(nnz);
+    for (int64_t e = 0; e < nnz; ++e) cs[e] = (int32_t)(ci_src[e] + S.col0);
+    if (nnz) {
+      HIPCHECK(hipMemcpyAsync(K_ci + S.nz0, cs.data(), sizeof(int32_t) * nnz, hipMemcpyHostToDevice, stream_));
+      HIPCHECK(hipMemcpyAsync(K_v64 + S.nz0, v_src, sizeof(double) * nnz, hipMemcpyHostToDevice, stream_));
     }
-    if (m) HIPCHECK(hipMemcpyAsync(q_o + S.row0, p.rhs, sizeof(double) * m, kind, stream_));
-    HIPCHECK(hipMemcpyAsync(c_o + S.col0, p.c, sizeof(double) * n, kind, stream_));
-    HIPCHECK(hipMemcpyAsync(l_o + S.col0, p.lb, sizeof(double) * n, kind, stream_));
-    HIPCHECK(hipMemcpyAsync(u_o + S.col0, p.ub, sizeof(double) * n, kind, stream_));
+    HIPCHECK(hipStreamSynchronize(stream_));
+    if (m) HIPCHECK(hipMemcpyAsync(q_o + S.row0, p.rhs, sizeof(double) * m, hipMemcpyHostToDevice, stream_));
+    HIPCHECK(hipMemcpyAsync(c_o + S.col0, p.c, sizeof(double) * n, hipMemcpyHostToDevice, stream_));
+    HIPCHECK(hipMemcpyAsync(l_o + S.col0, p.lb, sizeof(double) * n, hipMemcpyHostToDevice, stream_));
+    HIPCHECK(hipMemcpyAsync(u_o + S.col0, p.ub, sizeof(double) * n, hipMemcpyHostToDevice, stream_));
     fill_kernel<<<nblk(m + 1), 256, 0, stream_>>>(Dr + S.row0, m + 1, 1.0);
     fill_kernel<<<nblk(n + 1), 256, 0, stream_>>>(Dc + S.col0, n + 1, 1.0);
     if (p.scaling.Dr) {
       if (m) HIPCHECK(hipMemcpyAsync(Dr + S.row0, p.scaling.Dr, sizeof(double) * m, hipMemcpyDeviceToDevice, stream_));
       HIPCHECK(hipMemcpyAsync(Dc + S.col0, p.scaling.Dc, sizeof(double) * n, hipMemcpyDeviceToDevice, stream_));
     }
+  }
+  if (on_device) {
+    load_device(probs, ids);
+    download_rows(ids, true, host_rp);
   }
   HIPCHECK(hipGetLastError());
   HIPCHECK(hipStreamSynchronize(stream_));
@@ -1061,13 +1135,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     k = e;
   }
   std::vector<std::vector<int32_t>> host_rpT(probs.size());
-  for (size_t t = 0; t < probs.size(); ++t) {
-    const Slot& S = slots_[ids[t]];
-    host_rpT[t].resize(S.n + 1);
-    HIPCHECK(hipMemcpyAsync(host_rpT[t].data(), KT_rp + S.col0, sizeof(int32_t) * (S.n + 1), hipMemcpyDeviceToHost,
-                            stream_));
-  }
-  HIPCHECK(hipStreamSynchronize(stream_));
+  download_rows(ids, false, host_rpT);
   for (size_t t = 0; t < probs.size(); ++t) {
     Slot& S = slots_[ids[t]];
     build_blocks(host_rpT[t].data(), S.n, S.col0, ids[t], NB, opt_.tile_rows, S.bP);

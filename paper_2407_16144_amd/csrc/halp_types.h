@@ -84,8 +84,7 @@ constexpr int kMinGroupBlocks = 240;
 constexpr int kCUs = 256;        // compute units of an MI355X
 // A plain block of the step kernels may be column-sorted too (kind
 // BK_SORTED, same packing, rp_off = the LP's first column): at most
-// kSortRowsPlain rows (its row sums share the step kernel's LDS with the
-// plain tile).
+// kSortRowsPlain rows.
 constexpr int kSortRowsPlain = 2048;
 // Its row sums, with the copies a block with a row of kRepRow entries or more
 // may keep (blk_rep_shift), take at most this many LDS words.
@@ -164,6 +163,15 @@ struct alignas(16) InstState {
   // power iteration
   double pw_scale, pw_prev, sigma_hat;
   int32_t pw_iter, pw_done;
+};
+
+// One LP of device-resident input and its places in the engine's spaces.
+struct LpInput {
+  const int32_t* rp;
+  const int32_t* ci;
+  const double *val, *c, *rhs, *lb, *ub;
+  const double *Dr, *Dc;  // given scaling, or null
+  int64_t m, n, nnz, row0, col0, nz0;
 };
 
 }  // namespace halp

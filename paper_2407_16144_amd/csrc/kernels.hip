@@ -8,8 +8,10 @@
 //                 residual steps the last workgroup of each LP (arrival
 //                 counter) reduces that LP's block partial sums in a fixed
 //                 order and runs its restart / termination controller.
-// Column-sorted blocks of either product run in sorted_step, and the products
-// of large LPs in slice kernels (sorted_group_step) before the step kernels.
+// Column-sorted blocks of either product run in sorted_step; the products of
+// large LPs in slice kernels (sorted_group_step), whose partial sums part_step
+// finishes; small LPs run all steps of a chunk in one workgroup
+// (resident_steps).
 // The path is bandwidth bound (about 2 flop per 12 bytes of matrix), so there
 // is no MFMA: the work is coalesced entry loads, gathers, LDS staging and
 // wave64 shuffle reductions.

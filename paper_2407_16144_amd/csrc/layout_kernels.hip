@@ -20,44 +20,77 @@ __global__ void narrow_row_ptr_kernel(const int64_t* src, int32_t* dst, int64_t 
   }
 }
 
-// flags: 1 bad row pointers, 2 column out of range or not increasing, 4 non-finite value
-__global__ void validate_rowptr_kernel(const int32_t* rp, int64_t m, int64_t nnz, int* flags) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r == 0 && (rp[0] != 0 || rp[m] != nnz)) atomicOr(flags, 1);
-  if (r >= m) return;
-  if (rp[r + 1] < rp[r] || rp[r] < 0 || rp[r + 1] > nnz) atomicOr(flags, 1);
+// ends[k] = first and last row pointer of LP k
+__global__ void row_ends_kernel(const LpInput* in, int count, int2* ends) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < count) ends[k] = make_int2(in[k].rp[0], in[k].rp[in[k].m]);
 }
 
-// One thread per entry: column in range and strictly above the previous
-// entry's unless the entry starts its row (found by a binary search of the
-// row pointers: the last row whose start is at or before it), finite value.
-// The search stays within rp[0..m] whatever the row pointers hold; invalid
-// row pointers are flagged by validate_rowptr_kernel.
-__global__ void validate_entries_kernel(const int32_t* rp, const int32_t* ci, const double* val, int64_t m,
-                                        int64_t n, int64_t nnz, int* flags) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nnz) return;
-  const int64_t c = ci[e];
-  if (c < 0 || c >= n) atomicOr(flags, 2);
-  if (!isfinite(val[e])) atomicOr(flags, 4);
-  if (e == 0) return;
-  int64_t lo = 0, hi = m;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi + 1) >> 1;
-    if ((int64_t)rp[mid] <= e) lo = mid; else hi = mid - 1;
+// Validation of device-resident LPs, `parts` workgroups each (one launch and
+// one answer for all of them; one LP after the other cost a batch of 128
+// 10 ms in launches and round trips).  flags[k]: 1 bad row pointers, 2
+// column out of range or not increasing, 4 non-finite value, 8 non-finite
+// objective or right-hand side, 16 bad bounds.
+// Entries: column in range and strictly above the previous entry's unless the
+// entry starts its row (found by a binary search of the row pointers: the
+// last row whose start is at or before it), finite value.  The search stays
+// within rp[0..m] whatever the row pointers hold; invalid row pointers have
+// a flag of their own.
+__global__ __launch_bounds__(kThreads) void validate_lps_kernel(const LpInput* in, int parts, int* flags) {
+  const LpInput p = in[blockIdx.x / parts];
+  const int64_t first = (int64_t)(blockIdx.x % parts) * kThreads + threadIdx.x, step = (int64_t)parts * kThreads;
+  int bad = 0;
+  if (first == 0 && (p.rp[0] != 0 || p.rp[p.m] != p.nnz)) bad |= 1;
+  for (int64_t r = first; r < p.m; r += step) {
+    if (p.rp[r + 1] < p.rp[r] || p.rp[r] < 0 || p.rp[r + 1] > p.nnz) bad |= 1;
+    if (!isfinite(p.rhs[r])) bad |= 8;
   }
-  if ((int64_t)rp[lo] != e && c <= (int64_t)ci[e - 1]) atomicOr(flags, 2);
+  if (p.m > 0) {
+    for (int64_t e = first; e < p.nnz; e += step) {
+      const int64_t c = p.ci[e];
+      if (c < 0 || c >= p.n) bad |= 2;
+      if (!isfinite(p.val[e])) bad |= 4;
+      if (e == 0) continue;
+      int64_t lo = 0, hi = p.m;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if ((int64_t)p.rp[mid] <= e) lo = mid; else hi = mid - 1;
+      }
+      if ((int64_t)p.rp[lo] != e && c <= (int64_t)p.ci[e - 1]) bad |= 2;
+    }
+  }
+  for (int64_t i = first; i < p.n; i += step) {
+    if (!isfinite(p.c[i])) bad |= 8;
+    const double a = p.lb[i], b = p.ub[i];
+    if (isnan(a) || isnan(b) || a > b || a == INFINITY || b == -INFINITY) bad |= 16;
+  }
+  if (bad) atomicOr(flags + blockIdx.x / parts, bad);
 }
 
-// flags: 8 non-finite c or rhs, 16 bad bounds
-__global__ void validate_vectors_kernel(const double* c, const double* rhs, const double* lb,
-                                        const double* ub, int64_t m, int64_t n, int* flags) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < m && !isfinite(rhs[i])) atomicOr(flags, 8);
-  if (i < n) {
-    if (!isfinite(c[i])) atomicOr(flags, 8);
-    const double a = lb[i], b = ub[i];
-    if (isnan(a) || isnan(b) || a > b || a == INFINITY || b == -INFINITY) atomicOr(flags, 16);
+// Device-resident LPs into the engine's spaces: row pointers and columns
+// become space positions; factors start at the given ones, or at 1.
+__global__ __launch_bounds__(kThreads) void load_lps_kernel(const LpInput* in, int parts, int32_t* K_rp, int32_t* K_ci,
+                                                            double* K_v, double* q, double* c, double* l, double* u,
+                                                            double* Dr, double* Dc) {
+  const LpInput p = in[blockIdx.x / parts];
+  const int64_t first = (int64_t)(blockIdx.x % parts) * kThreads + threadIdx.x, step = (int64_t)parts * kThreads;
+#pragma unroll 4
+  for (int64_t e = first; e < p.nnz; e += step) {
+    K_ci[p.nz0 + e] = (int32_t)(p.ci[e] + p.col0);
+    K_v[p.nz0 + e] = p.val[e];
+  }
+  for (int64_t r = first; r <= p.m; r += step) {
+    K_rp[p.row0 + r] = (int32_t)(p.rp[r] + p.nz0);
+    Dr[p.row0 + r] = p.Dr && r < p.m ? p.Dr[r] : 1.0;
+    if (r < p.m) q[p.row0 + r] = p.rhs[r];
+  }
+  for (int64_t j = first; j <= p.n; j += step) {
+    Dc[p.col0 + j] = p.Dc && j < p.n ? p.Dc[j] : 1.0;
+    if (j < p.n) {
+      c[p.col0 + j] = p.c[j];
+      l[p.col0 + j] = p.lb[j];
+      u[p.col0 + j] = p.ub[j];
+    }
   }
 }
 
