@@ -377,6 +377,10 @@ constexpr int64_t kSortRun = 1 << 26;
 // temporary memory per entry of a transpose and its radix sort
 constexpr int64_t kTransposeBytes = 29;
 
+// Most blocks of K^T over the LPs of an add for which the power iteration's
+// last block ends an iteration itself (pw_backward_kernel).
+constexpr int kPowerFuse = 512;
+
 struct Slot {
   bool used = false;
   int64_t n = 0, m = 0, m_eq = 0, nnz = 0;
@@ -1222,7 +1226,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Proble
   int4* d_nr = nullptr;
   double *d_pp = nullptr, *d_pd = nullptr;
   double* d_norms = nullptr;
-  int* d_active = nullptr;
+  int* d_done = nullptr;
   InstState* d_src = nullptr;
   auto cleanup = [&]() {
     dfree(d_nP);
@@ -1232,7 +1236,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Proble
     dfree(d_pd);
     dfree(d_pp);
     dfree(d_norms);
-    dfree(d_active);
+    dfree(d_done);
     dfree(d_src);
   };
   try {
@@ -1243,7 +1247,7 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Proble
     talloc(&d_pp, (int64_t)nP.size() * kNS);
     talloc(&d_pd, (int64_t)nD.size() * kNS);
     talloc(&d_norms, 2 * ni);
-    talloc(&d_active, 1);
+    talloc(&d_done, 1);
     talloc(&d_src, ni);
     HIPCHECK(hipMemcpyAsync(d_nP, nP.data(), sizeof(Blk) * nP.size(), hipMemcpyHostToDevice, stream_));
     HIPCHECK(hipMemcpyAsync(d_nD, nD.data(), sizeof(Blk) * nD.size(), hipMemcpyHostToDevice, stream_));
@@ -1284,6 +1288,8 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Proble
       s.m_eq = (int32_t)S.m_eq;
       s.n = (int32_t)S.n;
       s.status = ST_ITER_LIMIT;  // parked until set_params
+      s.pb0 = nr[k].x;  // of the temporary schedule
+      s.pb1 = nr[k].y;
       s.pw_done = opt_.eta > 0.0 || given ? 1 : 0;
       if (given) {
         s.sigma_hat = probs[k].scaling.sigma_hat;
@@ -1298,20 +1304,23 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Proble
     int piters = 0;
     if (opt_.eta <= 0.0 && !given) {
       pw_start_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, d_st, opt_.seed, fn, d_pp);
-      HIPCHECK(hipMemsetAsync(d_active, 0, sizeof(int), stream_));
-      pw_control_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_nr, d_pp, 1, opt_.power_min_iters,
-                                                      opt_.power_max_iters, opt_.power_rtol, d_active);
-      int active = 1;
-      while (active > 0 && piters < opt_.power_max_iters) {
+      HIPCHECK(hipMemsetAsync(d_done, 0, sizeof(int), stream_));
+      pw_control_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_pp, 1, opt_.power_min_iters, opt_.power_max_iters,
+                                                      opt_.power_rtol, d_done);
+      int done = 0;
+      const bool fused = gP <= (unsigned)kPowerFuse;
+      const auto backward = fused ? pw_backward_kernel<true> : pw_backward_kernel<false>;
+      while (done < ni && piters < opt_.power_max_iters) {
         const int batch = 8;
         for (int b = 0; b < batch && piters < opt_.power_max_iters; ++b, ++piters) {
           pw_forward_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, d_st, K_rp, K_ci, K_v64, fn, fm);
-          pw_backward_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, d_st, KT_rp, KT_ci, KT_v64, fm, fn, d_pp);
-          HIPCHECK(hipMemsetAsync(d_active, 0, sizeof(int), stream_));
-          pw_control_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_nr, d_pp, 0, opt_.power_min_iters,
-                                                          opt_.power_max_iters, opt_.power_rtol, d_active);
+          backward<<<gP, kThreads, 0, stream_>>>(d_nP, d_st, KT_rp, KT_ci, KT_v64, fm, fn, d_pp, d_cnt,
+                                                 opt_.power_min_iters, opt_.power_max_iters, opt_.power_rtol, d_done);
+          if (!fused)
+            pw_control_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_pp, 0, opt_.power_min_iters,
+                                                            opt_.power_max_iters, opt_.power_rtol, d_done);
         }
-        HIPCHECK(hipMemcpyAsync(&active, d_active, sizeof(int), hipMemcpyDeviceToHost, stream_));
+        HIPCHECK(hipMemcpyAsync(&done, d_done, sizeof(int), hipMemcpyDeviceToHost, stream_));
         HIPCHECK(hipStreamSynchronize(stream_));
       }
     }

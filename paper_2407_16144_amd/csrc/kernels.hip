@@ -1639,18 +1639,54 @@ __global__ __launch_bounds__(kThreads) void pw_forward_kernel(const Blk* schedD,
   if ((int)threadIdx.x < nrows) u[(int64_t)b.r0 + threadIdx.x] = s_rsum[0][threadIdx.x];
 }
 
-// w = K~^T u over the rows of K^T (primal schedule), with the partial sum w^2
-__global__ __launch_bounds__(kThreads) void pw_backward_kernel(const Blk* schedP, const InstState* st,
+// Ends a power iteration of one LP: the estimate sqrt(||w||) and the stop
+// rule; *done counts the LPs that have stopped.
+__device__ __forceinline__ void pw_update(InstState& S, double w2, int start, int min_iters, int max_iters, double rtol,
+                                          int* done) {
+  const double nw = sqrt(w2);
+  bool stop = !(nw > 0.0);
+  if (start) {
+    S.pw_scale = stop ? 0.0 : 1.0 / nw;
+    S.pw_iter = 0;
+    S.pw_prev = -1.0;
+    S.sigma_hat = 0.0;
+  } else {
+    S.pw_iter += 1;
+    if (stop) {
+      S.sigma_hat = 0.0;
+    } else {
+      const double s = sqrt(nw);
+      S.sigma_hat = s;
+      S.pw_scale = 1.0 / nw;
+      stop = (S.pw_prev >= 0.0 && S.pw_iter >= min_iters && fabs(s - S.pw_prev) <= rtol * s) || S.pw_iter >= max_iters;
+      if (!stop) S.pw_prev = s;
+    }
+  }
+  if (stop) {
+    S.pw_done = 1;
+    atomicAdd(done, 1);
+  }
+}
+
+// w = K~^T u over the rows of K^T (primal schedule), with the partial sum
+// w^2.  FUSED: the last of the LP's blocks also ends the iteration, which
+// saves small LPs a launch per iteration; the device-wide fence that each
+// block then takes is dearer than the launch where there are many (see
+// kPowerFuse).
+template <bool FUSED>
+__global__ __launch_bounds__(kThreads) void pw_backward_kernel(const Blk* schedP, InstState* st,
                                                                const int32_t* rp, const int32_t* ci,
                                                                const double* val, const double* u,
-                                                               double* w, double* partP) {
+                                                               double* w, double* partP, int* cnt, int min_iters,
+                                                               int max_iters, double rtol, int* done) {
   __shared__ double s_prod[Tile<double>::NB];
   __shared__ double s_rsum[3][kMaxRows];
   __shared__ int s_rp[kMaxRows + 1];
   __shared__ double s_red[kThreads / 64][kNS];
   __shared__ double s_out[kNS];
+  __shared__ int s_last;
   const Blk b = schedP[blockIdx.x];
-  const InstState& S = st[b.inst];
+  InstState& S = st[b.inst];
   if (S.pw_done) return;
   block_spmv<double, 1>(b, rp + b.r0, ci, val, u, u, u, s_prod, s_rsum, s_rp, s_red);
   double v[kNS];
@@ -1663,46 +1699,35 @@ __global__ __launch_bounds__(kThreads) void pw_backward_kernel(const Blk* schedP
   }
   block_sum_ns(v, s_red, s_out);
   if (threadIdx.x < kNS) partP[(int64_t)blockIdx.x * kNS + threadIdx.x] = s_out[threadIdx.x];
+  if constexpr (FUSED) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __threadfence();
+      const int last =
+          __hip_atomic_fetch_add(cnt + b.inst, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S.pb1 - S.pb0 - 1;
+      if (last) {
+        cnt[b.inst] = 0;
+        __threadfence();
+      }
+      s_last = last;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    sum_partials(partP + (int64_t)S.pb0 * kNS, S.pb1 - S.pb0, s_red, s_out);
+    if (threadIdx.x == 0) pw_update(S, s_out[0], 0, min_iters, max_iters, rtol, done);
+  }
 }
 
-// one block per LP: ||w|| from the partials, estimate sqrt(||w||), stop rule
-__global__ __launch_bounds__(kThreads) void pw_control_kernel(InstState* st, const int* ids,
-                                                              const int4* ranges, const double* partP,
+// one block per LP: ||w|| from the partials, then pw_update
+__global__ __launch_bounds__(kThreads) void pw_control_kernel(InstState* st, const int* ids, const double* partP,
                                                               int start, int min_iters, int max_iters,
-                                                              double rtol, int* active) {
+                                                              double rtol, int* done) {
   __shared__ double s_red[kThreads / 64][kNS];
   __shared__ double s_sum[kNS];
   InstState& S = st[ids[blockIdx.x]];
   if (S.pw_done) return;
-  const int4 rg = ranges[blockIdx.x];
-  sum_partials(partP + (int64_t)rg.x * kNS, rg.y - rg.x, s_red, s_sum);
-  if (threadIdx.x != 0) return;
-  const double nw = sqrt(s_sum[0]);
-  if (start) {
-    S.pw_scale = nw > 0.0 ? 1.0 / nw : 0.0;
-    S.pw_iter = 0;
-    S.pw_prev = -1.0;
-    S.sigma_hat = 0.0;
-    if (!(nw > 0.0)) S.pw_done = 1;
-    else atomicAdd(active, 1);
-    return;
-  }
-  S.pw_iter += 1;
-  if (!(nw > 0.0)) {
-    S.sigma_hat = 0.0;
-    S.pw_done = 1;
-    return;
-  }
-  const double s = sqrt(nw);
-  S.sigma_hat = s;
-  S.pw_scale = 1.0 / nw;
-  if ((S.pw_prev >= 0.0 && S.pw_iter >= min_iters && fabs(s - S.pw_prev) <= rtol * s) ||
-      S.pw_iter >= max_iters) {
-    S.pw_done = 1;
-    return;
-  }
-  S.pw_prev = s;
-  atomicAdd(active, 1);
+  sum_partials(partP + (int64_t)S.pb0 * kNS, S.pb1 - S.pb0, s_red, s_sum);
+  if (threadIdx.x == 0) pw_update(S, s_sum[0], start, min_iters, max_iters, rtol, done);
 }
 
 // ---------------------------------------------------------------------------
