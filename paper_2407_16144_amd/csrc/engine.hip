@@ -377,8 +377,12 @@ constexpr int64_t kSortRun = 1 << 26;
 // temporary memory per entry of a transpose and its radix sort
 constexpr int64_t kTransposeBytes = 29;
 
-// Most blocks of K^T over the LPs of an add for which the power iteration's
-// last block ends an iteration itself (pw_backward_kernel).
+// Most blocks of K^T over the LPs of an add for which the last block of a power
+// iteration ends it itself (pw_block_end).  Up to as many row-major tiles the
+// power iteration runs on those, before the layouts: its kernels are then bound
+// by latency, and small LPs have more tiles than sorted blocks (creation of
+// 60 x 120 1.03 ms against 1.13 on its two sorted blocks, 2.4k x 8k 1.90
+// against 2.05; 100k x 400k 5.95 on tiles, 5.33 on sorted blocks).
 constexpr int kPowerFuse = 512;
 
 struct Slot {
@@ -490,8 +494,10 @@ class Engine final : public EngineBase {
   void load_device(const std::vector<Problem>& probs, const std::vector<int>& ids);
   void download_rows(const std::vector<int>& ids, bool dual, std::vector<std::vector<int32_t>>& out);
   void transpose_group(int64_t z0, int64_t nnz, int64_t c0, int64_t c1, const std::vector<Blk>& bD);
-  void preprocess(const std::vector<int>& ids, const std::vector<Problem>& probs, const std::vector<Blk>& nP,
-                  const std::vector<Blk>& nD, const std::vector<int4>& nr);
+  int preprocess(const std::vector<int>& ids, const std::vector<Problem>& probs, const std::vector<Blk>& nP,
+                 const std::vector<Blk>& nD, const std::vector<int4>& nr, std::vector<double>& norms);
+  void power_iterate(const std::vector<int>& ids, int running);
+  void finish_states(const std::vector<int>& ids, const std::vector<double>& norms);
   void slice_matrix(int id, bool dual);
   void need_partials(bool dual, int nsl);
   void group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int64_t ngroups, int64_t cap);
@@ -668,6 +674,11 @@ void Engine<T>::allocate() {
   const int lds_res = 2 * (int)sizeof(double) * kSortWordsPlain + 2 * (int)sizeof(T) * kResRows;
   for (const void* f : {(const void*)resident_steps<T, 256>, (const void*)resident_steps<T, kResRows>})
     HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_res));
+  for (const void* f : {(const void*)pw_group_kernel<512>, (const void*)pw_group_kernel<1024>})
+    HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
+  for (const void* f : {(const void*)pw_sorted_kernel<true, false>, (const void*)pw_sorted_kernel<false, true>,
+                        (const void*)pw_sorted_kernel<false, false>})
+    HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(double) * (kSortWordsPlain + kSpareWords)));
   HIPCHECK(hipStreamSynchronize(stream_));
 }
 
@@ -1160,7 +1171,12 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     nr.push_back(r);
   }
   compacted_ = false;
-  preprocess(ids, probs, nP, nD, nr);
+  std::vector<double> norms;
+  int running = preprocess(ids, probs, nP, nD, nr, norms);
+  if (running > 0 && nP.size() <= (size_t)kPowerFuse) {
+    power_iterate(ids, running);
+    running = 0;
+  }
   // Layout of each product.  A product whose gathered vector would not stay
   // in one XCD's L2 is column-sliced: in sorted groups by default, in row-major
   // slice tiles with slice_sort = 0.  With sorted layouts on, a product with
@@ -1171,6 +1187,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   // column-sorted plain blocks (plain_sort) or plain tiles.
   std::vector<int> plain[2];  // LPs whose K^T / K gets column-sorted plain blocks
   std::vector<const int32_t*> plain_rp[2];
+  std::vector<std::pair<int, bool>> sliced;  // row-major slices, cut after the power iteration
   for (size_t t = 0; t < ids.size(); ++t) {
     const int id = ids[t];
     const Slot& S = slots_[id];
@@ -1185,7 +1202,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
       int nsl = 0;
       int64_t ngroups = 0, cap = 0;
       if (slice && !opt_.slice_sort) {
-        slice_matrix(id, dual);
+        sliced.push_back({id, dual});
       } else if (S.nnz > 0 && opt_.slice_sort && (slice || opt_.plain_sort) &&
                  group_shape(nrows, width, nsl_min, &nsl, &ngroups, &cap) &&
                  (slice || nrows > kCUs * std::min<int64_t>(opt_.sort_rows, kSortRowsPlain))) {
@@ -1210,14 +1227,17 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   }
   for (const bool dual : {true, false})
     sort_blocks(plain[dual], dual, plain_rp[dual], maxb, minr, false, kSortRun);
+  if (running > 0) power_iterate(ids, running);
+  finish_states(ids, norms);
+  for (auto& [id, dual] : sliced) slice_matrix(id, dual);
   sched_dirty_ = true;
   for (int id : ids) slots_[id].watched = true;
   return ids;
 }
 
 template <class T>
-void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Problem>& probs,
-                           const std::vector<Blk>& nP, const std::vector<Blk>& nD, const std::vector<int4>& nr) {
+int Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Problem>& probs, const std::vector<Blk>& nP,
+                          const std::vector<Blk>& nD, const std::vector<int4>& nr, std::vector<double>& norms) {
   const int ni = (int)ids.size();
   // scaling and spectral norm of every LP are given (Problem::scaling)
   const bool given = std::all_of(probs.begin(), probs.end(), [](const Problem& p) { return p.scaling.Dr != nullptr; });
@@ -1300,29 +1320,14 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Proble
     write_states_kernel<<<nblk(ni), 256, 0, stream_>>>(d_st, d_status, d_cnt, d_ids, d_src, ni);
     inst_norms_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_nr, d_pp, d_pd, d_norms);
 
-    // power iteration on K~^T K~ (u in fm, w in fn)
-    int piters = 0;
+    // start of the power iteration on K~^T K~ (u in fm, w in fn)
+    int done = ni;
     if (opt_.eta <= 0.0 && !given) {
       pw_start_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, d_st, opt_.seed, fn, d_pp);
       HIPCHECK(hipMemsetAsync(d_done, 0, sizeof(int), stream_));
       pw_control_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_pp, 1, opt_.power_min_iters, opt_.power_max_iters,
                                                       opt_.power_rtol, d_done);
-      int done = 0;
-      const bool fused = gP <= (unsigned)kPowerFuse;
-      const auto backward = fused ? pw_backward_kernel<true> : pw_backward_kernel<false>;
-      while (done < ni && piters < opt_.power_max_iters) {
-        const int batch = 8;
-        for (int b = 0; b < batch && piters < opt_.power_max_iters; ++b, ++piters) {
-          pw_forward_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, d_st, K_rp, K_ci, K_v64, fn, fm);
-          backward<<<gP, kThreads, 0, stream_>>>(d_nP, d_st, KT_rp, KT_ci, KT_v64, fm, fn, d_pp, d_cnt,
-                                                 opt_.power_min_iters, opt_.power_max_iters, opt_.power_rtol, d_done);
-          if (!fused)
-            pw_control_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_pp, 0, opt_.power_min_iters,
-                                                            opt_.power_max_iters, opt_.power_rtol, d_done);
-        }
-        HIPCHECK(hipMemcpyAsync(&done, d_done, sizeof(int), hipMemcpyDeviceToHost, stream_));
-        HIPCHECK(hipStreamSynchronize(stream_));
-      }
+      HIPCHECK(hipMemcpyAsync(&done, d_done, sizeof(int), hipMemcpyDeviceToHost, stream_));
     }
     if (sizeof(T) != 8) {
       for (int id : ids) {
@@ -1337,68 +1342,180 @@ void Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Proble
     init_dual_kernel<T><<<gD, kThreads, 0, stream_>>>(d_nD, y, y0, acty);
     HIPCHECK(hipGetLastError());
 
-    // step size and primal weight, then park the LPs until set_params
-    std::vector<double> norms(2 * ni);
+    norms.resize(2 * ni);
     HIPCHECK(hipMemcpyAsync(norms.data(), d_norms, sizeof(double) * 2 * ni, hipMemcpyDeviceToHost, stream_));
-    std::vector<InstState> cur(ni);
-    for (int k = 0; k < ni; ++k)
-      HIPCHECK(hipMemcpyAsync(&cur[k], d_st + ids[k], sizeof(InstState), hipMemcpyDeviceToHost, stream_));
     HIPCHECK(hipStreamSynchronize(stream_));
-    for (int k = 0; k < ni; ++k) {
-      InstState& s = cur[k];
-      const double sh = s.sigma_hat;
-      double eta;
-      if (opt_.eta > 0.0) {
-        eta = opt_.eta;
-        s.sigma_hat = NAN;
-      } else {
-        eta = sh > 0.0 ? opt_.step_safety / sh : opt_.step_safety;
-      }
-      const double nq = norms[2 * k], nc = norms[2 * k + 1];
-      double omega = 1.0;
-      if (opt_.omega0 > 0.0) omega = opt_.omega0;
-      else if (opt_.primal_weight && nc > 1e-10 && nq > 1e-10) omega = nc / nq;
-      s.eta = eta;
-      s.omega = omega;
-      s.tau = eta / omega;
-      s.sigma = eta * omega;
-      s.reflect = opt_.method == 1;
-      s.avg = opt_.method == 2;
-      s.avg_b1 = opt_.avg_beta_sufficient;
-      s.avg_b2 = opt_.avg_beta_necessary;
-      s.kkt_anchor = NAN;
-      s.kkt_prev = INFINITY;
-      s.act_changes = 0;
-      s.ident_iters = 0;
-      s.C = opt_.check_every;
-      s.primal_weight = opt_.primal_weight;
-      s.beta = opt_.restart_beta;
-      s.artificial = opt_.artificial_restart;
-      s.restart_mode = opt_.restart_mode;
-      s.fixed_len = opt_.fixed_restart_len;
-      s.eps_inf = opt_.eps_infeas;
-      s.r0 = NAN;
-      s.status = ST_ITER_LIMIT;  // parked
-      s.phase = PH_NORMAL;
-      s.nrest = 0;
-      s.checks = 0;
-      s.ray = 0;
-      s.iters = 0;
-      s.kkt = NAN;
-      s.best_kkt = INFINITY;
-      s.best_check = 0;
-      s.stall_checks = 0;
-      h_st_[ids[k]] = s;
-    }
-    HIPCHECK(hipMemcpyAsync(d_src, cur.data(), sizeof(InstState) * ni, hipMemcpyHostToDevice, stream_));
-    write_states_kernel<<<nblk(ni), 256, 0, stream_>>>(d_st, d_status, d_cnt, d_ids, d_src, ni);
-    HIPCHECK(hipGetLastError());
-    HIPCHECK(hipStreamSynchronize(stream_));
+    cleanup();
+    return ni - done;
   } catch (...) {
     cleanup();
     throw;
   }
-  cleanup();
+}
+
+// Power iteration on K~^T K~ of new LPs over the blocks their products now
+// have (u in fm, w in fn, the state as preprocess left it).
+template <class T>
+void Engine<T>::power_iterate(const std::vector<int>& ids, int running) {
+  const int ni = (int)ids.size();
+  // tiles, column-sorted blocks, rows and slice blocks of sorted groups, for K^T and K
+  std::vector<Blk> tile[2], sorted[2], part[2], group[2];
+  std::vector<int4> rg;
+  int g = 0;
+  size_t lds_sorted[2] = {0, 0}, lds_group[2] = {0, 0};
+  for (int id : ids) {
+    const Slot& S = slots_[id];
+    const int g0 = g;
+    for (const int d : {0, 1}) {
+      for (Blk k : d ? S.bD : S.bP) {
+        if (!d) k.gid = g++;  // its partial sum
+        if (blk_kind(k) == BK_SORTED)
+          lds_sorted[d] = std::max(lds_sorted[d], sizeof(double) * (((size_t)(k.r1 - k.r0) << blk_rep_shift(k)) + kSpareWords));
+        (blk_part(k) ? part : blk_kind(k) == BK_SORTED ? sorted : tile)[d].push_back(k);
+      }
+      const std::vector<Blk>& sl = d ? S.bDS : S.bPS;
+      group[d].insert(group[d].end(), sl.begin(), sl.end());
+      for (const Blk& k : sl) lds_group[d] = std::max(lds_group[d], sizeof(double) * (size_t)(k.r1 - k.r0 + kSpareWords));
+    }
+    rg.push_back(make_int4(g0, g, 0, 0));
+  }
+  mark_streaming(ids, {&tile[0], &sorted[0], &group[0], &group[1], &tile[1], &sorted[1]});
+  Blk* d_blk[8] = {nullptr};
+  int* d_ids = nullptr;
+  int4* d_rg = nullptr;
+  double* d_pp = nullptr;
+  int* d_done = nullptr;
+  const std::vector<Blk>* lists[8] = {&tile[0], &sorted[0], &part[0], &group[0], &tile[1], &sorted[1], &part[1], &group[1]};
+  for (int k = 0; k < 8; ++k) {
+    talloc(&d_blk[k], (int64_t)lists[k]->size());
+    if (!lists[k]->empty())
+      HIPCHECK(hipMemcpyAsync(d_blk[k], lists[k]->data(), sizeof(Blk) * lists[k]->size(), hipMemcpyHostToDevice, stream_));
+  }
+  talloc(&d_ids, ni);
+  talloc(&d_rg, ni);
+  talloc(&d_pp, (int64_t)g * kNS);
+  talloc(&d_done, 1);
+  HIPCHECK(hipMemcpyAsync(d_ids, ids.data(), sizeof(int) * ni, hipMemcpyHostToDevice, stream_));
+  HIPCHECK(hipMemcpyAsync(d_rg, rg.data(), sizeof(int4) * ni, hipMemcpyHostToDevice, stream_));
+  HIPCHECK(hipMemsetAsync(d_done, 0, sizeof(int), stream_));
+  set_ranges_kernel<<<nblk(ni), 256, 0, stream_>>>(d_st, d_ids, d_rg, ni);
+  const bool fused = g <= kPowerFuse;
+  const PowerEnd E{d_pp, d_cnt, d_done, opt_.power_min_iters, opt_.power_max_iters, opt_.power_rtol};
+  auto groups = [&](int d, const double* src, double* sums, int64_t space) {
+    const size_t nb = group[d].size();
+    const int32_t* ci = d ? K_ci : KT_ci;
+    const double* val = d ? K_v64 : KT_v64;
+    if (nb <= (size_t)kCUs)
+      pw_group_kernel<1024><<<(unsigned)nb, 1024, lds_group[d], stream_>>>(d_blk[3 + 4 * d], d_st, ci, val, src, sums, space);
+    else
+      pw_group_kernel<512><<<(unsigned)nb, 512, lds_group[d], stream_>>>(d_blk[3 + 4 * d], d_st, ci, val, src, sums, space);
+  };
+  const auto tile_back = fused ? pw_backward_kernel<true> : pw_backward_kernel<false>;
+  const auto sorted_back = fused ? pw_sorted_kernel<false, true> : pw_sorted_kernel<false, false>;
+  const auto part_back = fused ? pw_part_kernel<false, true> : pw_part_kernel<false, false>;
+  // the slices' FP64 sums use the step's room for three vectors of type T
+  static_assert(3 * sizeof(T) >= sizeof(double), "slice sums");
+  double *sumsD = (double*)spartD, *sumsP = (double*)spartP;
+  int done = 0;
+  for (int it = 0; done < running && it < opt_.power_max_iters;) {
+    for (int b = 0; b < 8 && it < opt_.power_max_iters; ++b, ++it) {
+      if (!group[1].empty()) groups(1, fn, sumsD, MS_);
+      if (!tile[1].empty())
+        pw_forward_kernel<<<(unsigned)tile[1].size(), kThreads, 0, stream_>>>(d_blk[4], d_st, K_rp, K_ci, K_v64, fn, fm);
+      if (!sorted[1].empty())
+        pw_sorted_kernel<true, false><<<(unsigned)sorted[1].size(), kThreads, lds_sorted[1], stream_>>>(
+            d_blk[5], d_st, K_ci, K_v64, fn, fm, E);
+      if (!part[1].empty())
+        pw_part_kernel<true, false><<<(unsigned)part[1].size(), kThreads, 0, stream_>>>(d_blk[6], d_st, sumsD, MS_, fm, E);
+      if (!group[0].empty()) groups(0, fm, sumsP, NS_);
+      if (!tile[0].empty())
+        tile_back<<<(unsigned)tile[0].size(), kThreads, 0, stream_>>>(d_blk[0], d_st, KT_rp, KT_ci, KT_v64, fm, fn, E);
+      if (!sorted[0].empty())
+        sorted_back<<<(unsigned)sorted[0].size(), kThreads, lds_sorted[0], stream_>>>(d_blk[1], d_st, KT_ci, KT_v64, fm, fn, E);
+      if (!part[0].empty())
+        part_back<<<(unsigned)part[0].size(), kThreads, 0, stream_>>>(d_blk[2], d_st, sumsP, NS_, fn, E);
+      if (!fused)
+        pw_control_kernel<<<ni, kThreads, 0, stream_>>>(d_st, d_ids, d_pp, 0, opt_.power_min_iters, opt_.power_max_iters,
+                                                        opt_.power_rtol, d_done);
+    }
+    HIPCHECK(hipGetLastError());
+    HIPCHECK(hipMemcpyAsync(&done, d_done, sizeof(int), hipMemcpyDeviceToHost, stream_));
+    HIPCHECK(hipStreamSynchronize(stream_));
+  }
+  HIPCHECK(hipStreamSynchronize(stream_));
+  dfree(d_done);
+  dfree(d_pp);
+  dfree(d_rg);
+  dfree(d_ids);
+  for (int k = 7; k >= 0; --k) dfree(d_blk[k]);
+}
+
+// Step size and primal weight of new LPs, which are parked until set_params.
+template <class T>
+void Engine<T>::finish_states(const std::vector<int>& ids, const std::vector<double>& norms) {
+  const int ni = (int)ids.size();
+  const int first = *std::min_element(ids.begin(), ids.end()), last = *std::max_element(ids.begin(), ids.end());
+  std::vector<InstState> all(last - first + 1), cur(ni);
+  HIPCHECK(hipMemcpyAsync(all.data(), d_st + first, sizeof(InstState) * all.size(), hipMemcpyDeviceToHost, stream_));
+  HIPCHECK(hipStreamSynchronize(stream_));
+  for (int k = 0; k < ni; ++k) cur[k] = all[ids[k] - first];
+  for (int k = 0; k < ni; ++k) {
+    InstState& s = cur[k];
+    const double sh = s.sigma_hat;
+    double eta;
+    if (opt_.eta > 0.0) {
+      eta = opt_.eta;
+      s.sigma_hat = NAN;
+    } else {
+      eta = sh > 0.0 ? opt_.step_safety / sh : opt_.step_safety;
+    }
+    const double nq = norms[2 * k], nc = norms[2 * k + 1];
+    double omega = 1.0;
+    if (opt_.omega0 > 0.0) omega = opt_.omega0;
+    else if (opt_.primal_weight && nc > 1e-10 && nq > 1e-10) omega = nc / nq;
+    s.eta = eta;
+    s.omega = omega;
+    s.tau = eta / omega;
+    s.sigma = eta * omega;
+    s.reflect = opt_.method == 1;
+    s.avg = opt_.method == 2;
+    s.avg_b1 = opt_.avg_beta_sufficient;
+    s.avg_b2 = opt_.avg_beta_necessary;
+    s.kkt_anchor = NAN;
+    s.kkt_prev = INFINITY;
+    s.act_changes = 0;
+    s.ident_iters = 0;
+    s.C = opt_.check_every;
+    s.primal_weight = opt_.primal_weight;
+    s.beta = opt_.restart_beta;
+    s.artificial = opt_.artificial_restart;
+    s.restart_mode = opt_.restart_mode;
+    s.fixed_len = opt_.fixed_restart_len;
+    s.eps_inf = opt_.eps_infeas;
+    s.r0 = NAN;
+    s.status = ST_ITER_LIMIT;  // parked
+    s.phase = PH_NORMAL;
+    s.nrest = 0;
+    s.checks = 0;
+    s.ray = 0;
+    s.iters = 0;
+    s.kkt = NAN;
+    s.best_kkt = INFINITY;
+    s.best_check = 0;
+    s.stall_checks = 0;
+    h_st_[ids[k]] = s;
+  }
+  int* d_ids = nullptr;
+  InstState* d_src = nullptr;
+  talloc(&d_ids, ni);
+  talloc(&d_src, ni);
+  HIPCHECK(hipMemcpyAsync(d_ids, ids.data(), sizeof(int) * ni, hipMemcpyHostToDevice, stream_));
+  HIPCHECK(hipMemcpyAsync(d_src, cur.data(), sizeof(InstState) * ni, hipMemcpyHostToDevice, stream_));
+  write_states_kernel<<<nblk(ni), 256, 0, stream_>>>(d_st, d_status, d_cnt, d_ids, d_src, ni);
+  HIPCHECK(hipGetLastError());
+  HIPCHECK(hipStreamSynchronize(stream_));
+  dfree(d_src);
+  dfree(d_ids);
 }
 
 // Reorders one LP's K (dual = true; slices over its variables) or K^T

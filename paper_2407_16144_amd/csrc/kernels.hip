@@ -1668,54 +1668,142 @@ __device__ __forceinline__ void pw_update(InstState& S, double w2, int start, in
   }
 }
 
-// w = K~^T u over the rows of K^T (primal schedule), with the partial sum
-// w^2.  FUSED: the last of the LP's blocks also ends the iteration, which
-// saves small LPs a launch per iteration; the device-wide fence that each
-// block then takes is dearer than the launch where there are many (see
-// kPowerFuse).
-template <bool FUSED>
-__global__ __launch_bounds__(kThreads) void pw_backward_kernel(const Blk* schedP, InstState* st,
-                                                               const int32_t* rp, const int32_t* ci,
-                                                               const double* val, const double* u,
-                                                               double* w, double* partP, int* cnt, int min_iters,
-                                                               int max_iters, double rtol, int* done) {
-  __shared__ double s_prod[Tile<double>::NB];
-  __shared__ double s_rsum[3][kMaxRows];
-  __shared__ int s_rp[kMaxRows + 1];
-  __shared__ double s_red[kThreads / 64][kNS];
-  __shared__ double s_out[kNS];
+// A block's part of ||w||^2 (every thread's v), and, FUSED, the end of the
+// iteration by the last of the LP's blocks, which saves small LPs a launch per
+// iteration; the device-wide fence that each block then takes is dearer than the
+// launch where there are many (kPowerFuse).
+struct PowerEnd {
+  double* partP;
+  int *cnt, *done;
+  int min_iters, max_iters;
+  double rtol;
+};
+template <bool FUSED, int TPB = kThreads>
+__device__ __forceinline__ void pw_block_end(const Blk& b, InstState& S, double v, const PowerEnd& E,
+                                             double (*s_red)[kNS], double* s_out) {
   __shared__ int s_last;
-  const Blk b = schedP[blockIdx.x];
-  InstState& S = st[b.inst];
-  if (S.pw_done) return;
-  block_spmv<double, 1>(b, rp + b.r0, ci, val, u, u, u, s_prod, s_rsum, s_rp, s_red);
-  double v[kNS];
-  for (int s = 0; s < kNS; ++s) v[s] = 0.0;
-  const int nrows = b.r1 - b.r0;
-  if ((int)threadIdx.x < nrows) {
-    const double a = s_rsum[0][threadIdx.x];
-    w[(int64_t)b.r0 + threadIdx.x] = a;
-    v[0] = a * a;
-  }
-  block_sum_ns(v, s_red, s_out);
-  if (threadIdx.x < kNS) partP[(int64_t)blockIdx.x * kNS + threadIdx.x] = s_out[threadIdx.x];
+  double ps[kNS];
+  for (int s = 0; s < kNS; ++s) ps[s] = 0.0;
+  ps[0] = v;
+  block_sum_ns<TPB>(ps, s_red, s_out);
+  if (threadIdx.x < kNS) E.partP[(int64_t)b.gid * kNS + threadIdx.x] = s_out[threadIdx.x];
   if constexpr (FUSED) {
     __syncthreads();
     if (threadIdx.x == 0) {
       __threadfence();
       const int last =
-          __hip_atomic_fetch_add(cnt + b.inst, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S.pb1 - S.pb0 - 1;
+          __hip_atomic_fetch_add(E.cnt + b.inst, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S.pb1 - S.pb0 - 1;
       if (last) {
-        cnt[b.inst] = 0;
+        E.cnt[b.inst] = 0;
         __threadfence();
       }
       s_last = last;
     }
     __syncthreads();
     if (!s_last) return;
-    sum_partials(partP + (int64_t)S.pb0 * kNS, S.pb1 - S.pb0, s_red, s_out);
-    if (threadIdx.x == 0) pw_update(S, s_out[0], 0, min_iters, max_iters, rtol, done);
+    sum_partials<TPB>(E.partP + (int64_t)S.pb0 * kNS, S.pb1 - S.pb0, s_red, s_out);
+    if (threadIdx.x == 0) pw_update(S, s_out[0], 0, E.min_iters, E.max_iters, E.rtol, E.done);
   }
+}
+
+// w = K~^T u over tiles of K^T, with the partial sum w^2
+template <bool FUSED>
+__global__ __launch_bounds__(kThreads) void pw_backward_kernel(const Blk* schedP, InstState* st,
+                                                               const int32_t* rp, const int32_t* ci,
+                                                               const double* val, const double* u, double* w,
+                                                               PowerEnd E) {
+  __shared__ double s_prod[Tile<double>::NB];
+  __shared__ double s_rsum[3][kMaxRows];
+  __shared__ int s_rp[kMaxRows + 1];
+  __shared__ double s_red[kThreads / 64][kNS];
+  __shared__ double s_out[kNS];
+  const Blk b = schedP[blockIdx.x];
+  InstState& S = st[b.inst];
+  if (S.pw_done) return;
+  block_spmv<double, 1>(b, rp + b.r0, ci, val, u, u, u, s_prod, s_rsum, s_rp, s_red);
+  double a = 0.0;
+  const int nrows = b.r1 - b.r0;
+  if ((int)threadIdx.x < nrows) {
+    a = s_rsum[0][threadIdx.x];
+    w[(int64_t)b.r0 + threadIdx.x] = a;
+  }
+  pw_block_end<FUSED>(b, S, a * a, E, s_red, s_out);
+}
+
+// The same products over column-sorted blocks: out = pw_scale * K~ w (DUAL)
+// or w = K~^T u.  The power iteration runs on the layouts of the steps: at
+// 500k x 2M its two products took 640 us in row-major tiles and take 260 us
+// in sorted groups.
+template <bool DUAL, bool FUSED>
+__global__ __launch_bounds__(kThreads) void pw_sorted_kernel(const Blk* sched, InstState* st, const int32_t* ci,
+                                                             const double* val, const double* src, double* out,
+                                                             PowerEnd E) {
+  extern __shared__ __align__(16) unsigned char sorted_lds[];
+  __shared__ double s_red[kThreads / 64][kNS];
+  __shared__ double s_out[kNS];
+  double* s_row = reinterpret_cast<double*>(sorted_lds);
+  const Blk b = sched[blockIdx.x];
+  InstState& S = st[b.inst];
+  if (S.pw_done) return;
+  SortedStream<double, kThreads, kPlainU, kPlainD> stream;
+  stream.open(b, ci, val);
+  const int nrows = b.r1 - b.r0, rs = blk_rep_shift(b), words = nrows << rs;
+  const int copy = threadIdx.x & ((1 << rs) - 1);
+  clear_rows(s_row, words, kThreads);
+  lds_barrier();
+  stream.sum(src + b.rp_off, s_row + copy, words - copy + (threadIdx.x & 63), rs);
+  lds_barrier();
+  const double scale = DUAL ? S.pw_scale : 1.0;
+  double v = 0.0;
+  for (int r = threadIdx.x; r < nrows; r += kThreads) {
+    double a = 0.0;
+    for (int c = 0; c < (1 << rs); ++c) a += s_row[(r << rs) + c];
+    a *= scale;
+    out[(int64_t)b.r0 + r] = a;
+    v += a * a;
+  }
+  if constexpr (!DUAL) pw_block_end<FUSED>(b, S, v, E, s_red, s_out);
+}
+
+// Slice partial sums of sorted groups, part[slice][row]
+template <int TPB>
+__global__ __launch_bounds__(TPB) void pw_group_kernel(const Blk* sched, const InstState* st, const int32_t* ci,
+                                                       const double* val, const double* src, double* part,
+                                                       int64_t space) {
+  extern __shared__ __align__(16) unsigned char group_lds[];
+  double* s_row = reinterpret_cast<double*>(group_lds);
+  const Blk b = sched[blockIdx.x];
+  if (st[b.inst].pw_done) return;
+  SortedStream<double, TPB, kGroupEntries / TPB, 1> stream;
+  stream.open(b, ci, val);
+  const int nrows = b.r1 - b.r0;
+  clear_rows(s_row, nrows, TPB);
+  lds_barrier();
+  stream.sum(src + b.rp_off, s_row, nrows + (threadIdx.x & 63));
+  lds_barrier();
+  for (int r = threadIdx.x; r < nrows; r += TPB) part[(int64_t)blk_slice(b) * space + b.r0 + r] = s_row[r];
+}
+
+// Rows of sorted groups from their slices' sums
+template <bool DUAL, bool FUSED>
+__global__ __launch_bounds__(kThreads) void pw_part_kernel(const Blk* sched, InstState* st, const double* part,
+                                                           int64_t space, double* out, PowerEnd E) {
+  __shared__ double s_red[kThreads / 64][kNS];
+  __shared__ double s_out[kNS];
+  const Blk b = sched[blockIdx.x];
+  InstState& S = st[b.inst];
+  if (S.pw_done) return;
+  const double scale = DUAL ? S.pw_scale : 1.0;
+  const int nsl = blk_nsl(b);
+  double v = 0.0;
+  for (int64_t i = (int64_t)b.r0 + threadIdx.x; i < b.r1; i += kThreads) {
+    double a = 0.0;
+    for (int q = 0; q < nsl; ++q) a += part[(int64_t)q * space + i];
+    a *= scale;
+    out[i] = a;
+    v += a * a;
+  }
+  if constexpr (!DUAL) pw_block_end<FUSED>(b, S, v, E, s_red, s_out);
 }
 
 // one block per LP: ||w|| from the partials, then pw_update
