@@ -316,6 +316,9 @@ def run_batch(args, copy=None):
         halp.lp_batch_destroy(hp)
     roofline = batch_roofline(bulk, s, not args.fixed_order)
     if not args.fixed_order:
+        # the kernel's name up to its run-time template arguments
+        side = "true" if roofline["kernel"] == "dual_step" else "false"
+        roofline["kernel"] = f"sorted_step<{'double' if s == 8 else 'float'}, {side}"
         roofline["traffic"] = measured_traffic(f"batch-{args.precision}", roofline["kernel"])
     roofline["sampled"] = "first 1,280 iterations of the whole batch, every chunk timed"
     if copy is not None:
