@@ -300,9 +300,10 @@ void run_polish(Polish& P, const halp::Options& opt, hipStream_t stream, halp::E
   P.id.assign(count, -1);
   P.first.assign(count, halp::Result());
   std::vector<int> which;
-  int64_t ms = 0, ns = 0, zs = 0, buf_len = 1;
+  int64_t ms = 0, ns = 0, zs = 0;
+  const std::vector<halp::Result> results = src.results(src_ids);
   for (int i = 0; i < count; ++i) {
-    const halp::Result r = src.result(src_ids[i]);
+    const halp::Result& r = results[i];
     if (!polish_wanted(r, max_iter)) continue;
     which.push_back(i);
     P.first[i] = r;
@@ -310,7 +311,6 @@ void run_polish(Polish& P, const halp::Options& opt, hipStream_t stream, halp::E
     ms += p.m_eq + p.m_ineq + 1;
     ns += p.n + 1;
     zs += raw[i]->nnz;
-    buf_len = std::max<int64_t>(buf_len, p.n + p.m_eq + p.m_ineq + 1);
   }
   if (which.empty() || (left_s >= 0.0 && left_s <= 0.0)) return;
   halp::Options o64 = opt;
@@ -322,24 +322,18 @@ void run_polish(Polish& P, const halp::Options& opt, hipStream_t stream, halp::E
     probs.back().scaling = src.scaling(src_ids[i]);
   }
   const std::vector<int> ids = P.eng->add(probs, raw[which[0]]->on_device);
-  double* buf = nullptr;
-  if (hipMalloc((void**)&buf, sizeof(double) * buf_len) != hipSuccess)
-    throw halp::Error(LP_ERR_OOM, "device allocation failed");
-  try {
-    for (size_t k = 0; k < which.size(); ++k) {
-      const int i = which[k];
-      const lp_problem& p = raw[i]->view;
-      double omega = 1.0;
-      src.export_point(src_ids[i], buf, buf + p.n, &omega);
-      P.eng->import_point(ids[k], buf, buf + p.n, polish_omega(opt, P.first[i], omega));
-      P.id[i] = ids[k];
-      P.eng->set_params({ids[k]}, tol, max_iter - P.first[i].iters);
-    }
-  } catch (...) {
-    (void)hipFree(buf);
-    throw;
+  std::vector<int> from;
+  std::vector<double> omega;
+  std::vector<int64_t> limit;
+  for (size_t k = 0; k < which.size(); ++k) {
+    const int i = which[k];
+    from.push_back(src_ids[i]);
+    omega.push_back(polish_omega(opt, P.first[i], P.first[i].omega));
+    limit.push_back(max_iter - P.first[i].iters);
+    P.id[i] = ids[k];
   }
-  (void)hipFree(buf);
+  P.eng->take_over(src, from, ids, omega);
+  P.eng->set_params(ids, tol, limit, 0);
   P.eng->run(left_s);
 }
 

@@ -25,6 +25,13 @@ struct Scaling {
   int power_iters = 0;
 };
 
+// The candidate T(z) of an LP that an engine holds (device pointers, scaled).
+struct Candidate {
+  const void* x = nullptr;
+  const void* y = nullptr;
+  bool fp32 = false;
+};
+
 struct Problem {  // one input LP; pointers are host or device memory
   int64_t n = 0, m_eq = 0, m_ineq = 0;
   const int32_t* rp = nullptr;
@@ -119,12 +126,16 @@ class EngineBase {
   // best KKT error (a low-precision phase that has reached its floor)
   virtual void set_params(const std::vector<int>& ids, double tol, int64_t max_iter,
                           int64_t stall_checks = 0) = 0;
+  // the same with an iteration limit for each LP
+  virtual void set_params(const std::vector<int>& ids, double tol, const std::vector<int64_t>& max_iter,
+                          int64_t stall_checks) = 0;
   // run until every listed slot has terminated (or the time limit)
   virtual void run(double time_limit_s) = 0;
   // advance all live slots by `chunks` chunks; returns slots that finished since last call
   virtual std::vector<int> advance(int chunks) = 0;
   virtual void remove(const std::vector<int>& ids) = 0;
   virtual Result result(int id) = 0;
+  virtual std::vector<Result> results(const std::vector<int>& ids) = 0;
   virtual void solution(int id, double* x, double* y, bool to_device) = 0;
   virtual void certificate(int id, double* ray, bool to_device) = 0;
   virtual int64_t n_of(int id) const = 0;
@@ -138,6 +149,11 @@ class EngineBase {
   virtual bool fits_empty(int64_t n, int64_t m, int64_t nnz) const = 0;
   virtual KernelTimes kernel_times() const = 0;
   // last check candidate T(z) in the scaled space, as float64 device arrays
+  // LPs `ids` (not started yet) continue from the candidates of the LPs
+  // src_ids of another engine on the same stream: import_point for all of them
+  virtual void take_over(const EngineBase& src, const std::vector<int>& src_ids, const std::vector<int>& ids,
+                         const std::vector<double>& omega) = 0;
+  virtual Candidate candidate(int id) const = 0;
   virtual Scaling scaling(int id) const = 0;
   virtual void export_point(int id, double* x, double* y, double* omega) = 0;
   // start the next solve of `id` from (x, y) (scaled, float64 device arrays)

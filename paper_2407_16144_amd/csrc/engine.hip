@@ -451,6 +451,15 @@ class Engine final : public EngineBase {
   std::vector<int> add(const std::vector<Problem>& probs, bool on_device, bool partial) override;
   void set_params(const std::vector<int>& ids, double tol, int64_t max_iter,
                   int64_t stall_checks = 0) override;
+  void set_params(const std::vector<int>& ids, double tol, const std::vector<int64_t>& max_iter,
+                  int64_t stall_checks) override;
+  std::vector<Result> results(const std::vector<int>& ids) override;
+  void take_over(const EngineBase& src, const std::vector<int>& src_ids, const std::vector<int>& ids,
+                 const std::vector<double>& omega) override;
+  Candidate candidate(int id) const override {
+    const Slot& S = slots_[id];
+    return {xT + S.col0, yT + S.row0, sizeof(T) == 4};
+  }
   void run(double time_limit_s) override;
   std::vector<int> advance(int chunks) override;
   void remove(const std::vector<int>& ids) override;
@@ -525,7 +534,7 @@ class Engine final : public EngineBase {
                    int64_t min_rows, bool reblock, int64_t max_entries);
   void reblock_for(const int* status);
   IterArgs<T> args() const;
-  void pull_states();
+  std::vector<InstState> states(const std::vector<int>& ids);
 
   Options opt_;
   hipStream_t stream_;
@@ -1454,11 +1463,7 @@ void Engine<T>::power_iterate(const std::vector<int>& ids, int running) {
 template <class T>
 void Engine<T>::finish_states(const std::vector<int>& ids, const std::vector<double>& norms) {
   const int ni = (int)ids.size();
-  const int first = *std::min_element(ids.begin(), ids.end()), last = *std::max_element(ids.begin(), ids.end());
-  std::vector<InstState> all(last - first + 1), cur(ni);
-  HIPCHECK(hipMemcpyAsync(all.data(), d_st + first, sizeof(InstState) * all.size(), hipMemcpyDeviceToHost, stream_));
-  HIPCHECK(hipStreamSynchronize(stream_));
-  for (int k = 0; k < ni; ++k) cur[k] = all[ids[k] - first];
+  std::vector<InstState> cur = states(ids);
   for (int k = 0; k < ni; ++k) {
     InstState& s = cur[k];
     const double sh = s.sigma_hat;
@@ -2038,17 +2043,31 @@ void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int
 
 template <class T>
 void Engine<T>::set_params(const std::vector<int>& ids, double tol, int64_t max_iter, int64_t stall_checks) {
+  set_params(ids, tol, std::vector<int64_t>(ids.size(), max_iter), stall_checks);
+}
+
+// The states of the LPs `ids`, in one copy of the slots they span.
+template <class T>
+std::vector<InstState> Engine<T>::states(const std::vector<int>& ids) {
+  const int first = *std::min_element(ids.begin(), ids.end()), last = *std::max_element(ids.begin(), ids.end());
+  std::vector<InstState> all(last - first + 1), out(ids.size());
+  HIPCHECK(hipMemcpyAsync(all.data(), d_st + first, sizeof(InstState) * all.size(), hipMemcpyDeviceToHost, stream_));
+  HIPCHECK(hipStreamSynchronize(stream_));
+  for (size_t k = 0; k < ids.size(); ++k) out[k] = all[ids[k] - first];
+  return out;
+}
+
+template <class T>
+void Engine<T>::set_params(const std::vector<int>& ids, double tol, const std::vector<int64_t>& max_iter,
+                           int64_t stall_checks) {
   HIPCHECK(hipStreamSynchronize(stream_));
   const int ni = (int)ids.size();
   if (ni == 0) return;
-  std::vector<InstState> cur(ni);
-  for (int k = 0; k < ni; ++k)
-    HIPCHECK(hipMemcpyAsync(&cur[k], d_st + ids[k], sizeof(InstState), hipMemcpyDeviceToHost, stream_));
-  HIPCHECK(hipStreamSynchronize(stream_));
+  std::vector<InstState> cur = states(ids);
   for (int k = 0; k < ni; ++k) {
     InstState& s = cur[k];
     s.tol = tol;
-    s.max_iter = max_iter;
+    s.max_iter = max_iter[k];
     s.stall_checks = stall_checks;
     s.best_kkt = INFINITY;
     s.best_check = s.checks;
@@ -2564,9 +2583,10 @@ void Engine<T>::remove(const std::vector<int>& ids) {
 template <class T>
 Result Engine<T>::result(int id) {
   if (id < 0 || id >= nslots_ || !slots_[id].used) throw Error(-1, "invalid LP id");
-  InstState s;
-  HIPCHECK(hipStreamSynchronize(stream_));
-  HIPCHECK(hipMemcpy(&s, d_st + id, sizeof(InstState), hipMemcpyDeviceToHost));
+  return results({id})[0];
+}
+
+static Result result_of(const InstState& s) {
   Result r;
   r.status = s.status;
   if (s.checks == 0 && s.status == ST_ITER_LIMIT) r.status = 0;  // parked, never run
@@ -2591,19 +2611,48 @@ Result Engine<T>::result(int id) {
 }
 
 template <class T>
+std::vector<Result> Engine<T>::results(const std::vector<int>& ids) {
+  std::vector<Result> out;
+  if (ids.empty()) return out;
+  for (const InstState& s : states(ids)) out.push_back(result_of(s));
+  return out;
+}
+
+template <class T>
+void Engine<T>::take_over(const EngineBase& src, const std::vector<int>& src_ids, const std::vector<int>& ids,
+                          const std::vector<double>& omega) {
+  std::vector<HandOver> in;
+  int64_t largest = 1;
+  for (size_t k = 0; k < ids.size(); ++k) {
+    const Slot& S = slots_[ids[k]];
+    const Candidate c = src.candidate(src_ids[k]);
+    in.push_back({c.x, c.y, omega[k], S.m, S.n, S.row0, S.col0, ids[k], c.fp32});
+    largest = std::max({largest, S.m, S.n});
+  }
+  if (in.empty()) return;
+  HandOver* d_in = nullptr;
+  dalloc(&d_in, (int64_t)in.size());
+  HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(HandOver) * in.size(), hipMemcpyHostToDevice, stream_));
+  const int parts = parts_for(largest, in.size());
+  take_over_kernel<T><<<(unsigned)(in.size() * parts), kThreads, 0, stream_>>>(d_in, parts, d_st, x, x0, y, y0);
+  HIPCHECK(hipGetLastError());
+  HIPCHECK(hipStreamSynchronize(stream_));
+  dfree(d_in);
+}
+
+template <class T>
 void Engine<T>::solution(int id, double* xo, double* yo, bool to_device) {
   if (id < 0 || id >= nslots_ || !slots_[id].used) throw Error(-1, "invalid LP id");
   const Slot& S = slots_[id];
-  double* tmp = nullptr;
-  dalloc(&tmp, S.n + S.m);
-  unscale_kernel<T><<<nblk(S.n), 256, 0, stream_>>>(xT, Dc, S.col0, S.n, tmp);
-  if (S.m) unscale_kernel<T><<<nblk(S.m), 256, 0, stream_>>>(yT, Dr, S.row0, S.m, tmp + S.n);
+  // the LP's part of the vectors that its creation worked in
+  double *xu = fn + S.col0, *yu = fm + S.row0;
+  unscale_kernel<T><<<nblk(S.n), 256, 0, stream_>>>(xT, Dc, S.col0, S.n, xu);
+  if (S.m) unscale_kernel<T><<<nblk(S.m), 256, 0, stream_>>>(yT, Dr, S.row0, S.m, yu);
   HIPCHECK(hipGetLastError());
   const auto kind = to_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  if (xo) HIPCHECK(hipMemcpyAsync(xo, tmp, sizeof(double) * S.n, kind, stream_));
-  if (yo && S.m) HIPCHECK(hipMemcpyAsync(yo, tmp + S.n, sizeof(double) * S.m, kind, stream_));
+  if (xo) HIPCHECK(hipMemcpyAsync(xo, xu, sizeof(double) * S.n, kind, stream_));
+  if (yo && S.m) HIPCHECK(hipMemcpyAsync(yo, yu, sizeof(double) * S.m, kind, stream_));
   HIPCHECK(hipStreamSynchronize(stream_));
-  dfree(tmp);
 }
 
 template <class T>

@@ -165,6 +165,14 @@ struct alignas(16) InstState {
   int32_t pw_iter, pw_done;
 };
 
+// One LP that continues from another engine's candidate.
+struct HandOver {
+  const void *x, *y;  // the candidate
+  double omega;       // primal weight, or <= 0 for the LP's own
+  int64_t m, n, row0, col0;
+  int32_t inst, fp32;
+};
+
 // One LP of device-resident input and its places in the engine's spaces.
 struct LpInput {
   const int32_t* rp;
