@@ -2269,20 +2269,19 @@ void Engine<T>::rebuild_schedules() {
   tpbDB_ = pick_sorted(DB);
   mark_streaming(live, {&P, &PB, &PS, &DS, &D, &DB});
   HIPCHECK(hipStreamSynchronize(stream_));
+  // a capacity counts once its buffer exists (an allocation may throw)
+  auto grow = [](auto*& d, int64_t& cap, int64_t n, int64_t words) {
+    if (n <= cap) return;
+    const int64_t want = std::max<int64_t>(n, 2 * cap);
+    dfree(d);
+    cap = 0;
+    dalloc(&d, want * words);
+    cap = want;
+  };
   auto upload = [&](std::vector<Blk>& v, Blk*& d, int64_t& cap, int64_t& n) {
-    if ((int64_t)v.size() > cap) {
-      dfree(d);
-      cap = std::max<int64_t>((int64_t)v.size(), 2 * cap);
-      dalloc(&d, cap);
-    }
+    grow(d, cap, (int64_t)v.size(), 1);
     n = (int64_t)v.size();
     if (n) HIPCHECK(hipMemcpyAsync(d, v.data(), sizeof(Blk) * n, hipMemcpyHostToDevice, stream_));
-  };
-  auto sums = [&](int64_t n, double*& part, int64_t& cap) {
-    if (n <= cap) return;
-    dfree(part);
-    cap = std::max<int64_t>(n, 2 * cap);
-    dalloc(&part, cap * kNS);
   };
   scheduled_ = (int)live.size();
   upload(P, d_schedP, capP_, nP_);
@@ -2294,8 +2293,8 @@ void Engine<T>::rebuild_schedules() {
   upload(DE, d_schedDE, capDE_, nDE_);
   upload(PS, d_schedPS, capPS_, nPS_);
   upload(DS, d_schedDS, capDS_, nDS_);
-  sums(gP, partP, cap_partP_);
-  sums(gD, partD, cap_partD_);
+  grow(partP, cap_partP_, gP, kNS);
+  grow(partD, cap_partD_, gD, kNS);
   if (!live.empty()) {
     int* d_ids = nullptr;
     int4* d_rg = nullptr;

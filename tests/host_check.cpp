@@ -1,0 +1,106 @@
+// Checks of the engine's host code on the CPU (see hip_stub.h).  Usage:
+// host_check NAME; prints "ok NAME".
+#include "hip_stub.h"
+
+#include "halp.h"
+
+#include <random>
+
+#define CHECK(c)                                                                     \
+  do {                                                                               \
+    if (!(c)) {                                                                      \
+      fprintf(stderr, "%s:%d: %s (%s)\n", __FILE__, __LINE__, #c, lp_last_error());  \
+      exit(1);                                                                       \
+    }                                                                                \
+  } while (0)
+
+namespace {
+
+struct LP {
+  int64_t m, n;
+  std::vector<int32_t> rp{0}, ci;
+  std::vector<double> val, c, rhs, lb, ub;
+  // row r: `len` entries at random in columns [first(r), first(r) + span)
+  LP(int64_t m_, int64_t n_, int64_t len, int64_t span, unsigned seed = 1) : m(m_), n(n_) {
+    std::mt19937_64 g(seed);
+    std::vector<int32_t> row;
+    for (int64_t r = 0; r < m; ++r) {
+      const int64_t first = m > 1 ? (n - span) * r / (m - 1) : 0;
+      row.clear();
+      for (int64_t k = 0; k < len; ++k) row.push_back((int32_t)(first + (int64_t)(g() % (uint64_t)span)));
+      std::sort(row.begin(), row.end());
+      row.erase(std::unique(row.begin(), row.end()), row.end());
+      ci.insert(ci.end(), row.begin(), row.end());
+      rp.push_back((int32_t)ci.size());
+    }
+    val.assign(ci.size(), 1.0);
+    c.assign(n, 1.0);
+    rhs.assign(m, 1.0);
+    lb.assign(n, 0.0);
+    ub.assign(n, 1.0);
+  }
+  lp_problem problem() const {
+    return {n, m, 0, rp.data(), ci.data(), val.data(), c.data(), rhs.data(), lb.data(), ub.data()};
+  }
+};
+
+lp_options options() {
+  lp_options o;
+  lp_default_options(&o);
+  o.use_graph = 0;
+  o.eta = 0.1;  // no power iteration: its kernels do nothing here
+  return o;
+}
+
+size_t step_kernels(size_t from) {
+  return stub::count("_step<double", from) + stub::count("resident_steps", from);
+}
+
+// Memory runs out after n allocations of a server's first steps, for every n:
+// the step after that, with memory again, finds every buffer it needs (a
+// launch with a null schedule or sums buffer would fault a GPU).
+void failed_schedule() {
+  const LP a(40, 60, 5, 60), b(3000, 5000, 8, 5000);
+  lp_options o = options();
+  for (const int sorted : {1, 0}) {
+    o.plain_sort = sorted;
+    bool failed = true;
+    for (long n = 0; failed; ++n) {
+      stub::reset();
+      lp_server* s = nullptr;
+      CHECK(lp_server_create(&s, 64 << 20, 8, nullptr, &o) == LP_OK);
+      int64_t t;
+      lp_problem p = a.problem();
+      CHECK(lp_server_submit(s, &p, 1e-6, 1000, 0.0, &t) == LP_OK);
+      p = b.problem();
+      CHECK(lp_server_submit(s, &p, 1e-6, 1000, 0.0, &t) == LP_OK);
+      stub::fail_at = n;
+      const int rc = lp_server_step(s, 1, nullptr);
+      failed = rc != LP_OK;
+      stub::fail_at = -1;
+      CHECK(rc == LP_OK || rc == LP_ERR_OOM);
+      stub::on_launch = [&](const stub::Launch& l, void** args) {
+        if (l.name.find("step<double") == std::string::npos) return;
+        const auto& A = stub::arg<halp::IterArgs<double>>(args, 0);
+        CHECK(A.partP && A.partD);
+        CHECK(sorted ? A.schedPB && A.schedDB : A.schedP && A.schedD);
+      };
+      const size_t from = stub::launches.size();
+      CHECK(lp_server_step(s, 1, nullptr) == LP_OK);
+      CHECK(step_kernels(from) > 0);
+      stub::on_launch = nullptr;
+      lp_server_destroy(s);
+    }
+  }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string name = argc > 1 ? argv[1] : "";
+  const std::map<std::string, void (*)()> checks = {{"failed_schedule", failed_schedule}};
+  if (!checks.count(name)) return 2;
+  checks.at(name)();
+  printf("ok %s\n", name.c_str());
+  return 0;
+}
