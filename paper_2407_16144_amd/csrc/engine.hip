@@ -1636,7 +1636,6 @@ void Engine<T>::reblock_for(const int* status) {
 template <class T>
 void Engine<T>::recut(const std::vector<int>& ids, int64_t maxb, int64_t minr, bool solo) {
   if (solo) maxb = minr = 1;
-  bool changed = false;
   for (const bool dual : {false, true}) {
     std::vector<int> todo;
     std::vector<std::vector<int32_t>> rp;
@@ -1654,12 +1653,14 @@ void Engine<T>::recut(const std::vector<int>& ids, int64_t maxb, int64_t minr, b
     }
     if (todo.empty()) continue;
     for (auto& v : rp) rps.push_back(v.data());
+    // the schedules are of the old blocks, also where an allocation below throws
+    // with some LPs laid out anew
+    sched_dirty_ = true;
+    compacted_ = false;
     TempScope temp(temp_bytes(largest));
     // temporary memory for the largest of them, as a server's budget allows
     sort_blocks(todo, dual, rps, maxb, minr, true, largest);
-    changed = true;
   }
-  if (changed) sched_dirty_ = true;
 }
 
 // Column-sorted blocks of one LP's K (dual = true) or K^T over its row pointers
@@ -2165,6 +2166,8 @@ void Engine<T>::mark_streaming(const std::vector<int>& live, std::initializer_li
 
 template <class T>
 void Engine<T>::rebuild_schedules() {
+  sched_dirty_ = true;  // until all of them are in place
+  compacted_ = false;
   // P / D: tiles; PB / DB: column-sorted blocks; PE / DE: rows of sliced
   // products; PS / DS: slice blocks; R: both blocks of each small LP.  gids number an LP's step blocks of all
   // three kinds in one range.
@@ -2500,8 +2503,13 @@ void Engine<T>::run(double time_limit_s) {
         HIPCHECK(hipMemcpy(h_status[0], d_status, sizeof(int) * nslots_, hipMemcpyDeviceToHost));
         std::memcpy(h_status[1], h_status[0], sizeof(int) * nslots_);
         finished_ = h_status[0];
-        reblock_for(h_status[0]);
-        rebuild_schedules();
+        try {
+          reblock_for(h_status[0]);
+          rebuild_schedules();
+        } catch (...) {
+          finished_ = nullptr;
+          throw;
+        }
         finished_ = nullptr;
         sched_dirty_ = true;  // the next add / remove / solve rebuilds the full schedules
         compacted_ = true;

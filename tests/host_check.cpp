@@ -94,11 +94,97 @@ void failed_schedule() {
   }
 }
 
+// Two small LPs of a server step on one CU each; a larger one joins, for which
+// they are laid out anew, and memory runs out somewhere on the way.
+// No later step may use the schedule of the old layout with re-laid matrices.
+void failed_admission() {
+  // (the small ones have more entries, so that laying them out takes the most
+  // memory, K more than K^T, which comes first)
+  const LP a(1000, 100, 8, 100), b(1000, 120, 8, 120), big(1100, 1100, 1, 1);
+  const lp_options o = options();
+  bool failed = true, relaid = false;
+  for (size_t room = 0; failed; room += 4096) {
+    stub::reset();
+    lp_server* s = nullptr;
+    CHECK(lp_server_create(&s, 64 << 20, 3, nullptr, &o) == LP_OK);
+    int64_t t;
+    lp_problem p = a.problem();
+    CHECK(lp_server_submit(s, &p, 1e-6, 1000, 0.0, &t) == LP_OK);
+    p = b.problem();
+    CHECK(lp_server_submit(s, &p, 1e-6, 1000, 0.0, &t) == LP_OK);
+    CHECK(lp_server_step(s, 1, nullptr) == LP_OK);
+    CHECK(stub::count("resident_steps") == 1);
+    p = big.problem();
+    CHECK(lp_server_submit(s, &p, 1e-6, 1000, 0.0, &t) == LP_OK);
+    const size_t from = stub::launches.size();
+    stub::limit = stub::bytes + room;
+    const int rc = lp_server_step(s, 1, nullptr);
+    failed = rc != LP_OK;
+    stub::limit = SIZE_MAX;
+    CHECK(rc == LP_OK || rc == LP_ERR_OOM);
+    const bool cut = stub::count("reblock_keys_kernel", from) > 0;
+    relaid |= failed && cut;
+    const size_t then = stub::launches.size();
+    CHECK(lp_server_step(s, 1, nullptr) == LP_OK);
+    if (cut) CHECK(stub::count("resident_steps", then) == 0);
+    CHECK(step_kernels(then) > 0);
+    lp_server_destroy(s);
+  }
+  CHECK(relaid);  // the case that matters came up
+}
+
+// The LPs of a batch still running when half have finished are laid out anew;
+// memory runs out after n allocations of that, for every n.  The next solve
+// starts from schedules built after the failure.
+void failed_reblocking() {
+  std::vector<LP> lps;
+  std::vector<lp_problem> ps;
+  for (int i = 0; i < 40; ++i) lps.emplace_back(1500, 2500, 6, 2500, i);
+  for (const LP& lp : lps) ps.push_back(lp.problem());
+  const lp_options o = options();
+  bool failed = true, relaid = false;
+  for (long n = 0; failed; ++n) {
+    stub::reset();
+    lp_batch* h = nullptr;
+    CHECK(lp_batch_create(&h, (int)ps.size(), ps.data(), 0, nullptr, &o) == LP_OK);
+    int steps = 0;
+    size_t from = 0;
+    stub::on_launch = [&](const stub::Launch& l, void** a) {
+      if (l.name.find("sorted_step<double, true") == std::string::npos) return;
+      const auto& A = stub::arg<halp::IterArgs<double>>(a, 0);
+      if (++steps == 64) {  // all but three finish in the first chunk
+        for (int i = 3; i < 40; ++i) A.status_out[i] = halp::ST_OPTIMAL;
+        from = stub::launches.size();
+        stub::fail_at = n;
+      }
+      if (steps > 64 * 40)  // the rest finish later
+        for (int i = 0; i < 3; ++i) A.status_out[i] = halp::ST_OPTIMAL;
+    };
+    const int rc = lp_batch_solve(h, 1e-6, 1000, -1.0);
+    failed = rc != LP_OK;
+    stub::fail_at = -1;
+    CHECK(rc == LP_OK || rc == LP_ERR_OOM);
+    relaid |= failed && stub::count("reblock_keys_kernel", from) > 0;
+    if (failed) {
+      const size_t then = stub::launches.size();
+      CHECK(lp_batch_solve(h, 1e-6, 1000, -1.0) == LP_OK);
+      size_t ranges = then, step = then;
+      while (ranges < stub::launches.size() && stub::launches[ranges].name != "set_ranges_kernel") ++ranges;
+      while (step < stub::launches.size() && stub::launches[step].name.find("sorted_step") == std::string::npos) ++step;
+      CHECK(step < stub::launches.size() && ranges < step);
+    }
+    lp_batch_destroy(h);
+  }
+  CHECK(relaid);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
-  const std::map<std::string, void (*)()> checks = {{"failed_schedule", failed_schedule}};
+  const std::map<std::string, void (*)()> checks = {{"failed_schedule", failed_schedule},
+                                                      {"failed_admission", failed_admission},
+                                                      {"failed_reblocking", failed_reblocking}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());
