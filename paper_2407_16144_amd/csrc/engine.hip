@@ -482,6 +482,7 @@ class Engine final : public EngineBase {
   void allocate();
   size_t carve(char* base);
   void release_all();
+  void release_slots(const std::vector<int>& ids);
   void rebuild_schedules();
   void pin_to_xcds(std::vector<Blk>& v, const std::vector<std::pair<int, int>>& ranges) const;
   void launch_slices(bool dual, const IterArgs<T>& A, int step);
@@ -1035,53 +1036,54 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   } else {
     validate_device(probs, nnzs);
   }
-  std::vector<int> fresh;
-  try {
-    for (size_t k = 0; k < probs.size(); ++k) {
-      const Problem& p = probs[k];
-      const int64_t m = p.m_eq + p.m_ineq;
-      int id = -1;
-      for (int s = 0; s < nslots_; ++s)
-        if (!slots_[s].used) {
-          id = s;
-          break;
-        }
-      if (id < 0) {
-        if (partial) break;
-        throw Error(-2, "no free LP slot");
+  // the slots are given back if anything below throws
+  struct Undo {
+    Engine* eng;
+    std::vector<int>* ids;
+    ~Undo() {
+      if (!ids || ids->empty()) return;
+      (void)hipStreamSynchronize(eng->stream_);
+      try {
+        eng->release_slots(*ids);
+      } catch (...) {  // no host memory for the lists of free ranges
       }
-      const int64_t r0 = am_.alloc(m + 1);
-      const int64_t c0 = r0 < 0 ? -1 : an_.alloc(p.n + 1);
-      const int64_t z0 = c0 < 0 ? -1 : az_.alloc(nnzs[k]);
-      if (r0 < 0 || c0 < 0 || z0 < 0) {
-        if (r0 >= 0) am_.release(r0, m + 1);
-        if (c0 >= 0) an_.release(c0, p.n + 1);
-        if (partial) break;
-        throw Error(-2, "not enough device memory reserved for this LP");
+    }
+  } undo{this, &ids};
+  for (size_t k = 0; k < probs.size(); ++k) {
+    const Problem& p = probs[k];
+    const int64_t m = p.m_eq + p.m_ineq;
+    int id = -1;
+    for (int s = 0; s < nslots_; ++s)
+      if (!slots_[s].used) {
+        id = s;
+        break;
       }
-      if (z0 + nnzs[k] > INT32_MAX) throw Error(-1, "more than 2^31 stored entries");
-      Slot& S = slots_[id];
-      S = Slot();
-      S.used = true;
-      S.n = p.n;
-      S.m = m;
-      S.m_eq = p.m_eq;
-      S.nnz = nnzs[k];
-      S.row0 = r0;
-      S.col0 = c0;
-      S.nz0 = z0;
-      ids.push_back(id);
-      fresh.push_back(id);
+    if (id < 0) {
+      if (partial) break;
+      throw Error(-2, "no free LP slot");
     }
-  } catch (...) {
-    for (int id : fresh) {
-      Slot& S = slots_[id];
-      am_.release(S.row0, S.m + 1);
-      an_.release(S.col0, S.n + 1);
-      az_.release(S.nz0, S.nnz);
-      S = Slot();
+    const int64_t r0 = am_.alloc(m + 1);
+    const int64_t c0 = r0 < 0 ? -1 : an_.alloc(p.n + 1);
+    const int64_t z0 = c0 < 0 ? -1 : az_.alloc(nnzs[k]);
+    if (r0 < 0 || c0 < 0 || z0 < 0 || z0 + nnzs[k] > INT32_MAX) {
+      if (r0 >= 0) am_.release(r0, m + 1);
+      if (c0 >= 0) an_.release(c0, p.n + 1);
+      if (z0 >= 0) az_.release(z0, nnzs[k]);
+      if (z0 >= 0) throw Error(-1, "more than 2^31 stored entries");
+      if (partial) break;
+      throw Error(-2, "not enough device memory reserved for this LP");
     }
-    throw;
+    Slot& S = slots_[id];
+    S = Slot();
+    S.used = true;
+    S.n = p.n;
+    S.m = m;
+    S.m_eq = p.m_eq;
+    S.nnz = nnzs[k];
+    S.row0 = r0;
+    S.col0 = c0;
+    S.nz0 = z0;
+    ids.push_back(id);
   }
 
   if (ids.size() < probs.size()) {
@@ -1241,6 +1243,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   for (auto& [id, dual] : sliced) slice_matrix(id, dual);
   sched_dirty_ = true;
   for (int id : ids) slots_[id].watched = true;
+  undo.ids = nullptr;
   return ids;
 }
 
@@ -1557,6 +1560,8 @@ void Engine<T>::slice_matrix(int id, bool dual) {
   build_sliced(cnt.data(), nrows, r0, id, NB, opt_.slice_rows, kPartRows(dual), S.nz0, at, grp, sl, brp, dst);
   if ((int64_t)brp.size() > cap) throw Error(-3, "sliced row pointer overflow");
   ab.release(at + (int64_t)brp.size(), cap - (int64_t)brp.size());
+  (dual ? S.brpD0 : S.brpP0) = at;
+  (dual ? S.brpDn : S.brpPn) = (int64_t)brp.size();
   int32_t* brp_d = dual ? brpK : brpKT;
   HIPCHECK(hipMemcpyAsync(brp_d + at, brp.data(), sizeof(int32_t) * brp.size(), hipMemcpyHostToDevice, stream_));
   int32_t* d_dst = nullptr;
@@ -1585,13 +1590,9 @@ void Engine<T>::slice_matrix(int id, bool dual) {
   if (dual) {
     S.bD = grp;
     S.bDS = sl;
-    S.brpD0 = at;
-    S.brpDn = (int64_t)brp.size();
   } else {
     S.bP = grp;
     S.bPS = sl;
-    S.brpP0 = at;
-    S.brpPn = (int64_t)brp.size();
   }
   need_partials(dual, kSlices);
 }
@@ -2572,6 +2573,11 @@ std::vector<int> Engine<T>::advance(int chunks) {
 template <class T>
 void Engine<T>::remove(const std::vector<int>& ids) {
   HIPCHECK(hipStreamSynchronize(stream_));
+  release_slots(ids);
+}
+
+template <class T>
+void Engine<T>::release_slots(const std::vector<int>& ids) {
   for (int id : ids) {
     Slot& S = slots_.at(id);
     if (!S.used) continue;

@@ -133,6 +133,40 @@ void failed_admission() {
   CHECK(relaid);  // the case that matters came up
 }
 
+// Memory runs out somewhere in the admission of an LP: its slot is free again
+// (a server of two slots has the second one filled by the next step).
+void failed_admission_frees_slots() {
+  const LP a(40, 60, 5, 60), b(3000, 5000, 8, 5000);
+  lp_options o = options();
+  for (const int sorted : {1, 0}) {
+    o.plain_sort = sorted;
+    bool failed = true;
+    size_t failures = 0;
+    for (long n = 0; failed; ++n) {
+      stub::reset();
+      lp_server* s = nullptr;
+      CHECK(lp_server_create(&s, 64 << 20, 2, nullptr, &o) == LP_OK);
+      int64_t t;
+      int queued = 0, live = 0;
+      lp_problem p = a.problem();
+      CHECK(lp_server_submit(s, &p, 1e-6, 1000, 0.0, &t) == LP_OK);
+      CHECK(lp_server_step(s, 1, nullptr) == LP_OK);
+      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 0 && live == 1);
+      p = b.problem();
+      CHECK(lp_server_submit(s, &p, 1e-6, 1000, 0.0, &t) == LP_OK);
+      stub::fail_at = n;
+      failed = lp_server_step(s, 0, nullptr) != LP_OK;  // admission alone
+      stub::fail_at = -1;
+      failures += failed;
+      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued + live == 2);
+      CHECK(lp_server_step(s, 1, nullptr) == LP_OK);
+      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 0 && live == 2);
+      lp_server_destroy(s);
+    }
+    CHECK(failures > 0);
+  }
+}
+
 // The LPs of a batch still running when half have finished are laid out anew;
 // memory runs out after n allocations of that, for every n.  The next solve
 // starts from schedules built after the failure.
@@ -184,6 +218,7 @@ int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   const std::map<std::string, void (*)()> checks = {{"failed_schedule", failed_schedule},
                                                       {"failed_admission", failed_admission},
+                                                      {"failed_admission_frees_slots", failed_admission_frees_slots},
                                                       {"failed_reblocking", failed_reblocking}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
