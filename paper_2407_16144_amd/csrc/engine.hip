@@ -1194,7 +1194,9 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   // more rows than one plain sorted block per CU holds is stored in sorted
   // groups of 1 or 2 slices (the fused step of plain blocks is the better one
   // as long as it fits: 100k x 400k, K^T in 256 plain blocks 36.5 us per
-  // iteration, in 2 slices x 128 groups 40.0).  The other products get
+  // iteration, in 2 slices x 128 groups 40.0), unless its groups may not hold
+  // more rows than a plain block either (20k x 70k with sort_rows = 256: K^T in
+  // groups 20.0 us, in plain blocks 15.0).  The other products get
   // column-sorted plain blocks (plain_sort) or plain tiles.
   std::vector<int> plain[2];  // LPs whose K^T / K gets column-sorted plain blocks
   std::vector<const int32_t*> plain_rp[2];
@@ -1216,7 +1218,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
         sliced.push_back({id, dual});
       } else if (S.nnz > 0 && opt_.slice_sort && (slice || opt_.plain_sort) &&
                  group_shape(nrows, width, nsl_min, &nsl, &ngroups, &cap) &&
-                 (slice || nrows > kCUs * std::min<int64_t>(opt_.sort_rows, kSortRowsPlain))) {
+                 (slice || (nrows > kCUs * kSortRowsPlain && cap > kSortRowsPlain))) {
         group_sorted(id, dual, (dual ? host_rp[t] : host_rpT[t]).data(), nsl, ngroups, cap);
       } else if (opt_.plain_sort) {
         plain[dual].push_back(id);

@@ -212,6 +212,27 @@ void failed_reblocking() {
   CHECK(relaid);
 }
 
+// A row limit that sorted groups cannot exceed any more than plain blocks can
+// keeps unsliced products in plain blocks; without it, products of more rows
+// than one plain block per CU holds go to groups.
+void row_limit() {
+  const LP wide(300, 70000, 200, 70000), tall(600, 530000, 900, 530000);
+  for (const int rows : {64, 256, 2048, 16384}) {
+    for (const LP* lp : {&wide, &tall}) {
+      stub::reset();
+      lp_options o = options();
+      o.slice_min_bytes = -1;
+      o.sort_rows = rows;
+      const lp_problem p = lp->problem();
+      lp_solver* s = nullptr;
+      CHECK(lp_create(&s, p.n, p.m_eq, 0, p.row_ptr, p.col_idx, p.val, p.c, p.rhs, p.lb, p.ub, 0, nullptr, &o) == LP_OK);
+      const bool groups = lp == &tall && rows > halp::kSortRowsPlain;
+      CHECK((stub::count("group_keys_kernel") > 0) == groups);
+      lp_destroy(s);
+    }
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -219,7 +240,8 @@ int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {{"failed_schedule", failed_schedule},
                                                       {"failed_admission", failed_admission},
                                                       {"failed_admission_frees_slots", failed_admission_frees_slots},
-                                                      {"failed_reblocking", failed_reblocking}};
+                                                      {"failed_reblocking", failed_reblocking},
+                                                      {"row_limit", row_limit}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());
