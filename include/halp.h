@@ -157,8 +157,8 @@ typedef struct {
                                2^(32 - log2 rows)).  Column-sorted plain blocks: blocks of
                                equal work of at most 2048 rows, at most 1024 / live LPs
                                of them per product (16..256) with at least 16..256 rows
-                               on average; engines re-block their running LPs as others
-                               finish.  Where every LP has at most 1024 rows on either
+                               on average, fewer where rows have more than 64 entries;
+                               engines re-block their running LPs as others finish.  Where every LP has at most 1024 rows on either
                                side and 8192 entries, each is one block per product and
                                steps in one workgroup (not with profile) */
   int plain_sort;           /* products neither sliced nor in sorted groups (those of

@@ -100,6 +100,8 @@ constexpr int kResEntries = 8;
 // Longest row of a column-sorted plain block; longer ones get a block of
 // their own (BK_LONG).
 constexpr int kSortedRowMax = 1 << 15;
+// Rows of more entries than this on average are cut into more blocks (plain_blocks)
+constexpr int kLongRows = 64;
 // Work of a block in entries: per row (its epilogue) and per block
 constexpr int kRowWeight = 4;
 constexpr int kBlockWeight = 256;

@@ -233,6 +233,33 @@ void row_limit() {
   }
 }
 
+// Few long rows are cut into blocks by their entries, short ones by the rows.
+void long_rows() {
+  const struct {
+    LP lp;
+    unsigned least, most;  // workgroups of K's product
+  } cases[] = {{LP(200, 50000, 2000, 50000), 180, 200},   // a row each
+               {LP(2000, 7000, 24, 7000), 100, 140},      // 16 rows each
+               {LP(3, 20000, 9000, 20000), 3, 3},
+               {LP(64, 3000, 128, 3000), 7, 9}};          // 1024 entries each
+  for (const auto& c : cases) {
+    stub::reset();
+    const lp_options o = options();
+    const lp_problem p = c.lp.problem();
+    lp_solver* s = nullptr;
+    unsigned grid = 0;
+    stub::on_launch = [&](const stub::Launch& l, void** a) {
+      if (l.name.find("sorted_step<double, true") == 0) grid = l.grid;
+      if (l.name.find("_step<double, true") == std::string::npos) return;
+      stub::arg<halp::IterArgs<double>>(a, 0).status_out[0] = halp::ST_OPTIMAL;
+    };
+    CHECK(lp_create(&s, p.n, p.m_eq, 0, p.row_ptr, p.col_idx, p.val, p.c, p.rhs, p.lb, p.ub, 0, nullptr, &o) == LP_OK);
+    CHECK(lp_solve(s, 1e-6, 1000, -1.0) == LP_OK);
+    CHECK(grid >= c.least && grid <= c.most);
+    lp_destroy(s);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -241,7 +268,8 @@ int main(int argc, char** argv) {
                                                       {"failed_admission", failed_admission},
                                                       {"failed_admission_frees_slots", failed_admission_frees_slots},
                                                       {"failed_reblocking", failed_reblocking},
-                                                      {"row_limit", row_limit}};
+                                                      {"row_limit", row_limit},
+                                                      {"long_rows", long_rows}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());
