@@ -1923,7 +1923,7 @@ int Engine<T>::group_lds_rows(bool dual) const {
 // Sorted groups of one LP's K (dual = true) or K^T over its row pointers hrp
 // on the host (space positions): about ngroups groups of equal work (entries
 // and rows), of at most cap rows and kSortEntries entries per slice on
-// average, each group's entries in nsl column slices, each (group, slice)
+// average, split where one slice holds most of them, each group's entries in nsl column slices, each (group, slice)
 // block's entries in column order with the row of the group packed beside the
 // column.  Built on the device from the row-major entries: keys, one stable
 // radix sort by block and column (rows of a column come in order), values.
@@ -1943,7 +1943,6 @@ void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int
   // average work, found by bisection (the work of rows 0 .. r - 1 is
   // hrp[r] - hrp[0] + r)
   std::vector<int32_t> gstart;
-  int64_t maxrows = 0;
   const double per = (double)(nnz + nrows) / (double)ngroups;
   const int64_t most_entries = (int64_t)kSortEntries * nsl;
   double bound = per;
@@ -1958,20 +1957,74 @@ void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int
       else lo = r + 1;
     }
     gstart.push_back((int32_t)start);
-    maxrows = std::max(maxrows, lo - start);
     start = lo;
   }
-  const int ng = (int)gstart.size(), nseg = ng * nsl;
   gstart.push_back((int32_t)nrows);
-  int rb = 0;
-  while (((int64_t)1 << rb) < maxrows) ++rb;
   const std::vector<Blk>& tiles = dual ? S.bD : S.bP;
   Blk* d_tiles = nullptr;
+  talloc(&d_tiles, (int64_t)tiles.size());
+  HIPCHECK(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(Blk) * tiles.size(), hipMemcpyHostToDevice, stream_));
+  // Where a group's entries crowd into few of its slices (a banded matrix), the
+  // blocks that hold them would be few and large: a group is split while a block
+  // of it holds more than 1.5 times the average of its slice's blocks (and
+  // kMinSplit) and of its group's.  A block that is large because its slice is
+  // (the slice's XCD has as much to do either way) or because of one long row
+  // (split rows 5% slower at 500k x 1M) is left.
+  const double groups0 = (double)gstart.size() - 1.0;
+  double most[kGroupSlices] = {0.0};
+  for (bool split = true; split;) {
+    const int n = (int)gstart.size() - 1;
+    int32_t *d_cut = nullptr, *d_cnt = nullptr;
+    talloc(&d_cut, n + 1);
+    talloc(&d_cnt, (int64_t)n * nsl);
+    HIPCHECK(hipMemcpyAsync(d_cut, gstart.data(), sizeof(int32_t) * gstart.size(), hipMemcpyHostToDevice, stream_));
+    HIPCHECK(hipMemsetAsync(d_cnt, 0, sizeof(int32_t) * n * nsl, stream_));
+    group_count_kernel<<<(unsigned)tiles.size(), kThreads, 0, stream_>>>(d_tiles, rp, ci, d_cut, n, r0, c0, len, nsl, d_cnt);
+    HIPCHECK(hipGetLastError());
+    std::vector<int32_t> cnt((size_t)n * nsl), cut;
+    HIPCHECK(hipMemcpyAsync(cnt.data(), d_cnt, sizeof(int32_t) * cnt.size(), hipMemcpyDeviceToHost, stream_));
+    HIPCHECK(hipStreamSynchronize(stream_));
+    dfree(d_cnt);
+    dfree(d_cut);
+    if (most[0] == 0.0) {
+      for (size_t i = 0; i < cnt.size(); ++i) most[i % nsl] += 1.5 / groups0 * (double)cnt[i];
+      for (double& v : most) v = std::max(v, (double)kMinSplit);
+    }
+    split = false;
+    for (int g = 0; g < n; ++g) {
+      const int64_t a = gstart[g], e = gstart[g + 1], total = (int64_t)hrp[e] - hrp[a];
+      int64_t parts = 1;
+      for (int q = 0; q < nsl; ++q) {
+        const int64_t full = cnt[(size_t)g * nsl + q];
+        if (2 * full * nsl > 3 * total) parts = std::max<int64_t>(parts, (int64_t)std::ceil((double)full / most[q]));
+      }
+      parts = std::min(parts, e - a);
+      cut.push_back((int32_t)a);
+      split |= parts > 1;
+      // parts of equal work, of at least a row each
+      for (int64_t k = 1; k < parts; ++k) {
+        const double at = (double)hrp[a] + (double)a + (double)((int64_t)hrp[e] - hrp[a] + e - a) * (double)k / (double)parts;
+        int64_t lo = (int64_t)cut.back() + 1, up = e - (parts - k);
+        while (lo < up) {
+          const int64_t r = (lo + up) >> 1;
+          if ((double)hrp[r] + (double)r < at) lo = r + 1;
+          else up = r;
+        }
+        cut.push_back((int32_t)lo);
+      }
+    }
+    cut.push_back((int32_t)nrows);
+    gstart.swap(cut);
+  }
+  const int ng = (int)gstart.size() - 1, nseg = ng * nsl;
+  int64_t maxrows = 0;
+  for (int g = 0; g < ng; ++g) maxrows = std::max<int64_t>(maxrows, gstart[g + 1] - gstart[g]);
+  int rb = 0;
+  while (((int64_t)1 << rb) < maxrows) ++rb;
   int32_t *d_g = nullptr, *d_off = nullptr, *src_in = nullptr, *src_out = nullptr;
   uint64_t *key_in = nullptr, *key_out = nullptr;
   T* v2 = nullptr;
   double* v642 = nullptr;
-  talloc(&d_tiles, (int64_t)tiles.size());
   talloc(&d_g, ng + 1);
   talloc(&d_off, nseg + 1);
   talloc(&key_in, nnz);
@@ -1980,7 +2033,6 @@ void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int
   talloc(&src_out, nnz);
   talloc(&v2, nnz);
   if (sizeof(T) != 8) talloc(&v642, nnz);
-  HIPCHECK(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(Blk) * tiles.size(), hipMemcpyHostToDevice, stream_));
   HIPCHECK(hipMemcpyAsync(d_g, gstart.data(), sizeof(int32_t) * gstart.size(), hipMemcpyHostToDevice, stream_));
   group_keys_kernel<<<(unsigned)tiles.size(), kThreads, 0, stream_>>>(d_tiles, rp, ci, d_g, ng, r0, S.nz0, c0, len, nsl,
                                                                       rb, key_in, src_in);
@@ -2173,6 +2225,11 @@ void Engine<T>::mark_streaming(const std::vector<int>& live, std::initializer_li
   }
 }
 
+// Blocks that have entries.
+static size_t with_entries(const std::vector<Blk>& v) {
+  return (size_t)std::count_if(v.begin(), v.end(), [](const Blk& b) { return b.pn > 0; });
+}
+
 template <class T>
 void Engine<T>::rebuild_schedules() {
   sched_dirty_ = true;  // until all of them are in place
@@ -2242,15 +2299,15 @@ void Engine<T>::rebuild_schedules() {
     ldsD_ = std::max(ldsD_, slots_[s2].rowsD);
   }
   // threads per sorted-group workgroup: the configured count, or 1024 where
-  // each CU has one workgroup, else enough for about eight waves per CU (the
+  // each CU has one workgroup (that has entries), else enough for about eight waves per CU (the
   // entries in flight are bound by the 32 KB of L1: more waves only queue)
   auto pick = [&](size_t nb) {
     if (opt_.group_threads > 0) return opt_.group_threads;
     if (nb <= (size_t)kCUs) return 1024;
     return (int64_t)kCUs * 8 * 64 / (int64_t)nb >= 512 ? 512 : 256;
   };
-  tpbP_ = pick(PS.size());
-  tpbD_ = pick(DS.size());
+  tpbP_ = pick(with_entries(PS));
+  tpbD_ = pick(with_entries(DS));
   auto words = [](const std::vector<Blk>& v) {
     int w = 1;
     for (const Blk& k : v)

@@ -74,10 +74,14 @@ __host__ __device__ constexpr int kPartRows(bool dual) { return dual ? 512 : 102
 // column (a space position) in rp_off.  The slice kernel adds a block's
 // products into LDS row sums (at most kSortRows rows per group) and writes
 // them as the group's slice-`slice` partial sums; the step kernel adds the
-// nsl partials of a row in slice order.  A block holds at most kSortEntries
-// entries.
+// nsl partials of a row in slice order.  A group holds at most kSortEntries
+// entries per slice on average, or one row; a block of one row at most 2^kSortColBits
+// entries, so that byte offsets into a block's values stay below 2^32.  Groups
+// whose entries crowd into few slices are split if a block holds more than
+// kMinSplit entries.
 constexpr int kSortRows = 16384;
 constexpr int kSortEntries = 1 << 18;
+constexpr int kMinSplit = 1 << 14;
 // Sorted-group products are cut into at least this many workgroups (about
 // one per CU); the engine gives each group as many rows as that allows.
 constexpr int kMinGroupBlocks = 240;

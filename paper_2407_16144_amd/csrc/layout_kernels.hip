@@ -154,6 +154,52 @@ __global__ void slice_scatter_kernel(const int32_t* rp, const int32_t* ci, const
   }
 }
 
+// cnt[g * nsl + q] += entries of group g (rows [gstart[g], gstart[g + 1]) of
+// the LP) in column slice q, over the row-major tiles: counted in LDS (a tile
+// has at most as many groups as rows), then added up.
+__global__ __launch_bounds__(kThreads) void group_count_kernel(const Blk* tiles, const int32_t* rp, const int32_t* ci,
+                                                               const int32_t* gstart, int ngroups, int64_t r0,
+                                                               int64_t c0, int64_t len, int nsl, int32_t* cnt) {
+  __shared__ int32_t s_rp[kMaxRows];
+  __shared__ int32_t s_g[kMaxRows];  // the row's group
+  __shared__ int32_t s_first[kGroupSlices + 1];
+  __shared__ int32_t s_cnt[kMaxRows * kGroupSlices];
+  const Blk b = tiles[blockIdx.x];
+  const int nrows = b.r1 - b.r0;
+  if (nrows == 0) return;
+  for (int r = threadIdx.x; r < nrows; r += kThreads) {
+    const int32_t row = (int32_t)(b.r0 + r - r0);
+    int lo = 0, up = ngroups - 1;  // the last group that starts at or before the row
+    while (lo < up) {
+      const int mid = (lo + up + 1) >> 1;
+      if (gstart[mid] <= row) lo = mid; else up = mid - 1;
+    }
+    s_rp[r] = rp[b.r0 + r];
+    s_g[r] = lo;
+  }
+  if ((int)threadIdx.x <= nsl) s_first[threadIdx.x] = (int32_t)((threadIdx.x * len + nsl - 1) / nsl);
+  __syncthreads();
+  const int g0 = s_g[0], words = (s_g[nrows - 1] - g0 + 1) * nsl;
+  for (int i = threadIdx.x; i < words; i += kThreads) s_cnt[i] = 0;
+  __syncthreads();
+#pragma unroll 4
+  for (int k = threadIdx.x; k < b.pn; k += kThreads) {
+    const int32_t e = b.p0 + k;
+    int lo = 0, up = words > nsl ? nrows - 1 : 0;  // (one group: any row of it)
+    while (lo < up) {
+      const int mid = (lo + up + 1) >> 1;
+      if (s_rp[mid] <= e) lo = mid; else up = mid - 1;
+    }
+    const int32_t c = (int32_t)(ci[e] - c0);
+    int q = 0;
+    for (int i = 1; i < nsl; ++i) q += c >= s_first[i];
+    atomicAdd(&s_cnt[(s_g[lo] - g0) * nsl + q], 1);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < words; i += kThreads)
+    if (s_cnt[i] > 0) atomicAdd(&cnt[(int64_t)g0 * nsl + i], s_cnt[i]);
+}
+
 // Sorted groups, step 1: for every entry of the row-major tiles, its
 // (group, slice) block in the high word of a 64-bit key, (column - first
 // column of the slice) << rb | (row - first row of the group) in the low word,

@@ -116,6 +116,13 @@ inline void run(const std::string& name, unsigned grid, void** a) {
               ((uint64_t)(g * nsl + q) << 32) | ((uint32_t)(c - first) << rb) | (uint32_t)(r - gs[g]);
           arg<int32_t*>(a, 12)[e - z0] = e;
         }
+  } else if (is("group_count_kernel")) {
+    const int32_t *rp = arg<const int32_t*>(a, 1), *ci = arg<const int32_t*>(a, 2), *gs = arg<const int32_t*>(a, 3);
+    const int64_t r0 = arg<int64_t>(a, 5), c0 = arg<int64_t>(a, 6), len = arg<int64_t>(a, 7);
+    const int ng = arg<int>(a, 4), nsl = arg<int>(a, 8);
+    for (int g = 0; g < ng; ++g)
+      for (int32_t e = rp[r0 + gs[g]]; e < rp[r0 + gs[g + 1]]; ++e)
+        ++arg<int32_t*>(a, 9)[(int64_t)g * nsl + (ci[e] - c0) * nsl / len];
   } else if (is("segment_offsets_kernel")) {
     const uint64_t* k = arg<const uint64_t*>(a, 0);
     for (int s = 0; s <= arg<int>(a, 2); ++s)

@@ -260,6 +260,50 @@ void long_rows() {
   }
 }
 
+// Groups whose entries crowd into one slice (a banded matrix) are split until no
+// block is left that is large for its slice; groups of evenly spread entries,
+// with one long row, or of a matrix with most entries in one slice are not.
+void crowded_slices() {
+  const int64_t m = 30000, n = 600000;
+  LP band(m, n, 40, 4000), even(m, n, 40, n), row(m, n, 10, n), left(m, n, 40, n / 8);
+  for (int64_t r = 0; r < m; ++r)  // all rows in the first slice
+    for (int32_t e = left.rp[r]; e < left.rp[r + 1]; ++e) left.ci[e] -= (int32_t)((n - n / 8) * r / (m - 1));
+  LP one(1, n, 500000, n);  // the long row takes the place of row 7
+  const int32_t add = one.rp[1] - (row.rp[8] - row.rp[7]);
+  row.ci.erase(row.ci.begin() + row.rp[7], row.ci.begin() + row.rp[8]);
+  row.ci.insert(row.ci.begin() + row.rp[7], one.ci.begin(), one.ci.end());
+  for (int64_t r = 8; r <= m; ++r) row.rp[r] += add;
+  row.val.assign(row.ci.size(), 1.0);
+  for (LP* lp : {&band, &even, &row, &left}) {
+    stub::reset();
+    const lp_options o = options();
+    const lp_problem p = lp->problem();
+    size_t counts = 0;
+    std::vector<halp::Blk> blocks;
+    stub::on_launch = [&](const stub::Launch& l, void** a) {
+      if (l.name.find("group_count_kernel") == 0 && stub::arg<int64_t>(a, 7) == n) ++counts;
+      if (l.name.find("sorted_group_step<double, true") == 0) {
+        const auto& A = stub::arg<halp::IterArgs<double>>(a, 0);
+        blocks.assign(A.schedDS, A.schedDS + l.grid);
+      }
+      if (l.name.find("part_step<double, true") != std::string::npos)
+        stub::arg<halp::IterArgs<double>>(a, 0).status_out[0] = halp::ST_OPTIMAL;
+    };
+    lp_solver* s = nullptr;
+    CHECK(lp_create(&s, p.n, p.m_eq, 0, p.row_ptr, p.col_idx, p.val, p.c, p.rhs, p.lb, p.ub, 0, nullptr, &o) == LP_OK);
+    CHECK(lp_solve(s, 1e-6, 1000, -1.0) == LP_OK);
+    int64_t nnz = 0, largest = 0, rows = 0;
+    for (const halp::Blk& b : blocks) {
+      nnz += b.pn;
+      if (halp::blk_slice(b) == 0) rows += b.r1 - b.r0;
+      largest = std::max<int64_t>(largest, b.pn);
+    }
+    CHECK(nnz == (int64_t)lp->ci.size() && rows == m);
+    CHECK(lp == &band ? counts > 1 && largest <= 1 << 14 : counts == 1 && blocks.size() <= 8 * 33);
+    lp_destroy(s);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -269,7 +313,8 @@ int main(int argc, char** argv) {
                                                       {"failed_admission_frees_slots", failed_admission_frees_slots},
                                                       {"failed_reblocking", failed_reblocking},
                                                       {"row_limit", row_limit},
-                                                      {"long_rows", long_rows}};
+                                                      {"long_rows", long_rows},
+                                                      {"crowded_slices", crowded_slices}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());

@@ -1,0 +1,75 @@
+"""Layouts of the step kernels that depend on how a matrix's entries are
+spread: sorted groups split because their entries crowd into few column
+slices, and blocks cut by the entries of few long rows.  Each trajectory
+agrees with the oracle's at the same step size to 1e-10, the bound of the
+other FP64 trajectory tests (both sides round the same sums in another
+order)."""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+import lpgen
+import oracle
+from oracle import core
+
+pytestmark = pytest.mark.gpu
+
+halp = pytest.importorskip("paper_2407_16144_amd")
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+
+def _lp(rows, cols, m, n, seed):
+    rng = np.random.default_rng(seed)
+    a = sp.csr_matrix((rng.standard_normal(rows.size), (rows, cols)), shape=(m, n))
+    a.sum_duplicates()
+    a.sort_indices()
+    m_eq = (3 * m) // 4
+    kx = a @ rng.uniform(1.0, 9.0, n)
+    rhs = np.concatenate([kx[:m_eq], kx[m_eq:] - rng.uniform(0.0, 1.0, m - m_eq)])
+    return lpgen.LP(n, m_eq, m - m_eq, a.indptr.astype(np.int32), a.indices.astype(np.int32), a.data,
+                    rng.standard_normal(n), rhs, np.zeros(n), np.full(n, 10.0))
+
+
+def _band(m, n, per_row, width, seed):
+    """Columns within `width` of the diagonal."""
+    rng = np.random.default_rng(seed)
+    rows = np.repeat(np.arange(m), per_row)
+    cols = np.clip(rows * n // m + rng.integers(-width // 2, width // 2, rows.size), 0, n - 1)
+    return _lp(rows, cols, m, n, seed + 1)
+
+
+def _uniform(lens, n, seed):
+    rng = np.random.default_rng(seed)
+    rows = np.repeat(np.arange(len(lens)), lens)
+    return _lp(rows, rng.integers(0, n, rows.size), len(lens), n, seed + 1)
+
+
+CASES = {
+    # 8 slices whatever the width: a group's entries lie in one or two of them
+    "banded groups": (lambda: _band(20000, 40000, 40, 400, 1), dict(slice_min_bytes=0)),
+    "banded groups in one pair of slices": (lambda: _band(40000, 20000, 30, 16000, 2), dict(slice_min_bytes=0)),
+    "few long rows": (lambda: _uniform([1500] * 150 + [5000, 30000], 60000, 3), {}),
+    "few long columns": (lambda: _uniform([12] * 20000, 150, 4), {}),
+}
+
+
+def _agrees(got, ref):
+    for a, b in zip(got, ref):
+        floor = max(1e-2 * float(np.max(np.abs(b))), 1e-300)
+        assert float(np.max(np.abs(a - b) / np.maximum(np.abs(b), floor))) <= 1e-10
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_trajectory(name):
+    make, options = CASES[name]
+    lp = make()
+    print(f"case layout {name} m={lp.m} n={lp.n} nnz={lp.nnz}", flush=True)
+    P = core.scaled_problem(lp)
+    s, _ = oracle.power_iteration(P.K, 0, max_iters=30)
+    eta = 0.9 / s
+    res, x, y, _ = halp.solve_lp(lp, tol=0.0, max_iter=130, opt=halp.lp_default_options(eta=eta, **options))
+    ref = oracle.solve(lp, oracle.Options(tol=0.0, max_iter=130, eta=eta))
+    assert res["iters"] == ref.iters and res["restarts"] == ref.restarts
+    _agrees((x, y), (ref.x, ref.y))
