@@ -76,8 +76,8 @@ class RangeAlloc {
 // ---------------------------------------------------------------------------
 // device memory
 //
-// Every buffer of an engine comes from dalloc or, where it lives only while
-// LPs are added or laid out anew, from talloc.  Normally dalloc is hipMalloc;
+// Every buffer of an engine comes from dalloc or, where it lives only for a
+// call, from talloc.  Normally dalloc is hipMalloc;
 // inside a WorkspaceScope (the allocation-free entry point) the buffers are
 // carved out of `scratch`, a static device array, by a stack allocator: a
 // freed block is reclaimed once every block above it is freed too (the
@@ -102,6 +102,7 @@ struct Workspace {
   size_t size = 0, used = 0, peak = 0;
   hipStream_t stream = nullptr;
   std::vector<std::pair<size_t, bool>> blocks;  // (offset, freed) in allocation order
+  std::vector<void*> extra;  // of a TempScope: blocks that did not fit its memory
 
   bool fits(size_t b) const { return b <= size - used; }
   char* take(size_t b) {
@@ -168,40 +169,59 @@ static void dalloc(P** p, int64_t count) {
   if (e != hipSuccess) throw Error(-2, std::string("device allocation failed: ") + hipGetErrorString(e));
 }
 
-// temporaries of add() and reblock_for()
+// temporaries of a call (TempScope)
 template <class P>
 static void talloc(P** p, int64_t count) {
   const size_t b = aligned_bytes(sizeof(P) * (size_t)std::max<int64_t>(count, 1));
-  if (t_temp && t_temp->fits(b)) *p = (P*)t_temp->take(b);
-  else dalloc(p, count);
+  if (t_temp && t_temp->fits(b)) {
+    *p = (P*)t_temp->take(b);
+  } else if (t_temp) {
+    t_temp->extra.push_back(nullptr);
+    dalloc(p, count);
+    t_temp->extra.back() = (void*)*p;
+  } else {
+    dalloc(p, count);
+  }
 }
 
 template <class P>
 static void dfree(P*& p) {
-  if (p && !(t_ws && t_ws->give_back((void*)p)) && !(t_temp && t_temp->give_back((void*)p))) (void)hipFree((void*)p);
+  if (p && !(t_ws && t_ws->give_back((void*)p)) && !(t_temp && t_temp->give_back((void*)p))) {
+    if (t_temp) {
+      auto& extra = t_temp->extra;
+      extra.erase(std::remove(extra.begin(), extra.end(), (void*)p), extra.end());
+    }
+    (void)hipFree((void*)p);
+  }
   p = nullptr;
 }
 
-// Gives talloc `bytes` of device memory on this thread while it lives.  If
-// they cannot be had in one piece (or inside another scope or a
-// WorkspaceScope) talloc allocates block by block.
+// While it lives, what talloc takes on this thread is freed with it at the
+// latest, also where an exception passes by, and comes out of the memory that
+// reserve() got.  If that cannot be had in one piece (or inside another scope or
+// a WorkspaceScope) talloc allocates block by block.
 class TempScope {
  public:
-  explicit TempScope(size_t bytes) {
+  explicit TempScope(size_t bytes = 0) {
     if (t_ws || t_temp) return;
+    t_temp = &w_;
+    reserve(bytes);
+  }
+  ~TempScope() {
+    if (t_temp != &w_) return;
+    t_temp = nullptr;
+    for (void* p : w_.extra) (void)hipFree(p);
+    (void)hipFree(w_.base);
+  }
+  void reserve(size_t bytes) {
     void* p = nullptr;
+    if (t_temp != &w_ || bytes == 0) return;
     if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return;
     }
     w_.base = (char*)p;
     w_.size = bytes;
-    t_temp = &w_;
-  }
-  ~TempScope() {
-    if (!w_.base) return;
-    t_temp = nullptr;
-    (void)hipFree(w_.base);
   }
   TempScope(const TempScope&) = delete;
   TempScope& operator=(const TempScope&) = delete;
@@ -929,9 +949,9 @@ void Engine<T>::validate_device(const std::vector<Problem>& probs, std::vector<i
   std::vector<int> flags;
   if (!in.empty()) {
     const int64_t most = (int64_t)in.size();
-    dalloc(&d_in, most);
-    dalloc(&d_ends, most);
-    dalloc(&d_flags, most);
+    talloc(&d_in, most);
+    talloc(&d_ends, most);
+    talloc(&d_flags, most);
     HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(LpInput) * in.size(), hipMemcpyHostToDevice, stream_));
     HIPCHECK(hipStreamSynchronize(stream_));
     // on the null stream, after the caller's work there that may still write the inputs
@@ -1022,6 +1042,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
   constexpr int NB = Tile<T>::NB;
   std::vector<int> ids;
   HIPCHECK(hipStreamSynchronize(stream_));
+  TempScope temp;
   // 1. validate and reserve
   std::vector<HostCSR> canon(probs.size());
   std::vector<char> use_canon(probs.size(), 0);
@@ -1098,7 +1119,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     total_nz += slots_[id].nnz;
     largest_nz = std::max(largest_nz, slots_[id].nnz);
   }
-  TempScope temp(std::max(kTransposeBytes * total_nz, temp_bytes(std::max(largest_nz, std::min(total_nz, kSortRun)))));
+  temp.reserve(std::max(kTransposeBytes * total_nz, temp_bytes(std::max(largest_nz, std::min(total_nz, kSortRun)))));
   // 2. upload (K values in FP64, row pointers / columns shifted to space positions)
   std::vector<std::vector<int32_t>> host_rp(probs.size());
   for (size_t k = 0; k < probs.size() && !on_device; ++k) {
@@ -2147,10 +2168,11 @@ void Engine<T>::set_params(const std::vector<int>& ids, double tol, const std::v
     slots_[ids[k]].watched = true;
     slots_[ids[k]].reported = false;
   }
+  TempScope temp;
   InstState* d_src = nullptr;
   int* d_ids = nullptr;
-  dalloc(&d_src, ni);
-  dalloc(&d_ids, ni);
+  talloc(&d_src, ni);
+  talloc(&d_ids, ni);
   HIPCHECK(hipMemcpyAsync(d_src, cur.data(), sizeof(InstState) * ni, hipMemcpyHostToDevice, stream_));
   HIPCHECK(hipMemcpyAsync(d_ids, ids.data(), sizeof(int) * ni, hipMemcpyHostToDevice, stream_));
   write_states_kernel<<<nblk(ni), 256, 0, stream_>>>(d_st, d_status, d_cnt, d_ids, d_src, ni);
@@ -2365,10 +2387,11 @@ void Engine<T>::rebuild_schedules() {
   grow(partP, cap_partP_, gP, kNS);
   grow(partD, cap_partD_, gD, kNS);
   if (!live.empty()) {
+    TempScope temp;
     int* d_ids = nullptr;
     int4* d_rg = nullptr;
-    dalloc(&d_ids, (int64_t)live.size());
-    dalloc(&d_rg, (int64_t)live.size());
+    talloc(&d_ids, (int64_t)live.size());
+    talloc(&d_rg, (int64_t)live.size());
     HIPCHECK(hipMemcpyAsync(d_ids, live.data(), sizeof(int) * live.size(), hipMemcpyHostToDevice, stream_));
     HIPCHECK(hipMemcpyAsync(d_rg, rg.data(), sizeof(int4) * rg.size(), hipMemcpyHostToDevice, stream_));
     set_ranges_kernel<<<nblk((int64_t)live.size()), 256, 0, stream_>>>(d_st, d_ids, d_rg, (int)live.size());
@@ -2708,8 +2731,9 @@ void Engine<T>::take_over(const EngineBase& src, const std::vector<int>& src_ids
     largest = std::max({largest, S.m, S.n});
   }
   if (in.empty()) return;
+  TempScope temp;
   HandOver* d_in = nullptr;
-  dalloc(&d_in, (int64_t)in.size());
+  talloc(&d_in, (int64_t)in.size());
   HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(HandOver) * in.size(), hipMemcpyHostToDevice, stream_));
   const int parts = parts_for(largest, in.size());
   take_over_kernel<T><<<(unsigned)(in.size() * parts), kThreads, 0, stream_>>>(d_in, parts, d_st, x, x0, y, y0);
@@ -2744,8 +2768,9 @@ void Engine<T>::certificate(int id, double* ray, bool to_device) {
     throw Error(-4, "no certificate: the LP was not found infeasible");
   const bool primal = s.status == ST_PRIMAL_INFEAS;
   const int64_t len = primal ? S.m : S.n;
+  TempScope temp;
   double* tmp = nullptr;
-  dalloc(&tmp, len);
+  talloc(&tmp, len);
   if (primal)
     unscale_kernel<T><<<nblk(len), 256, 0, stream_>>>(s.ray == 1 ? cy1 : cy2, Dr, S.row0, len, tmp);
   else
@@ -2785,10 +2810,11 @@ void Engine<T>::import_point(int id, const double* xi, const double* yi, double 
     st.tau = st.eta / omega;
     st.sigma = st.eta * omega;
   }
+  TempScope temp;
   InstState* d_src = nullptr;
   int* d_ids = nullptr;
-  dalloc(&d_src, 1);
-  dalloc(&d_ids, 1);
+  talloc(&d_src, 1);
+  talloc(&d_ids, 1);
   HIPCHECK(hipMemcpyAsync(d_src, &st, sizeof(InstState), hipMemcpyHostToDevice, stream_));
   HIPCHECK(hipMemcpyAsync(d_ids, &id, sizeof(int), hipMemcpyHostToDevice, stream_));
   write_states_kernel<<<1, 256, 0, stream_>>>(d_st, d_status, d_cnt, d_ids, d_src, 1);
@@ -2822,8 +2848,9 @@ void Engine<T>::stored_matrix(int id, bool transpose, int32_t* rp, int32_t* ci, 
 
 int narrow_row_ptr(const int64_t* src, int32_t* dst, int64_t count, hipStream_t stream) {
   if (count <= 0) return 0;
+  TempScope temp;
   int* d_bad = nullptr;
-  dalloc(&d_bad, 1);
+  talloc(&d_bad, 1);
   HIPCHECK(hipMemsetAsync(d_bad, 0, sizeof(int), stream));
   narrow_row_ptr_kernel<<<nblk(count), 256, 0, stream>>>(src, dst, count, d_bad);
   HIPCHECK(hipGetLastError());

@@ -1,7 +1,7 @@
 // The HIP runtime calls that the library makes, on host memory, for CPU tests
 // of its host code (linked in place of the HIP runtime).  A kernel launch is
-// recorded by name; the kernels that lay out matrices run as plain loops, all
-// others do nothing (every LP then stays "running").  A device allocation can
+// recorded by name; those that load, lay out and start LPs run as plain loops, all
+// others do nothing (an LP then runs until a limit ends it).  A device allocation can
 // be made to fail.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -74,11 +74,32 @@ void radix_scatter(void** a) {
   }
 }
 
-// The kernels that lay out matrices.
+// The kernels that load, lay out and start LPs.
 inline void run(const std::string& name, unsigned grid, void** a) {
   using halp::Blk;
   auto is = [&](const char* k) { return name.compare(0, strlen(k), k) == 0; };
-  if (is("shift_copy_kernel")) {
+  if (is("row_ends_kernel")) {
+    for (int k = 0; k < arg<int>(a, 1); ++k) {
+      const halp::LpInput& p = arg<const halp::LpInput*>(a, 0)[k];
+      arg<int2*>(a, 2)[k] = make_int2(p.rp[0], p.rp[p.m]);
+    }
+  } else if (is("load_lps_kernel")) {
+    for (unsigned k = 0; k < grid / arg<int>(a, 1); ++k) {
+      const halp::LpInput& p = arg<const halp::LpInput*>(a, 0)[k];
+      for (int64_t r = 0; r <= p.m; ++r) arg<int32_t*>(a, 2)[p.row0 + r] = (int32_t)(p.rp[r] + p.nz0);
+      for (int64_t e = 0; e < p.nnz; ++e) arg<int32_t*>(a, 3)[p.nz0 + e] = (int32_t)(p.ci[e] + p.col0);
+    }
+  } else if (is("write_states_kernel")) {
+    for (int i = 0; i < arg<int>(a, 5); ++i) {
+      const int id = arg<const int*>(a, 3)[i];
+      arg<halp::InstState*>(a, 0)[id] = arg<const halp::InstState*>(a, 4)[i];
+      arg<int*>(a, 1)[id] = arg<const halp::InstState*>(a, 4)[i].status;
+    }
+  } else if (is("set_limit_status_kernel")) {
+    for (int i = 0; i < arg<int>(a, 2); ++i)
+      if (arg<halp::InstState*>(a, 0)[i].status == halp::ST_RUNNING)
+        arg<halp::InstState*>(a, 0)[i].status = arg<int*>(a, 1)[i] = arg<int>(a, 3);
+  } else if (is("shift_copy_kernel")) {
     for (int64_t i = 0; i < arg<int64_t>(a, 2); ++i)
       arg<int32_t*>(a, 0)[i] = (int32_t)(arg<const int32_t*>(a, 1)[i] + arg<int64_t>(a, 3));
   } else if (is("iota_kernel")) {
@@ -144,6 +165,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
+  if (!p) return hipSuccess;
   auto it = stub::memory.find(p);
   if (it == stub::memory.end()) {
     fprintf(stderr, "release of memory that was not allocated\n");

@@ -52,6 +52,13 @@ lp_options options() {
   return o;
 }
 
+// LP i reaches its tolerance in this step.
+void finish(void** args, int i) {
+  const auto& A = stub::arg<halp::IterArgs<double>>(args, 0);
+  A.st[i].status = A.status_out[i] = halp::ST_OPTIMAL;
+  A.st[i].checks = 1;
+}
+
 size_t step_kernels(size_t from) {
   return stub::count("_step<double", from) + stub::count("resident_steps", from);
 }
@@ -159,8 +166,9 @@ void failed_admission_frees_slots() {
       stub::fail_at = -1;
       failures += failed;
       CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued + live == 2);
+      const bool again = queued == 1;  // (else the LP is admitted, without its limits)
       CHECK(lp_server_step(s, 1, nullptr) == LP_OK);
-      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 0 && live == 2);
+      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 0 && (!again || live == 2));
       lp_server_destroy(s);
     }
     CHECK(failures > 0);
@@ -185,14 +193,13 @@ void failed_reblocking() {
     size_t from = 0;
     stub::on_launch = [&](const stub::Launch& l, void** a) {
       if (l.name.find("sorted_step<double, true") == std::string::npos) return;
-      const auto& A = stub::arg<halp::IterArgs<double>>(a, 0);
       if (++steps == 64) {  // all but three finish in the first chunk
-        for (int i = 3; i < 40; ++i) A.status_out[i] = halp::ST_OPTIMAL;
+        for (int i = 3; i < 40; ++i) finish(a, i);
         from = stub::launches.size();
         stub::fail_at = n;
       }
       if (steps > 64 * 40)  // the rest finish later
-        for (int i = 0; i < 3; ++i) A.status_out[i] = halp::ST_OPTIMAL;
+        for (int i = 0; i < 3; ++i) finish(a, i);
     };
     const int rc = lp_batch_solve(h, 1e-6, 1000, -1.0);
     failed = rc != LP_OK;
@@ -250,8 +257,7 @@ void long_rows() {
     unsigned grid = 0;
     stub::on_launch = [&](const stub::Launch& l, void** a) {
       if (l.name.find("sorted_step<double, true") == 0) grid = l.grid;
-      if (l.name.find("_step<double, true") == std::string::npos) return;
-      stub::arg<halp::IterArgs<double>>(a, 0).status_out[0] = halp::ST_OPTIMAL;
+      if (l.name.find("_step<double, true") != std::string::npos) finish(a, 0);
     };
     CHECK(lp_create(&s, p.n, p.m_eq, 0, p.row_ptr, p.col_idx, p.val, p.c, p.rhs, p.lb, p.ub, 0, nullptr, &o) == LP_OK);
     CHECK(lp_solve(s, 1e-6, 1000, -1.0) == LP_OK);
@@ -286,8 +292,7 @@ void crowded_slices() {
         const auto& A = stub::arg<halp::IterArgs<double>>(a, 0);
         blocks.assign(A.schedDS, A.schedDS + l.grid);
       }
-      if (l.name.find("part_step<double, true") != std::string::npos)
-        stub::arg<halp::IterArgs<double>>(a, 0).status_out[0] = halp::ST_OPTIMAL;
+      if (l.name.find("part_step<double, true") != std::string::npos) finish(a, 0);
     };
     lp_solver* s = nullptr;
     CHECK(lp_create(&s, p.n, p.m_eq, 0, p.row_ptr, p.col_idx, p.val, p.c, p.rhs, p.lb, p.ub, 0, nullptr, &o) == LP_OK);
@@ -304,6 +309,40 @@ void crowded_slices() {
   }
 }
 
+// Memory runs out after n allocations of a creation or a solve, for every n:
+// nothing is left allocated.
+void failed_creation() {
+  const LP lps[] = {LP(40, 60, 5, 60), LP(3000, 5000, 8, 5000), LP(6000, 300000, 8, 300000)};
+  std::vector<lp_problem> ps;
+  for (const LP& lp : lps) ps.push_back(lp.problem());
+  for (const int device : {0, 1}) {
+    for (const int sorted : {1, 0}) {
+      for (const double eta : {0.1, 0.0}) {
+        for (const int precision : {LP_PREC_FP64, LP_PREC_FP32}) {
+          lp_options o = options();
+          o.plain_sort = o.slice_sort = sorted;
+          o.eta = eta;
+          o.precision = precision;
+          o.power_max_iters = 8;
+          bool failed = true;
+          for (long n = 0; failed; ++n) {
+            stub::reset();
+            const size_t before = stub::bytes;
+            stub::fail_at = n;
+            lp_batch* h = nullptr;
+            int rc = lp_batch_create(&h, 3, ps.data(), device, nullptr, &o);
+            if (rc == LP_OK) rc = lp_batch_solve(h, 1e-6, 100, 0.0);
+            failed = rc != LP_OK;
+            CHECK(rc == LP_OK || rc == LP_ERR_OOM);
+            if (h) lp_batch_destroy(h);
+            CHECK(stub::bytes == before);
+          }
+        }
+      }
+    }
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -314,7 +353,8 @@ int main(int argc, char** argv) {
                                                       {"failed_reblocking", failed_reblocking},
                                                       {"row_limit", row_limit},
                                                       {"long_rows", long_rows},
-                                                      {"crowded_slices", crowded_slices}};
+                                                      {"crowded_slices", crowded_slices},
+                                                      {"failed_creation", failed_creation}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());
