@@ -166,6 +166,14 @@ static void dalloc(P** p, int64_t count) {
     return;
   }
   hipError_t e = hipMalloc((void**)p, sizeof(P) * (size_t)count);
+  if (e != hipSuccess && t_temp && t_temp->base && t_temp->used == 0) {
+    // the thread's temporary memory is not in use just now
+    (void)hipGetLastError();
+    (void)hipFree(t_temp->base);
+    t_temp->base = nullptr;
+    t_temp->size = 0;
+    e = hipMalloc((void**)p, sizeof(P) * (size_t)count);
+  }
   if (e != hipSuccess) throw Error(-2, std::string("device allocation failed: ") + hipGetErrorString(e));
 }
 
@@ -199,7 +207,8 @@ static void dfree(P*& p) {
 // While it lives, what talloc takes on this thread is freed with it at the
 // latest, also where an exception passes by, and comes out of the memory that
 // reserve() got.  If that cannot be had in one piece (or inside another scope or
-// a WorkspaceScope) talloc allocates block by block.
+// a WorkspaceScope) talloc allocates block by block; so it does once dalloc has
+// found no memory left and taken that back.
 class TempScope {
  public:
   explicit TempScope(size_t bytes = 0) {

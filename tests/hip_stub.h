@@ -35,13 +35,14 @@ inline std::map<const void*, std::string>& kernels() {
 }
 inline std::vector<Launch> launches;
 inline std::map<void*, size_t> memory;
-inline size_t bytes = 0, peak = 0, limit = SIZE_MAX;
+inline std::vector<size_t> sizes;  // of the allocations made
+inline size_t bytes = 0, limit = SIZE_MAX;
 inline long fail_at = -1;  // >= 0: after so many device allocations all fail
 inline std::function<void(const Launch&, void**)> on_launch;
 
 inline void reset() {
   launches.clear();
-  peak = bytes;
+  sizes.clear();
   limit = SIZE_MAX;
   fail_at = -1;
   on_launch = nullptr;
@@ -161,7 +162,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   *p = calloc(std::max<size_t>(n, 1), 1);
   stub::memory[*p] = n;
   stub::bytes += n;
-  stub::peak = std::max(stub::peak, stub::bytes);
+  stub::sizes.push_back(n);
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {

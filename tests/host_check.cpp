@@ -343,6 +343,28 @@ void failed_creation() {
   }
 }
 
+// The temporary memory of a creation is in nobody's way: where there is no room
+// for it beside the partial sums of sliced products, it makes room.
+void least_memory_partials() {
+  const LP lp(300000, 600000, 2, 600000);
+  const lp_options o = options();
+  const lp_problem p = lp.problem();
+  lp_solver* s = nullptr;
+  size_t limit = SIZE_MAX;
+  for (const bool tight : {false, true}) {
+    stub::reset();
+    stub::limit = limit;
+    CHECK(lp_create(&s, p.n, p.m_eq, 0, p.row_ptr, p.col_idx, p.val, p.c, p.rhs, p.lb, p.ub, 0, nullptr, &o) == LP_OK);
+    if (!tight) {
+      // the engine, the temporary memory, the partial sums of K and of K^T
+      CHECK(stub::sizes.size() >= 4 && stub::sizes[1] >= 29 * lp.ci.size());
+      limit = stub::sizes[0] + stub::sizes[2] + std::max(stub::sizes[1], stub::sizes[3]) + 4096;
+      CHECK(limit < stub::sizes[0] + stub::sizes[1] + stub::sizes[2] + stub::sizes[3]);
+    }
+    lp_destroy(s);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -354,7 +376,8 @@ int main(int argc, char** argv) {
                                                       {"row_limit", row_limit},
                                                       {"long_rows", long_rows},
                                                       {"crowded_slices", crowded_slices},
-                                                      {"failed_creation", failed_creation}};
+                                                      {"failed_creation", failed_creation},
+                                                      {"least_memory_partials", least_memory_partials}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());
