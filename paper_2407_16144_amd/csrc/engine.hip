@@ -222,15 +222,16 @@ class TempScope {
     for (void* p : w_.extra) (void)hipFree(p);
     (void)hipFree(w_.base);
   }
-  void reserve(size_t bytes) {
+  bool reserve(size_t bytes) {
     void* p = nullptr;
-    if (t_temp != &w_ || bytes == 0) return;
+    if (t_temp != &w_ || bytes == 0) return false;
     if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
-      return;
+      return false;
     }
     w_.base = (char*)p;
     w_.size = bytes;
+    return true;
   }
   TempScope(const TempScope&) = delete;
   TempScope& operator=(const TempScope&) = delete;
@@ -1128,7 +1129,14 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     total_nz += slots_[id].nnz;
     largest_nz = std::max(largest_nz, slots_[id].nnz);
   }
-  temp.reserve(std::max(kTransposeBytes * total_nz, temp_bytes(std::max(largest_nz, std::min(total_nz, kSortRun)))));
+  // the LPs' blocks are sorted together, or, where memory is short, in runs that
+  // take no more than the transpose and the largest LP do
+  const int64_t least = std::max(kTransposeBytes * total_nz, temp_bytes(largest_nz));
+  int64_t sort_run = kSortRun;
+  if (!temp.reserve(std::max(least, temp_bytes(std::min(total_nz, kSortRun))))) {
+    sort_run = std::min(kSortRun, (least - temp_bytes(0)) / (temp_bytes(1) - temp_bytes(0)));
+    temp.reserve(least);
+  }
   // 2. upload (K values in FP64, row pointers / columns shifted to space positions)
   std::vector<std::vector<int32_t>> host_rp(probs.size());
   for (size_t k = 0; k < probs.size() && !on_device; ++k) {
@@ -1269,7 +1277,7 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     recut(single, maxb, minr, false);
   }
   for (const bool dual : {true, false})
-    sort_blocks(plain[dual], dual, plain_rp[dual], maxb, minr, false, kSortRun);
+    sort_blocks(plain[dual], dual, plain_rp[dual], maxb, minr, false, sort_run);
   if (running > 0) power_iterate(ids, running);
   finish_states(ids, norms);
   for (auto& [id, dual] : sliced) slice_matrix(id, dual);

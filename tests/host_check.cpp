@@ -365,6 +365,36 @@ void least_memory_partials() {
   }
 }
 
+// A batch needs no more memory to be sorted together than its transpose and
+// its largest LP need: with less than the whole sort takes it is sorted in runs.
+void least_memory_batch() {
+  std::vector<LP> lps;
+  std::vector<lp_problem> ps;
+  size_t nnz = 0, largest = 0;
+  for (int i = 0; i < 20; ++i) lps.emplace_back(2000 + 10 * i, 7000, 20, 7000, i);
+  for (const LP& lp : lps) {
+    ps.push_back(lp.problem());
+    nnz += lp.ci.size();
+    largest = std::max(largest, lp.ci.size());
+  }
+  for (const int precision : {LP_PREC_FP64, LP_PREC_FP32}) {
+    lp_options o = options();
+    o.precision = precision;
+    size_t limit = SIZE_MAX, sorts[2];
+    for (const bool tight : {false, true}) {
+      stub::reset();
+      stub::limit = limit;
+      lp_batch* h = nullptr;
+      CHECK(lp_batch_create(&h, (int)ps.size(), ps.data(), 0, nullptr, &o) == LP_OK);
+      sorts[tight] = stub::count("block_keys_kernel");
+      // the engine, the temporary memory, and a little for what is small
+      if (!tight) limit = stub::sizes[0] + std::max(29 * nnz, 49 * largest + (1 << 18)) + 65536;
+      lp_batch_destroy(h);
+    }
+    CHECK(sorts[0] == 2 && sorts[1] > 2 && sorts[1] <= 8);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -377,7 +407,8 @@ int main(int argc, char** argv) {
                                                       {"long_rows", long_rows},
                                                       {"crowded_slices", crowded_slices},
                                                       {"failed_creation", failed_creation},
-                                                      {"least_memory_partials", least_memory_partials}};
+                                                      {"least_memory_partials", least_memory_partials},
+                                                      {"least_memory_batch", least_memory_batch}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());
