@@ -776,8 +776,8 @@ halp::Problem request_problem(const Request& r) {
 // per stored entry as the engine allocates them; `staging`: plus the FP64
 // phase's staging of one candidate, 8 bytes per row and variable), one
 // quarter for the transient buffers of an admission (transpose and layout
-// sorts, about kAdmitBytesPerEntry per stored entry of the LPs admitted in
-// one step).  Servers never column-slice a product, so no slice partial
+// sorts of the LPs admitted in one step together, at most kAdmitBytesPerEntry
+// per stored entry: 45, and lists of blocks).  Servers never column-slice a product, so no slice partial
 // sums are allocated.
 constexpr int64_t kAdmitBytesPerEntry = 48;
 

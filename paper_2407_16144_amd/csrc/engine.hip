@@ -401,8 +401,7 @@ static void plain_shape(int64_t live, int64_t* max_blocks, int64_t* min_rows) {
   *min_rows = std::max<int64_t>(16, std::min<int64_t>(256, 8 * live));
 }
 
-// Entries that one sort of plain blocks takes together at most (48 bytes of
-// temporary memory each).
+// Entries that one sort of plain blocks takes together at most (temp_bytes).
 constexpr int64_t kSortRun = 1 << 26;
 // temporary memory per entry of a transpose and its radix sort
 constexpr int64_t kTransposeBytes = 29;
@@ -558,7 +557,8 @@ class Engine final : public EngineBase {
   void recut(const std::vector<int>& ids, int64_t max_blocks, int64_t min_rows, bool solo);
   // temporary memory of a sort of nnz entries into blocks: keys and positions
   // twice over and once more for the radix sort, its counts, and the values
-  static int64_t temp_bytes(int64_t nnz) { return (sizeof(T) == 8 ? 45 : 49) * nnz + (1 << 18); }
+  // (44.5 bytes per entry; lists of blocks take the rest)
+  static int64_t temp_bytes(int64_t nnz) { return 45 * nnz + (1 << 14); }
   std::vector<Blk> cut_blocks(int id, bool dual, const int32_t* rp, int64_t max_blocks, int64_t min_rows, int* rb,
                               int* cb) const;
   void sort_blocks(const std::vector<int>& ids, bool dual, const std::vector<const int32_t*>& rps, int64_t max_blocks,
@@ -1862,8 +1862,7 @@ void Engine<T>::sort_blocks(const std::vector<int>& ids, bool dual, const std::v
     int2* d_where = nullptr;
     int32_t *src_in = nullptr, *src_out = nullptr;
     uint64_t *key_in = nullptr, *key_out = nullptr;
-    T* v_tmp = nullptr;
-    double* v64_tmp = nullptr;
+    double* v_tmp = nullptr;
     const unsigned nall = (unsigned)all.size(), nseg = (unsigned)sorted.size();
     talloc(&d_all, nall);
     talloc(&d_blk, nseg);
@@ -1872,7 +1871,6 @@ void Engine<T>::sort_blocks(const std::vector<int>& ids, bool dual, const std::v
     talloc(&src_in, total);
     talloc(&src_out, total);
     talloc(&v_tmp, total);
-    if (sizeof(T) != 8) talloc(&v64_tmp, total);
     HIPCHECK(hipMemcpyAsync(d_all, all.data(), sizeof(Blk) * nall, hipMemcpyHostToDevice, stream_));
     HIPCHECK(hipMemcpyAsync(d_blk, sorted.data(), sizeof(Blk) * nseg, hipMemcpyHostToDevice, stream_));
     if (!reblock) {
@@ -1891,13 +1889,12 @@ void Engine<T>::sort_blocks(const std::vector<int>& ids, bool dual, const std::v
     radix_shifts(shifts, rb_min, key_bits);
     radix_shifts(shifts, 32, 32 + bits_for((int64_t)nall - 1));
     radix_sort_pairs<uint64_t>(key_in, src_in, key_out, src_out, total, shifts, stream_);
-    sorted_block_gather_kernel<T><<<nseg, kThreads, 0, stream_>>>(d_blk, key_out, src_out, val, v64, ci, v_tmp, v64_tmp);
-    sorted_block_store_kernel<T><<<nseg, kThreads, 0, stream_>>>(d_blk, v_tmp, v64_tmp, val, v64);
+    sorted_block_gather_kernel<<<nseg, kThreads, 0, stream_>>>(d_blk, key_out, src_out, v64, ci, v_tmp);
+    sorted_block_store_kernel<T><<<nseg, kThreads, 0, stream_>>>(d_blk, v_tmp, val, v64);
     HIPCHECK(hipGetLastError());
     HIPCHECK(hipStreamSynchronize(stream_));
     dfree(d_where);
     dfree(d_old);
-    dfree(v64_tmp);
     dfree(v_tmp);
     dfree(src_out);
     dfree(src_in);
@@ -2061,8 +2058,7 @@ void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int
   while (((int64_t)1 << rb) < maxrows) ++rb;
   int32_t *d_g = nullptr, *d_off = nullptr, *src_in = nullptr, *src_out = nullptr;
   uint64_t *key_in = nullptr, *key_out = nullptr;
-  T* v2 = nullptr;
-  double* v642 = nullptr;
+  double* v2 = nullptr;
   talloc(&d_g, ng + 1);
   talloc(&d_off, nseg + 1);
   talloc(&key_in, nnz);
@@ -2070,7 +2066,6 @@ void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int
   talloc(&src_in, nnz);
   talloc(&src_out, nnz);
   talloc(&v2, nnz);
-  if (sizeof(T) != 8) talloc(&v642, nnz);
   HIPCHECK(hipMemcpyAsync(d_g, gstart.data(), sizeof(int32_t) * gstart.size(), hipMemcpyHostToDevice, stream_));
   group_keys_kernel<<<(unsigned)tiles.size(), kThreads, 0, stream_>>>(d_tiles, rp, ci, d_g, ng, r0, S.nz0, c0, len, nsl,
                                                                       rb, key_in, src_in);
@@ -2080,14 +2075,13 @@ void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int
   radix_shifts(shifts, 32, 32 + bits_for(nseg - 1));
   radix_sort_pairs<uint64_t>(key_in, src_in, key_out, src_out, nnz, shifts, stream_);
   segment_offsets_kernel<<<nblk(nseg + 1), 256, 0, stream_>>>(key_out, nnz, nseg, d_off);
-  sorted_gather_kernel<T><<<nblk(nnz), 256, 0, stream_>>>(key_out, src_out, val, v64, nnz, ci + S.nz0, v2, v642);
+  sorted_gather_kernel<<<nblk(nnz), 256, 0, stream_>>>(key_out, src_out, v64, nnz, ci + S.nz0, v2);
+  if (sizeof(T) != 8) cast_kernel<T><<<nblk(nnz), 256, 0, stream_>>>(v2, val + S.nz0, nnz);
   HIPCHECK(hipGetLastError());
-  HIPCHECK(hipMemcpyAsync(val + S.nz0, v2, sizeof(T) * nnz, hipMemcpyDeviceToDevice, stream_));
-  if (v642) HIPCHECK(hipMemcpyAsync(v64 + S.nz0, v642, sizeof(double) * nnz, hipMemcpyDeviceToDevice, stream_));
+  HIPCHECK(hipMemcpyAsync(v64 + S.nz0, v2, sizeof(double) * nnz, hipMemcpyDeviceToDevice, stream_));
   std::vector<int32_t> off(nseg + 1);
   HIPCHECK(hipMemcpyAsync(off.data(), d_off, sizeof(int32_t) * off.size(), hipMemcpyDeviceToHost, stream_));
   HIPCHECK(hipStreamSynchronize(stream_));
-  dfree(v642);
   dfree(v2);
   dfree(src_out);
   dfree(src_in);

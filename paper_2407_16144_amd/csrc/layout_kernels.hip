@@ -315,33 +315,31 @@ __global__ __launch_bounds__(kThreads) void reblock_keys_kernel(const Blk* old, 
 }
 
 // Step 2 (after the keys are sorted): the entries of every BK_SORTED block
-// take the low words of the sorted keys as packed column indices and the
-// values of the entries they came from (staged in v_tmp / v64_tmp, in the
-// order of the key arrays).
-template <class V>
+// take the low words of the sorted keys as packed column indices and the FP64
+// values of the entries they came from (staged in v_tmp, in the order of the
+// key arrays).
 __global__ __launch_bounds__(kThreads) void sorted_block_gather_kernel(const Blk* blks, const uint64_t* key,
-                                                                       const int32_t* src, const V* val,
-                                                                       const double* v64, int32_t* ci_out, V* v_tmp,
-                                                                       double* v64_tmp) {
+                                                                       const int32_t* src, const double* v64,
+                                                                       int32_t* ci_out, double* v_tmp) {
   const Blk b = blks[blockIdx.x];
   const int64_t at = (int64_t)b.p0 + b.gid;
   for (int e = threadIdx.x; e < b.pn; e += kThreads) {
-    const int32_t from = src[at + e];
     ci_out[b.p0 + e] = (int32_t)(uint32_t)key[at + e];
-    v_tmp[at + e] = val[from];
-    if (v64_tmp) v64_tmp[at + e] = v64[from];
+    v_tmp[at + e] = v64[src[at + e]];
   }
 }
 
-// Step 3: the staged values take their places.
+// Step 3: the staged values take their places, also as the compute type's
+// (val is v64 itself where that is FP64).
 template <class V>
-__global__ __launch_bounds__(kThreads) void sorted_block_store_kernel(const Blk* blks, const V* v_tmp,
-                                                                      const double* v64_tmp, V* val, double* v64) {
+__global__ __launch_bounds__(kThreads) void sorted_block_store_kernel(const Blk* blks, const double* v_tmp, V* val,
+                                                                      double* v64) {
   const Blk b = blks[blockIdx.x];
   const int64_t at = (int64_t)b.p0 + b.gid;
   for (int e = threadIdx.x; e < b.pn; e += kThreads) {
-    val[b.p0 + e] = v_tmp[at + e];
-    if (v64_tmp) v64[b.p0 + e] = v64_tmp[at + e];
+    const double v = v_tmp[at + e];
+    v64[b.p0 + e] = v;
+    if constexpr (sizeof(V) != 8) val[b.p0 + e] = (V)v;
   }
 }
 
@@ -358,17 +356,14 @@ __global__ void segment_offsets_kernel(const uint64_t* key, int64_t nnz, int nse
   off[s] = (int32_t)lo;
 }
 
-// Sorted groups, step 3: entry p takes the sorted key as its packed column index and the value of
-// the entry it came from.
-template <class V>
-__global__ void sorted_gather_kernel(const uint64_t* key, const int32_t* src, const V* val, const double* v64,
-                                     int64_t nnz, int32_t* ci_out, V* val_out, double* v64_out) {
+// Sorted groups, step 3: entry p takes the sorted key as its packed column
+// index and the FP64 value of the entry it came from.
+__global__ void sorted_gather_kernel(const uint64_t* key, const int32_t* src, const double* v64, int64_t nnz,
+                                     int32_t* ci_out, double* v_out) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= nnz) return;
-  const int32_t e = src[p];
   ci_out[p] = (int32_t)(uint32_t)key[p];
-  val_out[p] = val[e];
-  if (v64_out) v64_out[p] = v64[e];
+  v_out[p] = v64[src[p]];
 }
 
 template <class V>
@@ -395,16 +390,8 @@ __global__ void transpose_rowptr_kernel(const uint32_t* keys, int64_t nnz, int64
   kt_rp[j] = (int32_t)(z0 + lo);
 }
 
-template __global__ void sorted_block_gather_kernel<double>(const Blk*, const uint64_t*, const int32_t*, const double*,
-                                                            const double*, int32_t*, double*, double*);
-template __global__ void sorted_block_gather_kernel<float>(const Blk*, const uint64_t*, const int32_t*, const float*,
-                                                           const double*, int32_t*, float*, double*);
-template __global__ void sorted_block_store_kernel<double>(const Blk*, const double*, const double*, double*, double*);
-template __global__ void sorted_block_store_kernel<float>(const Blk*, const float*, const double*, float*, double*);
-template __global__ void sorted_gather_kernel<double>(const uint64_t*, const int32_t*, const double*,
-                                                      const double*, int64_t, int32_t*, double*, double*);
-template __global__ void sorted_gather_kernel<float>(const uint64_t*, const int32_t*, const float*,
-                                                     const double*, int64_t, int32_t*, float*, double*);
+template __global__ void sorted_block_store_kernel<double>(const Blk*, const double*, double*, double*);
+template __global__ void sorted_block_store_kernel<float>(const Blk*, const double*, float*, double*);
 template __global__ void slice_scatter_kernel<double>(const int32_t*, const int32_t*, const double*,
                                                       const double*, int64_t, int64_t, int64_t, int64_t,
                                                       const int32_t*, int32_t*, double*, double*);

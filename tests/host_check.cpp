@@ -388,10 +388,40 @@ void least_memory_batch() {
       CHECK(lp_batch_create(&h, (int)ps.size(), ps.data(), 0, nullptr, &o) == LP_OK);
       sorts[tight] = stub::count("block_keys_kernel");
       // the engine, the temporary memory, and a little for what is small
-      if (!tight) limit = stub::sizes[0] + std::max(29 * nnz, 49 * largest + (1 << 18)) + 65536;
+      if (!tight) limit = stub::sizes[0] + std::max(29 * nnz, 45 * largest + (1 << 14)) + 65536;
       lp_batch_destroy(h);
     }
     CHECK(sorts[0] == 2 && sorts[1] > 2 && sorts[1] <= 8);
+  }
+}
+
+// The largest admission that a server takes stays within its budget (up to the
+// alignment of its buffers).
+void server_budget() {
+  for (const int precision : {LP_PREC_FP64, LP_PREC_FP32}) {
+    for (const double polish : {0.0, 1e-3}) {
+      for (const size_t budget : {4 << 20, 16 << 20, 64 << 20}) {
+        lp_options o = options();
+        o.precision = precision;
+        o.polish_tol = polish;
+        int64_t fits = 4, t;
+        size_t peak = 0;
+        for (int64_t not_so = 20000; not_so - fits > 1 + fits / 500;) {
+          const int64_t m = (fits + not_so) / 2;
+          const LP lp(m, 4 * m, 36, 4 * m);
+          const lp_problem p = lp.problem();
+          stub::reset();
+          lp_server* s = nullptr;
+          CHECK(lp_server_create(&s, (int64_t)budget, 4, nullptr, &o) == LP_OK);
+          const int rc = lp_server_submit(s, &p, 1e-6, 1000, 0.0, &t);
+          (rc == LP_OK ? fits : not_so) = m;
+          stub::on_launch = [&](const stub::Launch&, void**) { peak = std::max(peak, stub::bytes); };
+          if (rc == LP_OK) CHECK(lp_server_step(s, 1, nullptr) == LP_OK);
+          lp_server_destroy(s);
+        }
+        CHECK(fits > 100 && peak <= budget + 16384);
+      }
+    }
   }
 }
 
@@ -408,7 +438,8 @@ int main(int argc, char** argv) {
                                                       {"crowded_slices", crowded_slices},
                                                       {"failed_creation", failed_creation},
                                                       {"least_memory_partials", least_memory_partials},
-                                                      {"least_memory_batch", least_memory_batch}};
+                                                      {"least_memory_batch", least_memory_batch},
+                                                      {"server_budget", server_budget}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());
