@@ -425,6 +425,52 @@ void server_budget() {
   }
 }
 
+// Copies of the row sums of a block that one long row dominates: 8, or 16 or 32
+// where the block has 16 times as many entries as they take words; none where
+// no row dominates or 8 do not fit.
+void copies_of_row_sums() {
+  struct {
+    int64_t rows, len, long_row;
+    int shift;
+  } const cases[] = {{1, 300, 300, 4}, {1, 600, 600, 5}, {30, 3, 255, 0}, {100, 20, 2000, 3}, {500, 3, 2000, 3},
+                     {11200, 3, 500, 0}, {100, 100, 500, 0}, {40, 200, 6000, 4}};
+  for (const auto& c : cases) {
+    stub::reset();
+    LP lp(c.rows, 20000, c.len, 20000);
+    const int64_t old = lp.rp[1], add = c.long_row - old;  // row 0 gets columns 0 ..
+    lp.ci.erase(lp.ci.begin(), lp.ci.begin() + old);
+    std::vector<int32_t> row(c.long_row);
+    for (int64_t k = 0; k < c.long_row; ++k) row[k] = (int32_t)(3 * k);
+    lp.ci.insert(lp.ci.begin(), row.begin(), row.end());
+    for (int64_t r = 1; r <= c.rows; ++r) lp.rp[r] += (int32_t)add;
+    lp.val.assign(lp.ci.size(), 1.0);
+    // (among many LPs a product gets a block per 256 rows or 16384 entries, at
+    // most 25 of them)
+    std::vector<lp_problem> ps(1, lp.problem());
+    const LP other(1, 2000, 1, 2000);
+    for (int i = 0; i < 40; ++i) ps.push_back(other.problem());
+    lp_options o = options();
+    int shift = -1, blocks = 0;
+    stub::on_launch = [&](const stub::Launch& l, void** a) {
+      if (l.name.find("sorted_step<double, true") == std::string::npos) return;
+      blocks = 0;
+      for (unsigned b = 0; b < l.grid; ++b) {
+        const halp::Blk& k = stub::arg<halp::IterArgs<double>>(a, 0).schedDB[b];
+        if (halp::blk_kind(k) != halp::BK_SORTED || k.inst != 0 || k.pn < c.long_row) continue;
+        shift = halp::blk_rep_shift(k);
+        blocks = 1;
+      }
+      for (int i = 0; i < 41; ++i) finish(a, i);
+    };
+    lp_batch* h = nullptr;
+    CHECK(lp_batch_create(&h, (int)ps.size(), ps.data(), 0, nullptr, &o) == LP_OK);
+    CHECK(lp_batch_solve(h, 1e-6, 1000, -1.0) == LP_OK);
+    if (shift != c.shift) fprintf(stderr, "%ld rows, long row %ld: shift %d\n", (long)c.rows, (long)c.long_row, shift);
+    CHECK(blocks == 1 && shift == c.shift);
+    lp_batch_destroy(h);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -439,7 +485,8 @@ int main(int argc, char** argv) {
                                                       {"failed_creation", failed_creation},
                                                       {"least_memory_partials", least_memory_partials},
                                                       {"least_memory_batch", least_memory_batch},
-                                                      {"server_budget", server_budget}};
+                                                      {"server_budget", server_budget},
+                                                      {"copies_of_row_sums", copies_of_row_sums}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());

@@ -39,7 +39,8 @@ def host_check(tmp_path_factory):
 @pytest.mark.parametrize("name", ["failed_schedule", "failed_admission", "failed_admission_frees_slots",
                                   "failed_reblocking", "row_limit", "long_rows",
                                   "crowded_slices", "failed_creation", "least_memory_partials",
-                                  "least_memory_batch", "server_budget"])
+                                  "least_memory_batch", "server_budget",
+                                  "copies_of_row_sums"])
 def test_host_engine(host_check, name):
     p = subprocess.run([host_check, name], capture_output=True, text=True, timeout=300)
     assert p.returncode == 0 and p.stdout.strip() == f"ok {name}", p.stdout[-2000:] + p.stderr[-4000:]
