@@ -1,6 +1,8 @@
 """Layouts of the step kernels that depend on how a matrix's entries are
 spread: sorted groups split because their entries crowd into few column
-slices, and blocks cut by the entries of few long rows.  Each trajectory
+slices, and blocks cut by the entries of few long rows; column-sorted blocks
+of small LPs in the kernels per product; the power iteration over either
+layout.  Each trajectory
 agrees with the oracle's at the same step size to 1e-10, the bound of the
 other FP64 trajectory tests (both sides round the same sums in another
 order)."""
@@ -11,6 +13,8 @@ import scipy.sparse as sp
 import lpgen
 import oracle
 from oracle import core
+
+from test_gpu_sorted_blocks import CASES as BLOCKS
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +77,63 @@ def test_trajectory(name):
     ref = oracle.solve(lp, oracle.Options(tol=0.0, max_iter=130, eta=eta))
     assert res["iters"] == ref.iters and res["restarts"] == ref.restarts
     _agrees((x, y), (ref.x, ref.y))
+
+
+@pytest.mark.parametrize("name", list(BLOCKS))
+def test_sorted_blocks_of_a_timed_engine(name):
+    """The blocks of test_gpu_sorted_blocks in the kernels per product: a timed
+    engine keeps its small LPs in them, which otherwise step on one CU."""
+    lp = BLOCKS[name]()
+    print(f"case timed sorted block {name} m={lp.m} n={lp.n} nnz={lp.nnz}", flush=True)
+    P = core.scaled_problem(lp)
+    s, _ = oracle.power_iteration(P.K, 0, max_iters=30)
+    eta = 0.9 / s
+    res, x, y, _ = halp.solve_lp(lp, tol=0.0, max_iter=130, opt=halp.lp_default_options(eta=eta, profile=1))
+    ref = oracle.solve(lp, oracle.Options(tol=0.0, max_iter=130, eta=eta))
+    assert res["iters"] == ref.iters and res["restarts"] == ref.restarts
+    _agrees((x, y), (ref.x, ref.y))
+
+
+def _holes(m, n, per_row, long_row, seed):
+    """Empty rows and columns, and one row of `long_row` entries."""
+    rng = np.random.default_rng(seed)
+    rows = np.repeat(np.arange(1, m, 3), per_row)
+    cols = rng.integers(0, n // 2, rows.size) * 2
+    extra = rng.choice(n // 2, long_row, replace=False) * 2
+    return _lp(np.concatenate([rows, np.full(long_row, 2)]), np.concatenate([cols, extra]), m, n, seed + 1)
+
+
+POWER = {
+    # (LPs of one add, options): K^T of more than 512 tiles in all, so that the
+    # power iteration runs on the layouts of the steps
+    "sorted blocks, copies, holes": (lambda: [_holes(6000, 150000, 60, 20000, 11)], {}),
+    "a row of its own beside sorted blocks": (lambda: [_holes(6000, 150000, 60, 40000, 12)], {}),
+    "more than 512 blocks": (lambda: [_uniform([20] * (1500 + 40 * i), 6000 + 100 * i, 20 + i) for i in range(40)], {}),
+    "groups of few rows": (lambda: [_uniform([12] * 20000, 140000, 13)], dict(slice_min_bytes=65536)),
+    "groups, split": (lambda: [_band(20000, 140000, 60, 2000, 14)], dict(slice_min_bytes=65536)),
+    "groups beside blocks and tiles": (lambda: [_holes(6000, 90000, 60, 40000, 15), _uniform([12] * 20000, 90000, 16),
+                                               _uniform([3] * 50, 100, 17)], dict(slice_min_bytes=65536)),
+    "groups and blocks, more than 512": (lambda: [_uniform([12] * 20000, 90000, 30)] +
+                                         [_uniform([20] * 1500, 6000, 31 + i) for i in range(40)],
+                                         dict(slice_min_bytes=65536)),
+}
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("name", list(POWER))
+def test_power_iteration(name, precision):
+    """sigma_hat of every LP of an add to 1e-10 of the oracle's (the same
+    iterates; the row sums are added in another order), after as many
+    iterations; the FP32 engine computes it in FP64 too."""
+    make, options = POWER[name]
+    lps = make()
+    print(f"case power {name} precision={precision} nnz={[lp.nnz for lp in lps][:4]}", flush=True)
+    h = halp.lp_batch_create(lps, opt=halp.lp_default_options(precision=precision, **options))
+    try:
+        got = [halp.lp_batch_status(h, i) for i in range(len(lps))]
+    finally:
+        halp.lp_batch_destroy(h)
+    for lp, r in zip(lps, got):
+        s, iters = oracle.power_iteration(core.scaled_problem(lp).K, 0)
+        assert r.sigma_hat == pytest.approx(s, rel=1e-10)
+        assert r.power_iters == iters
