@@ -171,8 +171,9 @@ typedef struct {
                                workgroup, else enough for about eight waves per CU over
                                the product's workgroups */
   int group_batched;        /* 1 (default): each thread issues the gathers of a batch of
-                               entries together, then adds them into the LDS row sums;
-                               0: one gather per add */
+                               entries together, then adds them into the LDS row sums
+                               (not where a product has very many groups of less than
+                               a batch); 0: one gather per add */
   int group_blocks;         /* fewest workgroups a product stored in sorted groups is cut
                                into (default 240; counts of about one per CU are rounded
                                up to the 256 CUs): groups get as many rows as that allows */

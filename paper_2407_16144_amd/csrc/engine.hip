@@ -519,6 +519,7 @@ class Engine final : public EngineBase {
   void launch_group(unsigned g, int tpb, size_t lds, const IterArgs<T>& A, int step);
   int ldsP_ = 0, ldsD_ = 0;  // rows of the largest sorted group in the current schedules
   int tpbP_ = 256, tpbD_ = 256;  // threads per workgroup of the sorted-group kernels
+  bool batchedP_ = true, batchedD_ = true;  // and whether they run the entries as a pipeline
   template <bool DUAL>
   void launch_sorted(const IterArgs<T>& A, int step);
   int ldsPB_ = 0, ldsDB_ = 0;      // LDS words of the largest column-sorted block in the current schedules
@@ -707,8 +708,9 @@ void Engine<T>::allocate() {
                         (const void*)sorted_group_step<T, false, 1024, true>,
                         (const void*)sorted_group_step<T, false, 1024, false>})
     HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
-  for (const void* f : {(const void*)sorted_step<T, true, 256>, (const void*)sorted_step<T, true, 512>,
-                        (const void*)sorted_step<T, false, 256>, (const void*)sorted_step<T, false, 512>})
+  for (const void* f : {(const void*)sorted_step<T, true, 128, 1>, (const void*)sorted_step<T, false, 128, 1>,
+                        (const void*)sorted_step<T, true, 256, kPlainD>, (const void*)sorted_step<T, true, 512, kPlainD>,
+                        (const void*)sorted_step<T, false, 256, kPlainD>, (const void*)sorted_step<T, false, 512, kPlainD>})
     HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(double) * (kSortWordsPlain + kSpareWords)));
   // row sums of both products with their copies, and the gathered vectors
   const int lds_res = 2 * (int)sizeof(double) * kSortWordsPlain + 2 * (int)sizeof(T) * kResRows;
@@ -2346,6 +2348,16 @@ void Engine<T>::rebuild_schedules() {
   };
   tpbP_ = pick(with_entries(PS));
   tpbD_ = pick(with_entries(DS));
+  // without the pipeline where many groups end before it is full (sort_rows = 32:
+  // 500k x 2M 547 us per iteration against 1310, 200k x 1M 154 against 265)
+  auto batched = [&](const std::vector<Blk>& v) {
+    int64_t entries = 0;
+    for (const Blk& k : v) entries += k.pn;
+    const size_t nb = with_entries(v);
+    return opt_.group_batched != 0 && !(nb > (size_t)kTinyGroups * kCUs && entries < kGroupEntries * (int64_t)nb);
+  };
+  batchedP_ = batched(PS);
+  batchedD_ = batched(DS);
   auto words = [](const std::vector<Blk>& v) {
     int w = 1;
     for (const Blk& k : v)
@@ -2366,10 +2378,18 @@ void Engine<T>::rebuild_schedules() {
   ldsDB_ = words(DB);
   // threads per column-sorted block: 512 where each CU has one large block
   // (100k x 400k: 42.6 us per iteration against 43.4 with 256), else 256 (20k x
-  // 70k: 16.0 against 16.3; a batch of 128: 146 against 155)
+  // 70k: 16.0 against 16.3; a batch of 128: 146 against 155), and 128 with a
+  // shorter pipeline for many blocks of few rows, which end before a longer one
+  // is full (sort_rows = 32: a batch of 32 82.9 us per iteration against 112.5,
+  // 20k x 70k 17.1 against 20.1; 4 LPs of 2.4k x 8k 11.0 against 12.2)
   auto pick_sorted = [](const std::vector<Blk>& v) {
     int64_t entries = 0;
-    for (const Blk& k : v) entries += k.pn;
+    int rows = 0;
+    for (const Blk& k : v) {
+      entries += k.pn;
+      rows = std::max(rows, k.r1 - k.r0);
+    }
+    if (v.size() > 2 * (size_t)kCUs && rows <= kTinyRows) return 128;
     return v.size() <= (size_t)kCUs && entries > 8192 * (int64_t)v.size() ? 512 : 256;
   };
   tpbPB_ = pick_sorted(PB);
@@ -2433,7 +2453,7 @@ template <class T>
 template <bool DUAL>
 void Engine<T>::launch_group(unsigned g, int tpb, size_t lds, const IterArgs<T>& A, int step) {
   auto go = [&](auto kern, int t) { kern<<<g, t, lds, stream_>>>(A, step); };
-  const bool b = opt_.group_batched != 0;
+  const bool b = DUAL ? batchedD_ : batchedP_;
   switch (tpb) {
     case 512:
       if (b) go(sorted_group_step<T, DUAL, 512, true>, 512);
@@ -2456,8 +2476,9 @@ void Engine<T>::launch_sorted(const IterArgs<T>& A, int step) {
   const unsigned g = (unsigned)(DUAL ? nDB_ : nPB_);
   const size_t lds = sizeof(double) * (size_t)((DUAL ? ldsDB_ : ldsPB_) + kSpareWords);
   switch (DUAL ? tpbDB_ : tpbPB_) {
-    case 512: sorted_step<T, DUAL, 512><<<g, 512, lds, stream_>>>(A, step); break;
-    default: sorted_step<T, DUAL, 256><<<g, 256, lds, stream_>>>(A, step); break;
+    case 128: sorted_step<T, DUAL, 128, 1><<<g, 128, lds, stream_>>>(A, step); break;
+    case 512: sorted_step<T, DUAL, 512, kPlainD><<<g, 512, lds, stream_>>>(A, step); break;
+    default: sorted_step<T, DUAL, 256, kPlainD><<<g, 256, lds, stream_>>>(A, step); break;
   }
 }
 

@@ -117,6 +117,11 @@ constexpr int kSortColBits = 28;
 constexpr int kGroupEntries = 1024;
 constexpr int kPlainU = 2;
 constexpr int kPlainD = 2;
+// Most rows of the blocks of a launch of more than two blocks per CU for the
+// 128-thread step kernel, and the workgroups per CU from which on groups of less
+// than a batch of entries go without the pipeline (Engine::rebuild_schedules)
+constexpr int kTinyRows = 128;
+constexpr int kTinyGroups = 32;
 // log2 of the copies of each LDS row sum that a BK_SORTED block keeps (in the
 // meta bits that hold the slice of a slice block)
 __host__ __device__ inline int blk_rep_shift(const Blk& b) { return (b.meta >> 16) & 0xff; }

@@ -337,6 +337,7 @@ __device__ __forceinline__ T rec_proj(T d, bool lf, bool uf) {
 template <class T, int TPB, int U, int D>
 struct SortedStream {
   static constexpr int NS = D + 2;  // batches in registers
+  static_assert(D >= 1, "a batch is loaded before it is gathered");
   static constexpr int BT = TPB * U;
   __amdgpu_buffer_rsrc_t rk, rv;
   int lo, hi, rb;
@@ -985,7 +986,7 @@ __global__ __launch_bounds__(kThreads) void dual_step(IterArgs<T> A, int step) {
 // copies of each row sum, lane l adding into copy l mod 2^shift.
 // The row sums sit in dynamic LDS (FP64 words for the largest block of the
 // schedule, and kSpareWords).
-template <class T, bool DUAL, int TPB>
+template <class T, bool DUAL, int TPB, int D>
 __global__ __launch_bounds__(TPB) void sorted_step(IterArgs<T> A, int step) {
   extern __shared__ __align__(16) unsigned char sorted_lds[];
   __shared__ double s_red[TPB / 64][kNS];
@@ -1016,7 +1017,7 @@ __global__ __launch_bounds__(TPB) void sorted_step(IterArgs<T> A, int step) {
     o3 = v3[p0];
     o4 = v4[p0];
   }
-  SortedStream<T, TPB, kPlainU, kPlainD> st;
+  SortedStream<T, TPB, kPlainU, D> st;
   st.open(b, ci, val);
   const int rs = blk_rep_shift(b);
   const int words = nrows << rs;

@@ -56,6 +56,14 @@ CASES = {
     "banded groups in one pair of slices": (lambda: _band(40000, 20000, 30, 16000, 2), dict(slice_min_bytes=0)),
     "few long rows": (lambda: _uniform([1500] * 150 + [5000, 30000], 60000, 3), {}),
     "few long columns": (lambda: _uniform([12] * 20000, 150, 4), {}),
+    # more than 512 blocks of at most 128 rows: the 128-thread kernel; one row
+    # more, or 512 blocks, the other one
+    "many small blocks": (lambda: _uniform([7] * 20000 + [3000] * 3, 70000, 5), dict(sort_rows=128)),
+    "many blocks of 129 rows": (lambda: _uniform([7] * 20000, 70000, 6), dict(sort_rows=129)),
+    "512 blocks": (lambda: _uniform([4] * 512, 512, 7), dict(sort_rows=1)),
+    "513 blocks": (lambda: _uniform([4] * 513, 513, 8), dict(sort_rows=1)),
+    # more than 32 groups per CU of less than a batch of entries
+    "many small groups": (lambda: _uniform([5] * 33000, 34000, 9), dict(sort_rows=32, slice_min_bytes=0)),
 }
 
 
