@@ -2014,7 +2014,9 @@ void Engine<T>::group_sorted(int id, bool dual, const int32_t* hrp, int nsl, int
   // (split rows 5% slower at 500k x 1M) is left.
   const double groups0 = (double)gstart.size() - 1.0;
   double most[kGroupSlices] = {0.0};
-  for (bool split = true; split;) {
+  bool split = false;  // (a group of fewer entries is not split: nothing to count)
+  for (size_t g = 0; g + 1 < gstart.size() && nsl > 1; ++g) split |= hrp[gstart[g + 1]] - hrp[gstart[g]] > kMinSplit;
+  while (split) {
     const int n = (int)gstart.size() - 1;
     int32_t *d_cut = nullptr, *d_cnt = nullptr;
     talloc(&d_cut, n + 1);

@@ -307,6 +307,15 @@ void crowded_slices() {
     CHECK(lp == &band ? counts > 1 && largest <= 1 << 14 : counts == 1 && blocks.size() <= 8 * 33);
     lp_destroy(s);
   }
+  // groups that are too small to be split are not counted
+  stub::reset();
+  lp_options o = options();
+  o.sort_rows = 256;
+  const lp_problem p = band.problem();
+  lp_solver* s = nullptr;
+  CHECK(lp_create(&s, p.n, p.m_eq, 0, p.row_ptr, p.col_idx, p.val, p.c, p.rhs, p.lb, p.ub, 0, nullptr, &o) == LP_OK);
+  CHECK(stub::count("group_keys_kernel") == 1 && stub::count("group_count_kernel") == 0);
+  lp_destroy(s);
 }
 
 // Memory runs out after n allocations of a creation or a solve, for every n:
