@@ -118,7 +118,8 @@ class Error : public std::runtime_error {
 class EngineBase {
  public:
   virtual ~EngineBase() = default;
-  // add LPs (validated, preprocessed, iterates initialised); returns slot ids.
+  // add LPs (sizes checked by the caller; validated, preprocessed, iterates
+  // initialised); returns slot ids.  A failed add holds no slot.
   // partial: admit the longest prefix that fits instead of failing.
   virtual std::vector<int> add(const std::vector<Problem>& probs, bool on_device, bool partial = false) = 0;
   // tolerance and iteration limit of the next solve; stall_checks > 0 also
@@ -148,13 +149,13 @@ class EngineBase {
   virtual bool fits(int64_t n, int64_t m, int64_t nnz) const = 0;
   virtual bool fits_empty(int64_t n, int64_t m, int64_t nnz) const = 0;
   virtual KernelTimes kernel_times() const = 0;
-  // last check candidate T(z) in the scaled space, as float64 device arrays
   // LPs `ids` (not started yet) continue from the candidates of the LPs
   // src_ids of another engine on the same stream: import_point for all of them
   virtual void take_over(const EngineBase& src, const std::vector<int>& src_ids, const std::vector<int>& ids,
                          const std::vector<double>& omega) = 0;
   virtual Candidate candidate(int id) const = 0;
   virtual Scaling scaling(int id) const = 0;
+  // last check candidate T(z) in the scaled space, as float64 device arrays
   virtual void export_point(int id, double* x, double* y, double* omega) = 0;
   // start the next solve of `id` from (x, y) (scaled, float64 device arrays)
   // with primal weight omega (omega <= 0: the LP's initial weight

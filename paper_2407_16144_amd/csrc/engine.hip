@@ -946,55 +946,47 @@ static int parts_for(int64_t largest, size_t lps) {
 template <class T>
 void Engine<T>::validate_device(const std::vector<Problem>& probs, std::vector<int64_t>& nnzs) {
   std::vector<LpInput> in;
-  const char* sizes = "sizes must satisfy n >= 1, m >= 0";
-  const char* fault = nullptr;  // what the LP after the last of `in` violates
-  for (const Problem& p : probs) {
-    if (p.n < 1 || p.m_eq < 0 || p.m_ineq < 0) {
-      fault = sizes;
-      break;
-    }
+  for (const Problem& p : probs)
     in.push_back({p.rp, p.ci, p.val, p.c, p.rhs, p.lb, p.ub, nullptr, nullptr, p.m_eq + p.m_ineq, p.n, 0, 0, 0, 0});
-  }
+  if (in.empty()) return;
   LpInput* d_in = nullptr;
   int2* d_ends = nullptr;
   int* d_flags = nullptr;
-  std::vector<int> flags;
-  if (!in.empty()) {
-    const int64_t most = (int64_t)in.size();
-    talloc(&d_in, most);
-    talloc(&d_ends, most);
-    talloc(&d_flags, most);
-    HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(LpInput) * in.size(), hipMemcpyHostToDevice, stream_));
-    HIPCHECK(hipStreamSynchronize(stream_));
-    // on the null stream, after the caller's work there that may still write the inputs
-    std::vector<int2> ends(in.size());
-    row_ends_kernel<<<nblk(most), 256, 0, nullptr>>>(d_in, (int)most, d_ends);
-    HIPCHECK(hipGetLastError());
-    HIPCHECK(hipMemcpy(ends.data(), d_ends, sizeof(int2) * in.size(), hipMemcpyDeviceToHost));
-    int64_t largest = 1;
-    for (size_t k = 0; k < in.size(); ++k) {
-      if (ends[k].x != 0 || ends[k].y < 0) {
-        fault = "row_ptr must start at 0 and end at nnz >= 0";
-        in.resize(k);
-        break;
-      }
-      in[k].nnz = nnzs[k] = ends[k].y;
-      largest = std::max({largest, in[k].nnz, in[k].m, in[k].n});
+  const int64_t most = (int64_t)in.size();
+  talloc(&d_in, most);
+  talloc(&d_ends, most);
+  talloc(&d_flags, most);
+  HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(LpInput) * in.size(), hipMemcpyHostToDevice, stream_));
+  HIPCHECK(hipStreamSynchronize(stream_));
+  // on the null stream, after the caller's work there that may still write the inputs
+  std::vector<int2> ends(in.size());
+  row_ends_kernel<<<nblk(most), 256, 0, nullptr>>>(d_in, (int)most, d_ends);
+  HIPCHECK(hipGetLastError());
+  HIPCHECK(hipMemcpy(ends.data(), d_ends, sizeof(int2) * in.size(), hipMemcpyDeviceToHost));
+  bool bad_ends = false;  // of the LP after the last of `in`
+  int64_t largest = 1;
+  for (size_t k = 0; k < in.size(); ++k) {
+    if (ends[k].x != 0 || ends[k].y < 0) {
+      bad_ends = true;
+      in.resize(k);
+      break;
     }
-    flags.assign(in.size(), 0);
-    if (!in.empty()) {
-      const int parts = parts_for(largest, in.size());
-      HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(LpInput) * in.size(), hipMemcpyHostToDevice, stream_));
-      HIPCHECK(hipMemsetAsync(d_flags, 0, sizeof(int) * in.size(), stream_));
-      validate_lps_kernel<<<(unsigned)(in.size() * parts), kThreads, 0, stream_>>>(d_in, parts, d_flags);
-      HIPCHECK(hipGetLastError());
-      HIPCHECK(hipMemcpyAsync(flags.data(), d_flags, sizeof(int) * in.size(), hipMemcpyDeviceToHost, stream_));
-      HIPCHECK(hipStreamSynchronize(stream_));
-    }
-    dfree(d_flags);
-    dfree(d_ends);
-    dfree(d_in);
+    in[k].nnz = nnzs[k] = ends[k].y;
+    largest = std::max({largest, in[k].nnz, in[k].m, in[k].n});
   }
+  std::vector<int> flags(in.size(), 0);
+  if (!in.empty()) {
+    const int parts = parts_for(largest, in.size());
+    HIPCHECK(hipMemcpyAsync(d_in, in.data(), sizeof(LpInput) * in.size(), hipMemcpyHostToDevice, stream_));
+    HIPCHECK(hipMemsetAsync(d_flags, 0, sizeof(int) * in.size(), stream_));
+    validate_lps_kernel<<<(unsigned)(in.size() * parts), kThreads, 0, stream_>>>(d_in, parts, d_flags);
+    HIPCHECK(hipGetLastError());
+    HIPCHECK(hipMemcpyAsync(flags.data(), d_flags, sizeof(int) * in.size(), hipMemcpyDeviceToHost, stream_));
+    HIPCHECK(hipStreamSynchronize(stream_));
+  }
+  dfree(d_flags);
+  dfree(d_ends);
+  dfree(d_in);
   for (const int f : flags) {
     if (f & 1) throw Error(-1, "row_ptr must be non-decreasing from 0 to nnz");
     if (f & 2) throw Error(-1, "device CSR needs in-range, strictly increasing column indices per row");
@@ -1002,7 +994,7 @@ void Engine<T>::validate_device(const std::vector<Problem>& probs, std::vector<i
     if (f & 8) throw Error(-1, "non-finite objective or right-hand side");
     if (f & 16) throw Error(-1, "invalid bounds (NaN, lb > ub, lb = +inf or ub = -inf)");
   }
-  if (fault) throw Error(-1, fault);
+  if (bad_ends) throw Error(-1, "row_ptr must start at 0 and end at nnz >= 0");
 }
 
 // Copies device-resident LPs into their places.
