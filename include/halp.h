@@ -147,9 +147,12 @@ typedef struct {
                                column order) whose products are added into the row sums
                                with LDS atomics (faster; the order of the additions
                                within a row, and so the last bits of the iterates, may
-                               differ from run to run); 0: sliced products in row-major
-                               slice tiles with fixed-order sums (slice_entries,
-                               slice_rows) */
+                               differ from run to run, and those of sigma_hat and eta
+                               too where the K^T products of the LPs created together
+                               have more than 512 tiles of at most tile_rows rows and
+                               1024 entries: the power iteration then runs on these
+                               layouts); 0: sliced products in row-major slice tiles
+                               with fixed-order sums (slice_entries, slice_rows) */
   int sort_rows;            /* most rows per sorted group or column-sorted block,
                                1..16384 (default 16384).  Sorted groups: groups of equal
                                work, about one workgroup per CU and product, that fit the
@@ -319,7 +322,9 @@ typedef struct lp_batch lp_batch;
  * advanced together: every step is one launch over all LPs' rows of K^T and
  * one over all rows of K.  Each LP keeps its own step size, primal weight,
  * Halpern counter, restart state and status, so an LP's result does not
- * depend on what else is in the batch. */
+ * depend on what else is in the batch, but for the rounding of its sums: the
+ * blocks of the default layouts are sized for the LPs that share the
+ * launches (plain_sort = 0 and slice_sort = 0: to the bit). */
 int lp_batch_create(lp_batch** out, int count, const lp_problem* problems, int inputs_on_device,
                     void* stream, const lp_options* opt);
 /* Solves every LP of the batch (same tolerance and iteration limit). */
