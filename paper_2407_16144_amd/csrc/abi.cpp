@@ -962,6 +962,16 @@ std::vector<std::pair<int64_t, int>> admit(lp_server* s, halp::EngineBase& eng, 
   return out;
 }
 
+// takes back what `admit` returned: the LPs leave the engine and wait again, in order
+void readmit(halp::EngineBase& eng, std::deque<int64_t>& queue, const std::vector<std::pair<int64_t, int>>& in) {
+  std::vector<int> ids;
+  for (auto it = in.rbegin(); it != in.rend(); ++it) {
+    queue.push_front(it->first);
+    ids.push_back(it->second);
+  }
+  eng.remove(ids);
+}
+
 }  // namespace
 
 extern "C" {
@@ -969,32 +979,49 @@ extern "C" {
 int lp_server_step(lp_server* s, int chunks, int* n_done) {
   return guarded([&]() -> int {
     if (!s || chunks < 0) return fail(LP_ERR_INVALID, "bad argument");
-    // admission to the first (or only) phase
+    // admission to the first (or only) phase; LPs whose limits cannot be set
+    // wait again (parked, they would be reported as finished)
     {
       std::map<std::tuple<double, int64_t, int64_t>, std::vector<int>> by_params;
-      for (auto& [t, id] : admit(s, *s->eng, s->queue, s->admit_nz)) {
-        Request& r = s->reqs.at(t);
-        const bool polish = s->eng64 && r.tol < s->opt.polish_tol;
-        by_params[{polish ? s->opt.polish_tol : r.tol, polish ? fp32_budget(r.max_iter) : r.max_iter,
-                   polish ? s->opt.stall_checks : 0}].push_back(id);
-        r.slot = id;
+      const auto in = admit(s, *s->eng, s->queue, s->admit_nz);
+      try {
+        for (auto& [t, id] : in) {
+          const Request& r = s->reqs.at(t);
+          const bool polish = s->eng64 && r.tol < s->opt.polish_tol;
+          by_params[{polish ? s->opt.polish_tol : r.tol, polish ? fp32_budget(r.max_iter) : r.max_iter,
+                     polish ? s->opt.stall_checks : 0}].push_back(id);
+        }
+        for (auto& kv : by_params)
+          s->eng->set_params(kv.second, std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first));
+      } catch (...) {
+        readmit(*s->eng, s->queue, in);
+        throw;
+      }
+      for (auto& [t, id] : in) {
+        s->reqs.at(t).slot = id;
         s->slot_ticket[id] = t;
       }
-      for (auto& kv : by_params)
-        s->eng->set_params(kv.second, std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first));
     }
     // admission to the FP64 polish phase, from the FP32 candidates
     if (s->eng64) {
-      for (auto& [t, id] : admit(s, *s->eng64, s->queue64, s->admit_nz64)) {
-        Request& r = s->reqs.at(t);
-        double* buf = s->staging(r.n + r.m_eq + r.m_ineq + 1);
-        hip_ok(hipMemcpy(buf, r.px.data(), sizeof(double) * r.n, hipMemcpyHostToDevice), "staging copy");
-        if (!r.py.empty())
-          hip_ok(hipMemcpy(buf + r.n, r.py.data(), sizeof(double) * r.py.size(), hipMemcpyHostToDevice),
-                 "staging copy");
-        s->eng64->import_point(id, buf, buf + r.n, polish_omega(s->opt, r.first, r.pomega));
-        s->eng64->set_params({id}, r.tol, r.max_iter - r.first.iters);
-        r.slot64 = id;
+      const auto in = admit(s, *s->eng64, s->queue64, s->admit_nz64);
+      try {
+        for (auto& [t, id] : in) {
+          const Request& r = s->reqs.at(t);
+          double* buf = s->staging(r.n + r.m_eq + r.m_ineq + 1);
+          hip_ok(hipMemcpy(buf, r.px.data(), sizeof(double) * r.n, hipMemcpyHostToDevice), "staging copy");
+          if (!r.py.empty())
+            hip_ok(hipMemcpy(buf + r.n, r.py.data(), sizeof(double) * r.py.size(), hipMemcpyHostToDevice),
+                   "staging copy");
+          s->eng64->import_point(id, buf, buf + r.n, polish_omega(s->opt, r.first, r.pomega));
+          s->eng64->set_params({id}, r.tol, r.max_iter - r.first.iters);
+        }
+      } catch (...) {
+        readmit(*s->eng64, s->queue64, in);
+        throw;
+      }
+      for (auto& [t, id] : in) {
+        s->reqs.at(t).slot64 = id;
         s->slot_ticket64[id] = t;
       }
     }

@@ -53,8 +53,9 @@ lp_options options() {
 }
 
 // LP i reaches its tolerance in this step.
+template <class T = double>
 void finish(void** args, int i) {
-  const auto& A = stub::arg<halp::IterArgs<double>>(args, 0);
+  const auto& A = stub::arg<halp::IterArgs<T>>(args, 0);
   A.st[i].status = A.status_out[i] = halp::ST_OPTIMAL;
   A.st[i].checks = 1;
 }
@@ -165,14 +166,50 @@ void failed_admission_frees_slots() {
       failed = lp_server_step(s, 0, nullptr) != LP_OK;  // admission alone
       stub::fail_at = -1;
       failures += failed;
-      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued + live == 2);
-      const bool again = queued == 1;  // (else the LP is admitted, without its limits)
-      CHECK(lp_server_step(s, 1, nullptr) == LP_OK);
-      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 0 && (!again || live == 2));
+      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == failed && live == 2 - failed);
+      int done = 0;
+      CHECK(lp_server_step(s, 1, &done) == LP_OK && done == 0);
+      CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 0 && live == 2);
       lp_server_destroy(s);
     }
     CHECK(failures > 0);
   }
+}
+
+// Memory runs out somewhere in the admission to an FP32 server's second phase:
+// the LP waits for it again.
+void failed_second_phase() {
+  const LP a(40, 60, 5, 60), b(50, 70, 5, 70);
+  lp_options o = options();
+  o.precision = LP_PREC_FP32;
+  bool failed = true;
+  size_t failures = 0;
+  for (long n = 0; failed; ++n) {
+    stub::reset();
+    lp_server* s = nullptr;
+    CHECK(lp_server_create(&s, 64 << 20, 4, nullptr, &o) == LP_OK);
+    int64_t t;
+    for (const LP* lp : {&a, &b}) {
+      const lp_problem p = lp->problem();
+      CHECK(lp_server_submit(s, &p, 1e-9, 1000, 0.0, &t) == LP_OK);
+    }
+    stub::on_launch = [&](const stub::Launch& l, void** args) {
+      if (l.name.find("resident_steps<float") != std::string::npos)
+        for (int i = 0; i < 2; ++i) finish<float>(args, i);
+    };
+    int queued = 0, live = 0, done = 0;
+    CHECK(lp_server_step(s, 1, &done) == LP_OK && done == 0);  // the first phase ends
+    CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 2 && live == 0);
+    stub::fail_at = n;
+    failed = lp_server_step(s, 0, nullptr) != LP_OK;
+    stub::fail_at = -1;
+    failures += failed;
+    CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 2 * failed && live == 2 - 2 * failed);
+    CHECK(lp_server_step(s, 1, &done) == LP_OK && done == 0);
+    CHECK(lp_server_info(s, &queued, &live, nullptr) == LP_OK && queued == 0 && live == 2);
+    lp_server_destroy(s);
+  }
+  CHECK(failures > 4);
 }
 
 // The LPs of a batch still running when half have finished are laid out anew;
@@ -487,6 +524,7 @@ int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {{"failed_schedule", failed_schedule},
                                                       {"failed_admission", failed_admission},
                                                       {"failed_admission_frees_slots", failed_admission_frees_slots},
+                                                      {"failed_second_phase", failed_second_phase},
                                                       {"failed_reblocking", failed_reblocking},
                                                       {"row_limit", row_limit},
                                                       {"long_rows", long_rows},

@@ -37,7 +37,7 @@ def host_check(tmp_path_factory):
 
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("name", ["failed_schedule", "failed_admission", "failed_admission_frees_slots",
-                                  "failed_reblocking", "row_limit", "long_rows",
+                                  "failed_second_phase", "failed_reblocking", "row_limit", "long_rows",
                                   "crowded_slices", "failed_creation", "least_memory_partials",
                                   "least_memory_batch", "server_budget",
                                   "copies_of_row_sums"])
