@@ -828,7 +828,10 @@ struct HostCSR {
   std::vector<double> val;
 };
 
-static void validate_host(const Problem& p, HostCSR& canon, bool& use_canon) {
+// At the start of a cache line: the loop over the entries is a few instructions
+// long, and where it lies across lines the checks of 24 submitted LPs of 500 x
+// 20,000 take 8.2 ms instead of 7.2, by the size of whatever is linked before it.
+__attribute__((aligned(64))) static void validate_host(const Problem& p, HostCSR& canon, bool& use_canon) {
   const int64_t m = p.m_eq + p.m_ineq, n = p.n;
   if (n < 1 || p.m_eq < 0 || p.m_ineq < 0) throw Error(-1, "sizes must satisfy n >= 1, m_eq >= 0, m_ineq >= 0");
   if (!p.rp || (m > 0 && (!p.c || !p.rhs)) || !p.c || !p.lb || !p.ub)
