@@ -319,7 +319,7 @@ void run_polish(Polish& P, const halp::Options& opt, hipStream_t stream, halp::E
   std::vector<halp::Problem> probs;
   for (int i : which) {
     probs.push_back(to_problem(raw[i]->view));
-    probs.back().scaling = src.scaling(src_ids[i]);
+    probs.back().norm = src.norm(src_ids[i]);
   }
   const std::vector<int> ids = P.eng->add(probs, raw[which[0]]->on_device);
   std::vector<int> from;

@@ -16,11 +16,9 @@
 
 namespace halp {
 
-// Scaling and spectral norm of an LP that an engine holds (device pointers,
-// valid while it does).
-struct Scaling {
-  const double* Dr = nullptr;
-  const double* Dc = nullptr;
+// Spectral norm of an LP's K~ as an engine estimated it.
+struct Norm {
+  bool known = false;
   double sigma_hat = 0.0;
   int power_iters = 0;
 };
@@ -41,7 +39,7 @@ struct Problem {  // one input LP; pointers are host or device memory
   const double* rhs = nullptr;
   const double* lb = nullptr;
   const double* ub = nullptr;
-  Scaling scaling;  // of the same LP in another engine with the same options: not computed again
+  Norm norm;  // of the same LP in another engine with the same options: not estimated again
 };
 
 struct Options {
@@ -154,7 +152,7 @@ class EngineBase {
   virtual void take_over(const EngineBase& src, const std::vector<int>& src_ids, const std::vector<int>& ids,
                          const std::vector<double>& omega) = 0;
   virtual Candidate candidate(int id) const = 0;
-  virtual Scaling scaling(int id) const = 0;
+  virtual Norm norm(int id) const = 0;
   // last check candidate T(z) in the scaled space, as float64 device arrays
   virtual void export_point(int id, double* x, double* y, double* omega) = 0;
   // start the next solve of `id` from (x, y) (scaled, float64 device arrays)

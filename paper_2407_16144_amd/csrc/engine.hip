@@ -495,10 +495,7 @@ class Engine final : public EngineBase {
   Result result(int id) override;
   void solution(int id, double* x, double* y, bool to_device) override;
   void certificate(int id, double* ray, bool to_device) override;
-  Scaling scaling(int id) const override {
-    const Slot& S = slots_[id];
-    return {Dr + S.row0, Dc + S.col0, h_st_[id].sigma_hat, h_st_[id].pw_iter};
-  }
+  Norm norm(int id) const override { return {true, h_st_[id].sigma_hat, h_st_[id].pw_iter}; }
   void export_point(int id, double* x, double* y, double* omega) override;
   void stored_matrix(int id, bool transpose, int32_t* rp, int32_t* ci, double* val) override;
   void refine_layouts() override {
@@ -950,7 +947,7 @@ template <class T>
 void Engine<T>::validate_device(const std::vector<Problem>& probs, std::vector<int64_t>& nnzs) {
   std::vector<LpInput> in;
   for (const Problem& p : probs)
-    in.push_back({p.rp, p.ci, p.val, p.c, p.rhs, p.lb, p.ub, nullptr, nullptr, p.m_eq + p.m_ineq, p.n, 0, 0, 0, 0});
+    in.push_back({p.rp, p.ci, p.val, p.c, p.rhs, p.lb, p.ub, p.m_eq + p.m_ineq, p.n, 0, 0, 0, 0});
   if (in.empty()) return;
   LpInput* d_in = nullptr;
   int2* d_ends = nullptr;
@@ -1008,8 +1005,7 @@ void Engine<T>::load_device(const std::vector<Problem>& probs, const std::vector
   for (size_t k = 0; k < ids.size(); ++k) {
     const Problem& p = probs[k];
     const Slot& S = slots_[ids[k]];
-    in.push_back({p.rp, p.ci, p.val, p.c, p.rhs, p.lb, p.ub, p.scaling.Dr, p.scaling.Dc, S.m, S.n, S.nnz, S.row0,
-                  S.col0, S.nz0});
+    in.push_back({p.rp, p.ci, p.val, p.c, p.rhs, p.lb, p.ub, S.m, S.n, S.nnz, S.row0, S.col0, S.nz0});
     largest = std::max({largest, S.nnz, S.m, S.n});
   }
   LpInput* d_in = nullptr;
@@ -1160,10 +1156,6 @@ std::vector<int> Engine<T>::add(const std::vector<Problem>& probs_in, bool on_de
     HIPCHECK(hipMemcpyAsync(u_o + S.col0, p.ub, sizeof(double) * n, hipMemcpyHostToDevice, stream_));
     fill_kernel<<<nblk(m + 1), 256, 0, stream_>>>(Dr + S.row0, m + 1, 1.0);
     fill_kernel<<<nblk(n + 1), 256, 0, stream_>>>(Dc + S.col0, n + 1, 1.0);
-    if (p.scaling.Dr) {
-      if (m) HIPCHECK(hipMemcpyAsync(Dr + S.row0, p.scaling.Dr, sizeof(double) * m, hipMemcpyDeviceToDevice, stream_));
-      HIPCHECK(hipMemcpyAsync(Dc + S.col0, p.scaling.Dc, sizeof(double) * n, hipMemcpyDeviceToDevice, stream_));
-    }
   }
   if (on_device) {
     load_device(probs, ids);
@@ -1288,8 +1280,8 @@ template <class T>
 int Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Problem>& probs, const std::vector<Blk>& nP,
                           const std::vector<Blk>& nD, const std::vector<int4>& nr, std::vector<double>& norms) {
   const int ni = (int)ids.size();
-  // scaling and spectral norm of every LP are given (Problem::scaling)
-  const bool given = std::all_of(probs.begin(), probs.end(), [](const Problem& p) { return p.scaling.Dr != nullptr; });
+  // the spectral norm of every LP is given
+  const bool given = std::all_of(probs.begin(), probs.end(), [](const Problem& p) { return p.norm.known; });
   Blk *d_nP = nullptr, *d_nD = nullptr;
   int* d_ids = nullptr;
   int4* d_nr = nullptr;
@@ -1325,21 +1317,19 @@ int Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Problem
     const unsigned gP = (unsigned)nP.size(), gD = (unsigned)nD.size();
 
     // scaling (Ruiz infinity-norm passes, then Pock-Chambolle): each pass
-    // reads the factors so far from one pair of buffers and writes the other,
-    // ending in Dr and Dc
+    // applies the factors of the one before and finds its own, a last one only
+    // applies.  K's rows keep theirs where the dual iterates will be, those
+    // that K^T gathers are in fm, the columns' in fn.
     const int passes = opt_.ruiz_iters + (opt_.pc_alpha > 0.0 ? 1 : 0);
-    for (int it = 0; it < passes && !given; ++it) {
-      const bool pc = it == opt_.ruiz_iters, last = (passes - it) & 1;
-      double *r_out = last ? Dr : fm, *c_out = last ? Dc : fn;
-      const double *r_in = it == 0 ? nullptr : last ? fm : Dr, *c_in = it == 0 ? nullptr : last ? fn : Dc;
-      row_factor_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_ci, K_v64, pc, pc ? 2.0 - opt_.pc_alpha : 1.0,
-                                                      c_in, r_in, r_out);
-      row_factor_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_ci, KT_v64, pc, pc ? opt_.pc_alpha : 1.0, r_in,
-                                                      c_in, c_out);
-    }
-    if (passes > 0) {
-      scale_values_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_ci, K_v64, Dr, Dc, 0);
-      scale_values_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_ci, KT_v64, Dr, Dc, 1);
+    const bool words = sizeof(T) != sizeof(double);
+    const RowFactors fr{words ? nullptr : (double*)y, words ? (uint32_t*)y : nullptr, words ? (uint32_t*)y0 : nullptr, fm};
+    const RowFactors fc{fn, nullptr, nullptr, nullptr};
+    for (int it = 0; it <= passes && passes > 0; ++it) {
+      const int op = it == passes ? 2 : it == opt_.ruiz_iters ? 1 : 0;
+      row_factor_kernel<<<gD, kThreads, 0, stream_>>>(d_nD, K_rp, K_ci, K_v64, op, op == 1 ? 2.0 - opt_.pc_alpha : 1.0,
+                                                      it == 0, false, fn, fr, Dr);
+      row_factor_kernel<<<gP, kThreads, 0, stream_>>>(d_nP, KT_rp, KT_ci, KT_v64, op, op == 1 ? opt_.pc_alpha : 1.0,
+                                                      it == 0, true, fm, fc, Dc);
     }
     scale_primal_kernel<T><<<gP, kThreads, 0, stream_>>>(d_nP, Dc, c_o, l_o, u_o, c, l, u, d_pp);
     scale_dual_kernel<T><<<gD, kThreads, 0, stream_>>>(d_nD, Dr, q_o, q, d_pd);
@@ -1361,8 +1351,8 @@ int Engine<T>::preprocess(const std::vector<int>& ids, const std::vector<Problem
       s.pb1 = nr[k].y;
       s.pw_done = opt_.eta > 0.0 || given ? 1 : 0;
       if (given) {
-        s.sigma_hat = probs[k].scaling.sigma_hat;
-        s.pw_iter = probs[k].scaling.power_iters;
+        s.sigma_hat = probs[k].norm.sigma_hat;
+        s.pw_iter = probs[k].norm.power_iters;
       }
     }
     HIPCHECK(hipMemcpyAsync(d_src, src.data(), sizeof(InstState) * ni, hipMemcpyHostToDevice, stream_));

@@ -189,7 +189,6 @@ struct LpInput {
   const int32_t* rp;
   const int32_t* ci;
   const double *val, *c, *rhs, *lb, *ub;
-  const double *Dr, *Dc;  // given scaling, or null
   int64_t m, n, nnz, row0, col0, nz0;
 };
 

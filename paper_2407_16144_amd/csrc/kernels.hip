@@ -1392,44 +1392,85 @@ __global__ void tick_kernel(int64_t* gbase, int64_t add) {
 }
 
 // ---------------------------------------------------------------------------
-// preprocessing: Ruiz / Pock-Chambolle factors and value scaling
+// preprocessing: Ruiz / Pock-Chambolle scaling
 // ---------------------------------------------------------------------------
 
-// One scaling pass over one side's rows.  The values stay as they came; with
-// D the row's own factor so far and G the other side's, the scaled row is
-// |v_rj| G[j] D[r], and out[r] = D[r] / sqrt(its largest entry) (op 0) or
-// D[r] / sqrt(sum of its entries^expo) (op 1); rows of zeros keep D[r].  D and
-// G are null in the first pass (all ones).  out is another buffer than D: the
-// other side's pass reads D.  Bound by the gathers of G; without the values
-// rewritten after each pass it streams 12 bytes per entry and side where
-// that took 28 (500k x 2M: 775 -> 317 us per pass and side).  Against extended
-// precision the stored matrix is Dr K Dc to 7e-17 (rms; 2.5e-16 with values
-// rewritten), and 600 iterations on it end 1.2 to 3.5 times closer in 9 of 10
-// vectors of 5 LPs.
-__global__ __launch_bounds__(kThreads) void row_factor_kernel(const Blk* sched, const int32_t* rp, const int32_t* ci,
-                                                              const double* val, int op, double expo, const double* G,
-                                                              const double* D, double* out) {
+// A pass's factors of one side's rows, from the previous pass to this one.
+// The other side's pass gathers the previous ones, so K's rows, which come
+// first, keep theirs apart (`held`, or two halves where the buffers at hand
+// hold 32-bit words) and pass the previous ones on (`prev`); the rows of K^T
+// overwrite theirs (`held`; prev null).
+struct RowFactors {
+  double* held;
+  uint32_t *lo, *hi;
+  double* prev;
+  __device__ double get(int64_t r) const {
+    return held ? held[r] : __hiloint2double((int)hi[r], (int)lo[r]);
+  }
+  __device__ void set(int64_t r, double v) const {
+    if (held) {
+      held[r] = v;
+    } else {
+      hi[r] = (uint32_t)__double2hiint(v);
+      lo[r] = (uint32_t)__double2loint(v);
+    }
+  }
+};
+
+// One scaling pass over one side's rows: entries divided by the previous
+// pass's factors (by that of the row of K, then by that of its column, on both
+// sides, so that K~ and its transpose hold the same bits; none in the first
+// pass), then each row's new factor, the root of its largest entry (op 0) or
+// of the sum of its entries^expo (op 1), 1 for rows of zeros, and D[r] divided
+// by it; op 2 divides the entries only.  Every entry is rounded after each
+// division: that is how the CPU oracle defines K~, and iterates are compared
+// with its over a thousand steps, where entries formed from the product of
+// the factors (as close to Dr K Dc, but rounded otherwise) end 2 to 3 times
+// further from it (200k x 1M, 1,030 steps, largest difference of y 6e-11 to
+// 1.0e-10 for 2e-11 to 5e-11).  Bound by the gathers of the other side's
+// factors and 20 bytes per entry; one kernel divides and reduces, so the
+// entries are read once per pass and side, coalesced, and staged in LDS.  A
+// thread divides its own entries, by the row noted for each: divided in the
+// rows' loops, one after another, 128 LPs took 36.5 ms to create instead of
+// 34.7 (33.3 with undivided entries), one of 2.4k x 8k 2.23 instead of 2.13.
+__global__ __launch_bounds__(kThreads) void row_factor_kernel(const Blk* sched, const int32_t* __restrict__ rp,
+                                                              const int32_t* __restrict__ ci, double* __restrict__ val,
+                                                              int op, double expo, bool first, bool transposed,
+                                                              const double* __restrict__ other, RowFactors F, double* D) {
   __shared__ double s_val[kPlainNB];
+  __shared__ double s_f[kMaxRows];
+  __shared__ uint8_t s_row[kPlainNB];  // row of an entry in the tile
   __shared__ int s_rp[kMaxRows + 1];
   __shared__ double s_red[kThreads / 64];
   const Blk b = sched[blockIdx.x];
   const int tid = threadIdx.x;
   const int nrows = b.r1 - b.r0;
-  auto entry = [&](int e) { return G ? fabs(val[e]) * G[ci[e]] : fabs(val[e]); };
-  auto add = [&](double a, double v, double d) {
+  // entry v of a row with factor f in a column with factor o
+  auto divide = [&](double v, double f, double o) { return transposed ? v / o / f : v / f / o; };
+  auto add = [&](double a, double v) {
+    v = fabs(v);
     if (op == 0) return fmax(a, v);
-    return a + (expo != 1.0 ? pow(v * d, expo) : v);
+    return a + (expo != 1.0 ? pow(v, expo) : v);
   };
-  auto finish = [&](int64_t r, double a, double d) {
-    // sums of powers already hold the row's factor
-    const double f = sqrt(op == 0 || expo == 1.0 ? a * d : a);
-    out[r] = f > 0.0 ? d / f : d;
+  auto finish = [&](int64_t r, double f, double a) {
+    if (!first && F.prev) F.prev[r] = f;
+    if (op == 2) return;
+    const double q = sqrt(a), g = q > 0.0 ? q : 1.0;
+    F.set(r, g);
+    D[r] = (first ? 1.0 : D[r]) / g;
   };
   if (blk_kind(b) == BK_LONG) {
-    const double d = D ? D[b.r0] : 1.0;
+    const double f = first ? 1.0 : F.get(b.r0);
     double a = 0.0;
 #pragma unroll 4
-    for (int k = tid; k < b.pn; k += kThreads) a = add(a, entry(b.p0 + k), d);
+    for (int k = tid; k < b.pn; k += kThreads) {
+      double v = val[b.p0 + k];
+      if (!first) {
+        v = divide(v, f, other[ci[b.p0 + k]]);
+        val[b.p0 + k] = v;
+      }
+      a = add(a, v);
+    }
     // max or sum over the block, in fixed order
     if (op == 0) {
       for (int off = 32; off > 0; off >>= 1) a = fmax(a, __shfl_xor(a, off, 64));
@@ -1441,56 +1482,52 @@ __global__ __launch_bounds__(kThreads) void row_factor_kernel(const Blk* sched, 
     if (tid == 0) {
       double r = s_red[0];
       for (int w = 1; w < kThreads / 64; ++w) r = op == 0 ? fmax(r, s_red[w]) : r + s_red[w];
-      finish(b.r0, r, d);
+      finish(b.r0, f, r);
     }
     return;
   }
   for (int r = tid; r <= nrows; r += kThreads) s_rp[r] = rp[b.r0 + r] - b.p0;
+  for (int r = tid; r < nrows; r += kThreads) s_f[r] = first ? 1.0 : F.get(b.r0 + r);
+  constexpr int kPer = kPlainNB / kThreads;
+  double v[kPer], o[kPer];
 #pragma unroll
-  for (int i = 0; i < (kPlainNB + kThreads - 1) / kThreads; ++i) {
+  for (int i = 0; i < kPer; ++i) {
     const int k = tid + i * kThreads;
-    if (k < b.pn) s_val[k] = entry(b.p0 + k);
+    if (k < b.pn) {
+      v[i] = val[b.p0 + k];
+      if (!first) o[i] = other[ci[b.p0 + k]];
+    }
   }
   __syncthreads();
   const int L = group_size(nrows);  // lanes per row
   const int lane = tid & (L - 1);
+  if (!first) {
+    for (int r = tid / L; r < nrows; r += kThreads / L)
+      for (int k = s_rp[r] + lane; k < s_rp[r + 1]; k += L) s_row[k] = (uint8_t)r;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int k = tid + i * kThreads;
+    if (k < b.pn) {
+      if (!first) {
+        v[i] = divide(v[i], s_f[s_row[k]], o[i]);
+        val[b.p0 + k] = v[i];
+      }
+      s_val[k] = v[i];
+    }
+  }
+  __syncthreads();
   for (int base = 0; base < nrows; base += kThreads / L) {
     const int r = base + tid / L;
-    const double d = r < nrows && D ? D[b.r0 + r] : 1.0;
     double a = 0.0;
     if (r < nrows)
-      for (int k = s_rp[r] + lane; k < s_rp[r + 1]; k += L) a = add(a, s_val[k], d);
+      for (int k = s_rp[r] + lane; k < s_rp[r + 1]; k += L) a = add(a, s_val[k]);
     for (int off = L >> 1; off > 0; off >>= 1) {
       const double o = __shfl_xor(a, off, 64);
       a = op == 0 ? fmax(a, o) : a + o;
     }
-    if (lane == 0 && r < nrows) finish((int64_t)b.r0 + r, a, d);
-  }
-}
-
-// v_e <- v_e * Dr[m-index] * Dc[n-index]; for K the row is the m-index,
-// for K^T the row is the n-index.  Same operation order for both, so K~ and
-// (K~)^T hold bit-identical values.
-__global__ __launch_bounds__(kThreads) void scale_values_kernel(const Blk* sched, const int32_t* rp,
-                                                                const int32_t* ci, double* val,
-                                                                const double* Dr, const double* Dc,
-                                                                int transposed) {
-  const Blk b = sched[blockIdx.x];
-  const int nrows = b.r1 - b.r0;
-  const int tid = threadIdx.x;
-  const int G = (blk_kind(b) == BK_LONG) ? kThreads : group_size(nrows);
-  const int lane = tid & (G - 1);
-  for (int base = 0; base < nrows; base += kThreads / G) {
-    const int r = base + tid / G;
-    if (r >= nrows) continue;
-    const int row = b.r0 + r;
-    const int p1 = rp[row + 1];
-    for (int e = rp[row] + lane; e < p1; e += G) {
-      const int c = ci[e];
-      const double a = transposed ? Dr[c] : Dr[row];
-      const double d = transposed ? Dc[row] : Dc[c];
-      val[e] = val[e] * a * d;
-    }
+    if (lane == 0 && r < nrows) finish((int64_t)b.r0 + r, s_f[r], a);
   }
 }
 

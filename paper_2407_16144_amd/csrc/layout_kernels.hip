@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kThreads) void validate_lps_kernel(const LpInput* i
 }
 
 // Device-resident LPs into the engine's spaces: row pointers and columns
-// become space positions; factors start at the given ones, or at 1.
+// become space positions, and the factors are 1.
 __global__ __launch_bounds__(kThreads) void load_lps_kernel(const LpInput* in, int parts, int32_t* K_rp, int32_t* K_ci,
                                                             double* K_v, double* q, double* c, double* l, double* u,
                                                             double* Dr, double* Dc) {
@@ -81,11 +81,11 @@ __global__ __launch_bounds__(kThreads) void load_lps_kernel(const LpInput* in, i
   }
   for (int64_t r = first; r <= p.m; r += step) {
     K_rp[p.row0 + r] = (int32_t)(p.rp[r] + p.nz0);
-    Dr[p.row0 + r] = p.Dr && r < p.m ? p.Dr[r] : 1.0;
+    Dr[p.row0 + r] = 1.0;
     if (r < p.m) q[p.row0 + r] = p.rhs[r];
   }
   for (int64_t j = first; j <= p.n; j += step) {
-    Dc[p.col0 + j] = p.Dc && j < p.n ? p.Dc[j] : 1.0;
+    Dc[p.col0 + j] = 1.0;
     if (j < p.n) {
       c[p.col0 + j] = p.c[j];
       l[p.col0 + j] = p.lb[j];
