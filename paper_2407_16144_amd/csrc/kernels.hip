@@ -1429,10 +1429,12 @@ struct RowFactors {
 // further from it (200k x 1M, 1,030 steps, largest difference of y 6e-11 to
 // 1.0e-10 for 2e-11 to 5e-11).  Bound by the gathers of the other side's
 // factors and 20 bytes per entry; one kernel divides and reduces, so the
-// entries are read once per pass and side, coalesced, and staged in LDS.  A
-// thread divides its own entries, by the row noted for each: divided in the
-// rows' loops, one after another, 128 LPs took 36.5 ms to create instead of
-// 34.7 (33.3 with undivided entries), one of 2.4k x 8k 2.23 instead of 2.13.
+// entries are read once per pass and side, coalesced, and staged in LDS (500k
+// x 2M, 30M entries: 367 us per pass and side; 775 in two kernels with a row's
+// entries read by its own lanes, 317 where entries are left alone).  A thread
+// divides its own entries, by the row noted for each: divided in the rows'
+// loops, one after another, 128 LPs took 36.5 ms to create instead of 34.7
+// (33.3 with undivided entries), one of 2.4k x 8k 2.23 instead of 2.13.
 __global__ __launch_bounds__(kThreads) void row_factor_kernel(const Blk* sched, const int32_t* __restrict__ rp,
                                                               const int32_t* __restrict__ ci, double* __restrict__ val,
                                                               int op, double expo, bool first, bool transposed,
