@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <memory>
 #include <stdexcept>
 #include <string>
@@ -190,6 +191,15 @@ void validate_host_problem(const Problem& p);
 // Device int64 row pointers narrowed into int32 (dst, count entries) on
 // `stream`; returns nonzero when an entry is negative or above 2^31 - 1.
 int narrow_row_ptr(const int64_t* src, int32_t* dst, int64_t count, hipStream_t stream);
+
+// Workgroups per LP of the kernels that take all LPs of an add at once: 16
+// items per thread of the largest, 2048 workgroups (8 per CU) for one LP, 64 for
+// each of many, fewer where the launch would reach 2^32 threads.
+inline int parts_for(int64_t largest, size_t lps) {
+  const int64_t most = std::max<int64_t>(64, 2048 / (int64_t)lps);
+  const int64_t launch = ((int64_t(1) << 32) / kThreads - 1) / (int64_t)lps;
+  return (int)std::max<int64_t>(1, std::min({most, launch, (largest + 16 * kThreads - 1) / (16 * kThreads)}));
+}
 
 // capacity: sizes of the three spaces and the slot count (0 = grow to fit)
 std::unique_ptr<EngineBase> make_engine(const Options& opt, hipStream_t stream, int64_t cap_m,

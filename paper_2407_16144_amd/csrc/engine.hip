@@ -933,14 +933,6 @@ void Engine<T>::transpose_group(int64_t z0, int64_t nnz, int64_t c0, int64_t c1,
   }
 }
 
-// Workgroups per LP of the kernels that take all LPs of an add at once: 16
-// items per thread of the largest, 2048 workgroups (8 per CU) for one LP, 64 for
-// each of many.
-static int parts_for(int64_t largest, size_t lps) {
-  const int64_t most = std::max<int64_t>(64, 2048 / (int64_t)lps);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(most, (largest + 16 * kThreads - 1) / (16 * kThreads)));
-}
-
 // Checks device-resident LPs (the first one at fault throws) and reads their
 // entry counts.
 template <class T>

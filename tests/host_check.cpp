@@ -2,6 +2,7 @@
 // host_check NAME; prints "ok NAME".
 #include "hip_stub.h"
 
+#include "engine.h"
 #include "halp.h"
 
 #include <random>
@@ -517,6 +518,18 @@ void copies_of_row_sums() {
   }
 }
 
+// a launch over all LPs of an add holds fewer than 2^32 threads, whatever the
+// size of the largest LP, and no LP is left without a workgroup
+void launches_of_many() {
+  for (size_t lps : {size_t(1), size_t(3), size_t(512), size_t(262143), size_t(262144), size_t(5000000)})
+    for (int64_t largest : {int64_t(1), int64_t(4096), int64_t(4097), int64_t(1) << 20, int64_t(1) << 31}) {
+      const int64_t parts = halp::parts_for(largest, lps);
+      CHECK(parts >= 1);
+      CHECK(parts * (int64_t)lps * halp::kThreads < int64_t(1) << 32);
+    }
+  CHECK(halp::parts_for(int64_t(1) << 31, 1) == 2048 && halp::parts_for(4097, 512) == 2);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -533,7 +546,8 @@ int main(int argc, char** argv) {
                                                       {"least_memory_partials", least_memory_partials},
                                                       {"least_memory_batch", least_memory_batch},
                                                       {"server_budget", server_budget},
-                                                      {"copies_of_row_sums", copies_of_row_sums}};
+                                                      {"copies_of_row_sums", copies_of_row_sums},
+                                                      {"launches_of_many", launches_of_many}};
   if (!checks.count(name)) return 2;
   checks.at(name)();
   printf("ok %s\n", name.c_str());

@@ -40,7 +40,7 @@ def host_check(tmp_path_factory):
                                   "failed_second_phase", "failed_reblocking", "row_limit", "long_rows",
                                   "crowded_slices", "failed_creation", "least_memory_partials",
                                   "least_memory_batch", "server_budget",
-                                  "copies_of_row_sums"])
+                                  "copies_of_row_sums", "launches_of_many"])
 def test_host_engine(host_check, name):
     p = subprocess.run([host_check, name], capture_output=True, text=True, timeout=300)
     assert p.returncode == 0 and p.stdout.strip() == f"ok {name}", p.stdout[-2000:] + p.stderr[-4000:]
